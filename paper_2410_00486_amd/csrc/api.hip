@@ -20,6 +20,7 @@ TileSortArgs tile_sort_args(const Plan& P, void* ws);
 int64_t scan_rounds(const Plan& P);
 int64_t rb_blocks(int64_t count);
 int64_t rb_gen_blocks(int64_t records);
+int64_t rb_gen_items(int64_t records, int64_t pairs);
 int rb_max_radix();
 hipError_t launch_radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0, uint32_t* vals1,
                              const int32_t* cnt, uint32_t* hist, uint32_t* digit_tot,
@@ -276,6 +277,7 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
                                     std::max(P->rb_rec_blocks, P->rb_pair_blocks) : 0);
   P->off_rb_dtot = take(radix ? (size_t)rb_max_radix() * 4 : 0);
   P->off_rb_part = take(radix ? (size_t)rb_gen_blocks(P->n_rec) * 4 : 0);
+  P->off_rb_items = take(radix ? (size_t)(1 + rb_gen_items(P->n_rec, pair_capacity)) * 8 : 0);
   P->off_rb_pay = take(rrec * 4);   // 16 bytes per visible record, list order
   P->off_rb_spay = take(rrec * 4);  // the same in depth order
   P->off_rb_zrec = take(rrec);      // depth bits by record id

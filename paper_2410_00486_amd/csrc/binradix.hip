@@ -38,9 +38,12 @@ constexpr int kRbTile = kRbThreads * kRbItems;  // keys per block
 constexpr int kRbWaves = kRbThreads / kWave;
 constexpr int kRbMaxBits = 9;  // tile passes: 18 bits of tile id in two
 constexpr int kRbMaxRadix = 1 << kRbMaxBits;
-// depth-sorted records per block of the pair generation (4 per thread)
+// depth-sorted records per group of the pair generation (4 per thread), and
+// the pairs of a group that one workgroup writes
 constexpr int kGenRecs = 1024;
 constexpr int kGenPer = kGenRecs / kRbThreads;
+constexpr uint32_t kGenPairs = 8192;
+constexpr int kGenScanThreads = 1024;
 
 static_assert(kRbMaxRadix == 2 * kRbThreads, "two digits per thread in the block scans");
 
@@ -408,43 +411,65 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_gen_count(const uint4* __rest
   }
 }
 
-// 3b. One block: exclusive scan of the block pair counts (in place).
-__global__ void __launch_bounds__(kRbThreads) k_rb_gen_scan(const int32_t* __restrict__ fl,
-                                                            uint32_t* __restrict__ part) {
+// 3b. One block: exclusive scan of the groups' pair counts (in place), and
+// the work items of the generation: a group of p pairs is ceil(p / kGenPairs)
+// items (group, first pair).  items[0].x holds their number, the items
+// follow.  Near cameras the first groups in depth order hold splats over
+// thousands of tiles each: one workgroup per group left the chip to the few
+// heaviest (generation of 6.0M pairs of 8 close and overview views 470 us,
+// with items 26 us; 25M pairs of 16 views 156 us, 82 us: 300 MB, 3.6 TB/s).
+__global__ void __launch_bounds__(kGenScanThreads) k_rb_gen_scan(const int32_t* __restrict__ fl,
+                                                                 uint32_t* __restrict__ part,
+                                                                 uint2* __restrict__ items) {
+  constexpr int NW = kGenScanThreads / kWave;
   const int64_t V = rb_count(fl, F_VISIBLE);
   const int64_t nb = (V + kGenRecs - 1) / kGenRecs;
-  __shared__ uint32_t ws[kRbWaves];
-  __shared__ uint32_t tot;
-  uint32_t carry = 0;
-  for (int64_t b0 = 0; b0 < nb; b0 += kRbThreads) {
+  __shared__ uint64_t ws[NW];
+  const int w = threadIdx.x / kWave, lane = lane_id();
+  uint64_t carry = 0;  // items << 32 | pairs (each below 2^31)
+  for (int64_t b0 = 0; b0 < nb; b0 += kGenScanThreads) {
     const int64_t b = b0 + threadIdx.x;
-    const uint32_t x = b < nb ? part[b] : 0u;
-    const uint32_t ex = rb_block_exscan(x, ws);
-    if (b < nb) part[b] = carry + ex;
-    if (threadIdx.x == kRbThreads - 1) tot = ex + x;
+    const uint32_t p = b < nb ? part[b] : 0u;
+    const uint64_t x = ((uint64_t)((p + kGenPairs - 1) / kGenPairs) << 32) | p;
+    const uint64_t incl = scan_dpp<6>(x);
+    if (lane == kWave - 1) ws[w] = incl;
     __syncthreads();
-    carry += tot;
-    __syncthreads();
+    uint64_t ex = carry + incl - x;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+      const uint64_t t = ws[k];
+      if (k < w) ex += t;
+      carry += t;
+    }
+    if (b < nb) {
+      part[b] = (uint32_t)ex;
+      uint2* dst = items + 1 + (ex >> 32);
+      for (uint32_t k = 0; k < p; k += kGenPairs) *dst++ = make_uint2((uint32_t)b, k);
+    }
+    __syncthreads();  // ws is rewritten by the next round
   }
+  if (threadIdx.x == 0) items[0] = make_uint2((uint32_t)(carry >> 32), 0u);
 }
 
-// 3c. Pair generation in depth order: the block's records (4 consecutive
-// per thread) get their first slots from a block scan plus the block's
-// offset; the block's pairs are then spread evenly over the threads (each
-// finds its record by binary search of the slots in LDS), so one large
-// footprint does not serialise on one thread.  Writes the tile key, the
-// generation index and the record id of every pair.
+// 3c. Pair generation in depth order, one work item per workgroup: the
+// group's records (4 consecutive per thread) get their first slots from a
+// block scan plus the group's offset; the item's pairs are spread evenly
+// over the threads, four consecutive 16-byte aligned output positions each
+// (the first one's record by binary search of the slots in LDS, the others
+// by walking on), so one large footprint does not serialise on one thread.
+// Writes the tile key, the generation index and the record id of every pair.
 __global__ void __launch_bounds__(kRbThreads) k_rb_generate(
-    const uint4* __restrict__ spay, int64_t n, ViewTable vt,
+    const uint4* __restrict__ spay, uint32_t n, ViewTable vt,
     const int32_t* __restrict__ fl, const uint32_t* __restrict__ part,
-    uint32_t* __restrict__ tkey, uint32_t* __restrict__ gidx, uint32_t* __restrict__ ridx) {
+    const uint2* __restrict__ items, uint32_t* __restrict__ tkey, uint32_t* __restrict__ gidx,
+    uint32_t* __restrict__ ridx) {
+  if (blockIdx.x >= items[0].x) return;
+  const uint2 item = items[1 + blockIdx.x];
   const int64_t V = rb_count(fl, F_VISIBLE);
-  const int64_t base = (int64_t)blockIdx.x * kGenRecs;
-  if (base >= V) return;
-  __shared__ uint32_t s_pre[kGenRecs], s_p0[kGenRecs], s_t0[kGenRecs], s_rid[kGenRecs];
+  const int64_t base = (int64_t)item.x * kGenRecs;
+  __shared__ uint32_t s_pre[kGenRecs + 1], s_p0[kGenRecs], s_t0[kGenRecs], s_rid[kGenRecs];
   __shared__ uint32_t s_bw[kGenRecs], s_tx[kGenRecs];
   __shared__ uint32_t ws[kRbWaves];
-  __shared__ uint32_t s_total;
   uint32_t c[kGenPer], sum = 0;
 #pragma unroll
   for (int q = 0; q < kGenPer; ++q) {
@@ -454,8 +479,7 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_generate(
     if (j < V) {
       const uint4 p = spay[j];
       const uint32_t r = p.w;
-      const int v = (int)(r / (uint64_t)n);
-      const ViewInfo& vi = vt.v[v];
+      const ViewInfo& vi = vt.v[r / n];
       c[q] = pay_tiles(p);
       s_rid[l] = r;
       s_p0[l] = p.z;
@@ -468,15 +492,18 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_generate(
   uint32_t run = rb_block_exscan(sum, ws);
 #pragma unroll
   for (int q = 0; q < kGenPer; ++q) {
-    // records past the end keep the block total: never chosen below
+    // records past the end keep the group's total: never chosen below
     s_pre[threadIdx.x * kGenPer + q] = run;
     run += c[q];
   }
-  if (threadIdx.x == kRbThreads - 1) s_total = run;
+  if (threadIdx.x == kRbThreads - 1) s_pre[kGenRecs] = run;
   __syncthreads();
-  const uint32_t total = s_total;
-  const uint32_t q0 = part[blockIdx.x];
-  for (uint32_t q = threadIdx.x; q < total; q += kRbThreads) {
+  const uint32_t total = s_pre[kGenRecs];
+  const uint32_t q0 = part[item.x];
+  const uint32_t g0 = q0 + item.y, g1 = q0 + min(total, item.y + kGenPairs);
+  for (uint32_t g = g0 / 4 + threadIdx.x; 4 * g < g1; g += kRbThreads) {
+    const uint32_t a = max(4 * g, g0), b = min(4 * g + 4, g1);
+    const uint32_t q = a - q0;
     // owner: the last record whose first slot is <= q (every record here
     // has at least one pair, so the slots strictly increase)
     int lo = 0, hi = kGenRecs - 1;
@@ -484,14 +511,46 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_generate(
       const int mid = (lo + hi + 1) >> 1;
       if (s_pre[mid] <= q) lo = mid; else hi = mid - 1;
     }
-    const uint32_t k = q - s_pre[lo];
-    const uint32_t bw = s_bw[lo];
-    const uint32_t row = k / bw;
-    const uint32_t t = s_t0[lo] + row * s_tx[lo] + (k - row * bw);
-    const uint32_t g = s_p0[lo] + k;
-    tkey[q0 + q] = t;
-    gidx[q0 + q] = g;
-    ridx[q0 + q] = s_rid[lo];
+    uint32_t k = q - s_pre[lo], left = s_pre[lo + 1] - q, bw = s_bw[lo];
+    uint32_t row = k / bw, col = k - row * bw;
+    uint32_t t[4], gi[4], ri[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t at = 4 * g + (uint32_t)u;
+      if (at >= a && at < b) {
+        t[u] = s_t0[lo] + row * s_tx[lo] + col;
+        gi[u] = s_p0[lo] + k;
+        ri[u] = s_rid[lo];
+        ++k;
+        if (++col == bw) {
+          col = 0u;
+          ++row;
+        }
+        if (--left == 0u && at + 1 < b) {  // the next record begins
+          ++lo;
+          left = s_pre[lo + 1] - s_pre[lo];
+          bw = s_bw[lo];
+          k = row = col = 0u;
+        }
+      } else {
+        t[u] = gi[u] = ri[u] = 0u;
+      }
+    }
+    if (b - a == 4) {
+      reinterpret_cast<uint4*>(tkey)[g] = make_uint4(t[0], t[1], t[2], t[3]);
+      reinterpret_cast<uint4*>(gidx)[g] = make_uint4(gi[0], gi[1], gi[2], gi[3]);
+      reinterpret_cast<uint4*>(ridx)[g] = make_uint4(ri[0], ri[1], ri[2], ri[3]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t at = 4 * g + (uint32_t)u;
+        if (at >= a && at < b) {
+          tkey[at] = t[u];
+          gidx[at] = gi[u];
+          ridx[at] = ri[u];
+        }
+      }
+    }
   }
 }
 
@@ -518,6 +577,7 @@ struct RbBuffers {
   const int32_t* fl;
   uint32_t *tt, *poff, *vis, *dk[2], *rid[2], *tk[2], *gx[2], *rx[2], *hist, *dtot, *part;
   uint4 *pay, *spay;
+  uint2* items;
   RbEmit emit;
 };
 
@@ -539,6 +599,7 @@ RbBuffers rb_buffers(const Plan& P, void* ws) {
   B.part = ws_at<uint32_t>(ws, P.off_rb_part);
   B.pay = ws_at<uint4>(ws, P.off_rb_pay);
   B.spay = ws_at<uint4>(ws, P.off_rb_spay);
+  B.items = ws_at<uint2>(ws, P.off_rb_items);
   B.emit = RbEmit{ws_at<uint64_t>(ws, P.off_keys), ws_at<uint32_t>(ws, P.off_vals),
                   ws_at<uint32_t>(ws, P.off_sorted_rec), ws_at<uint32_t>(ws, P.off_rb_zrec),
                   nullptr, nullptr};
@@ -574,6 +635,10 @@ void rb_pass(const RbBuffers& B, hipStream_t s, const uint32_t* kin, const uint3
 // blocks) for a plan's record and pair capacities.
 int64_t rb_blocks(int64_t count) { return (count + kRbTile - 1) / kRbTile; }
 int64_t rb_gen_blocks(int64_t records) { return (records + kGenRecs - 1) / kGenRecs; }
+// Work items of the generation: each group's last item may be partial.
+int64_t rb_gen_items(int64_t records, int64_t pairs) {
+  return rb_gen_blocks(records) + pairs / kGenPairs;
+}
 int rb_max_radix() { return kRbMaxRadix; }
 
 // Steps 1-3 of the radix binning (after the binning scan, which kept the
@@ -601,9 +666,10 @@ hipError_t launch_rb_generate(const Plan& P, void* ws, hipStream_t s) {
   const int64_t gb = rb_gen_blocks(P.n_rec);
   hipLaunchKernelGGL(k_rb_gen_count, dim3((unsigned)gb), dim3(kRbThreads), 0, s, B.spay, B.fl,
                      B.part);
-  hipLaunchKernelGGL(k_rb_gen_scan, dim3(1), dim3(kRbThreads), 0, s, B.fl, B.part);
-  hipLaunchKernelGGL(k_rb_generate, dim3((unsigned)gb), dim3(kRbThreads), 0, s, B.spay, P.n,
-                     P.vt, B.fl, B.part, B.tk[0], B.gx[0], B.rx[0]);
+  hipLaunchKernelGGL(k_rb_gen_scan, dim3(1), dim3(kGenScanThreads), 0, s, B.fl, B.part, B.items);
+  hipLaunchKernelGGL(k_rb_generate, dim3((unsigned)rb_gen_items(P.n_rec, P.pair_cap)),
+                     dim3(kRbThreads), 0, s, B.spay, (uint32_t)P.n, P.vt, B.fl, B.part, B.items,
+                     B.tk[0], B.gx[0], B.rx[0]);
   return hipGetLastError();
 }
 

@@ -166,9 +166,10 @@ struct Plan {
   // radix binning (GS_RADIX_BIN): depth keys and record ids of the visible
   // records (two buffers each), tile keys, generation indices and record
   // ids of the pairs (two each), per-block digit counts, digit totals, and
-  // the pair offsets of blocks of depth-sorted records
+  // the pair offsets and work items of groups of depth-sorted records
   size_t off_rb_dkey[2], off_rb_rid[2], off_rb_tkey[2], off_rb_gidx[2], off_rb_ridx[2];
-  size_t off_rb_hist, off_rb_dtot, off_rb_part, off_rb_pay, off_rb_spay, off_rb_zrec;
+  size_t off_rb_hist, off_rb_dtot, off_rb_part, off_rb_items, off_rb_pay, off_rb_spay;
+  size_t off_rb_zrec;
   int64_t rb_rec_blocks, rb_pair_blocks;
   size_t ws_size;
 };
