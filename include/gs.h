@@ -66,10 +66,12 @@ typedef int32_t gs_status;
 #define GS_FUSED_L1 (1u << 1)         /* gs_render_bwd derives dL/dC, dL/dD from the L1
                                          loss against the targets instead of inputs */
 #define GS_ACCUMULATE_GRADS (1u << 2) /* gs_render_bwd adds into the gradient buffers */
-#define GS_PERSISTENT (1u << 3)       /* render kernels are resident and walk the
-                                         tiles in chunks with a static stride (in
+#define GS_PERSISTENT (1u << 3)       /* the pixel-wise backward is resident and walks
+                                         the tiles in chunks with a static stride (in
                                          either mode tiles with long lists run
-                                         first, the order gs_bin_sort writes) */
+                                         first, the order gs_bin_sort writes; the
+                                         forward always gives each block of pixels
+                                         a workgroup of its own) */
 #define GS_SPLAT_BWD (1u << 4)        /* splat-wise backward (Sec. III-C-1, Fig. 4a):
                                          the forward stores per-pixel (T, RGB, D) states
                                          at every 64th splat of a tile; the backward
@@ -111,7 +113,8 @@ typedef struct gs_raster_cfg {
   int32_t tile_w;       /* 8 or 16 */
   int32_t tile_h;       /* 8 or 16 (16x16, 16x8, 8x8) */
   int32_t chunk;        /* tiles per work item in GS_PERSISTENT mode, 1..16 */
-  int32_t lds_batch;    /* records staged in LDS per batch: 64, 128 or 256 */
+  int32_t lds_batch;    /* records staged in LDS per batch of the pixel-wise
+                           backward: 64, 128 or 256 */
   uint32_t flags;       /* GS_* flags above */
   float lambda_depth;   /* weight of the depth term of the fused L1 loss */
 } gs_raster_cfg;
@@ -203,8 +206,8 @@ gs_status gs_preprocess(const gs_plan* plan, const gs_gaussians* g, const float*
  * order, so the lists are unique and bit-exact.  Needs the per-tile and
  * per-chunk (64 Gaussians of a view) pair counts of the gs_preprocess call
  * just before on the same workspace.  Also writes the render kernels' work
- * order: tiles with at least 32 pairs first, in tile order, then the others
- * in reverse tile order (results do not depend on the order).
+ * order: the tiles by the length class of their lists, longest first
+ * (results do not depend on the order).
  * Overflow of the plan's pair capacity sets flag [0]. */
 gs_status gs_bin_sort(const gs_plan* plan, void* ws, void* stream);
 
@@ -486,8 +489,8 @@ gs_status gs_graph_time(gs_graph* graph, void* stream, int32_t warmup, int32_t r
  * `stream` at each mark below, synchronises, and writes the milliseconds
  * between consecutive marks: ms[r * (GS_N_MARKS - 1) + k] is the span from
  * mark k to mark k + 1 of rep r (host array of reps * (GS_N_MARKS - 1)).
- * A span whose launches the iteration does not make (no SSIM term, short
- * lists sorted by the forward) is the empty span between two marks. */
+ * A span whose launches the iteration does not make (no SSIM term) is the
+ * empty span between two marks. */
 #define GS_MARK_START 0
 #define GS_MARK_PREPROCESS 1       /* after the counter clear and the projection */
 #define GS_MARK_BIN_SCAN 2         /* after the binning's scans */

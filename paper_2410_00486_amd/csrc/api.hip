@@ -14,9 +14,8 @@
 namespace gs {
 hipError_t launch_preprocess(const Plan& P, const gs_gaussians& g, const float* cams, void* ws,
                              hipStream_t s);
-hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, bool defer_short_sorts = false,
+hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s,
                            const StepAdvance* step = nullptr, const Marks* marks = nullptr);
-TileSortArgs tile_sort_args(const Plan& P, void* ws);
 int64_t scan_rounds(const Plan& P);
 int64_t rb_blocks(int64_t count);
 int64_t rb_gen_blocks(int64_t records);
@@ -31,8 +30,7 @@ uint32_t* sorted_vals(const Plan& P, void* ws);
 hipError_t launch_render_fwd(const Plan& P, void* ws, const float* cams, float* color,
                              float* depth, float* T_final, uint32_t* last,
                              const float* target_rgb, const float* target_depth,
-                             float* loss_per_view, const uint32_t* order, int32_t* queue,
-                             int grid, hipStream_t s, const TileSortArgs& sort = TileSortArgs{});
+                             float* loss_per_view, hipStream_t s);
 hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const float* color,
                              const float* depth, const float* T_final, const uint32_t* last,
                              const float* dL_dcolor, const float* dL_ddepth,
@@ -47,7 +45,8 @@ hipError_t launch_adam(const gs_param_group* groups, int n_groups, int step, dou
                        int32_t* step_dev, hipStream_t s, const uint32_t* const* vis = nullptr,
                        const int32_t* per = nullptr, const int32_t* overflow = nullptr,
                        const AdamFold* fold = nullptr);
-int render_blocks_per_cu(const Plan& P, bool bwd);
+int render_bwd_blocks_per_cu(const Plan& P);
+int blocks_per_tile(const Plan& P);
 int splat_blocks_per_cu(const Plan& P);
 int64_t ssim_tiles(const Plan& P);
 size_t densify_tmp_bytes(int64_t n);
@@ -241,11 +240,13 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_sorted_rec = take(cap * 4);
   P->off_srec = take(tcap * sizeof(Rec));
   P->off_ranges = take(T * 2 * 4);
-  P->off_tile_last = take(T * 4);
-  P->off_tile_loss = take(T * 2 * 4);
+  // (per 8x8 block of pixels of a tile)
+  const size_t blocks8 = T * (size_t)(tw * th / 64);
+  P->off_tile_last = take(blocks8 * 4);
+  P->off_tile_loss = take(blocks8 * 2 * 4);
   P->off_grad_pair = take(cap * kPairGrad * 4);
   P->off_pose_part = take((size_t)n_views * std::max<int64_t>(P->proj_blocks, 1) * 6 * 8);
-  P->off_order = take(T * 4);
+  P->off_order = take(T * 4 * kOrderClasses);
   P->off_rec_terms = take(n_views > 1 ? nrec * 14 * 8 : 0);
   P->off_gp_tmp = take(n_views > 1 ? (size_t)n * 4 * 8 : 0);
   P->off_ssim_maps = take((size_t)pix * 9 * 4);
@@ -360,8 +361,9 @@ gs_status gs_bin_sort(const gs_plan* plan, void* ws, void* stream) {
   return hip_check(e, "gs_bin_sort");
 }
 
-static int persistent_grid(const Plan& P, bool bwd) {
-  const int per_cu = render_blocks_per_cu(P, bwd);
+// Grid of the persistent pixel-wise backward.
+static int persistent_grid(const Plan& P) {
+  const int per_cu = render_bwd_blocks_per_cu(P);
   const int64_t items = (P.vt.total_tiles + P.cfg.chunk - 1) / P.cfg.chunk;
   return (int)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)device_cus() * per_cu));
 }
@@ -376,16 +378,10 @@ gs_status gs_render_fwd(const gs_plan* plan, void* ws, const float* cams_dev, fl
   if (!cams_dev) return fail(GS_ERR_INVALID_ARG, "cams_dev is null");
   if (!color || !depth || !T_final || !last) return fail(GS_ERR_INVALID_ARG, "output image pointer is null");
   if (target_rgb && !loss_per_view) return fail(GS_ERR_INVALID_ARG, "target_rgb given without loss_per_view");
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool pers = (P.cfg.flags & GS_PERSISTENT) != 0;
-  int32_t* fl = ws_at<int32_t>(ws, P.off_flags);
-  hipError_t e = hipSuccess;
-  if (e == hipSuccess)
-    e = launch_render_fwd(P, ws, cams_dev, color, depth, T_final, last, target_rgb, target_depth,
-                          loss_per_view, ws_at<uint32_t>(ws, P.off_order),
-                          pers ? fl + F_QUEUE_FWD : nullptr,
-                          pers ? persistent_grid(P, false) : P.vt.total_tiles, s);
-  return hip_check(e, "gs_render_fwd");
+  return hip_check(launch_render_fwd(P, ws, cams_dev, color, depth, T_final, last, target_rgb,
+                                     target_depth, loss_per_view,
+                                     static_cast<hipStream_t>(stream)),
+                   "gs_render_fwd");
 }
 
 }  // extern "C"
@@ -413,7 +409,7 @@ gs_status gs_render_bwd_raster(const gs_plan* plan, void* ws, const float* cams_
   hipError_t e = hipSuccess;
   // splat-wise: grid-stride over the buckets, as many waves as stay resident
   const int grid = splat ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu(P)))
-                         : (pers ? persistent_grid(P, true) : P.vt.total_tiles);
+                         : (pers ? persistent_grid(P) : P.vt.total_tiles);
   if (e == hipSuccess)
     e = launch_render_bwd(P, ws, cams_dev, color, depth, T_final, last, dL_dcolor, dL_ddepth,
                           target_rgb, target_depth, fused ? 1 : 0, sorted_vals(P, ws),
@@ -777,7 +773,7 @@ static gs_status iteration_enqueue(const gs_iteration* it, void* stream, const M
     if (st != GS_OK) return st;
     if ((st = hip_check(mk.at(GS_MARK_PREPROCESS, strm), "timing mark")) != GS_OK) return st;
     if ((st = check_ws(P, it->ws)) != GS_OK) return st;
-    st = hip_check(launch_bin_sort(P, it->ws, strm, false, nullptr, marks), "gs_bin_sort");
+    st = hip_check(launch_bin_sort(P, it->ws, strm, nullptr, marks), "gs_bin_sort");
     if (st != GS_OK) return st;
     st = gs_render_fwd(it->plan, it->ws, it->cams_dev, it->color, it->depth, it->T_final, it->last,
                        ssim ? nullptr : it->target_rgb, ssim ? nullptr : it->target_depth,
@@ -869,8 +865,8 @@ static gs_status iteration_enqueue(const gs_iteration* it, void* stream, const M
   const bool fold_loss = !ssim && it->target_rgb && adam_elems > 0;
   if (fold_loss) {
     const ViewInfo& vi = P.vt.v[0];
-    fold.tile_loss = ws_at<float2>(it->ws, P.off_tile_loss) + vi.tile_off;
-    fold.loss_tiles = vi.tiles_x * vi.tiles_y;
+    fold.tile_loss = ws_at<float2>(it->ws, P.off_tile_loss) + (int64_t)vi.tile_off * blocks_per_tile(P);
+    fold.loss_tiles = vi.tiles_x * vi.tiles_y * blocks_per_tile(P);
     fold.loss_has_depth = it->target_depth ? 1 : 0;
     fold.loss_pixels = (double)vi.W * vi.H;
     fold.lambda_depth = P.cfg.lambda_depth;
@@ -883,22 +879,12 @@ static gs_status iteration_enqueue(const gs_iteration* it, void* stream, const M
   st = preprocess_enqueue(it->plan, &it->gaussians, it->cams_dev, it->ws, s, false);
   if (st != GS_OK) return st;
   if ((st = hip_check(mk.at(GS_MARK_PREPROCESS, s), "timing mark")) != GS_OK) return st;
-  // the binning leaves the short lists to the forward, which sorts each
-  // tile's list right before compositing it (one launch fewer; the sort's
-  // memory latency hides behind other wavefronts' compositing); its scan
-  // advances the Adam step unless the pairs overflow
-  hipError_t e = launch_bin_sort(P, it->ws, s, true, it->step_dev ? &adv : nullptr, marks);
-  TileSortArgs fwd_sort = tile_sort_args(P, it->ws);
-  fwd_sort.long_after = false;  // the long lists were sorted by the binning
+  // the binning's scan advances the Adam step unless the pairs overflow
+  hipError_t e = launch_bin_sort(P, it->ws, s, it->step_dev ? &adv : nullptr, marks);
   if (e != hipSuccess) return hip_check(e, "gs_iteration_enqueue (binning)");
-  const bool pers = (P.cfg.flags & GS_PERSISTENT) != 0;
-  int32_t* fl = ws_at<int32_t>(it->ws, P.off_flags);
-  e = launch_render_fwd(
-      P, it->ws, it->cams_dev, it->color, it->depth, it->T_final, it->last,
-      ssim ? nullptr : it->target_rgb, ssim ? nullptr : it->target_depth,
-      (ssim || fold_loss) ? nullptr : it->loss_per_view,
-      ws_at<uint32_t>(it->ws, P.off_order), pers ? fl + F_QUEUE_FWD : nullptr,
-      pers ? persistent_grid(P, false) : P.vt.total_tiles, s, fwd_sort);
+  e = launch_render_fwd(P, it->ws, it->cams_dev, it->color, it->depth, it->T_final, it->last,
+                        ssim ? nullptr : it->target_rgb, ssim ? nullptr : it->target_depth,
+                        (ssim || fold_loss) ? nullptr : it->loss_per_view, s);
   if (e == hipSuccess) e = mk.at(GS_MARK_FORWARD, s);
   if (e != hipSuccess) return hip_check(e, "gs_iteration_enqueue (forward)");
   const float* gC = it->dL_dcolor;

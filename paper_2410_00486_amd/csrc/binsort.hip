@@ -10,12 +10,11 @@
 // list at an atomically taken slot with the key (depth bits << 32 |
 // generation index); a per-tile sort orders those keys (one wavefront per
 // tile: ranks in registers up to 64 keys, a bitonic network in LDS up to
-// 128; longer lists go to 1024-thread blocks, in LDS up to 8192 keys and in
-// global memory beyond).  Four launches whatever the pair count, no
+// 128; longer lists take a wavefront, or a 1024-thread block, each).  No
 // spin-waits; graph-capturable.
 //
-// The scan block also writes the work order of the render kernels: tiles
-// with long lists first.  The general stable LSD
+// The scan also writes the work order of the render kernels: tiles with long
+// lists first.  The general stable LSD
 // radix sort (8-bit digits, wave64 ballot ranking) below serves the
 // standalone key/value sort.
 #include "tilesort.h"
@@ -70,7 +69,7 @@ struct ScanArgs {
   uint32_t* boff;          // splat-wise only (else null): bucket offset per tile, [T] = total
   uint32_t* fstart;        // position of the tile's first full bucket in queue 0
   uint32_t* hstart;        // position of the tile's half bucket in queue 1
-  uint32_t* order;         // work order of the render kernels, longest tiles first
+  uint32_t* order;         // work order of the render kernels: kOrderClasses rows of T
   uint4* long_list;        // (tile, list start, pairs, -) of the lists for the long-list sort
   // kScanBoth: chunks and tile counts (the projection's); kScanChunks: the
   // chunks alone (radix binning, before the pairs exist); kScanTiles: the
@@ -80,11 +79,15 @@ struct ScanArgs {
 };
 constexpr int kScanBoth = 0, kScanChunks = 1, kScanTiles = 2;
 
-// Work order of the render kernels: tiles with at least kLongTile pairs
-// first (in tile order), then the others (in reverse tile order), so that
-// the long lists start in the first round of the dispatch and the tail is
-// made of short ones.  Both positions come out of the scan.
-constexpr uint32_t kLongTile = 32;
+// Work order of the render kernels: the tiles by the length class of their
+// lists, longest class first, in tile order within a class.  A wavefront
+// composites a list serially, so what matters is that the longest ones start
+// first.  A class has a row of its own in `order` (a tile's position in it
+// is the scan's count of the class before it) and its size in the flags.
+__device__ __forceinline__ int order_class(uint32_t c) {
+  return c > 1024 ? 0 : c > 512 ? 1 : c > 256 ? 2 : c > kTileSortSmall ? 3 : c > 48 ? 4 : 5;
+}
+static_assert(kTileSortSmall == 128 && kOrderClasses == 6, "classes 0..3 are the long-list sort's");
 
 // Block-wide exclusive scan of N64 64-bit and N32 32-bit per-thread sums
 // (replaced by the thread's start); the carries (uniform) are added and
@@ -165,12 +168,37 @@ __device__ __forceinline__ void store4(uint32_t* __restrict__ a, int64_t i, int6
   if (i + 2 < n) a[i + 2] = x.z;
 }
 
+// The 32-bit channels of a round, scanned packed: a round has at most
+// kTileRound tiles, so its class and half-bucket counts fit 16 bits and go
+// two to a word (five words scanned instead of eight: the one-block scan of
+// a small plan is a chain of these).  s: per-thread sums in, exclusive
+// starts out (the carries c added); c advanced by the round's totals.
+template <int N64, int N32>
+__device__ __forceinline__ void round_exscan(uint64_t (&s64)[N64], uint32_t (&s)[N32],
+                                             uint64_t (&c64)[N64], uint32_t (&c)[N32],
+                                             uint64_t* w64, uint32_t* w32) {
+  static_assert(N32 == 8 && kTileRound < 65536, "buckets, half, visible, five classes");
+  uint32_t p[5] = {s[0], s[2], s[1] | s[3] << 16, s[4] | s[5] << 16, s[6] | s[7] << 16};
+  uint32_t t[5] = {};
+  block_exscan<N64, 5>(s64, p, c64, t, w64, w32);
+  const uint32_t e[8] = {p[0], p[2] & 0xFFFFu, p[1], p[2] >> 16, p[3] & 0xFFFFu, p[3] >> 16,
+                         p[4] & 0xFFFFu, p[4] >> 16};
+  const uint32_t d[8] = {t[0], t[2] & 0xFFFFu, t[1], t[2] >> 16, t[3] & 0xFFFFu, t[3] >> 16,
+                         t[4] & 0xFFFFu, t[4] >> 16};
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    s[k] = c[k] + e[k];
+    c[k] += d[k];
+  }
+}
+
 // Per-thread inputs of one round: 4 * kScanVec tiles and 2 * kScanVec
 // chunks, and the thread's sums over them.  Channels: 64-bit tile pairs and
-// chunk pairs; 32-bit buckets, half buckets, visible records, tiles with at
-// least kLongTile pairs (work order), lists longer than kTileSortSmall
-// (long-list sort).
-constexpr int kScanN32 = 5;
+// chunk pairs; 32-bit buckets, half buckets, visible records, and the tiles
+// of each length class but the last (work order; the first four together are
+// the lists of the long-list sort).
+constexpr int kScanClass = 3;
+constexpr int kScanN32 = kScanClass + kOrderClasses - 1;
 struct ScanRound {
   static constexpr int NT = 4 * kScanVec, NC = 2 * kScanVec;
   int64_t it, ic;  // first tile and first chunk of the thread
@@ -206,8 +234,9 @@ __device__ __forceinline__ void scan_load(const ScanArgs& A, int64_t r, ScanRoun
     R.s64[0] += R.tc[k];
     R.s32[0] += R.nb[k];
     R.s32[1] += R.h[k];
-    R.s32[3] += R.tc[k] >= kLongTile ? 1u : 0u;
-    R.s32[4] += R.tc[k] > kTileSortSmall ? 1u : 0u;
+    const int oc = order_class(R.tc[k]);
+#pragma unroll
+    for (int c = 0; c < kOrderClasses - 1; ++c) R.s32[kScanClass + c] += oc == c ? 1u : 0u;
   }
 #pragma unroll
   for (int k = 0; k < ScanRound::NC; ++k) {
@@ -230,21 +259,29 @@ __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
     for (int e = 0; e < 4; ++e) {
       const int64_t t = R.it + 4 * k + e;
       const uint32_t c = R.tc[4 * k + e];
-      // work order: long tiles from the front, the others from the back
-      // (both positions follow from the long tiles before t)
-      if (t < T)
-        A.order[c >= kLongTile ? R.s32[3] : (uint32_t)(T - 1 - (t - R.s32[3]))] = (uint32_t)t;
-      // lists too long for one wavefront: listed for the long-list sort
+      // work order: the tile's place in its class (the last class takes the
+      // tiles that none of the others counts)
+      const int oc = order_class(c);
+      uint32_t counted = 0, place = 0;
+#pragma unroll
+      for (int k5 = 0; k5 < kOrderClasses - 1; ++k5) {
+        counted += R.s32[kScanClass + k5];
+        place = oc == k5 ? R.s32[kScanClass + k5] : place;
+      }
+      if (oc == kOrderClasses - 1) place = (uint32_t)t - counted;
+      if (t < T) A.order[(int64_t)oc * T + place] = (uint32_t)t;
+      // lists for the long-list sort (in tile order)
       if (t < T && c > kTileSortSmall)
-        A.long_list[R.s32[4]] = make_uint4((uint32_t)t, (uint32_t)R.s64[0], c, 0u);
+        A.long_list[R.s32[kScanClass] + R.s32[kScanClass + 1] + R.s32[kScanClass + 2] +
+                    R.s32[kScanClass + 3]] = make_uint4((uint32_t)t, (uint32_t)R.s64[0], c, 0u);
       ts[e] = (uint32_t)R.s64[0];
       bs[e] = R.s32[0];
       hs[e] = R.s32[1];
       R.s64[0] += c;
       R.s32[0] += R.nb[4 * k + e];
       R.s32[1] += R.h[4 * k + e];
-      R.s32[3] += c >= kLongTile ? 1u : 0u;
-      R.s32[4] += c > kTileSortSmall ? 1u : 0u;
+#pragma unroll
+      for (int k5 = 0; k5 < kOrderClasses - 1; ++k5) R.s32[kScanClass + k5] += oc == k5 ? 1u : 0u;
     }
     store4(A.tstart, R.it + 4 * k, T, make_uint4(ts[0], ts[1], ts[2], ts[3]));
     // the scatter's cursors start at zero; the radix binning's per-tile
@@ -273,10 +310,14 @@ __device__ __forceinline__ void scan_finish(const ScanArgs& A, const uint64_t (&
                                             const uint32_t (&c32)[kScanN32], int64_t cap,
                                             int32_t* __restrict__ fl, const StepAdvance& st) {
   const bool splat = A.boff != nullptr;
+  const uint32_t long_lists =
+      c32[kScanClass] + c32[kScanClass + 1] + c32[kScanClass + 2] + c32[kScanClass + 3];
+  if (A.mode != kScanChunks)
+    for (int c = 0; c < kOrderClasses - 1; ++c) fl[F_CLASS + c] = (int32_t)c32[kScanClass + c];
   if (A.mode == kScanTiles) {
     // the pair totals were settled by the chunk scan before
     const bool over = fl[F_OVERFLOW] != 0;
-    fl[F_LONG_TILES] = over ? 0 : (int32_t)c32[4];
+    fl[F_LONG_TILES] = over ? 0 : (int32_t)long_lists;
     fl[F_BQ_FULL] = (over || !splat) ? 0 : (int32_t)(c32[0] - c32[1]);
     fl[F_BQ_HALF] = (over || !splat) ? 0 : (int32_t)c32[1];
     if (splat) A.boff[A.n_tiles] = c32[0];
@@ -295,7 +336,7 @@ __device__ __forceinline__ void scan_finish(const ScanArgs& A, const uint64_t (&
   if (!chunks_only) {
     // the bucket queues are filled by the tile sort at the positions scanned
     // here; the long lists are sorted by their own kernel (none on overflow)
-    fl[F_LONG_TILES] = (int32_t)c32[4];
+    fl[F_LONG_TILES] = (int32_t)long_lists;
     fl[F_BQ_FULL] = (over || !splat) ? 0 : (int32_t)(c32[0] - c32[1]);
     fl[F_BQ_HALF] = (over || !splat) ? 0 : (int32_t)c32[1];
     if (splat) A.boff[A.n_tiles] = c32[0];
@@ -313,14 +354,14 @@ __global__ void __launch_bounds__(kScanBlock) k_scans(ScanArgs A, int64_t cap,
   __shared__ uint64_t w64[2 * (NW + 1)];
   __shared__ uint32_t w32[kScanN32 * (NW + 1)];
   uint64_t c64[2] = {0, 0};
-  uint32_t c32[kScanN32] = {0, 0, 0, 0, 0};
+  uint32_t c32[kScanN32] = {};
   const int64_t rt = (A.n_tiles + kTileRound - 1) / kTileRound;
   const int64_t rc = (A.n_chunks + kChunkRound - 1) / kChunkRound;
   const int64_t rounds = rt > rc ? rt : rc;
   for (int64_t r = 0; r < rounds; ++r) {
     ScanRound R;
     scan_load(A, r, R);
-    block_exscan<2, kScanN32>(R.s64, R.s32, c64, c32, w64, w32);
+    round_exscan(R.s64, R.s32, c64, c32, w64, w32);
     scan_emit(A, R);
   }
   if (threadIdx.x == 0) scan_finish(A, c64, c32, cap, fl, st);
@@ -341,10 +382,10 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_reduce(ScanArgs A,
   __shared__ uint64_t w64[2 * (NW + 1)];
   __shared__ uint32_t w32[kScanN32 * (NW + 1)];
   uint64_t c64[2] = {0, 0};
-  uint32_t c32[kScanN32] = {0, 0, 0, 0, 0};
+  uint32_t c32[kScanN32] = {};
   ScanRound R;
   scan_load(A, blockIdx.x, R);
-  block_exscan<2, kScanN32>(R.s64, R.s32, c64, c32, w64, w32);  // c64 / c32: block totals
+  round_exscan(R.s64, R.s32, c64, c32, w64, w32);  // c64 / c32: block totals
   if (threadIdx.x == 0) {
     ScanPart p;
     p.p64[0] = c64[0];
@@ -363,11 +404,11 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_top(ScanArgs A, ScanPart* _
   __shared__ uint64_t w64[2 * (NW + 1)];
   __shared__ uint32_t w32[kScanN32 * (NW + 1)];
   uint64_t c64[2] = {0, 0};
-  uint32_t c32[kScanN32] = {0, 0, 0, 0, 0};
+  uint32_t c32[kScanN32] = {};
   for (int64_t base = 0; base < n_parts; base += kScanBlock) {
     const int64_t i = base + threadIdx.x;
     uint64_t s64[2] = {0, 0};
-    uint32_t s32[kScanN32] = {0, 0, 0, 0, 0};
+    uint32_t s32[kScanN32] = {};
     if (i < n_parts) {
       const ScanPart p = part[i];
       s64[0] = p.p64[0];
@@ -401,7 +442,7 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_down(ScanArgs A,
   for (int c = 0; c < kScanN32; ++c) c32[c] = p.p32[c];
   ScanRound R;
   scan_load(A, blockIdx.x, R);
-  block_exscan<2, kScanN32>(R.s64, R.s32, c64, c32, w64, w32);
+  round_exscan(R.s64, R.s32, c64, c32, w64, w32);
   scan_emit(A, R);
 }
 
@@ -492,7 +533,7 @@ __global__ void __launch_bounds__(256) k_scatter(
 
 __global__ void __launch_bounds__(kWave) k_tile_sort(TileSortArgs A) {
   __shared__ uint64_t sk[kTileSortSmall];
-  (void)sort_tile_wave(A, blockIdx.x, threadIdx.x, sk);
+  sort_tile_wave(A, blockIdx.x, threadIdx.x, sk);
 }
 
 // Lists of kTileSortSmall + 1 .. kTileSortMid pairs: one wavefront per list
@@ -501,8 +542,8 @@ __global__ void __launch_bounds__(kWave) k_tile_sort(TileSortArgs A) {
 // of a lane's positions looked up in one round trip.
 constexpr int kMidWaves = 4;
 __global__ void __launch_bounds__(kMidWaves * kWave) k_tile_sort_mid(
-    uint32_t* __restrict__ cnt, const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
-    const uint64_t* __restrict__ skey, TileSortOut out, int clear) {
+    const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
+    const uint64_t* __restrict__ skey, TileSortOut out) {
   __shared__ uint64_t sk_all[kMidWaves][kTileSortMid];
   const int w = threadIdx.x / kWave, lane = lane_id();
   uint64_t* sk = sk_all[w];
@@ -544,14 +585,12 @@ __global__ void __launch_bounds__(kMidWaves * kWave) k_tile_sort_mid(
       }
     }
     wave_lds_sync();  // every key read before the next list overwrites them
-    // counter consumed (when the per-tile pass ran before this kernel)
-    if (clear && lane == 0) cnt[t] = 0u;
   }
 }
 
 __global__ void __launch_bounds__(kLongThreads) k_tile_sort_long(
-    uint32_t* __restrict__ cnt, const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
-    uint64_t* __restrict__ skey, TileSortOut out, int clear) {
+    const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
+    uint64_t* __restrict__ skey, TileSortOut out) {
   __shared__ uint64_t sk[kTileSortLong];
   const int n_long = fl[F_OVERFLOW] ? 0 : fl[F_LONG_TILES];
   for (int li = blockIdx.x; li < n_long; li += gridDim.x) {
@@ -571,8 +610,6 @@ __global__ void __launch_bounds__(kLongThreads) k_tile_sort_long(
         emit_sorted(out, start + k, tkey, skey[start + k]);
     }
     __syncthreads();  // the LDS is reused by the next list
-    // counter consumed (when the per-tile pass ran before this kernel)
-    if (clear && threadIdx.x == 0) cnt[t] = 0u;
   }
 }
 
@@ -810,9 +847,8 @@ hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Arguments of the per-tile sort (k_tile_sort, or the forward of a whole
-// iteration, which sorts its tiles itself).
-TileSortArgs tile_sort_args(const Plan& P, void* ws) {
+// Arguments of the per-tile sort.
+static TileSortArgs tile_sort_args(const Plan& P, void* ws) {
   const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
   TileSortArgs A{};
   A.cnt = ws_at<uint32_t>(ws, P.off_tile_cnt);
@@ -830,15 +866,11 @@ TileSortArgs tile_sort_args(const Plan& P, void* ws) {
   A.bq = splat ? ws_at<uint2>(ws, P.off_bq) : nullptr;
   A.bq_stride = P.ckpt_slots;
   A.presorted = radix;
-  A.long_after = !A.presorted;
   return A;
 }
 
-// defer_short_sorts: the lists of at most kTileSortSmall pairs are left to
-// the forward (a whole iteration), which sorts each tile before compositing
-// it; the long lists are sorted here in either case.
-hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, bool defer_short_sorts,
-                           const StepAdvance* step, const Marks* marks) {
+hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdvance* step,
+                           const Marks* marks) {
   const Marks none{};
   const Marks& mk = marks ? *marks : none;
   int32_t* fl = ws_at<int32_t>(ws, P.off_flags);
@@ -887,8 +919,8 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, bool defer_sh
     // records by depth, their pairs in that order, then the pairs by tile;
     // the list starts and ends found in the sorted keys give the per-tile
     // counts (the projection counted none), scanned like the projection's;
-    // the per-tile pass (here, or the forward's when deferred) writes the
-    // ranges and queue entries and zeroes the counters
+    // the per-tile pass writes the ranges and queue entries and zeroes the
+    // counters
     if ((e = launch_rb_generate(P, ws, s)) != hipSuccess) return e;
     if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;
     if ((e = launch_rb_tile_sort(P, ws, s)) != hipSuccess) return e;
@@ -898,7 +930,7 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, bool defer_sh
     st.n_chunks = 0;
     st.mode = kScanTiles;
     scan(st, StepAdvance{});
-    if (T > 0 && !defer_short_sorts) {
+    if (T > 0) {
       hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)T), dim3(kWave), 0, s, tile_sort_args(P, ws));
     }
     if ((e = mk.at(GS_MARK_BIN_LONG_SORT, s)) != hipSuccess) return e;
@@ -915,22 +947,21 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, bool defer_sh
   }
   if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;
   if (T > 0) {
-    // the per-tile pass (here, or the forward's when deferred) and the
-    // long-list kernel each zero the counters they consume, so that every
-    // counter is zero again after the binning of an iteration
+    // the per-tile pass zeroes the counters, so that every counter is zero
+    // again after the binning of an iteration
     const TileSortArgs A = tile_sort_args(P, ws);
-    if (!defer_short_sorts) hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)T), dim3(kWave), 0, s, A);
+    hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)T), dim3(kWave), 0, s, A);
     if ((e = mk.at(GS_MARK_BIN_SHORT_SORT, s)) != hipSuccess) return e;
     // lists up to kTileSortMid pairs: a wavefront each; longer: a block each
     // (at most one long list per kTileSortSmall + 1 pairs of capacity; five
     // workgroups per CU are resident, the waves loop over the lists)
     const int64_t max_long = std::min<int64_t>(T, P.pair_cap / (kTileSortSmall + 1) + 1);
     const int mid_grid = (int)std::min<int64_t>((max_long + kMidWaves - 1) / kMidWaves, 1280);
-    hipLaunchKernelGGL(k_tile_sort_mid, dim3((unsigned)mid_grid), dim3(kMidWaves * kWave), 0, s,
-                       tcnt, fl, long_list, skey, A.out, defer_short_sorts ? 0 : 1);
+    hipLaunchKernelGGL(k_tile_sort_mid, dim3((unsigned)mid_grid), dim3(kMidWaves * kWave), 0, s, fl,
+                       long_list, skey, A.out);
     const int long_grid = (int)std::min<int64_t>(T, 512);  // two blocks per CU
     hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)long_grid), dim3(kLongThreads), 0, s,
-                       tcnt, fl, long_list, skey, A.out, defer_short_sorts ? 0 : 1);
+                       fl, long_list, skey, A.out);
   } else if ((e = mk.at(GS_MARK_BIN_SHORT_SORT, s)) != hipSuccess) {
     return e;
   }

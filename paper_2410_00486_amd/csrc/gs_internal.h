@@ -30,8 +30,11 @@ enum Flag : int {
   F_BQ_HALF = 9,     // splat-wise buckets with at most 32 pairs
   F_NF_ACC = 10,     // non-finite Gaussians counted by the projection, published
                      // in F_NONFINITE (and cleared) by the binning scan
+  F_CLASS = 11,      // tiles of each length class of the work order but the last
   F_COUNT = 16
 };
+// Length classes of the render kernels' work order (longest lists first).
+constexpr int kOrderClasses = 6;
 
 // Per-view geometry of the tile grid and of the concatenated image buffers.
 struct ViewInfo {
@@ -75,10 +78,14 @@ constexpr double kLn2 = 0.6931471805599453;    // ln(2), its inverse
 // Base-2 exponent of record r at offset (dx, dy) = mean - sample point (the
 // FP64 difference rounded to FP32): the splat's opacity times its Gaussian
 // is 2^that.  Never above lo <= 0.
+__device__ __forceinline__ float exponent(float t, float s1, float s2, float lo, float dx,
+                                          float dy) {
+  const float p = fmaf(t, dy, dx), q = fmaf(-t, dx, dy);
+  const float u = s1 * p, w = s2 * q;
+  return fmaf(-u, p, fmaf(-w, q, lo));
+}
 __device__ __forceinline__ float rec_exponent(const Rec& r, float dx, float dy) {
-  const float p = fmaf(r.t, dy, dx), q = fmaf(-r.t, dx, dy);
-  const float u = r.s1 * p, w = r.s2 * q;
-  return fmaf(-u, p, fmaf(-w, q, r.lo));
+  return exponent(r.t, r.s1, r.s2, r.lo, dx, dy);
 }
 
 // The conic [[a, b], [b, c]] of record r (natural exponent -d^T Q d / 2),
@@ -97,9 +104,8 @@ __device__ __forceinline__ void rec_conic(const Rec& r, float& a, float& b, floa
 struct RecSrc {
   const Rec* base;
   const uint32_t* idx;
-  __device__ __forceinline__ const Rec* at(uint32_t k) const {
-    return idx ? base + idx[k] : base + k;
-  }
+  __device__ __forceinline__ uint32_t id(uint32_t k) const { return idx ? idx[k] : k; }
+  __device__ __forceinline__ const Rec* at(uint32_t k) const { return base + id(k); }
 };
 
 // Per-pair gradient partial written by the backward raster kernel:
@@ -128,6 +134,20 @@ __device__ __forceinline__ void store_pair(float* gp, int64_t k, float4 a, float
   p[2] = make_float2(b.x, b.y);
   p[3] = make_float2(b.z, b.w);
   p[4] = c;
+}
+
+// Tile at place `slot` of the work order: the classes in turn.  (Uniform
+// operands: scalar loads.)
+__device__ __forceinline__ int order_tile(const uint32_t* __restrict__ order,
+                                          const int32_t* __restrict__ fl, int n_tiles,
+                                          uint32_t slot) {
+  int c = 0;
+  for (; c < kOrderClasses - 1; ++c) {
+    const uint32_t m = (uint32_t)fl[F_CLASS + c];
+    if (slot < m) break;
+    slot -= m;
+  }
+  return (int)order[(int64_t)c * n_tiles + slot];
 }
 
 struct Plan {

@@ -1,23 +1,34 @@
 // a3-a5: per-tile compositing (Eq. (1)), its pixel-wise backward
-// (Eqs. (2)-(4)) and the splat-wise backward (Sec. III-C-1, below).  One wave64 per tile: a lane owns PPL = tile pixels / 64
-// pixels (2x2 quads on 16x16 tiles, horizontal pairs on 16x8, one pixel on
-// 8x8), so the per-Gaussian work that does not depend on the pixel -- the
-// LDS read of the record, the wavefront reduction of the backward -- is
-// shared by up to 256 pixels.  Single-wave workgroups need no workgroup
-// barriers beyond LDS reuse, and many of them fit a CU.
+// (Eqs. (2)-(4)) and the splat-wise backward (Sec. III-C-1, below).
 //
-// Forward: records of the tile's depth-sorted list are staged in LDS in
-// batches; every lane walks the batch front to back for each of its pixels.
-// The wavefront leaves as soon as the ballot of lanes with an unfinished
-// pixel is empty.
+// Forward: one wave64 per 8x8 block of pixels, one pixel per lane.  The
+// tile's depth-sorted list is taken in batches of 64: a lane holds one
+// record, forms its offsets from the block's columns and rows of sample
+// points, and drops it when it is below alpha 1/255 over the whole block (a
+// tile box is the axis-aligned box of an ellipse: 18-22 % of the pairs of
+// 8x8 tiles reach no pixel of theirs, 55 % of the blocks of a 16x16 tile's
+// pairs).  What is left goes to LDS in list order and every lane walks it
+// front to back.  The wavefront leaves when every pixel has stopped.
 //
-// Backward: back to front from the tile's last used position.  Each lane
+// Measured (forward kernel, before -> after): 1200x680 view in 16x16 tiles,
+// 627k pairs: 398 -> 69 us (before: one wavefront per 16x16 tile, four
+// pixels per lane); four such views, 2.7M pairs: 778 -> 188 us; 8x8 tiles:
+// 16 views, 25M pairs: 1443 -> 860 us; 8 mixed views, 6.0M pairs: 579 ->
+// 338 us (the longest list, 4562 pairs, is one wavefront's serial work).
+// Bound by VALU issue (about 80 instructions for four splats of 64 pixels)
+// and, for the longest lists, by the latency of one wavefront.
+//
+// Backward (pixel-wise): one wave64 per tile, a lane owns PPL = tile pixels /
+// 64 pixels (2x2 quads on 16x16 tiles, horizontal pairs on 16x8, one pixel
+// on 8x8); back to front from the tile's last used position.  Each lane
 // recomputes alpha with the forward's code (so every skip decision is the
 // forward's), undoes the transmittance by division from T_final and keeps
 // the sums of what lies behind.  The ten per-pair partial gradients of a
 // Gaussian are summed over the lane's pixels, then over the wavefront with
 // DPP (skipped when no lane contributes), and written to the pair's own
 // slot: no atomics, deterministic.
+#include <type_traits>
+
 #include "tilesort.h"
 
 namespace gs {
@@ -123,41 +134,122 @@ __device__ __forceinline__ int find_view(const ViewTable& vt, int gtile) {
 
 // Records of a tile list: a copy in list order written by the per-tile
 // binning, so that a batch is one contiguous, coalesced read, or (radix
-// binning) gathered from the record array by record id.  fresh (a copy
-// only): the records were written by this wavefront in this kernel, so they
-// are read at device scope, past the vector L1 (which may hold an older copy
-// of the line, loaded for a neighbouring tile).
+// binning) gathered from the record array by record id.
 __device__ __forceinline__ void stage(Rec* srec, uint32_t* sval, RecSrc lrec,
                                       const uint32_t* __restrict__ sorted_vals, uint32_t first,
-                                      int count, int lane, bool fresh = false) {
+                                      int count, int lane) {
   for (int k = lane; k < count; k += kWave) {
-    uint64_t* dst = reinterpret_cast<uint64_t*>(srec + k);
-    if (fresh) {
-      const uint64_t* src = reinterpret_cast<const uint64_t*>(lrec.base + first + k);
-      uint64_t w[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-        w[q] = __hip_atomic_load(src + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) dst[q] = w[q];
-    } else {
-      const float4* src = reinterpret_cast<const float4*>(lrec.at(first + k));
-      float4* d4 = reinterpret_cast<float4*>(dst);
-      const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-      d4[0] = a0; d4[1] = a1; d4[2] = a2; d4[3] = a3;
-    }
-    if (sval) sval[k] = sorted_vals[first + k];
+    const float4* src = reinterpret_cast<const float4*>(lrec.at(first + k));
+    float4* dst = reinterpret_cast<float4*>(srec + k);
+    const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
+    dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
+    sval[k] = sorted_vals[first + k];
   }
 }
 
 // ------------------------------------------------------------------ forward
-// Splats per step of the forward's compositing loop.
-constexpr int kFwdSplats = 4;
+// A wavefront composites one 8x8 block of pixels ("sub-tile", one pixel per
+// lane): the whole tile of 8x8 plans, one of the two or four blocks of 16x8
+// and 16x16 tiles (a wavefront per tile there left 3225 wavefronts for a
+// 1200x680 view, three per SIMD, and the longest list set the time).
+constexpr int kSub = 8;
+template <int TW, int TH>
+constexpr int sub_tiles() {
+  return TW * TH / (kSub * kSub);
+}
+
+// Unit u of the forward's grid -> (slot of the work order, sub-tile).  The
+// sub-tiles of a tile read the same list: consecutive workgroups go to the
+// eight XCDs in turn, so a tile's sub-tiles are eight units apart, on one
+// XCD's L2.
+template <int NS>
+__device__ __forceinline__ void unit_of(uint32_t u, uint32_t n_tiles, uint32_t& slot,
+                                        uint32_t& sub) {
+  if constexpr (NS == 1) {
+    slot = u;
+    sub = 0;
+  } else {
+    const uint32_t full = n_tiles / 8 * 8;
+    if (u < full * NS) {
+      const uint32_t q = u / 8;
+      slot = q / NS * 8 + u % 8;
+      sub = q % NS;
+    } else {  // the last tiles, fewer than eight
+      const uint32_t q = u - full * NS;
+      slot = full + q / NS;
+      sub = q % NS;
+    }
+  }
+}
+
+// The largest last position over a tile's sub-tiles.
+template <int NS>
+__device__ __forceinline__ uint32_t tile_last_of(const uint32_t* __restrict__ tile_last,
+                                                 int gtile) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int k = 0; k < NS; ++k) m = max(m, tile_last[(int64_t)gtile * NS + k]);
+  return m;
+}
+
+// What the compositing reads of a record.
+struct FwdRec {
+  double mx, my;
+  float t, s1, s2, lo, z, r, g, b;
+};
+static_assert(sizeof(FwdRec) == 48 && offsetof(Rec, b) == 44, "first 48 bytes of a record");
+
+// Highest exponent (base 2) at which a splat may still be skipped as a
+// whole: alpha < 1/255 is an exponent below -7.9944, so what lies under -8
+// is skipped at every pixel by the alpha test as well, whatever the rounding
+// of either (about 1e-6 of the exponent).
+constexpr float kCullExp = -8.0f;
+// Above this log2(opacity) the clamp at 0.99 can act (log2(0.99) = -0.0145).
+constexpr float kClampLo = -0.0146f;
+
+// Upper bound of the splat's exponent over the sample points of a block of
+// pixels whose offsets (mean - sample point) span [xl, xh] x [yl, yh].  The
+// quadratic's minimum over the rectangle is 0 when it holds the origin, and
+// otherwise lies on an edge that faces the origin: the nearest x (y) of the
+// rectangle with the best y (x) on it.  Both candidates lie in the
+// rectangle, and near the best point an error of the argument is of second
+// order, so the bound holds to the rounding of the exponent itself.
+__device__ __forceinline__ float max_exponent(const FwdRec& r, float xl, float xh, float yl,
+                                              float yh) {
+  const float tt = r.t * r.t;
+  const float ca = fmaf(r.s2, tt, r.s1), cb = r.t * (r.s1 - r.s2), cc = fmaf(r.s1, tt, r.s2);
+  const float x0 = fminf(fmaxf(0.0f, xl), xh), y0 = fminf(fmaxf(0.0f, yl), yh);
+  const float y1 = fminf(fmaxf(-cb * x0 * __builtin_amdgcn_rcpf(cc), yl), yh);
+  const float x1 = fminf(fmaxf(-cb * y0 * __builtin_amdgcn_rcpf(ca), xl), xh);
+  auto quad = [&](float dx, float dy) {
+    const float p = fmaf(r.t, dy, dx), q = fmaf(-r.t, dx, dy);
+    return fmaf(r.s1 * p, p, r.s2 * q * q);
+  };
+  return r.lo - fminf(quad(x0, y1), quad(x1, y0));
+}
+
+// LDS of one forward wavefront: the batch's splats that can reach the
+// sub-tile, in list order.  The offsets of a splat from the block's eight
+// columns and eight rows of sample points are formed once per splat, in
+// FP64, and rounded to FP32 -- the values each evaluation used to form for
+// itself (two FP64 differences and two conversions, 20 of its about 92
+// issue cycles).  A lane reads the offsets of four splats from its own
+// column and row at once; rows of 68 floats keep the eight columns' 16-byte
+// reads on different banks.
+constexpr int kFwdSplats = 4;  // splats per step of the compositing loop
+constexpr int kOffStride = kWave + 4;
+struct FwdLds {
+  float dx[kSub][kOffStride], dy[kSub][kOffStride];
+  float4 shape[kWave];   // t, s1, s2, lo
+  float4 colour[kWave];  // r, g, b, z
+  uint32_t pos[kWave];   // 1 + position in the tile's list
+};
+
 template <int TW, int TH, bool CKPT>
-__device__ __forceinline__ void fwd_tile(int gtile, RecSrc lrec,
+__device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
                                          const uint32_t* __restrict__ ranges,
                                          const float* __restrict__ cams, const ViewTable& vt,
-                                         int B, float* __restrict__ color,
+                                         float* __restrict__ color,
                                          float* __restrict__ depth, float* __restrict__ T_final,
                                          uint32_t* __restrict__ last,
                                          uint32_t* __restrict__ tile_last,
@@ -165,214 +257,236 @@ __device__ __forceinline__ void fwd_tile(int gtile, RecSrc lrec,
                                          const float* __restrict__ target_depth,
                                          float* __restrict__ tile_loss,
                                          const uint32_t* __restrict__ boff,
-                                         float* __restrict__ ckpt, Rec* srec,
-                                         const TileList* known = nullptr) {
-  using TG = Tile<TW, TH>;
-  constexpr int PPL = TG::PPL;
-  constexpr int NPX = TG::NPX;
+                                         float* __restrict__ ckpt, FwdLds& S) {
+  constexpr int NPX = TW * TH, NS = sub_tiles<TW, TH>();
   const int v = find_view(vt, gtile);
   const ViewInfo vi = vt.v[v];
   const int lt = gtile - vi.tile_off;
-  const int tx0 = (lt % vi.tiles_x) * TW, ty0 = (lt / vi.tiles_x) * TH;
   const int lane = threadIdx.x;
-  // the list: from the binning's ranges, or from this wavefront's own sort
-  // (range in registers, records possibly staged already)
-  const uint32_t s = known ? known->start : ranges[2 * (int64_t)gtile];
-  const uint32_t e = known ? known->end : ranges[2 * (int64_t)gtile + 1];
-  const bool fresh = known && known->fresh, staged = known && known->staged;
-  // the long lists start first (work order) and end last: their wavefronts
-  // take precedence at instruction issue over the short tiles sharing a SIMD
-  if (e - s >= (uint32_t)kWave) __builtin_amdgcn_s_setprio(2);
+  const int sx0 = NS == 1 ? 0 : kSub * (sub % (TW / kSub)), sy0 = NS == 1 ? 0 : kSub * (sub / (TW / kSub));
+  const int bx0 = (lt % vi.tiles_x) * TW + sx0, by0 = (lt / vi.tiles_x) * TH + sy0;
+  const int col = lane & (kSub - 1), row = lane / kSub;
+  const int px = bx0 + col, py = by0 + row;
+  const uint32_t s = ranges[2 * (int64_t)gtile], e = ranges[2 * (int64_t)gtile + 1];
+  // the longest lists start first (work order) and end last: their
+  // wavefronts take precedence at instruction issue over the shorter ones
+  // sharing a SIMD
+  if (e - s > 512) __builtin_amdgcn_s_setprio(3);
+  else if (e - s > 128) __builtin_amdgcn_s_setprio(2);
+  else if (e - s > 48) __builtin_amdgcn_s_setprio(1);
 
-  double sx[PPL], sy[PPL];
-  float T[PPL], c0[PPL], c1[PPL], c2[PPL], D[PPL];
-  uint32_t lastpos[PPL];
-  bool done[PPL], inside[PPL];
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int px = tx0 + TG::x(lane, k), py = ty0 + TG::y(lane, k);
-    inside[k] = (px < vi.W) && (py < vi.H);
-    sx[k] = px + 0.5;
-    sy[k] = py + 0.5;
-
-    T[k] = 1.0f; c0[k] = c1[k] = c2[k] = D[k] = 0.0f;
-    lastpos[k] = 0;
-    done[k] = !inside[k];
-  }
-  auto active = [&]() {
-    bool a = false;
-#pragma unroll
-    for (int k = 0; k < PPL; ++k) a = a || !done[k];
-    return a;
+  const bool inside = (px < vi.W) && (py < vi.H);
+  float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, D = 0.0f;
+  uint32_t lastpos = 0;
+  // pixels that have not stopped; the least alpha that is blended (none once
+  // the pixel has stopped)
+  uint64_t live = ballot64(inside);
+  float amin = inside ? kAlphaMin : INFINITY;
+  const double cx0 = (double)bx0 + 0.5, cy0 = (double)by0 + 0.5;
+  // the next batch's records are fetched while this one is composited, and
+  // the record ids of the batch after that one
+  const uint32_t lane_u = (uint32_t)lane;
+  auto fetch = [&](FwdRec& r, uint32_t id) {
+    const float4* src = reinterpret_cast<const float4*>(lrec.base + id);
+    float4* d4 = reinterpret_cast<float4*>(&r);
+    d4[0] = src[0]; d4[1] = src[1]; d4[2] = src[2];
   };
-  bool more = true;
-  for (uint32_t b = s; more && b < e; b += (uint32_t)B) {
-    if (ballot64(active()) == 0) break;
-    const int nb = (int)min((uint32_t)B, e - b);
-    if (!(staged && b == s)) {  // the sort staged the first batch
-      __syncthreads();
-      stage(srec, nullptr, lrec, nullptr, b, nb, lane, fresh);
-      __syncthreads();
+  FwdRec r{};
+  uint32_t id = 0;
+  if (s + lane_u < e) fetch(r, lrec.id(s + lane_u));
+  if (s + kWave + lane_u < e) id = lrec.id(s + kWave + lane_u);
+  for (uint32_t b = s; live != 0 && b < e; b += (uint32_t)kWave) {
+    const bool has = b + lane_u < e;
+    // (the sample points' coordinates are counted up from the block's corner
+    // in each batch: kept over the batches they would take 32 registers)
+    float ox[kSub], oy[kSub];
+    double ax = cx0, ay = cy0;
+    asm volatile("" : "+v"(ax), "+v"(ay));
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) {
+      ox[k] = (float)(r.mx - ax);
+      oy[k] = (float)(r.my - ay);
+      ax += 1.0;
+      ay += 1.0;
     }
-    // segments between the 64-position bucket boundaries of the list, so
-    // that the pixel states are stored outside the per-splat loop
-    for (int j = 0; more && j < nb;) {
-      const uint32_t q0 = b - s + (uint32_t)j;
-      if constexpr (CKPT) {
-        // state of every pixel before each 64th splat of the tile list (the
-        // state before the first splat is the empty one and is not stored)
-        if (q0 != 0 && (q0 & (kBucket - 1)) == 0) {
-          float* cp = ckpt + (int64_t)(boff[gtile] + q0 / kBucket) * (kStateFloats * NPX);
+    const bool keep = has && !(max_exponent(r, ox[kSub - 1], ox[0], oy[kSub - 1], oy[0]) < kCullExp);
+    const uint64_t kept = ballot64(keep);
+    const int n = (int)__popcll(kept);
+    const bool clamps = ballot64(keep && r.lo > kClampLo) != 0;
+    __syncthreads();  // (one wavefront: orders the LDS reads before its writes)
+    if (keep) {
+      const int at = (int)__popcll(kept & lanemask_lt());
 #pragma unroll
-          for (int k = 0; k < PPL; ++k) {
-            const int jj = TG::y(lane, k) * TW + TG::x(lane, k);
-            cp[jj] = T[k];
-            cp[NPX + jj] = c0[k];
-            cp[2 * NPX + jj] = c1[k];
-            cp[3 * NPX + jj] = c2[k];
-            cp[4 * NPX + jj] = D[k];
-          }
-        }
+      for (int k = 0; k < kSub; ++k) {
+        S.dx[k][at] = ox[k];
+        S.dy[k][at] = oy[k];
       }
-      const int jend = min(nb, j + (int)(kBucket - (q0 & (kBucket - 1))));
-      for (; j < jend; j += kFwdSplats) {
-        // kFwdSplats records at once (whole records, broadcast LDS reads):
-        // their alphas are independent, only the blends are ordered.  Every
-        // decision of eval_alpha is a select: no divergent branches.
-        constexpr int NS = kFwdSplats;
-        Rec rr[NS];
-        bool hasu[NS];
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-          hasu[u] = j + u < jend;
-          rr[u] = srec[hasu[u] ? j + u : j];
-        }
-        const uint32_t pos0 = b - s + (uint32_t)j + 1u;
-#pragma unroll
-        for (int k = 0; k < PPL; ++k) {
-          float au[NS];
-#pragma unroll
-          for (int u = 0; u < NS; ++u) {
-            const double dx = rr[u].mx - sx[k], dy = rr[u].my - sy[k];
-            au[u] = fminf(kAlphaMax,
-                          __builtin_amdgcn_exp2f(rec_exponent(rr[u], (float)dx, (float)dy)));
-          }
-          // a splat that is not blended gets weight 0: colour, depth are
-          // non-negative and finite, so fma(x, 0, acc) leaves acc as it is
-          // and one select replaces four
-#pragma unroll
-          for (int u = 0; u < NS; ++u) {
-            const bool hit = hasu[u] && !done[k] && au[u] >= kAlphaMin;
-            const float w0 = au[u] * T[k];
-            const float Tn = T[k] - w0;  // T (1 - alpha)
-            const bool stop = Tn < kTMin;
-            const bool blend = hit && !stop;
-            const float w = blend ? w0 : 0.0f;
-            c0[k] = fmaf(rr[u].r, w, c0[k]);
-            c1[k] = fmaf(rr[u].g, w, c1[k]);
-            c2[k] = fmaf(rr[u].b, w, c2[k]);
-            D[k] = fmaf(rr[u].z, w, D[k]);
-            T[k] -= w;
-            lastpos[k] = blend ? pos0 + (uint32_t)u : lastpos[k];
-            done[k] = done[k] || (hit && stop);
-          }
-        }
-        if (ballot64(active()) == 0) {
-          more = false;
-          break;
-        }
-      }
-      // the next segment starts at jend, whatever the step: a step of
-      // kFwdSplats may pass it (its splats past jend are masked off)
-      if (more) j = jend;
+      S.shape[at] = make_float4(r.t, r.s1, r.s2, r.lo);
+      S.colour[at] = make_float4(r.r, r.g, r.b, r.z);
+      S.pos[at] = b - s + (uint32_t)lane + 1u;
     }
+    // the last step's missing splats: alpha = 2^-inf = 0
+    if (lane < kFwdSplats && n + lane < ((n + kFwdSplats - 1) & ~(kFwdSplats - 1))) {
+#pragma unroll
+      for (int k = 0; k < kSub; ++k) S.dx[k][n + lane] = S.dy[k][n + lane] = 0.0f;
+      S.shape[n + lane] = make_float4(0.0f, 0.0f, 0.0f, -INFINITY);
+      S.colour[n + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      S.pos[n + lane] = 0u;
+    }
+    __syncthreads();
+    if (b + kWave + lane_u < e) fetch(r, id);
+    if (b + 2 * kWave + lane_u < e) id = lrec.id(b + 2 * kWave + lane_u);
+    if constexpr (CKPT) {
+      // state of every pixel before each 64th splat of the tile list (the
+      // state before the first splat is the empty one and is not stored)
+      if (b != s) {
+        float* cp = ckpt + (int64_t)(boff[gtile] + (b - s) / kBucket) * (kStateFloats * NPX);
+        const int jj = (sy0 + row) * TW + sx0 + col;
+        cp[jj] = T;
+        cp[NPX + jj] = c0;
+        cp[2 * NPX + jj] = c1;
+        cp[3 * NPX + jj] = c2;
+        cp[4 * NPX + jj] = D;
+      }
+    }
+    // kFwdSplats splats at once: their alphas are independent, only the
+    // blends are ordered.  Every decision is a select: no divergent branches.
+    // CLAMP: some splat of the batch can exceed the 0.99 clamp.
+    // One step = kFwdSplats splats: their alphas first (independent), then
+    // the blends in order.  All of a step's LDS reads are requested ahead of
+    // its arithmetic (left to itself, the compiler saves registers by reading
+    // each colour just before its use, an LDS latency per splat).  The
+    // transmittance runs through the step as if no pixel stopped: it never
+    // rises, so the splats that the stop rule leaves out are those whose
+    // transmittance ends below the limit, and a step at whose end no lane is
+    // below it (no pixel stops) needs no further test.  CLAMP: some splat of
+    // the batch can exceed the 0.99 clamp.
+    uint32_t lastslot = 0;  // 1 + slot of the last blended splat of the batch
+    auto composite = [&](auto clamp_c) {
+      constexpr bool CLAMP = decltype(clamp_c)::value;
+      constexpr int NU = kFwdSplats;
+      for (int j = 0; j < n; j += NU) {
+        const float4 dx4 = *reinterpret_cast<const float4*>(&S.dx[col][j]);
+        const float4 dy4 = *reinterpret_cast<const float4*>(&S.dy[row][j]);
+        float4 sh[NU], cl[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) sh[u] = S.shape[j + u];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) cl[u] = S.colour[j + u];
+        __builtin_amdgcn_sched_barrier(0);
+        const float dx[NU] = {dx4.x, dx4.y, dx4.z, dx4.w};
+        const float dy[NU] = {dy4.x, dy4.y, dy4.z, dy4.w};
+        float w[NU], Tu[NU];
+        bool hit[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          w[u] = __builtin_amdgcn_exp2f(exponent(sh[u].x, sh[u].y, sh[u].z, sh[u].w, dx[u], dy[u]));
+          if (CLAMP) w[u] = fminf(kAlphaMax, w[u]);
+          hit[u] = w[u] >= amin;
+          w[u] = hit[u] ? w[u] : 0.0f;  // a splat that is not blended weighs 0
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          const float Tb = u == 0 ? T : Tu[u - 1];
+          w[u] *= Tb;
+          Tu[u] = Tb - w[u];  // T (1 - alpha)
+        }
+        const uint64_t low = ballot64(Tu[NU - 1] < kTMin);
+        if (low == 0) {
+          T = Tu[NU - 1];
+#pragma unroll
+          for (int u = 0; u < NU; ++u) lastslot = hit[u] ? (uint32_t)(j + u + 1) : lastslot;
+        } else {
+#pragma unroll
+          for (int u = 0; u < NU; ++u) {
+            const bool go = Tu[u] >= kTMin;
+            w[u] = go ? w[u] : 0.0f;
+            T = go ? Tu[u] : T;
+            lastslot = (hit[u] & go) ? (uint32_t)(j + u + 1) : lastslot;
+          }
+          amin = Tu[NU - 1] < kTMin ? INFINITY : amin;
+          live &= ~low;
+        }
+        // (colour and depth are non-negative and finite, so fma(x, 0, acc)
+        // leaves acc as it is)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          c0 = fmaf(cl[u].x, w[u], c0);
+          c1 = fmaf(cl[u].y, w[u], c1);
+          c2 = fmaf(cl[u].z, w[u], c2);
+          D = fmaf(cl[u].w, w[u], D);
+        }
+        if (live == 0) break;
+      }
+    };
+    if (clamps) composite(std::true_type{});
+    else composite(std::false_type{});
+    if (lastslot) lastpos = S.pos[lastslot - 1];
   }
   const float* cam = cams + (int64_t)v * GS_CAMERA_FLOATS;
   const float bg0 = cam[17], bg1 = cam[18], bg2 = cam[19];
   const int64_t npx = (int64_t)vi.W * vi.H;
   float lrgb = 0.0f, ld = 0.0f;
-  uint32_t lmax = 0;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    lmax = max(lmax, lastpos[k]);
-    if (!inside[k]) continue;
-    const int px = tx0 + TG::x(lane, k), py = ty0 + TG::y(lane, k);
+  if (inside) {
     const int64_t pl = (int64_t)py * vi.W + px;
     const int64_t pix = (int64_t)vi.pix_off + pl;
     const int64_t cbase = 3 * (int64_t)vi.pix_off + pl;
-    const float o0 = fmaf(T[k], bg0, c0[k]), o1 = fmaf(T[k], bg1, c1[k]), o2 = fmaf(T[k], bg2, c2[k]);
+    const float o0 = fmaf(T, bg0, c0), o1 = fmaf(T, bg1, c1), o2 = fmaf(T, bg2, c2);
     color[cbase] = o0;
     color[cbase + npx] = o1;
     color[cbase + 2 * npx] = o2;
-    depth[pix] = D[k];
-    T_final[pix] = T[k];
-    last[pix] = lastpos[k];
+    depth[pix] = D;
+    T_final[pix] = T;
+    last[pix] = lastpos;
     if (target_rgb) {
       lrgb += fabsf(o0 - target_rgb[cbase]) + fabsf(o1 - target_rgb[cbase + npx]) +
               fabsf(o2 - target_rgb[cbase + 2 * npx]);
-      if (target_depth) ld += fabsf(D[k] - target_depth[pix]);
+      if (target_depth) ld += fabsf(D - target_depth[pix]);
     }
   }
-  const uint32_t m = wave_max(lmax);
+  const uint32_t m = wave_max(lastpos);
   if (target_rgb) {
     lrgb = wave_sum_to_last(lrgb);
     ld = wave_sum_to_last(ld);
   }
   if (lane == kWave - 1) {
-    tile_last[gtile] = m;
+    const int64_t u = (int64_t)gtile * NS + sub;
+    tile_last[u] = m;
     if (target_rgb) {
-      tile_loss[2 * (int64_t)gtile] = lrgb;
-      tile_loss[2 * (int64_t)gtile + 1] = ld;
+      tile_loss[2 * u] = lrgb;
+      tile_loss[2 * u + 1] = ld;
     }
   }
 }
 
+struct FwdArgs {
+  RecSrc lrec;
+  const uint32_t* ranges;
+  const float* cams;
+  float *color, *depth, *T_final;
+  uint32_t *last, *tile_last;
+  const float *target_rgb, *target_depth;
+  float* tile_loss;
+  const uint32_t* order;
+  const int32_t* fl;
+  const uint32_t* boff;
+  float* ckpt;
+};
+
+// One workgroup per unit, handed out by the hardware in work order: a
+// resident grid that walks the units with a static stride (one unit's cost
+// varies a hundredfold) left the chip to the unluckiest wavefronts at the
+// end (16 views, 25M pairs: 1141 us, this way 878).
 template <int TW, int TH, bool CKPT>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 7 : 1))) k_render_fwd(
-    RecSrc lrec,
-    const uint32_t* __restrict__ ranges, const float* __restrict__ cams, ViewTable vt, int B,
-    float* __restrict__ color, float* __restrict__ depth, float* __restrict__ T_final,
-    uint32_t* __restrict__ last, uint32_t* __restrict__ tile_last,
-    const float* __restrict__ target_rgb, const float* __restrict__ target_depth,
-    float* __restrict__ tile_loss, const uint32_t* __restrict__ order,
-    int32_t* __restrict__ queue, int chunk, const uint32_t* __restrict__ boff,
-    float* __restrict__ ckpt, TileSortArgs sort) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  Rec* srec = reinterpret_cast<Rec*>(smem);
-  // With sort.cnt set (a whole iteration), the wavefront first sorts its
-  // tile's list (lists of at most kTileSortSmall pairs; longer ones are
-  // sorted already), in the same LDS; the barrier makes the sorted records
-  // and the range visible to every lane before the compositing reads them.
-  auto tile = [&](int g) {
-    if (sort.cnt) {
-      // the list's first B records are staged by the sort itself
-      const TileList L = sort_tile_wave(sort, g, (int)threadIdx.x,
-                                        reinterpret_cast<uint64_t*>(smem), srec, B);
-      __syncthreads();
-      fwd_tile<TW, TH, CKPT>(g, lrec, ranges, cams, vt, B, color, depth, T_final, last,
-                             tile_last, target_rgb, target_depth, tile_loss, boff, ckpt, srec,
-                             &L);
-      return;
-    }
-    fwd_tile<TW, TH, CKPT>(g, lrec, ranges, cams, vt, B, color, depth, T_final, last,
-                           tile_last, target_rgb, target_depth, tile_loss, boff, ckpt, srec);
-  };
-  if (queue == nullptr) {
-    tile(order ? (int)order[blockIdx.x] : (int)blockIdx.x);
-    return;
-  }
-  // persistent: chunks of `chunk` tiles of the work order, taken with a
-  // static stride (the order is longest first, so the first round takes the
-  // longest tiles; no shared counter)
-  const int n_items = (vt.total_tiles + chunk - 1) / chunk;
-  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int first = item * chunk;
-    const int lastt = min(vt.total_tiles, first + chunk);
-    for (int k = first; k < lastt; ++k) {
-      __syncthreads();  // the LDS of the previous tile is reused
-      tile(order ? (int)order[k] : k);
-    }
-  }
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) k_render_fwd(
+    FwdArgs A, ViewTable vt) {
+  __shared__ __align__(16) FwdLds S;
+  uint32_t slot, sub;
+  unit_of<sub_tiles<TW, TH>()>(blockIdx.x, (uint32_t)vt.total_tiles, slot, sub);
+  const int gtile = order_tile(A.order, A.fl, vt.total_tiles, slot);
+  fwd_tile<TW, TH, CKPT>(gtile, (int)sub, A.lrec, A.ranges, A.cams, vt, A.color, A.depth,
+                         A.T_final, A.last, A.tile_last, A.target_rgb, A.target_depth,
+                         A.tile_loss, A.boff, A.ckpt, S);
 }
 
 // Per-view L1 loss from the per-tile sums, in a fixed order.
@@ -382,8 +496,9 @@ __global__ void __launch_bounds__(kLossThreads) k_loss_reduce(const float* __res
                                                               int has_depth, float* __restrict__ loss) {
   const int v = blockIdx.x;
   const ViewInfo vi = vt.v[v];
-  loss_reduce_view<kLossThreads>(reinterpret_cast<const float2*>(tile_loss) + vi.tile_off,
-                                 vi.tiles_x * vi.tiles_y, (double)vi.W * vi.H, lambda_depth,
+  const int ns = vt.tw * vt.th / (kSub * kSub);  // partials per tile
+  loss_reduce_view<kLossThreads>(reinterpret_cast<const float2*>(tile_loss) + (int64_t)vi.tile_off * ns,
+                                 vi.tiles_x * vi.tiles_y * ns, (double)vi.W * vi.H, lambda_depth,
                                  has_depth, loss + v);
 }
 
@@ -406,7 +521,7 @@ __device__ __forceinline__ void bwd_tile(
   const int tx0 = (lt % vi.tiles_x) * TW, ty0 = (lt / vi.tiles_x) * TH;
   const int lane = threadIdx.x;
   const uint32_t s = ranges[2 * (int64_t)gtile], e = ranges[2 * (int64_t)gtile + 1];
-  const uint32_t tl = tile_last[gtile];
+  const uint32_t tl = tile_last_of<sub_tiles<TW, TH>()>(tile_last, gtile);
   const float* cam = cams + (int64_t)v * GS_CAMERA_FLOATS;
   const float bg0 = cam[17], bg1 = cam[18], bg2 = cam[19];
 
@@ -541,12 +656,12 @@ __global__ void __launch_bounds__(kWave) k_render_bwd(
     const float* __restrict__ dL_dcolor, const float* __restrict__ dL_ddepth,
     const float* __restrict__ target_rgb, const float* __restrict__ target_depth, int fused,
     float lambda_depth, float* __restrict__ grad_pair, const uint32_t* __restrict__ order,
-    int32_t* __restrict__ queue, int chunk) {
+    const int32_t* __restrict__ fl, int32_t* __restrict__ queue, int chunk) {
   extern __shared__ __align__(16) unsigned char smem[];
   Rec* srec = reinterpret_cast<Rec*>(smem);
   uint32_t* sval = reinterpret_cast<uint32_t*>(smem + (size_t)B * sizeof(Rec));
   if (queue == nullptr) {
-    const int g = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
+    const int g = order_tile(order, fl, vt.total_tiles, blockIdx.x);
     bwd_tile<TW, TH>(g, lrec, sorted_vals, ranges, tile_last, cams, vt, B, color, depth,
                      T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused,
                      lambda_depth, grad_pair, srec, sval);
@@ -557,7 +672,7 @@ __global__ void __launch_bounds__(kWave) k_render_bwd(
     const int first = item * chunk;
     const int lastt = min(vt.total_tiles, first + chunk);
     for (int k = first; k < lastt; ++k) {
-      const int g = order ? (int)order[k] : k;
+      const int g = order_tile(order, fl, vt.total_tiles, (uint32_t)k);
       bwd_tile<TW, TH>(g, lrec, sorted_vals, ranges, tile_last, cams, vt, B, color,
                        depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth,
                        fused, lambda_depth, grad_pair, srec, sval);
@@ -652,7 +767,7 @@ __device__ __forceinline__ void splat_wave(
   if (has) {
     s = ranges[2 * (int64_t)gtile];
     npairs = ranges[2 * (int64_t)gtile + 1] - s;
-    tl = tile_last[gtile];
+    tl = tile_last_of<sub_tiles<TW, TH>()>(tile_last, gtile);
   }
   const uint32_t q0 = k * kBucket;
   const uint32_t pos = q0 + (uint32_t)ls;
@@ -884,26 +999,17 @@ hipError_t bwd_splat_launch(const Plan& P, void* ws, const float* cams, const fl
 template <int TW, int TH>
 hipError_t fwd_launch(const Plan& P, void* ws, const float* cams, float* color, float* depth,
                       float* T_final, uint32_t* last, const float* target_rgb,
-                      const float* target_depth, const uint32_t* order, int32_t* queue,
-                      int grid, const TileSortArgs& sort, hipStream_t s) {
-  const int B = P.cfg.lds_batch;
-  const size_t lds = std::max((size_t)B * sizeof(Rec),
-                              sort.cnt ? (size_t)kTileSortSmall * sizeof(uint64_t) : (size_t)0);
-  if (P.cfg.flags & GS_SPLAT_BWD) {
-    hipLaunchKernelGGL((k_render_fwd<TW, TH, true>), dim3(grid), dim3(kWave), lds, s,
-                       rec_src(P, ws),
-                       ws_at<uint32_t>(ws, P.off_ranges), cams, P.vt, B, color, depth, T_final,
-                       last, ws_at<uint32_t>(ws, P.off_tile_last), target_rgb, target_depth,
-                       ws_at<float>(ws, P.off_tile_loss), order, queue, P.cfg.chunk,
-                       ws_at<uint32_t>(ws, P.off_boff), ws_at<float>(ws, P.off_ckpt), sort);
-  } else {
-    hipLaunchKernelGGL((k_render_fwd<TW, TH, false>), dim3(grid), dim3(kWave), lds, s,
-                       rec_src(P, ws),
-                       ws_at<uint32_t>(ws, P.off_ranges), cams, P.vt, B, color, depth, T_final,
-                       last, ws_at<uint32_t>(ws, P.off_tile_last), target_rgb, target_depth,
-                       ws_at<float>(ws, P.off_tile_loss), order, queue, P.cfg.chunk,
-                       nullptr, nullptr, sort);
-  }
+                      const float* target_depth, hipStream_t s) {
+  const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
+  const FwdArgs A{rec_src(P, ws), ws_at<uint32_t>(ws, P.off_ranges), cams, color, depth, T_final,
+                  last, ws_at<uint32_t>(ws, P.off_tile_last), target_rgb, target_depth,
+                  ws_at<float>(ws, P.off_tile_loss), ws_at<uint32_t>(ws, P.off_order),
+                  ws_at<int32_t>(ws, P.off_flags),
+                  splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr,
+                  splat ? ws_at<float>(ws, P.off_ckpt) : nullptr};
+  const dim3 g((unsigned)P.vt.total_tiles * sub_tiles<TW, TH>()), block(kWave);
+  if (splat) hipLaunchKernelGGL((k_render_fwd<TW, TH, true>), g, block, 0, s, A, P.vt);
+  else hipLaunchKernelGGL((k_render_fwd<TW, TH, false>), g, block, 0, s, A, P.vt);
   return hipGetLastError();
 }
 
@@ -920,7 +1026,8 @@ hipError_t bwd_launch(const Plan& P, void* ws, const float* cams, const float* c
                      ws_at<uint32_t>(ws, P.off_ranges), ws_at<uint32_t>(ws, P.off_tile_last), cams,
                      P.vt, B, color, depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb,
                      target_depth, fused, P.cfg.lambda_depth,
-                     ws_at<float>(ws, P.off_grad_pair), order, queue, P.cfg.chunk);
+                     ws_at<float>(ws, P.off_grad_pair), order, ws_at<int32_t>(ws, P.off_flags),
+                     queue, P.cfg.chunk);
   return hipGetLastError();
 }
 
@@ -934,14 +1041,16 @@ int occupancy(K kernel, size_t lds) {
 
 }  // namespace
 
-// Resident single-wave workgroups per CU of the render kernel for this plan.
-int render_blocks_per_cu(const Plan& P, bool bwd) {
-  const int B = P.cfg.lds_batch;
-  const size_t lf = (size_t)B * sizeof(Rec), lb = (size_t)B * (sizeof(Rec) + sizeof(uint32_t));
+// 8x8 blocks of pixels per tile: the forward's wavefronts per tile.
+int blocks_per_tile(const Plan& P) { return P.cfg.tile_w * P.cfg.tile_h / (kSub * kSub); }
+
+// Resident single-wave workgroups per CU of the pixel-wise backward.
+int render_bwd_blocks_per_cu(const Plan& P) {
+  const size_t lds = (size_t)P.cfg.lds_batch * (sizeof(Rec) + sizeof(uint32_t));
   const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
-  if (tw == 16 && th == 16) return bwd ? occupancy(k_render_bwd<16, 16>, lb) : occupancy(k_render_fwd<16, 16, false>, lf);
-  if (tw == 16 && th == 8) return bwd ? occupancy(k_render_bwd<16, 8>, lb) : occupancy(k_render_fwd<16, 8, false>, lf);
-  return bwd ? occupancy(k_render_bwd<8, 8>, lb) : occupancy(k_render_fwd<8, 8, false>, lf);
+  if (tw == 16 && th == 16) return occupancy(k_render_bwd<16, 16>, lds);
+  if (tw == 16 && th == 8) return occupancy(k_render_bwd<16, 8>, lds);
+  return occupancy(k_render_bwd<8, 8>, lds);
 }
 
 // Resident workgroups per CU of the splat-wise backward.
@@ -952,22 +1061,19 @@ int splat_blocks_per_cu(const Plan& P) {
   return occupancy(k_render_bwd_splat<8, 8>, 0);
 }
 
-// sort (optional, cnt non-null): the forward sorts each tile's short list
-// itself (a whole iteration whose binning deferred those sorts).
 hipError_t launch_render_fwd(const Plan& P, void* ws, const float* cams, float* color,
                              float* depth, float* T_final, uint32_t* last,
                              const float* target_rgb, const float* target_depth,
-                             float* loss_per_view, const uint32_t* order, int32_t* queue,
-                             int grid, hipStream_t s, const TileSortArgs& sort) {
+                             float* loss_per_view, hipStream_t s) {
   if (P.vt.total_tiles == 0) return hipSuccess;
   hipError_t e;
   const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
   if (tw == 16 && th == 16)
-    e = fwd_launch<16, 16>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, order, queue, grid, sort, s);
+    e = fwd_launch<16, 16>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, s);
   else if (tw == 16 && th == 8)
-    e = fwd_launch<16, 8>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, order, queue, grid, sort, s);
+    e = fwd_launch<16, 8>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, s);
   else
-    e = fwd_launch<8, 8>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, order, queue, grid, sort, s);
+    e = fwd_launch<8, 8>(P, ws, cams, color, depth, T_final, last, target_rgb, target_depth, s);
   if (e != hipSuccess) return e;
   if (target_rgb && loss_per_view) {
     hipLaunchKernelGGL(k_loss_reduce, dim3(P.vt.n_views), dim3(kLossThreads), 0, s,

@@ -1,6 +1,4 @@
-// Per-tile list sort of the binning, shared by the stand-alone tile sort and
-// the forward kernel of a whole iteration (which sorts its tile's list
-// itself before compositing it).
+// Per-tile list sort of the binning.
 //
 // Output per tile: sorted keys (tile << 32 | depth bits), generation
 // indices, record ids, the records in list order, the [start, end) range
@@ -8,16 +6,12 @@
 // in the two bucket queues.  Keys are unique, so any correct sort gives the
 // same lists.  One wavefront sorts lists up to 64 keys in registers (rank =
 // number of smaller keys) and up to kTileSortSmall keys with a bitonic
-// network in LDS; longer lists (listed by the binning scan) go to 1024-thread
-// blocks, with the same network in LDS up to kTileSortLong keys and in place
-// in global memory beyond.  The limit is low on purpose: inside a whole
-// iteration the wavefront that sorts a list also composites it, and a
-// long list sorted there would hold back the end of the forward (its
-// wavefront starts first but finishes last), while the binning sorts the
-// few long lists in parallel before the forward starts.  The block's LDS
-// holds kTileSortLong keys (64 KB), so that two blocks share a CU and one
-// block's barrier waits overlap the other's compares: views with thousands
-// of pairs per tile send almost every list here.
+// network in LDS; longer lists (listed by the binning scan) take a
+// wavefront each up to kTileSortMid keys and 1024-thread blocks beyond, with
+// the same network in LDS up to kTileSortLong keys and in place in global
+// memory beyond.  The block's LDS holds kTileSortLong keys (64 KB), so that
+// two blocks share a CU and one block's barrier waits overlap the other's
+// compares.
 //
 // The network keeps every merge ascending (the first compare of a merge
 // pairs i with its mirror in the block), so positions past the list end act
@@ -55,10 +49,9 @@ struct TileSortOut {
 };
 
 // Writes the pair of key (depth bits << 32 | generation index) at list
-// position pos: sorted key, generation index, record id, record; the record
-// also to lds_dst when given.
+// position pos: sorted key, generation index, record id, record.
 __device__ __forceinline__ void emit_sorted(const TileSortOut& o, uint32_t pos, uint64_t tkey,
-                                            uint64_t key, Rec* lds_dst = nullptr) {
+                                            uint64_t key) {
   const uint32_t g = (uint32_t)key;
   const uint32_t r = o.pair_rec[g];
   o.keys[pos] = tkey | (key >> 32);
@@ -68,10 +61,6 @@ __device__ __forceinline__ void emit_sorted(const TileSortOut& o, uint32_t pos, 
   float4* dst = reinterpret_cast<float4*>(o.lrec + pos);
   const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
   dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
-  if (lds_dst) {
-    float4* l = reinterpret_cast<float4*>(lds_dst);
-    l[0] = a0; l[1] = a1; l[2] = a2; l[3] = a3;
-  }
 }
 
 __device__ __forceinline__ void cmp_swap(uint64_t* k, uint32_t a, uint32_t b, uint32_t n) {
@@ -140,33 +129,16 @@ struct TileSortArgs {
   const uint32_t* hstart;
   uint2* bq;
   int64_t bq_stride;
-  // the long-list kernel runs after this one (it then clears the counters of
-  // the long lists itself) rather than before
-  bool long_after;
   // the lists were sorted by the radix binning: ranges, queue entries and
   // counter clears only
   bool presorted;
 };
 
-// What a wavefront that sorted a tile knows about its list: the range
-// ((0, 0) when empty), whether this wavefront wrote the sorted records (then
-// a read of them inside the same kernel must not be served by the vector L1,
-// which may hold an older copy of the line), and whether its first
-// stage_cap records are also in the staging LDS already.
-struct TileList {
-  uint32_t start, end;
-  bool fresh, staged;
-};
-
 // One wavefront (lane = lane of a single-wave workgroup): range and bucket
 // queue entries of tile t, then, for a list of at most kTileSortSmall pairs,
 // the sort and the sorted outputs.  sk: kTileSortSmall keys of LDS.
-// Longer lists are left to the long-list kernel.  stage (optional, at least
-// stage_cap records of LDS, may alias sk): the list's first stage_cap
-// records also land there in list order (all of a list of at most 64 pairs
-// only if it fits).
-__device__ inline TileList sort_tile_wave(const TileSortArgs& A, int t, int lane, uint64_t* sk,
-                                          Rec* stage = nullptr, int stage_cap = 0) {
+// Longer lists are left to the long-list kernels.
+__device__ inline void sort_tile_wave(const TileSortArgs& A, int t, int lane, uint64_t* sk) {
   const uint64_t P = (uint64_t)A.fl[F_PAIRS];
   const uint32_t c = A.cnt[t];
   const uint32_t n = A.fl[F_OVERFLOW] ? 0u : c;
@@ -175,9 +147,8 @@ __device__ inline TileList sort_tile_wave(const TileSortArgs& A, int t, int lane
   if (lane == 0) {
     A.ranges[2 * (int64_t)t] = ok ? (uint32_t)start64 : 0u;
     A.ranges[2 * (int64_t)t + 1] = ok ? (uint32_t)(start64 + n) : 0u;
-    // the counter is consumed: zero again for the next projection (a long
-    // list's counter is still read by a long-list kernel that runs after)
-    if (!(A.long_after && c > kTileSortSmall)) A.cnt[t] = 0u;
+    // the counter is consumed: zero again for the next projection
+    A.cnt[t] = 0u;
   }
   if (A.bq && ok) {
     // splat-wise work queues at the scanned positions: the tile's buckets
@@ -189,9 +160,7 @@ __device__ inline TileList sort_tile_wave(const TileSortArgs& A, int t, int lane
     for (uint32_t k = lane; k < full; k += kWave) A.bq[f0 + k] = make_uint2((uint32_t)t, k);
     if (half && lane == 0) A.bq[A.bq_stride + A.hstart[t]] = make_uint2((uint32_t)t, nb - 1);
   }
-  TileList L{ok ? (uint32_t)start64 : 0u, ok ? (uint32_t)(start64 + n) : 0u, false, false};
-  if (!ok || n > kTileSortSmall || A.presorted) return L;  // uniform
-  L.fresh = true;
+  if (!ok || n > kTileSortSmall || A.presorted) return;  // uniform
   const uint32_t start = (uint32_t)start64;
   const uint64_t tkey = (uint64_t)(uint32_t)t << 32;
   if (n <= (uint32_t)kWave) {
@@ -203,9 +172,8 @@ __device__ inline TileList sort_tile_wave(const TileSortArgs& A, int t, int lane
                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, j);
       rank += kj < key ? 1u : 0u;
     }
-    L.staged = stage && n <= (uint32_t)stage_cap;
-    if (has) emit_sorted(A.out, start + rank, tkey, key, L.staged ? stage + rank : nullptr);
-    return L;
+    if (has) emit_sorted(A.out, start + rank, tkey, key);
+    return;
   }
   for (uint32_t k = lane; k < n; k += kWave) sk[k] = A.skey[start + k];
   __syncthreads();
@@ -243,7 +211,6 @@ __device__ inline TileList sort_tile_wave(const TileSortArgs& A, int t, int lane
     const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
     dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
   }
-  return L;
 }
 
 }  // namespace gs
