@@ -531,85 +531,50 @@ __global__ void __launch_bounds__(256) k_scatter(
 // ---------------------------------------------------------------- tile sort
 // (per-tile sort helpers in tilesort.h)
 
-__global__ void __launch_bounds__(kWave) k_tile_sort(TileSortArgs A) {
-  __shared__ uint64_t sk[kTileSortSmall];
-  sort_tile_wave(A, blockIdx.x, threadIdx.x, sk);
-}
-
-// Lists of kTileSortSmall + 1 .. kTileSortMid pairs: one wavefront per list
-// (four per workgroup, each with its own LDS), bitonic network with
-// wavefront-level syncs, then the sorted outputs with the record ids of all
-// of a lane's positions looked up in one round trip.
-constexpr int kMidWaves = 4;
-__global__ void __launch_bounds__(kMidWaves * kWave) k_tile_sort_mid(
-    const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
-    const uint64_t* __restrict__ skey, TileSortOut out) {
-  __shared__ uint64_t sk_all[kMidWaves][kTileSortMid];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  uint64_t* sk = sk_all[w];
-  const int n_long = fl[F_OVERFLOW] ? 0 : fl[F_LONG_TILES];
-  constexpr int KMAX = kTileSortMid / kWave;
-  for (int li = blockIdx.x * kMidWaves + w; li < n_long; li += gridDim.x * kMidWaves) {
-    const uint4 e = long_list[li];  // (tile, list start, pairs, -)
-    const uint32_t n = e.z;
-    if (n > kTileSortMid) continue;  // uniform: the long-list kernel's
-    const int t = (int)e.x;
-    const uint32_t start = e.y;
-    const uint64_t tkey = (uint64_t)(uint32_t)t << 32;
-    for (uint32_t k = lane; k < n; k += kWave) sk[k] = skey[start + k];
-    wave_lds_sync();
-    bitonic_sort_wave(sk, n, (uint32_t)lane);
-    uint32_t r[KMAX];
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-      const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
-      r[q] = 0u;
-      if (k < n) {
-        const uint64_t key = sk[k];
-        const uint32_t g = (uint32_t)key;
-        out.keys[start + k] = tkey | (key >> 32);
-        out.vals[start + k] = g;
-        r[q] = out.pair_rec[g];
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-      const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
-      if (k < n) {
-        const uint32_t rk = r[q];
-        out.sorted_rec[start + k] = rk;
-        const float4* src = reinterpret_cast<const float4*>(out.rec + rk);
-        float4* dst = reinterpret_cast<float4*>(out.lrec + start + k);
-        const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-        dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
-      }
-    }
-    wave_lds_sync();  // every key read before the next list overwrites them
-  }
-}
-
-__global__ void __launch_bounds__(kLongThreads) k_tile_sort_long(
-    const int32_t* __restrict__ fl, const uint4* __restrict__ long_list,
-    uint64_t* __restrict__ skey, TileSortOut out) {
+// Blocks [0, long_blocks): the listed long lists -- those beyond
+// kTileSortMid pairs a workgroup each, the others a wavefront each.  The
+// other blocks: the tiles, a wavefront each (the long lists' wavefronts only
+// write the range and queue entries there).  One launch where there were
+// three: the long lists, first in the grid, hide behind the short ones
+// (1200x680 view, 12750 lists of 34 pairs on average: 44 -> 35 us; in 16x16
+// tiles, 3225 lists of 194: 116 -> 64 us; a 128x96 view: 30 -> 15 us).  Held
+// to 64 registers so that two workgroups share a CU (2.7M pairs in 12900
+// lists: 247 us with one, 183 us with two); bound by the LDS traffic of the
+// networks (two reads and two writes per compare).
+__global__ void __launch_bounds__(kSortWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) k_tile_sort(
+    TileSortArgs A, uint64_t* __restrict__ skey, const uint4* __restrict__ long_list,
+    int long_blocks, int n_tiles) {
   __shared__ uint64_t sk[kTileSortLong];
-  const int n_long = fl[F_OVERFLOW] ? 0 : fl[F_LONG_TILES];
-  for (int li = blockIdx.x; li < n_long; li += gridDim.x) {
-    const uint4 e = long_list[li];  // the scan recorded the list's start and length
-    const int t = (int)e.x;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+  uint64_t* wsk = sk + w * kTileSortMid;
+  if ((int)blockIdx.x >= long_blocks) {
+    const int t = ((int)blockIdx.x - long_blocks) * kSortWaves + w;
+    if (t < n_tiles) sort_tile_wave(A, t, lane, wsk);
+    return;
+  }
+  const int n_long = A.fl[F_OVERFLOW] ? 0 : A.fl[F_LONG_TILES];
+  for (int li = blockIdx.x; li < n_long; li += long_blocks) {
+    const uint4 e = long_list[li];  // the scan recorded (tile, list start, pairs, -)
     const uint32_t start = e.y, n = e.z;
-    if (n <= kTileSortMid) continue;  // uniform: sorted by k_tile_sort_mid
-    const uint64_t tkey = (uint64_t)(uint32_t)t << 32;
+    if (n <= kTileSortMid) continue;  // uniform: a wavefront's, below
+    const uint64_t tkey = (uint64_t)e.x << 32;
+    constexpr uint32_t NT = kSortWaves * kWave;
     if (n <= kTileSortLong) {
-      for (uint32_t k = threadIdx.x; k < n; k += kLongThreads) sk[k] = skey[start + k];
+      for (uint32_t k = threadIdx.x; k < n; k += NT) sk[k] = skey[start + k];
       __syncthreads();
-      bitonic_sort(sk, n, threadIdx.x, kLongThreads);
-      for (uint32_t k = threadIdx.x; k < n; k += kLongThreads) emit_sorted(out, start + k, tkey, sk[k]);
+      bitonic_sort(sk, n, threadIdx.x, NT);
+      for (uint32_t k = threadIdx.x; k < n; k += NT) emit_sorted(A.out, start + k, tkey, sk[k]);
     } else {
-      bitonic_sort(skey + start, n, threadIdx.x, kLongThreads);
-      for (uint32_t k = threadIdx.x; k < n; k += kLongThreads)
-        emit_sorted(out, start + k, tkey, skey[start + k]);
+      bitonic_sort(skey + start, n, threadIdx.x, NT);
+      for (uint32_t k = threadIdx.x; k < n; k += NT)
+        emit_sorted(A.out, start + k, tkey, skey[start + k]);
     }
-    __syncthreads();  // the LDS is reused by the next list
+    __syncthreads();  // the LDS is reused
+  }
+  for (int li = blockIdx.x + w * long_blocks; li < n_long; li += long_blocks * kSortWaves) {
+    const uint4 e = long_list[li];
+    if (e.z <= kTileSortMid)
+      sort_list_wave<kTileSortMid>(A.out, skey, (uint64_t)e.x << 32, e.y, e.z, lane, wsk);
   }
 }
 
@@ -930,9 +895,10 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
     st.n_chunks = 0;
     st.mode = kScanTiles;
     scan(st, StepAdvance{});
-    if (T > 0) {
-      hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)T), dim3(kWave), 0, s, tile_sort_args(P, ws));
-    }
+    if (T > 0)
+      hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)((T + kSortWaves - 1) / kSortWaves)),
+                         dim3(kSortWaves * kWave), 0, s, tile_sort_args(P, ws), nullptr, long_list,
+                         0, T);
     if ((e = mk.at(GS_MARK_BIN_LONG_SORT, s)) != hipSuccess) return e;
     return hipGetLastError();
   }
@@ -947,24 +913,18 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
   }
   if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;
   if (T > 0) {
-    // the per-tile pass zeroes the counters, so that every counter is zero
-    // again after the binning of an iteration
-    const TileSortArgs A = tile_sort_args(P, ws);
-    hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)T), dim3(kWave), 0, s, A);
-    if ((e = mk.at(GS_MARK_BIN_SHORT_SORT, s)) != hipSuccess) return e;
-    // lists up to kTileSortMid pairs: a wavefront each; longer: a block each
-    // (at most one long list per kTileSortSmall + 1 pairs of capacity; five
-    // workgroups per CU are resident, the waves loop over the lists)
+    // the pass over the tiles zeroes the counters, so that every counter is
+    // zero again after the binning of an iteration.  At most one long list
+    // per kTileSortSmall + 1 pairs of capacity; two workgroups per CU are
+    // resident and loop over the lists
     const int64_t max_long = std::min<int64_t>(T, P.pair_cap / (kTileSortSmall + 1) + 1);
-    const int mid_grid = (int)std::min<int64_t>((max_long + kMidWaves - 1) / kMidWaves, 1280);
-    hipLaunchKernelGGL(k_tile_sort_mid, dim3((unsigned)mid_grid), dim3(kMidWaves * kWave), 0, s, fl,
-                       long_list, skey, A.out);
-    const int long_grid = (int)std::min<int64_t>(T, 512);  // two blocks per CU
-    hipLaunchKernelGGL(k_tile_sort_long, dim3((unsigned)long_grid), dim3(kLongThreads), 0, s,
-                       fl, long_list, skey, A.out);
-  } else if ((e = mk.at(GS_MARK_BIN_SHORT_SORT, s)) != hipSuccess) {
-    return e;
+    const int long_blocks = (int)std::min<int64_t>(max_long, 512);
+    hipLaunchKernelGGL(k_tile_sort,
+                       dim3((unsigned)(long_blocks + (T + kSortWaves - 1) / kSortWaves)),
+                       dim3(kSortWaves * kWave), 0, s, tile_sort_args(P, ws), skey, long_list,
+                       long_blocks, T);
   }
+  if ((e = mk.at(GS_MARK_BIN_SHORT_SORT, s)) != hipSuccess) return e;
   if ((e = mk.at(GS_MARK_BIN_LONG_SORT, s)) != hipSuccess) return e;
   return hipGetLastError();
 }

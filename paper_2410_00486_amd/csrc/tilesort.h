@@ -4,14 +4,13 @@
 // indices, record ids, the records in list order, the [start, end) range
 // ((0, 0) when empty) and, for the splat-wise backward, the tile's entries
 // in the two bucket queues.  Keys are unique, so any correct sort gives the
-// same lists.  One wavefront sorts lists up to 64 keys in registers (rank =
-// number of smaller keys) and up to kTileSortSmall keys with a bitonic
-// network in LDS; longer lists (listed by the binning scan) take a
-// wavefront each up to kTileSortMid keys and 1024-thread blocks beyond, with
-// the same network in LDS up to kTileSortLong keys and in place in global
-// memory beyond.  The block's LDS holds kTileSortLong keys (64 KB), so that
-// two blocks share a CU and one block's barrier waits overlap the other's
-// compares.
+// same lists.  One launch: a wavefront sorts lists up to 64 keys in
+// registers (rank = number of smaller keys) and up to kTileSortMid keys with a
+// bitonic network in LDS; longer lists take a whole 1024-thread workgroup,
+// with the same network in LDS up to kTileSortLong keys and in place in
+// global memory beyond.  The workgroup's LDS holds kTileSortLong keys
+// (64 KB), so that two share a CU (32 wavefronts, all it holds) and one's
+// barrier waits overlap the other's compares.
 //
 // The network keeps every merge ascending (the first compare of a merge
 // pairs i with its mirror in the block), so positions past the list end act
@@ -22,11 +21,12 @@
 
 namespace gs {
 
+// lists of more pairs are listed by the binning scan and sorted apart from
+// the pass over the tiles
 constexpr uint32_t kTileSortSmall = 128;
-// lists of kTileSortSmall + 1 .. kTileSortMid pairs: one wavefront each
-constexpr uint32_t kTileSortMid = 1024;
 constexpr uint32_t kTileSortLong = 8192;
-constexpr int kLongThreads = 1024;
+constexpr int kSortWaves = 16;                                  // wavefronts per workgroup
+constexpr uint32_t kTileSortMid = kTileSortLong / kSortWaves;   // 512: one wavefront's share
 
 // Splits a tile of c pairs into buckets of 64 positions: all but possibly
 // the last hold more than 32 pairs (full); a last bucket with at most 32
@@ -134,10 +134,48 @@ struct TileSortArgs {
   bool presorted;
 };
 
-// One wavefront (lane = lane of a single-wave workgroup): range and bucket
-// queue entries of tile t, then, for a list of at most kTileSortSmall pairs,
-// the sort and the sorted outputs.  sk: kTileSortSmall keys of LDS.
-// Longer lists are left to the long-list kernels.
+// Sorts the n <= MAX keys of a list with one wavefront and writes the sorted
+// outputs: the lane's positions are written out and their record ids looked
+// up all at once (one memory round trip for all of them instead of one per
+// position), then the records.  sk: MAX keys of LDS of this wavefront.
+template <uint32_t MAX>
+__device__ inline void sort_list_wave(const TileSortOut& o, const uint64_t* __restrict__ skey,
+                                      uint64_t tkey, uint32_t start, uint32_t n, int lane,
+                                      uint64_t* sk) {
+  constexpr int KMAX = MAX / kWave;
+  for (uint32_t k = lane; k < n; k += kWave) sk[k] = skey[start + k];
+  wave_lds_sync();
+  bitonic_sort_wave(sk, n, (uint32_t)lane);
+  uint32_t r[KMAX];
+#pragma unroll
+  for (int q = 0; q < KMAX; ++q) {
+    const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
+    r[q] = 0u;
+    if (k < n) {
+      const uint64_t key = sk[k];
+      const uint32_t g = (uint32_t)key;
+      o.keys[start + k] = tkey | (key >> 32);
+      o.vals[start + k] = g;
+      r[q] = o.pair_rec[g];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < KMAX; ++q) {
+    const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
+    if (k < n) {
+      o.sorted_rec[start + k] = r[q];
+      const float4* src = reinterpret_cast<const float4*>(o.rec + r[q]);
+      float4* dst = reinterpret_cast<float4*>(o.lrec + start + k);
+      const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
+      dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
+    }
+  }
+  wave_lds_sync();  // every key read before the next list overwrites them
+}
+
+// One wavefront: range and bucket queue entries of tile t, then, for a list
+// of at most kTileSortSmall pairs, the sort and the sorted outputs.  sk:
+// kTileSortSmall keys of LDS of this wavefront.
 __device__ inline void sort_tile_wave(const TileSortArgs& A, int t, int lane, uint64_t* sk) {
   const uint64_t P = (uint64_t)A.fl[F_PAIRS];
   const uint32_t c = A.cnt[t];
@@ -175,42 +213,7 @@ __device__ inline void sort_tile_wave(const TileSortArgs& A, int t, int lane, ui
     if (has) emit_sorted(A.out, start + rank, tkey, key);
     return;
   }
-  for (uint32_t k = lane; k < n; k += kWave) sk[k] = A.skey[start + k];
-  __syncthreads();
-  bitonic_sort(sk, n, lane, kWave);
-  // The lane's sorted keys are written out and their record ids looked up
-  // all at once (one memory round trip for all of them instead of one per
-  // position); the ids then wait in the keys' LDS for the record gathers.
-  constexpr int KMAX = kTileSortSmall / kWave;
-  const TileSortOut& o = A.out;
-  uint32_t r[KMAX];
-#pragma unroll
-  for (int q = 0; q < KMAX; ++q) {
-    const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
-    r[q] = 0u;
-    if (k < n) {
-      const uint64_t key = sk[k];
-      const uint32_t g = (uint32_t)key;
-      o.keys[start + k] = tkey | (key >> 32);
-      o.vals[start + k] = g;
-      r[q] = o.pair_rec[g];
-    }
-  }
-  __syncthreads();  // every key has been read
-  uint32_t* sr = reinterpret_cast<uint32_t*>(sk);
-#pragma unroll
-  for (int q = 0; q < KMAX; ++q) {
-    const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
-    if (k < n) sr[k] = r[q];
-  }
-  for (uint32_t k = lane; k < n; k += kWave) {  // this lane's own positions
-    const uint32_t rk = sr[k];
-    o.sorted_rec[start + k] = rk;
-    const float4* src = reinterpret_cast<const float4*>(o.rec + rk);
-    float4* dst = reinterpret_cast<float4*>(o.lrec + start + k);
-    const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-    dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
-  }
+  sort_list_wave<kTileSortSmall>(A.out, A.skey, tkey, start, n, lane, sk);
 }
 
 }  // namespace gs

@@ -81,3 +81,23 @@ def test_forward_blocks_match_oracle(n, width, height, log_scale):
             first = (col, dep, T)
         for a, b in zip(first, (col, dep, T)):
             np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 512, 513, 1025, 8192, 8193])
+def test_tile_sort_list_length_edges(n):
+    """One tile's list at the lengths where the sort changes its form
+    (registers, a wavefront in LDS, a workgroup in LDS, global memory): keys,
+    records and ranges equal the oracle's order."""
+    w = scenes.crowded_scene(7, n=n)
+    cam = w.cameras[0]
+    print(f"tile sort, {n} pairs in one tile", flush=True)
+    it = run_gpu(w.scene, [cam], tile=(16, 16))
+    pre = oracle.preprocess(w.scene, cam, (16, 16))
+    keys, vals, ranges = oracle.sort_pairs(pre, cam, (16, 16))
+    r = ranges.reshape(-1, 2).astype(np.int64)
+    assert (r[:, 1] - r[:, 0]).max() == n
+    P, T = keys.shape[0], it.plan.total_tiles
+    got = lambda reg, dt, m: it.plan.region(it.ws, reg, dt, m).cpu().numpy()
+    np.testing.assert_array_equal(got(L.GS_WS_SORTED_KEYS, torch.int64, P).view(np.uint64), keys)
+    np.testing.assert_array_equal(got(L.GS_WS_SORTED_RECS, torch.int32, P), vals.astype(np.int32))
+    np.testing.assert_array_equal(got(L.GS_WS_RANGES, torch.int32, 2 * T).view(np.uint32), ranges)
