@@ -66,12 +66,12 @@ typedef int32_t gs_status;
 #define GS_FUSED_L1 (1u << 1)         /* gs_render_bwd derives dL/dC, dL/dD from the L1
                                          loss against the targets instead of inputs */
 #define GS_ACCUMULATE_GRADS (1u << 2) /* gs_render_bwd adds into the gradient buffers */
-#define GS_PERSISTENT (1u << 3)       /* the pixel-wise backward is resident and walks
-                                         the tiles in chunks with a static stride (in
-                                         either mode tiles with long lists run
-                                         first, the order gs_bin_sort writes; the
-                                         forward always gives each block of pixels
-                                         a workgroup of its own) */
+#define GS_PERSISTENT (1u << 3)       /* accepted, no effect: the render kernels get
+                                         their blocks of pixels from the hardware's
+                                         dispatcher, those of the longest lists first
+                                         (the order gs_bin_sort writes), which
+                                         balances them better than resident kernels
+                                         with a static share did */
 #define GS_SPLAT_BWD (1u << 4)        /* splat-wise backward (Sec. III-C-1, Fig. 4a):
                                          the forward stores per-pixel (T, RGB, D) states
                                          at every 64th splat of a tile; the backward
@@ -112,9 +112,9 @@ typedef struct gs_gaussian_grads {
 typedef struct gs_raster_cfg {
   int32_t tile_w;       /* 8 or 16 */
   int32_t tile_h;       /* 8 or 16 (16x16, 16x8, 8x8) */
-  int32_t chunk;        /* tiles per work item in GS_PERSISTENT mode, 1..16 */
-  int32_t lds_batch;    /* records staged in LDS per batch of the pixel-wise
-                           backward: 64, 128 or 256 */
+  int32_t chunk;        /* 1..16 (checked; no effect, as GS_PERSISTENT) */
+  int32_t lds_batch;    /* a multiple of 32 in 32..256 (checked; no effect: the
+                           render kernels stage 64 records per batch) */
   uint32_t flags;       /* GS_* flags above */
   float lambda_depth;   /* weight of the depth term of the fused L1 loss */
 } gs_raster_cfg;

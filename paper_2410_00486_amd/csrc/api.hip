@@ -35,8 +35,7 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                              const float* depth, const float* T_final, const uint32_t* last,
                              const float* dL_dcolor, const float* dL_ddepth,
                              const float* target_rgb, const float* target_depth, int fused,
-                             const uint32_t* sorted_vals, const uint32_t* order, int32_t* queue,
-                             int grid, hipStream_t s);
+                             const uint32_t* sorted_vals, int splat_grid, hipStream_t s);
 hipError_t launch_project_bwd(const Plan& P, const gs_gaussians& g, const float* cams, void* ws,
                               const gs_gaussian_grads& out, float* dL_dpose, int accumulate,
                               bool zeroed, hipStream_t s);
@@ -45,7 +44,6 @@ hipError_t launch_adam(const gs_param_group* groups, int n_groups, int step, dou
                        int32_t* step_dev, hipStream_t s, const uint32_t* const* vis = nullptr,
                        const int32_t* per = nullptr, const int32_t* overflow = nullptr,
                        const AdamFold* fold = nullptr);
-int render_bwd_blocks_per_cu(const Plan& P);
 int blocks_per_tile(const Plan& P);
 int splat_blocks_per_cu(const Plan& P);
 int64_t ssim_tiles(const Plan& P);
@@ -361,13 +359,6 @@ gs_status gs_bin_sort(const gs_plan* plan, void* ws, void* stream) {
   return hip_check(e, "gs_bin_sort");
 }
 
-// Grid of the persistent pixel-wise backward.
-static int persistent_grid(const Plan& P) {
-  const int per_cu = render_bwd_blocks_per_cu(P);
-  const int64_t items = (P.vt.total_tiles + P.cfg.chunk - 1) / P.cfg.chunk;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)device_cus() * per_cu));
-}
-
 gs_status gs_render_fwd(const gs_plan* plan, void* ws, const float* cams_dev, float* color,
                         float* depth, float* T_final, uint32_t* last, const float* target_rgb,
                         const float* target_depth, float* loss_per_view, void* stream) {
@@ -403,18 +394,14 @@ gs_status gs_render_bwd_raster(const gs_plan* plan, void* ws, const float* cams_
   if (fused && !target_rgb) return fail(GS_ERR_INVALID_ARG, "GS_FUSED_L1 needs target_rgb");
   if (!fused && !dL_dcolor) return fail(GS_ERR_INVALID_ARG, "dL_dcolor is null (and GS_FUSED_L1 not set)");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
-  const bool pers = !splat && (P.cfg.flags & GS_PERSISTENT) != 0;
-  int32_t* fl = ws_at<int32_t>(ws, P.off_flags);
-  hipError_t e = hipSuccess;
   // splat-wise: grid-stride over the buckets, as many waves as stay resident
-  const int grid = splat ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu(P)))
-                         : (pers ? persistent_grid(P) : P.vt.total_tiles);
-  if (e == hipSuccess)
-    e = launch_render_bwd(P, ws, cams_dev, color, depth, T_final, last, dL_dcolor, dL_ddepth,
-                          target_rgb, target_depth, fused ? 1 : 0, sorted_vals(P, ws),
-                          ws_at<uint32_t>(ws, P.off_order),
-                          pers ? fl + F_QUEUE_BWD : nullptr, grid, s);
+  const int splat_grid =
+      (P.cfg.flags & GS_SPLAT_BWD)
+          ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu(P)))
+          : 0;
+  const hipError_t e = launch_render_bwd(P, ws, cams_dev, color, depth, T_final, last, dL_dcolor,
+                                         dL_ddepth, target_rgb, target_depth, fused ? 1 : 0,
+                                         sorted_vals(P, ws), splat_grid, s);
   return hip_check(e, "gs_render_bwd_raster");
 }
 

@@ -18,15 +18,14 @@
 // Bound by VALU issue (about 80 instructions for four splats of 64 pixels)
 // and, for the longest lists, by the latency of one wavefront.
 //
-// Backward (pixel-wise): one wave64 per tile, a lane owns PPL = tile pixels /
-// 64 pixels (2x2 quads on 16x16 tiles, horizontal pairs on 16x8, one pixel
-// on 8x8); back to front from the tile's last used position.  Each lane
+// Backward (pixel-wise): a workgroup per tile, again a wavefront per 8x8
+// block, back to front from the tile's last used position.  Each lane
 // recomputes alpha with the forward's code (so every skip decision is the
 // forward's), undoes the transmittance by division from T_final and keeps
-// the sums of what lies behind.  The ten per-pair partial gradients of a
-// Gaussian are summed over the lane's pixels, then over the wavefront with
-// DPP (skipped when no lane contributes), and written to the pair's own
-// slot: no atomics, deterministic.
+// the loss-weighted sum of what lies behind.  The ten per-pair partial
+// gradients of a Gaussian are summed over the wavefront with DPP, over the
+// tile's blocks in LDS in a fixed order, and written to the pair's own slot:
+// no atomics, deterministic.
 #include <type_traits>
 
 #include "tilesort.h"
@@ -37,18 +36,6 @@ namespace {
 constexpr float kAlphaMax = 0.99f;
 constexpr float kAlphaMin = 1.0f / 255.0f;
 constexpr float kTMin = 1e-4f;
-
-// alpha of record r at sample point (sx, sy): oG = opacity x Gaussian, a =
-// oG clamped at 0.99.  Returns false when the Gaussian is skipped (alpha
-// below 1/255; its exponent is never positive).
-__device__ __forceinline__ bool eval_alpha(const Rec& r, double sx, double sy, double& dx,
-                                           double& dy, float& oG, float& a) {
-  dx = r.mx - sx;
-  dy = r.my - sy;
-  oG = __builtin_amdgcn_exp2f(rec_exponent(r, (float)dx, (float)dy));
-  a = fminf(kAlphaMax, oG);
-  return a >= kAlphaMin;
-}
 
 // DPP move with zero fill where the lane has no source or its row is masked.
 template <int CTRL, int ROW_MASK = 0xF>
@@ -75,26 +62,38 @@ __device__ __forceinline__ float wave_sum_to_last(float x) {
 // its values and adds the partner's copy of that half: row mirror (partner
 // differs in bit 3), half-row mirror (bit 2), quad reversal (bit 1), quad
 // swap (bit 0) -- then the row pairs (bit 4) and half-waves (bit 5) are
-// added with the gfx950 lane swaps.  37 VALU operations instead of the 60
-// of ten separate reductions.  Every lane must be active.
+// added with the gfx950 lane swaps.  In the first two steps the halves are
+// whole banks of four lanes, so the lanes that keep the other value are
+// written by a second DPP add with a bank mask and nothing is selected (two
+// instructions for two values instead of three).  28 VALU operations instead
+// of the 60 of ten separate reductions.  Every lane must be active.  (A DPP
+// read needs two wait states after the VALU write of its register.)
 __device__ __forceinline__ float sel(bool c, float a, float b) { return c ? a : b; }
 
+#define GS_ADD_MIRROR(D, X, CTRL, BANKS) \
+  "v_add_f32_dpp " D ", " X ", " X " " CTRL " row_mask:0xf bank_mask:" BANKS "\n\t"
 __device__ __forceinline__ float reduce_scatter10(const float* g) {
   const int l = threadIdx.x & 15;
-  const bool b3 = l & 8, b2 = l & 4, b1 = l & 2, b0 = l & 1;
-  float h[6], u[4], w[2];
-#pragma unroll
-  for (int k = 0; k < 5; ++k)
-    h[k] = sel(b3, g[k + 5], g[k]) + dpp<0x140>(sel(b3, g[k], g[k + 5]));  // row_mirror
-  h[5] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    u[k] = sel(b2, h[k + 3], h[k]) + dpp<0x141>(sel(b2, h[k], h[k + 3]));  // row_half_mirror
-  u[3] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < 2; ++k)
-    w[k] = sel(b1, u[k + 2], u[k]) + dpp<0x1B>(sel(b1, u[k], u[k + 2]));  // quad [3,2,1,0]
-  float z = sel(b0, w[1], w[0]) + dpp<0xB1>(sel(b0, w[0], w[1]));         // quad [1,0,3,2]
+  const bool b1 = l & 2, b0 = l & 1;
+  float h0, h1, h2, h3, h4, u0, u1, u2;
+  asm("s_nop 1\n\t"
+      GS_ADD_MIRROR("%0", "%5", "row_mirror", "0xf") GS_ADD_MIRROR("%1", "%6", "row_mirror", "0xf")
+      GS_ADD_MIRROR("%2", "%7", "row_mirror", "0xf") GS_ADD_MIRROR("%3", "%8", "row_mirror", "0xf")
+      GS_ADD_MIRROR("%4", "%9", "row_mirror", "0xf") GS_ADD_MIRROR("%0", "%10", "row_mirror", "0xc")
+      GS_ADD_MIRROR("%1", "%11", "row_mirror", "0xc") GS_ADD_MIRROR("%2", "%12", "row_mirror", "0xc")
+      GS_ADD_MIRROR("%3", "%13", "row_mirror", "0xc") GS_ADD_MIRROR("%4", "%14", "row_mirror", "0xc")
+      : "=&v"(h0), "=&v"(h1), "=&v"(h2), "=&v"(h3), "=&v"(h4)
+      : "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]),
+        "v"(g[8]), "v"(g[9]));
+  asm("s_nop 1\n\t"
+      GS_ADD_MIRROR("%0", "%3", "row_half_mirror", "0xf") GS_ADD_MIRROR("%1", "%4", "row_half_mirror", "0xf")
+      GS_ADD_MIRROR("%2", "%5", "row_half_mirror", "0xf") GS_ADD_MIRROR("%0", "%6", "row_half_mirror", "0xa")
+      GS_ADD_MIRROR("%1", "%7", "row_half_mirror", "0xa")
+      : "=&v"(u0), "=&v"(u1), "=&v"(u2)
+      : "v"(h0), "v"(h1), "v"(h2), "v"(h3), "v"(h4));
+  const float w0 = sel(b1, u2, u0) + dpp<0x1B>(sel(b1, u0, u2));  // quad [3,2,1,0]
+  const float w1 = u1 + dpp<0x1B>(u1);                            // (lanes with b1: unused)
+  float z = sel(b0, w1, w0) + dpp<0xB1>(sel(b0, w0, w1));         // quad [1,0,3,2]
   const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(z), __float_as_uint(z),
                                                     false, false);
   z = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
@@ -102,6 +101,7 @@ __device__ __forceinline__ float reduce_scatter10(const float* g) {
                                                     false, false);
   return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
 }
+#undef GS_ADD_MIRROR
 
 // Which of the ten values reduce_scatter10 leaves in lane l (first 16 lanes
 // meaningful), -1 for none.
@@ -114,37 +114,10 @@ __device__ __forceinline__ int rs_index(int lane) {
   return ((l & 8) ? 5 : 0) + hidx;
 }
 
-template <int TW, int TH>
-struct Tile {
-  static constexpr int NPX = TW * TH;
-  static constexpr int PPL = NPX / kWave;  // pixels per lane: 1, 2 or 4
-  static __device__ __forceinline__ int x(int l, int k) {
-    return PPL == 1 ? (l & 7) : 2 * (l & 7) + (k & 1);
-  }
-  static __device__ __forceinline__ int y(int l, int k) {
-    return PPL == 4 ? 2 * (l >> 3) + (k >> 1) : (l >> 3);
-  }
-};
-
 __device__ __forceinline__ int find_view(const ViewTable& vt, int gtile) {
   int v = 0;
   while (v + 1 < vt.n_views && gtile >= vt.v[v + 1].tile_off) ++v;
   return v;
-}
-
-// Records of a tile list: a copy in list order written by the per-tile
-// binning, so that a batch is one contiguous, coalesced read, or (radix
-// binning) gathered from the record array by record id.
-__device__ __forceinline__ void stage(Rec* srec, uint32_t* sval, RecSrc lrec,
-                                      const uint32_t* __restrict__ sorted_vals, uint32_t first,
-                                      int count, int lane) {
-  for (int k = lane; k < count; k += kWave) {
-    const float4* src = reinterpret_cast<const float4*>(lrec.at(first + k));
-    float4* dst = reinterpret_cast<float4*>(srec + k);
-    const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-    dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
-    sval[k] = sorted_vals[first + k];
-  }
 }
 
 // ------------------------------------------------------------------ forward
@@ -503,180 +476,243 @@ __global__ void __launch_bounds__(kLossThreads) k_loss_reduce(const float* __res
 }
 
 // ------------------------------------------------------------------ backward
+// Loss gradients of a pixel: given, or those of the fused L1 loss.
+struct PixelLoss {
+  const float *dL_dcolor, *dL_ddepth, *target_rgb, *target_depth;
+  int fused;
+  float lambda_depth;
+  // (r, g, b, depth) gradients at the colour buffers' index cbase and the
+  // one-channel buffers' index pix; o0..od: the pixel's outputs
+  __device__ __forceinline__ float4 at(int64_t cbase, int64_t npx, int64_t pix, float o0, float o1,
+                                       float o2, float od) const {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (fused) {
+      const float inv3 = 1.0f / (3.0f * (float)npx);
+      const float d0 = o0 - target_rgb[cbase];
+      const float d1 = o1 - target_rgb[cbase + npx];
+      const float d2 = o2 - target_rgb[cbase + 2 * npx];
+      a.x = d0 > 0.0f ? inv3 : (d0 < 0.0f ? -inv3 : 0.0f);
+      a.y = d1 > 0.0f ? inv3 : (d1 < 0.0f ? -inv3 : 0.0f);
+      a.z = d2 > 0.0f ? inv3 : (d2 < 0.0f ? -inv3 : 0.0f);
+      if (target_depth) {
+        const float dd = od - target_depth[pix];
+        const float sc = lambda_depth / (float)npx;
+        a.w = dd > 0.0f ? sc : (dd < 0.0f ? -sc : 0.0f);
+      }
+    } else {
+      a.x = dL_dcolor[cbase];
+      a.y = dL_dcolor[cbase + npx];
+      a.z = dL_dcolor[cbase + 2 * npx];
+      a.w = dL_ddepth ? dL_ddepth[pix] : 0.0f;
+    }
+    return a;
+  }
+};
+
+struct BwdArgs {
+  RecSrc lrec;
+  const uint32_t *sorted_vals, *ranges, *tile_last;
+  const float *cams, *color, *depth, *T_final;
+  const uint32_t* last;
+  PixelLoss loss;
+  float* grad_pair;
+  const uint32_t* order;
+  const int32_t* fl;
+};
+
+// LDS of a workgroup of the pixel-wise backward: a batch of 64 list
+// positions -- offsets from every column and row of the tile's sample points,
+// shapes and colours by position -- the positions each block keeps, and each
+// block's sums of the ten partials by position.
 template <int TW, int TH>
-__device__ __forceinline__ void bwd_tile(
-    int gtile, RecSrc lrec,
-    const uint32_t* __restrict__ sorted_vals, const uint32_t* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_last, const float* __restrict__ cams, const ViewTable& vt,
-    int B, const float* __restrict__ color, const float* __restrict__ depth,
-    const float* __restrict__ T_final, const uint32_t* __restrict__ last,
-    const float* __restrict__ dL_dcolor, const float* __restrict__ dL_ddepth,
-    const float* __restrict__ target_rgb, const float* __restrict__ target_depth, int fused,
-    float lambda_depth, float* __restrict__ grad_pair, Rec* srec, uint32_t* sval) {
-  using TG = Tile<TW, TH>;
-  constexpr int PPL = TG::PPL;
+struct BwdLds {
+  static constexpr int NS = sub_tiles<TW, TH>();
+  float dx[TW][kWave + 1], dy[TH][kWave + 1];  // (odd rows: a lane's column is its bank)
+  float4 shape[kWave], colour[kWave];
+  float o[kWave];
+  uint64_t kept[NS];
+  float part[NS][kWave][10];
+};
+
+// Pixel-wise backward of a tile: a workgroup of one wavefront per 8x8 block,
+// one pixel per lane, over the tile's list from its last used position to
+// the front, 64 positions a batch.  As in the forward, a wavefront leaves out
+// the splats that cannot reach its block, and a splat's offsets are formed
+// once; then every wavefront walks its own kept positions and leaves the ten
+// sums of each in LDS, which the workgroup adds over its blocks in a fixed
+// order and writes to the pairs' slots.
+//
+// One wavefront per tile with four pixels per lane left 3225 wavefronts (and
+// one serial chain per tile) for a 1200x680 view in 16x16 tiles: 1206 us for
+// 627k pairs, this form 228 us (a 128x96 view, 48 tiles: 369 -> 53 us).
+// Bound by VALU issue (88.6M instructions, 144 us of the 228): about 80 per
+// kept splat and block, a third of them the reduction of the ten partials
+// over the lanes.
+template <int TW, int TH>
+__global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
+                                                                            ViewTable vt) {
+  constexpr int NS = sub_tiles<TW, TH>(), NT = kWave * NS, BX = TW / kSub;
+  __shared__ __align__(16) BwdLds<TW, TH> S;
+  const int lane = lane_id(), sub = NS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int gtile = order_tile(A.order, A.fl, vt.total_tiles, blockIdx.x);
   const int v = find_view(vt, gtile);
   const ViewInfo vi = vt.v[v];
   const int lt = gtile - vi.tile_off;
   const int tx0 = (lt % vi.tiles_x) * TW, ty0 = (lt / vi.tiles_x) * TH;
-  const int lane = threadIdx.x;
-  const uint32_t s = ranges[2 * (int64_t)gtile], e = ranges[2 * (int64_t)gtile + 1];
-  const uint32_t tl = tile_last_of<sub_tiles<TW, TH>()>(tile_last, gtile);
-  const float* cam = cams + (int64_t)v * GS_CAMERA_FLOATS;
-  const float bg0 = cam[17], bg1 = cam[18], bg2 = cam[19];
+  const int sx = sub % BX, sy = sub / BX;  // the block's place in the tile
+  const int col = lane & (kSub - 1), row = lane / kSub;
+  const int px = tx0 + kSub * sx + col, py = ty0 + kSub * sy + row;
+  const uint32_t s = A.ranges[2 * (int64_t)gtile], e = A.ranges[2 * (int64_t)gtile + 1];
+  const uint32_t tl = tile_last_of<NS>(A.tile_last, gtile);
 
   // pairs beyond the last used position get zero gradients
-  for (uint32_t k = tl + (uint32_t)lane; k < e - s; k += kWave) {
+  for (uint32_t k = tl + threadIdx.x; k < e - s; k += NT) {
     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    store_pair(grad_pair, sorted_vals[s + k], z, z, make_float2(0.f, 0.f));
+    store_pair(A.grad_pair, A.sorted_vals[s + k], z, z, make_float2(0.f, 0.f));
   }
 
-  // lanes of the first row write the scattered sums of the ten partials;
-  // the conic and mean entries carry their sign and halves here
+  float T = 1.0f, B = 0.0f;  // transmittance behind; loss-weighted output behind
+  float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t L = 0;
+  if (px < vi.W && py < vi.H) {
+    const float* cam = A.cams + (int64_t)v * GS_CAMERA_FLOATS;
+    const int64_t npx = (int64_t)vi.W * vi.H, pl = (int64_t)py * vi.W + px;
+    const int64_t pix = (int64_t)vi.pix_off + pl, cbase = 3 * (int64_t)vi.pix_off + pl;
+    T = A.T_final[pix];
+    L = A.last[pix];
+    if (A.loss.fused)
+      g = A.loss.at(cbase, npx, pix, A.color[cbase], A.color[cbase + npx], A.color[cbase + 2 * npx],
+                    A.depth[pix]);
+    else
+      g = A.loss.at(cbase, npx, pix, 0.f, 0.f, 0.f, 0.f);
+    // behind: the background seen through T_final, nothing in depth
+    B = T * (g.x * cam[17] + g.y * cam[18] + g.z * cam[19]);
+  }
+  const uint32_t Lmax = wave_max(L);
   const int my_idx = lane < 16 ? rs_index(lane) : -1;
-  const float my_scale = (my_idx == 5 || my_idx == 7) ? -0.5f : (my_idx >= 6 ? -1.0f : 1.0f);
-  double sx[PPL], sy[PPL];
-  float T[PPL], gC0[PPL], gC1[PPL], gC2[PPL], gD[PPL], Sc0[PPL], Sc1[PPL], Sc2[PPL], Sd[PPL];
-  uint32_t L[PPL];
-  const int64_t npx = (int64_t)vi.W * vi.H;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int px = tx0 + TG::x(lane, k), py = ty0 + TG::y(lane, k);
-    sx[k] = px + 0.5;
-    sy[k] = py + 0.5;
-    T[k] = 1.0f; gC0[k] = gC1[k] = gC2[k] = gD[k] = 0.0f;
-    L[k] = 0;
-    if (px < vi.W && py < vi.H) {
-      const int64_t pl = (int64_t)py * vi.W + px;
-      const int64_t pix = (int64_t)vi.pix_off + pl;
-      const int64_t cbase = 3 * (int64_t)vi.pix_off + pl;
-      T[k] = T_final[pix];
-      L[k] = last[pix];
-      if (fused) {
-        const float inv3 = 1.0f / (3.0f * (float)npx);
-        const float d0 = color[cbase] - target_rgb[cbase];
-        const float d1 = color[cbase + npx] - target_rgb[cbase + npx];
-        const float d2 = color[cbase + 2 * npx] - target_rgb[cbase + 2 * npx];
-        gC0[k] = d0 > 0.0f ? inv3 : (d0 < 0.0f ? -inv3 : 0.0f);
-        gC1[k] = d1 > 0.0f ? inv3 : (d1 < 0.0f ? -inv3 : 0.0f);
-        gC2[k] = d2 > 0.0f ? inv3 : (d2 < 0.0f ? -inv3 : 0.0f);
-        if (target_depth) {
-          const float dd = depth[pix] - target_depth[pix];
-          const float sc = lambda_depth / (float)npx;
-          gD[k] = dd > 0.0f ? sc : (dd < 0.0f ? -sc : 0.0f);
-        }
-      } else {
-        gC0[k] = dL_dcolor[cbase];
-        gC1[k] = dL_dcolor[cbase + npx];
-        gC2[k] = dL_dcolor[cbase + 2 * npx];
-        gD[k] = dL_ddepth ? dL_ddepth[pix] : 0.0f;
-      }
-    }
-    // behind-sums: background seen through T_final, nothing behind in depth
-    Sc0[k] = T[k] * bg0;
-    Sc1[k] = T[k] * bg1;
-    Sc2[k] = T[k] * bg2;
-    Sd[k] = 0.0f;
-  }
+  const double ax0 = (double)(tx0 + kSub * sx) + 0.5, ay0 = (double)(ty0 + kSub * sy) + 0.5;
 
-  for (int bend = (int)tl; bend > 0; bend -= B) {
-    const int bstart = max(0, bend - B);
+  for (int bend = (int)tl; bend > 0; bend -= kWave) {
+    const int bstart = bend > kWave ? bend - kWave : 0;
     const int nb = bend - bstart;
-    __syncthreads();
-    stage(srec, sval, lrec, sorted_vals, s + (uint32_t)bstart, nb, lane);
-    __syncthreads();
-#pragma unroll 2
-    for (int j = nb - 1; j >= 0; --j) {
-      const uint32_t pos = (uint32_t)(bstart + j);
-      const Rec& r = srec[j];
-      float ca, cb, cc;
-      rec_conic(r, ca, cb, cc);
-      float g[10];
+    const bool has = lane < nb;
+    FwdRec r{};
+    float ro = 0.0f;
+    if (has) {
+      const Rec* rec = A.lrec.at(s + (uint32_t)(bstart + lane));
+      const float4* src = reinterpret_cast<const float4*>(rec);
+      float4* d4 = reinterpret_cast<float4*>(&r);
+      d4[0] = src[0]; d4[1] = src[1]; d4[2] = src[2];
+      if (sub == 0) ro = rec->o;
+    }
+    float ox[kSub], oy[kSub];
+    double ax = ax0, ay = ay0;
+    asm volatile("" : "+v"(ax), "+v"(ay));
 #pragma unroll
-      for (int f = 0; f < 10; ++f) g[f] = 0.0f;
-      bool contrib = false;
+    for (int k = 0; k < kSub; ++k) {
+      ox[k] = (float)(r.mx - ax);
+      oy[k] = (float)(r.my - ay);
+      ax += 1.0;
+      ay += 1.0;
+    }
+    uint64_t kept = ballot64(has && !(max_exponent(r, ox[kSub - 1], ox[0], oy[kSub - 1], oy[0]) < kCullExp));
+    // (nothing of this block is used from position Lmax on)
+    const int used = (int)Lmax - bstart;
+    kept &= used >= kWave ? ~0ull : (used <= 0 ? 0ull : (1ull << used) - 1ull);
+    // the first block of a column (row) of blocks writes its offsets
+    if (sy == 0) {
 #pragma unroll
-      for (int k = 0; k < PPL; ++k) {
-        if (pos < L[k]) {
-          double dx, dy;
-          float oG, a;
-          if (eval_alpha(r, sx[k], sy[k], dx, dy, oG, a)) {
-            contrib = true;
-            const float inv_om = __builtin_amdgcn_rcpf(1.0f - a);
-            const float Tk = T[k] * inv_om;
-            const float wgt = a * Tk;
-            g[0] = fmaf(wgt, gC0[k], g[0]);
-            g[1] = fmaf(wgt, gC1[k], g[1]);
-            g[2] = fmaf(wgt, gC2[k], g[2]);
-            g[3] = fmaf(wgt, gD[k], g[3]);
-            const float front = gC0[k] * r.r + gC1[k] * r.g + gC2[k] * r.b + gD[k] * r.z;
-            const float behind = gC0[k] * Sc0[k] + gC1[k] * Sc1[k] + gC2[k] * Sc2[k] + gD[k] * Sd[k];
-            const float g_alpha = Tk * front - behind * inv_om;
-            Sc0[k] = fmaf(r.r, wgt, Sc0[k]);
-            Sc1[k] = fmaf(r.g, wgt, Sc1[k]);
-            Sc2[k] = fmaf(r.b, wgt, Sc2[k]);
-            Sd[k] = fmaf(r.z, wgt, Sd[k]);
-            T[k] = Tk;
-            // unclamped alpha only (no gradient through the 0.99 clamp);
-            // the conic and mean partials are formed from t = gpow dx,
-            // u = gpow dy, their signs and halves applied after the sum
-            const bool open = oG <= kAlphaMax;
-            const float gpow = open ? a * g_alpha : 0.0f;
-            const float fx = (float)dx, fy = (float)dy;
-            const float t = gpow * fx, u = gpow * fy;
-            g[4] += gpow;  // (divided by the opacity at the store)
-            g[5] = fmaf(t, fx, g[5]);
-            g[6] = fmaf(t, fy, g[6]);
-            g[7] = fmaf(u, fy, g[7]);
-            g[8] = fmaf(ca, t, fmaf(cb, u, g[8]));
-            g[9] = fmaf(cb, t, fmaf(cc, u, g[9]));
-          }
+      for (int k = 0; k < kSub; ++k) S.dx[kSub * sx + k][lane] = ox[k];
+    }
+    if (sx == 0) {
+#pragma unroll
+      for (int k = 0; k < kSub; ++k) S.dy[kSub * sy + k][lane] = oy[k];
+    }
+    if (sub == 0) {
+      S.shape[lane] = make_float4(r.t, r.s1, r.s2, r.lo);
+      S.colour[lane] = make_float4(r.r, r.g, r.b, r.z);
+      S.o[lane] = ro;
+    }
+    if (lane == 0) S.kept[sub] = kept;
+    __syncthreads();
+    // N kept positions j[0] > j[1] .. at once: independent alphas and
+    // reductions, only T and B run through them in order
+    auto step = [&](auto n_c, const int* j) {
+      constexpr int N = decltype(n_c)::value;
+      float dx[N], dy[N], oG[N], a[N], front[N];
+      bool hit[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        dx[k] = S.dx[kSub * sx + col][j[k]];
+        dy[k] = S.dy[kSub * sy + row][j[k]];
+        const float4 sh = S.shape[j[k]], cl = S.colour[j[k]];
+        oG[k] = __builtin_amdgcn_exp2f(exponent(sh.x, sh.y, sh.z, sh.w, dx[k], dy[k]));
+        front[k] = fmaf(g.w, cl.w, fmaf(g.z, cl.z, fmaf(g.y, cl.y, g.x * cl.x)));
+        a[k] = fminf(kAlphaMax, oG[k]);
+        hit[k] = (a[k] >= kAlphaMin) & ((uint32_t)(bstart + j[k]) < L);
+        // alpha of a blended splat, 0 otherwise: then 1 - alpha = 1 and every
+        // term below is 0 or leaves its sum as it is
+        a[k] = hit[k] ? a[k] : 0.0f;
+      }
+      float z[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const float inv_om = __builtin_amdgcn_rcpf(1.0f - a[k]);
+        T *= inv_om;  // in front of this splat
+        const float wgt = a[k] * T;
+        const float g_alpha = fmaf(T, front[k], -(B * inv_om));
+        B = fmaf(front[k], wgt, B);
+        // unclamped alpha only (no gradient through the 0.99 clamp); the
+        // conic and mean partials are moments of gpow = alpha dL/dalpha,
+        // their signs and factors applied after the sums
+        const float gpow = oG[k] <= kAlphaMax ? a[k] * g_alpha : 0.0f;
+        const float t = gpow * dx[k], u = gpow * dy[k];
+        const float p[10] = {wgt * g.x, wgt * g.y, wgt * g.z, wgt * g.w, gpow,
+                             t * dx[k], t * dy[k], u * dy[k], t,         u};
+        z[k] = reduce_scatter10(p);
+      }
+      if (my_idx >= 0) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) S.part[sub][j[k]][my_idx] = z[k];
+      }
+    };
+    for (uint64_t m = kept; m;) {
+      int j[2];
+      j[0] = 63 - __builtin_clzll(m);
+      m &= ~(1ull << j[0]);
+      if (m == 0) {
+        step(std::integral_constant<int, 1>{}, j);
+        break;
+      }
+      j[1] = 63 - __builtin_clzll(m);
+      m &= ~(1ull << j[1]);
+      step(std::integral_constant<int, 2>{}, j);
+    }
+    __syncthreads();
+    for (int q = (int)threadIdx.x; q < nb; q += NT) {
+      float f[10];
+#pragma unroll
+      for (int k = 0; k < 10; ++k) f[k] = 0.0f;
+#pragma unroll
+      for (int b = 0; b < NS; ++b)
+        if ((S.kept[b] >> q) & 1ull) {
+#pragma unroll
+          for (int k = 0; k < 10; ++k) f[k] += S.part[b][q][k];
         }
-      }
-      float* gpf = grad_pair + (int64_t)sval[j] * kPairGrad;
-      if (ballot64(contrib) != 0) {
-        const float z = reduce_scatter10(g);
-        const float sc = my_idx == 4 ? (r.o > 0.0f ? 1.0f / r.o : 0.0f) : my_scale;
-        if (my_idx >= 0) gpf[my_idx] = z * sc;
-      } else if (lane == 0) {
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        store_pair(gpf, 0, z, z, make_float2(0.f, 0.f));
-      }
+      Rec c;
+      const float4 sh = S.shape[q];
+      c.t = sh.x;
+      c.s1 = sh.y;
+      c.s2 = sh.z;
+      float ca, cb, cc;
+      rec_conic(c, ca, cb, cc);
+      const float o = S.o[q];
+      store_pair(A.grad_pair, A.sorted_vals[s + (uint32_t)(bstart + q)],
+                 make_float4(f[0], f[1], f[2], f[3]),
+                 make_float4(o > 0.0f ? f[4] / o : 0.0f, -0.5f * f[5], -f[6], -0.5f * f[7]),
+                 make_float2(-(ca * f[8] + cb * f[9]), -(cb * f[8] + cc * f[9])));
     }
-  }
-}
-
-template <int TW, int TH>
-__global__ void __launch_bounds__(kWave) k_render_bwd(
-    RecSrc lrec,
-    const uint32_t* __restrict__ sorted_vals, const uint32_t* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_last, const float* __restrict__ cams, ViewTable vt, int B,
-    const float* __restrict__ color, const float* __restrict__ depth,
-    const float* __restrict__ T_final, const uint32_t* __restrict__ last,
-    const float* __restrict__ dL_dcolor, const float* __restrict__ dL_ddepth,
-    const float* __restrict__ target_rgb, const float* __restrict__ target_depth, int fused,
-    float lambda_depth, float* __restrict__ grad_pair, const uint32_t* __restrict__ order,
-    const int32_t* __restrict__ fl, int32_t* __restrict__ queue, int chunk) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  Rec* srec = reinterpret_cast<Rec*>(smem);
-  uint32_t* sval = reinterpret_cast<uint32_t*>(smem + (size_t)B * sizeof(Rec));
-  if (queue == nullptr) {
-    const int g = order_tile(order, fl, vt.total_tiles, blockIdx.x);
-    bwd_tile<TW, TH>(g, lrec, sorted_vals, ranges, tile_last, cams, vt, B, color, depth,
-                     T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused,
-                     lambda_depth, grad_pair, srec, sval);
-    return;
-  }
-  const int n_items = (vt.total_tiles + chunk - 1) / chunk;
-  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int first = item * chunk;
-    const int lastt = min(vt.total_tiles, first + chunk);
-    for (int k = first; k < lastt; ++k) {
-      const int g = order_tile(order, fl, vt.total_tiles, (uint32_t)k);
-      bwd_tile<TW, TH>(g, lrec, sorted_vals, ranges, tile_last, cams, vt, B, color,
-                       depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth,
-                       fused, lambda_depth, grad_pair, srec, sval);
-    }
+    __syncthreads();
   }
 }
 
@@ -1016,18 +1052,13 @@ hipError_t fwd_launch(const Plan& P, void* ws, const float* cams, float* color, 
 template <int TW, int TH>
 hipError_t bwd_launch(const Plan& P, void* ws, const float* cams, const float* color,
                       const float* depth, const float* T_final, const uint32_t* last,
-                      const float* dL_dcolor, const float* dL_ddepth, const float* target_rgb,
-                      const float* target_depth, int fused, const uint32_t* sorted_vals,
-                      const uint32_t* order, int32_t* queue, int grid, hipStream_t s) {
-  const int B = P.cfg.lds_batch;
-  const size_t lds = (size_t)B * (sizeof(Rec) + sizeof(uint32_t));
-  hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3(grid), dim3(kWave), lds, s,
-                     rec_src(P, ws), sorted_vals,
-                     ws_at<uint32_t>(ws, P.off_ranges), ws_at<uint32_t>(ws, P.off_tile_last), cams,
-                     P.vt, B, color, depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb,
-                     target_depth, fused, P.cfg.lambda_depth,
-                     ws_at<float>(ws, P.off_grad_pair), order, ws_at<int32_t>(ws, P.off_flags),
-                     queue, P.cfg.chunk);
+                      const PixelLoss& loss, const uint32_t* sorted_vals, hipStream_t s) {
+  const BwdArgs A{rec_src(P, ws), sorted_vals, ws_at<uint32_t>(ws, P.off_ranges),
+                  ws_at<uint32_t>(ws, P.off_tile_last), cams, color, depth, T_final, last, loss,
+                  ws_at<float>(ws, P.off_grad_pair), ws_at<uint32_t>(ws, P.off_order),
+                  ws_at<int32_t>(ws, P.off_flags)};
+  hipLaunchKernelGGL((k_render_bwd<TW, TH>), dim3((unsigned)P.vt.total_tiles),
+                     dim3(kWave * sub_tiles<TW, TH>()), 0, s, A, P.vt);
   return hipGetLastError();
 }
 
@@ -1043,15 +1074,6 @@ int occupancy(K kernel, size_t lds) {
 
 // 8x8 blocks of pixels per tile: the forward's wavefronts per tile.
 int blocks_per_tile(const Plan& P) { return P.cfg.tile_w * P.cfg.tile_h / (kSub * kSub); }
-
-// Resident single-wave workgroups per CU of the pixel-wise backward.
-int render_bwd_blocks_per_cu(const Plan& P) {
-  const size_t lds = (size_t)P.cfg.lds_batch * (sizeof(Rec) + sizeof(uint32_t));
-  const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
-  if (tw == 16 && th == 16) return occupancy(k_render_bwd<16, 16>, lds);
-  if (tw == 16 && th == 8) return occupancy(k_render_bwd<16, 8>, lds);
-  return occupancy(k_render_bwd<8, 8>, lds);
-}
 
 // Resident workgroups per CU of the splat-wise backward.
 int splat_blocks_per_cu(const Plan& P) {
@@ -1088,22 +1110,22 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                              const float* depth, const float* T_final, const uint32_t* last,
                              const float* dL_dcolor, const float* dL_ddepth,
                              const float* target_rgb, const float* target_depth, int fused,
-                             const uint32_t* sorted_vals, const uint32_t* order, int32_t* queue,
-                             int grid, hipStream_t s) {
+                             const uint32_t* sorted_vals, int splat_grid, hipStream_t s) {
   if (P.vt.total_tiles == 0) return hipSuccess;
   const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
   if (P.cfg.flags & GS_SPLAT_BWD) {
     if (tw == 16 && th == 16)
-      return bwd_splat_launch<16, 16>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, grid, s);
+      return bwd_splat_launch<16, 16>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
     if (tw == 16 && th == 8)
-      return bwd_splat_launch<16, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, grid, s);
-    return bwd_splat_launch<8, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, grid, s);
+      return bwd_splat_launch<16, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
+    return bwd_splat_launch<8, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
   }
+  const PixelLoss loss{dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, P.cfg.lambda_depth};
   if (tw == 16 && th == 16)
-    return bwd_launch<16, 16>(P, ws, cams, color, depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, order, queue, grid, s);
+    return bwd_launch<16, 16>(P, ws, cams, color, depth, T_final, last, loss, sorted_vals, s);
   if (tw == 16 && th == 8)
-    return bwd_launch<16, 8>(P, ws, cams, color, depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, order, queue, grid, s);
-  return bwd_launch<8, 8>(P, ws, cams, color, depth, T_final, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, order, queue, grid, s);
+    return bwd_launch<16, 8>(P, ws, cams, color, depth, T_final, last, loss, sorted_vals, s);
+  return bwd_launch<8, 8>(P, ws, cams, color, depth, T_final, last, loss, sorted_vals, s);
 }
 
 }  // namespace gs

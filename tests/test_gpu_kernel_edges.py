@@ -10,7 +10,8 @@ import paper_2410_00486_amd as gsr
 from paper_2410_00486_amd import _lib as L
 from synth import scenes
 
-from gpu_common import assert_forward_close, run_gpu, view_images
+from gpu_common import (assert_forward_close, assert_grads_close, assert_pose_close, grads_np,
+                        oracle_reference, run_gpu, view_images)
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +102,22 @@ def test_tile_sort_list_length_edges(n):
     np.testing.assert_array_equal(got(L.GS_WS_SORTED_KEYS, torch.int64, P).view(np.uint64), keys)
     np.testing.assert_array_equal(got(L.GS_WS_SORTED_RECS, torch.int32, P), vals.astype(np.int32))
     np.testing.assert_array_equal(got(L.GS_WS_RANGES, torch.int32, 2 * T).view(np.uint32), ranges)
+
+
+@pytest.mark.parametrize("n,width,height", [(1, 1, 1), (3, 17, 8), (64, 16, 16), (65, 33, 19),
+                                            (130, 40, 25), (300, 90, 70)])
+@pytest.mark.parametrize("tile", [(8, 8), (16, 8), (16, 16)])
+def test_pixelwise_backward_blocks_match_oracle(n, width, height, tile):
+    """The pixel-wise backward, a wavefront per 8x8 block with the blocks'
+    sums added per tile: gradients and camera tangent within the gradient
+    tolerance of the oracle, for lists around one and two batches and images
+    that end inside a block."""
+    w = scenes.tiny_scene(31 + n, n=n, width=width, height=height, f=0.9 * max(width, 8), degree=1)
+    w.scene.opacity_logits[::7] = 8.0  # above the 0.99 clamp
+    cam = w.cameras[0]
+    print(f"pixel-wise backward n {n} {width}x{height} tile {tile}", flush=True)
+    gcs, gds = scenes.linear_loss_weights(70 + n, [cam])
+    it = run_gpu(w.scene, [cam], tile=tile, dL_dcolor=gcs, dL_ddepth=gds, pose=True)
+    grads, poses, exclude, poses_f = oracle_reference(w.scene, [cam], gcs, gds, tile)
+    assert_grads_close(grads_np(it), grads, exclude)
+    assert_pose_close(it.dL_dpose.cpu().numpy(), poses, poses_f)
