@@ -72,11 +72,14 @@ typedef int32_t gs_status;
                                          (the order gs_bin_sort writes), which
                                          balances them better than resident kernels
                                          with a static share did */
-#define GS_SPLAT_BWD (1u << 4)        /* splat-wise backward (Sec. III-C-1, Fig. 4a):
-                                         the forward stores per-pixel (T, RGB, D) states
-                                         at every 64th splat of a tile; the backward
-                                         gives each lane one splat of a 64-splat bucket
-                                         and streams pixel states across the lanes */
+#define GS_SPLAT_BWD (1u << 4)        /* splat-wise backward (Sec. III-C-1, Fig. 4a) of
+                                         8x8 tiles: the forward stores per-pixel (T,
+                                         RGB, D) states at every 64th splat it kept of
+                                         a tile; the backward gives each lane one splat
+                                         of a 64-splat bucket and takes the pixels in
+                                         turn.  Larger tiles take the pixel-wise
+                                         backward, which is faster there; the gradients
+                                         differ by the summation order only */
 #define GS_RADIX_BIN (1u << 5)        /* gs_bin_sort by two stable radix sorts (the
                                          visible records by depth, then their pairs,
                                          generated in depth order, by tile id) instead
@@ -228,9 +231,9 @@ gs_status gs_render_fwd(const gs_plan* plan, void* ws, const float* cams_dev, fl
 /* a4-a6. Backward of one iteration (Eqs. (2)-(4)).  Default (pixel-wise):
  * per pixel, back to front from its last blended Gaussian, with the
  * transmittance recomputed by division from T_final; per-pair gradients are
- * reduced across the tile's wavefront.  With GS_SPLAT_BWD (splat-wise,
+ * reduced across the wavefronts of the tile.  With GS_SPLAT_BWD (splat-wise,
  * Sec. III-C-1): one lane per splat of a 64-splat bucket, pixel states
- * resumed from those the forward stored and handed from lane to lane.
+ * resumed from those the forward stored and advanced across the lanes.
  * Either way the per-pair gradients are then summed per Gaussian in a fixed
  * order (deterministic) and carried through the projection to the
  * parameters.  Upstream gradients

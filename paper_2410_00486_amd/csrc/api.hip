@@ -45,7 +45,7 @@ hipError_t launch_adam(const gs_param_group* groups, int n_groups, int step, dou
                        const int32_t* per = nullptr, const int32_t* overflow = nullptr,
                        const AdamFold* fold = nullptr);
 int blocks_per_tile(const Plan& P);
-int splat_blocks_per_cu(const Plan& P);
+int splat_blocks_per_cu();
 int64_t ssim_tiles(const Plan& P);
 size_t densify_tmp_bytes(int64_t n);
 hipError_t launch_grad_stats(const Plan& P, void* ws, float* accum, float* denom, hipStream_t s);
@@ -249,16 +249,19 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_gp_tmp = take(n_views > 1 ? (size_t)n * 4 * 8 : 0);
   P->off_ssim_maps = take((size_t)pix * 9 * 4);
   P->off_ssim_part = take((size_t)ssim_tiles(*P) * 12 * 4);
-  // splat-wise backward: bucket k of tile t uses checkpoint slot boff[t] + k,
-  // boff the exclusive scan of ceil(pairs of tile / 64); at most
-  // pair_capacity / 64 + tiles slots
-  const bool splat = (cfg->flags & GS_SPLAT_BWD) != 0;
+  // splat-wise backward, a form of the 8x8 tiles (larger tiles take the
+  // pixel-wise one, see launch_render_bwd): bucket k of tile t uses checkpoint
+  // slot boff[t] + k, boff the exclusive scan of ceil(pairs of tile / 64); at
+  // most pair_capacity / 64 + tiles slots
+  const bool splat = (cfg->flags & GS_SPLAT_BWD) != 0 && tw == 8 && th == 8;
+  P->splat = splat ? 1 : 0;
   P->ckpt_slots = splat ? pair_capacity / kBucket + tiles : 0;
   P->off_boff = take(splat ? (T + 1) * 4 : 0);
-  P->off_bq = take((size_t)P->ckpt_slots * 2 * 8);  // two bucket queues of (tile, k)
-  P->off_full_start = take(splat ? T * 4 : 0);
-  P->off_half_start = take(splat ? T * 4 : 0);
-  P->off_ckpt = take((size_t)P->ckpt_slots * tw * th * kStateFloats * 4);
+  P->off_bq = take((size_t)P->ckpt_slots * 8);  // bucket queue of (tile, k)
+  P->off_cand = take((size_t)P->ckpt_slots * kBucket * 4);
+  P->off_kept = take((size_t)P->ckpt_slots * 8);
+  P->off_seen = take(splat ? T * 8 : 0);
+  P->off_ckpt = take((size_t)P->ckpt_slots * 64 * kStateFloats * 4);
   P->scan_rounds = scan_rounds(*P);
   P->off_scan_part = take((size_t)P->scan_rounds * 64);
   // radix binning buffers, only when the plan asks for that binning
@@ -396,8 +399,8 @@ gs_status gs_render_bwd_raster(const gs_plan* plan, void* ws, const float* cams_
   hipStream_t s = static_cast<hipStream_t>(stream);
   // splat-wise: grid-stride over the buckets, as many waves as stay resident
   const int splat_grid =
-      (P.cfg.flags & GS_SPLAT_BWD)
-          ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu(P)))
+      P.splat
+          ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu()))
           : 0;
   const hipError_t e = launch_render_bwd(P, ws, cams_dev, color, depth, T_final, last, dL_dcolor,
                                          dL_ddepth, target_rgb, target_depth, fused ? 1 : 0,

@@ -43,8 +43,8 @@ __global__ void k_fill2_u32(uint32_t* __restrict__ a, int64_t na, uint32_t* __re
 // wavefront), its pair count and its number of visible records; and the
 // pair count of every tile.  One block scans both: chunks -> generation
 // offset and visible-list position of the chunk's first record; tiles ->
-// list start, bucket offset and positions in the two splat-wise bucket
-// queues.  One block needs no inter-block handshake (a grid-wide fence
+// list start and bucket offset (the tile's place in the splat-wise bucket
+// queue).  One block needs no inter-block handshake (a grid-wide fence
 // costs more than the scan itself at these sizes), and the results are
 // absolute, so the consumers add nothing.
 //
@@ -67,8 +67,6 @@ struct ScanArgs {
   uint32_t* tstart;        // list start per tile
   int64_t n_tiles;
   uint32_t* boff;          // splat-wise only (else null): bucket offset per tile, [T] = total
-  uint32_t* fstart;        // position of the tile's first full bucket in queue 0
-  uint32_t* hstart;        // position of the tile's half bucket in queue 1
   uint32_t* order;         // work order of the render kernels: kOrderClasses rows of T
   uint4* long_list;        // (tile, list start, pairs, -) of the lists for the long-list sort
   // kScanBoth: chunks and tile counts (the projection's); kScanChunks: the
@@ -168,41 +166,38 @@ __device__ __forceinline__ void store4(uint32_t* __restrict__ a, int64_t i, int6
   if (i + 2 < n) a[i + 2] = x.z;
 }
 
+// Per-thread inputs of one round: 4 * kScanVec tiles and 2 * kScanVec
+// chunks, and the thread's sums over them.  Channels: 64-bit tile pairs and
+// chunk pairs; 32-bit buckets, visible records, and the tiles
+// of each length class but the last (work order; the first four together are
+// the lists of the long-list sort).
+constexpr int kScanClass = 2;
+constexpr int kScanN32 = kScanClass + kOrderClasses - 1;
 // The 32-bit channels of a round, scanned packed: a round has at most
-// kTileRound tiles, so its class and half-bucket counts fit 16 bits and go
-// two to a word (five words scanned instead of eight: the one-block scan of
-// a small plan is a chain of these).  s: per-thread sums in, exclusive
-// starts out (the carries c added); c advanced by the round's totals.
-template <int N64, int N32>
-__device__ __forceinline__ void round_exscan(uint64_t (&s64)[N64], uint32_t (&s)[N32],
-                                             uint64_t (&c64)[N64], uint32_t (&c)[N32],
+// kTileRound tiles, so its class counts fit 16 bits and go two to a word (the
+// one-block scan of a small plan is a chain of these).  s: per-thread sums in,
+// exclusive starts out (the carries c added); c advanced by the round's
+// totals.
+__device__ __forceinline__ void round_exscan(uint64_t (&s64)[2], uint32_t (&s)[kScanN32],
+                                             uint64_t (&c64)[2], uint32_t (&c)[kScanN32],
                                              uint64_t* w64, uint32_t* w32) {
-  static_assert(N32 == 8 && kTileRound < 65536, "buckets, half, visible, five classes");
-  uint32_t p[5] = {s[0], s[2], s[1] | s[3] << 16, s[4] | s[5] << 16, s[6] | s[7] << 16};
+  static_assert(kScanN32 == 7 && kTileRound < 65536, "buckets, visible, five classes");
+  uint32_t p[5] = {s[0], s[1], s[2] | s[3] << 16, s[4] | s[5] << 16, s[6]};
   uint32_t t[5] = {};
-  block_exscan<N64, 5>(s64, p, c64, t, w64, w32);
-  const uint32_t e[8] = {p[0], p[2] & 0xFFFFu, p[1], p[2] >> 16, p[3] & 0xFFFFu, p[3] >> 16,
-                         p[4] & 0xFFFFu, p[4] >> 16};
-  const uint32_t d[8] = {t[0], t[2] & 0xFFFFu, t[1], t[2] >> 16, t[3] & 0xFFFFu, t[3] >> 16,
-                         t[4] & 0xFFFFu, t[4] >> 16};
+  block_exscan<2, 5>(s64, p, c64, t, w64, w32);
+  const uint32_t e[7] = {p[0], p[1], p[2] & 0xFFFFu, p[2] >> 16, p[3] & 0xFFFFu, p[3] >> 16, p[4]};
+  const uint32_t d[7] = {t[0], t[1], t[2] & 0xFFFFu, t[2] >> 16, t[3] & 0xFFFFu, t[3] >> 16, t[4]};
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < 7; ++k) {
     s[k] = c[k] + e[k];
     c[k] += d[k];
   }
 }
 
-// Per-thread inputs of one round: 4 * kScanVec tiles and 2 * kScanVec
-// chunks, and the thread's sums over them.  Channels: 64-bit tile pairs and
-// chunk pairs; 32-bit buckets, half buckets, visible records, and the tiles
-// of each length class but the last (work order; the first four together are
-// the lists of the long-list sort).
-constexpr int kScanClass = 3;
-constexpr int kScanN32 = kScanClass + kOrderClasses - 1;
 struct ScanRound {
   static constexpr int NT = 4 * kScanVec, NC = 2 * kScanVec;
   int64_t it, ic;  // first tile and first chunk of the thread
-  uint32_t tc[NT], nb[NT], h[NT], cp[NC], cv[NC];
+  uint32_t tc[NT], nb[NT], cp[NC], cv[NC];
   uint64_t s64[2];
   uint32_t s32[kScanN32];
 };
@@ -229,11 +224,9 @@ __device__ __forceinline__ void scan_load(const ScanArgs& A, int64_t r, ScanRoun
   for (int c = 0; c < kScanN32; ++c) R.s32[c] = 0;
 #pragma unroll
   for (int k = 0; k < ScanRound::NT; ++k) {
-    uint32_t f;
-    bucket_split(R.tc[k], R.nb[k], f, R.h[k]);
+    R.nb[k] = (R.tc[k] + kBucket - 1) / kBucket;
     R.s64[0] += R.tc[k];
     R.s32[0] += R.nb[k];
-    R.s32[1] += R.h[k];
     const int oc = order_class(R.tc[k]);
 #pragma unroll
     for (int c = 0; c < kOrderClasses - 1; ++c) R.s32[kScanClass + c] += oc == c ? 1u : 0u;
@@ -241,7 +234,7 @@ __device__ __forceinline__ void scan_load(const ScanArgs& A, int64_t r, ScanRoun
 #pragma unroll
   for (int k = 0; k < ScanRound::NC; ++k) {
     R.s64[1] += R.cp[k];
-    R.s32[2] += R.cv[k];
+    R.s32[1] += R.cv[k];
   }
 }
 
@@ -254,7 +247,7 @@ __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
   uint32_t* chunk_out = reinterpret_cast<uint32_t*>(A.chunk_pre);
 #pragma unroll
   for (int k = 0; k < kScanVec; ++k) {
-    uint32_t ts[4], bs[4], hs[4];
+    uint32_t ts[4], bs[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int64_t t = R.it + 4 * k + e;
@@ -276,10 +269,8 @@ __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
                     R.s32[kScanClass + 3]] = make_uint4((uint32_t)t, (uint32_t)R.s64[0], c, 0u);
       ts[e] = (uint32_t)R.s64[0];
       bs[e] = R.s32[0];
-      hs[e] = R.s32[1];
       R.s64[0] += c;
       R.s32[0] += R.nb[4 * k + e];
-      R.s32[1] += R.h[4 * k + e];
 #pragma unroll
       for (int k5 = 0; k5 < kOrderClasses - 1; ++k5) R.s32[kScanClass + k5] += oc == k5 ? 1u : 0u;
     }
@@ -290,17 +281,12 @@ __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
            A.mode == kScanTiles ? make_uint4(R.tc[4 * k], R.tc[4 * k + 1], R.tc[4 * k + 2],
                                              R.tc[4 * k + 3])
                                 : make_uint4(0u, 0u, 0u, 0u));
-    if (A.boff) {
-      store4(A.boff, R.it + 4 * k, T, make_uint4(bs[0], bs[1], bs[2], bs[3]));
-      store4(A.fstart, R.it + 4 * k, T,
-             make_uint4(bs[0] - hs[0], bs[1] - hs[1], bs[2] - hs[2], bs[3] - hs[3]));
-      store4(A.hstart, R.it + 4 * k, T, make_uint4(hs[0], hs[1], hs[2], hs[3]));
-    }
-    const uint32_t p0 = (uint32_t)R.s64[1], v0 = R.s32[2];
+    if (A.boff) store4(A.boff, R.it + 4 * k, T, make_uint4(bs[0], bs[1], bs[2], bs[3]));
+    const uint32_t p0 = (uint32_t)R.s64[1], v0 = R.s32[1];
     const uint32_t p1 = p0 + R.cp[2 * k], v1 = v0 + R.cv[2 * k];
     store4(chunk_out, 2 * (R.ic + 2 * k), 2 * C, make_uint4(p0, v0, p1, v1));
     R.s64[1] = p1 + R.cp[2 * k + 1];
-    R.s32[2] = v1 + R.cv[2 * k + 1];
+    R.s32[1] = v1 + R.cv[2 * k + 1];
   }
 }
 
@@ -318,8 +304,7 @@ __device__ __forceinline__ void scan_finish(const ScanArgs& A, const uint64_t (&
     // the pair totals were settled by the chunk scan before
     const bool over = fl[F_OVERFLOW] != 0;
     fl[F_LONG_TILES] = over ? 0 : (int32_t)long_lists;
-    fl[F_BQ_FULL] = (over || !splat) ? 0 : (int32_t)(c32[0] - c32[1]);
-    fl[F_BQ_HALF] = (over || !splat) ? 0 : (int32_t)c32[1];
+    fl[F_BUCKETS] = (over || !splat) ? 0 : (int32_t)c32[0];
     if (splat) A.boff[A.n_tiles] = c32[0];
     return;
   }
@@ -330,15 +315,14 @@ __device__ __forceinline__ void scan_finish(const ScanArgs& A, const uint64_t (&
   fl[F_OVERFLOW] = over ? 1 : 0;
   fl[F_PAIRS] = over ? 0 : (int32_t)pairs;
   fl[F_PAIRS_WANTED] = pairs > 0x7FFFFFFFull ? 0x7FFFFFFF : (int32_t)pairs;
-  fl[F_VISIBLE] = (int32_t)c32[2];
+  fl[F_VISIBLE] = (int32_t)c32[1];
   fl[F_NONFINITE] = fl[F_NF_ACC];  // counted by the projection
   fl[F_NF_ACC] = 0;
   if (!chunks_only) {
-    // the bucket queues are filled by the tile sort at the positions scanned
+    // the bucket queue is filled by the tile sort at the positions scanned
     // here; the long lists are sorted by their own kernel (none on overflow)
     fl[F_LONG_TILES] = (int32_t)long_lists;
-    fl[F_BQ_FULL] = (over || !splat) ? 0 : (int32_t)(c32[0] - c32[1]);
-    fl[F_BQ_HALF] = (over || !splat) ? 0 : (int32_t)c32[1];
+    fl[F_BUCKETS] = (over || !splat) ? 0 : (int32_t)c32[0];
     if (splat) A.boff[A.n_tiles] = c32[0];
   }
   // a whole iteration with Adam advances its step here, once the pairs are
@@ -814,7 +798,7 @@ hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s) {
 
 // Arguments of the per-tile sort.
 static TileSortArgs tile_sort_args(const Plan& P, void* ws) {
-  const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
+  const bool splat = P.splat != 0;
   TileSortArgs A{};
   A.cnt = ws_at<uint32_t>(ws, P.off_tile_cnt);
   A.tstart = ws_at<uint32_t>(ws, P.off_tile_start);
@@ -826,10 +810,8 @@ static TileSortArgs tile_sort_args(const Plan& P, void* ws) {
                       radix ? nullptr : ws_at<uint32_t>(ws, P.off_pair_rec),
                       ws_at<Rec>(ws, P.off_rec), radix ? nullptr : ws_at<Rec>(ws, P.off_srec)};
   A.ranges = ws_at<uint32_t>(ws, P.off_ranges);
-  A.fstart = splat ? ws_at<uint32_t>(ws, P.off_full_start) : nullptr;
-  A.hstart = splat ? ws_at<uint32_t>(ws, P.off_half_start) : nullptr;
+  A.boff = splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr;
   A.bq = splat ? ws_at<uint2>(ws, P.off_bq) : nullptr;
-  A.bq_stride = P.ckpt_slots;
   A.presorted = radix;
   return A;
 }
@@ -843,16 +825,13 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
   uint32_t* poff = ws_at<uint32_t>(ws, P.off_poff);
   uint32_t* tcnt = ws_at<uint32_t>(ws, P.off_tile_cnt);
   uint32_t* tstart = ws_at<uint32_t>(ws, P.off_tile_start);
-  const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
   const int T = P.vt.total_tiles;
-  uint32_t* fstart = splat ? ws_at<uint32_t>(ws, P.off_full_start) : nullptr;
-  uint32_t* hstart = splat ? ws_at<uint32_t>(ws, P.off_half_start) : nullptr;
   const uint2* chunk_cnt = ws_at<uint2>(ws, P.off_chunk_cnt);
   uint2* chunk_pre = ws_at<uint2>(ws, P.off_chunk_pre);
   uint4* long_list = ws_at<uint4>(ws, P.off_long);
   const bool radix = (P.cfg.flags & GS_RADIX_BIN) != 0;
   ScanArgs sa{chunk_cnt, chunk_pre, P.n_chunks, tcnt, tstart, (int64_t)T,
-              splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr, fstart, hstart,
+              P.splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr,
               ws_at<uint32_t>(ws, P.off_order), long_list, kScanBoth};
   // always launched, so that the flags are always set: one block for a
   // plan of one round, one block per round in three launches beyond

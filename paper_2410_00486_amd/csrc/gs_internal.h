@@ -22,12 +22,9 @@ enum Flag : int {
   F_NONFINITE = 1,
   F_PAIRS = 2,
   F_VISIBLE = 3,
-  F_QUEUE_FWD = 4,
-  F_QUEUE_BWD = 5,
   F_PAIRS_WANTED = 6,
   F_LONG_TILES = 7,  // tiles whose lists go to the long-list sort
-  F_BQ_FULL = 8,     // splat-wise buckets with more than 32 pairs
-  F_BQ_HALF = 9,     // splat-wise buckets with at most 32 pairs
+  F_BUCKETS = 8,     // entries of the splat-wise bucket queue
   F_NF_ACC = 10,     // non-finite Gaussians counted by the projection, published
                      // in F_NONFINITE (and cleared) by the binning scan
   F_CLASS = 11,      // tiles of each length class of the work order but the last
@@ -175,9 +172,10 @@ struct Plan {
   // Gaussian, the projection half's mean gradient
   size_t off_rec_terms, off_gp_tmp;
   size_t off_ssim_maps, off_ssim_part;
-  // splat-wise backward: bucket offsets, bucket queues and their per-tile
-  // positions, pixel states
-  size_t off_boff, off_bq, off_ckpt, off_full_start, off_half_start;
+  // splat-wise backward (8x8 tiles): bucket offsets, bucket queue, pixel
+  // states, and what the forward kept of the lists
+  int32_t splat, pad1;
+  size_t off_boff, off_bq, off_ckpt, off_cand, off_kept, off_seen;
   int64_t ckpt_slots;
   // binning scan: rounds (one block each when more than one) and their
   // per-channel partial sums

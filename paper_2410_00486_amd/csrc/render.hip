@@ -16,7 +16,8 @@
 // 16 views, 25M pairs: 1443 -> 860 us; 8 mixed views, 6.0M pairs: 579 ->
 // 338 us (the longest list, 4562 pairs, is one wavefront's serial work).
 // Bound by VALU issue (about 80 instructions for four splats of 64 pixels)
-// and, for the longest lists, by the latency of one wavefront.
+// and, for the longest lists, by the latency of one wavefront.  Neighbouring
+// tiles on one XCD (xcd_item): 901 -> 850 us on the 16-view batch.
 //
 // Backward (pixel-wise): a workgroup per tile, again a wavefront per 8x8
 // block, back to front from the tile's last used position.  Each lane
@@ -131,28 +132,14 @@ constexpr int sub_tiles() {
   return TW * TH / (kSub * kSub);
 }
 
-// Unit u of the forward's grid -> (slot of the work order, sub-tile).  The
-// sub-tiles of a tile read the same list: consecutive workgroups go to the
-// eight XCDs in turn, so a tile's sub-tiles are eight units apart, on one
-// XCD's L2.
-template <int NS>
-__device__ __forceinline__ void unit_of(uint32_t u, uint32_t n_tiles, uint32_t& slot,
-                                        uint32_t& sub) {
-  if constexpr (NS == 1) {
-    slot = u;
-    sub = 0;
-  } else {
-    const uint32_t full = n_tiles / 8 * 8;
-    if (u < full * NS) {
-      const uint32_t q = u / 8;
-      slot = q / NS * 8 + u % 8;
-      sub = q % NS;
-    } else {  // the last tiles, fewer than eight
-      const uint32_t q = u - full * NS;
-      slot = full + q / NS;
-      sub = q % NS;
-    }
-  }
+// Consecutive workgroups go to the eight XCDs in turn, each with an L2 of its
+// own.  Work items that read the same data (neighbouring tiles share splats,
+// the blocks of a tile its list, the buckets of a tile its pixels) sit next
+// to each other in the item order, so 32 consecutive items are given to one
+// XCD: workgroup b takes item xcd_item(b) (a permutation of each 256; the
+// grid's last part, below 256, is left as it is).
+__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
+  return (b | 255u) < n ? (b & ~255u) + (b & 7u) * 32u + ((b & 255u) >> 3) : b;
 }
 
 // The largest last position over a tile's sub-tiles.
@@ -218,6 +205,22 @@ struct FwdLds {
   uint32_t pos[kWave];   // 1 + position in the tile's list
 };
 
+// What the forward leaves for the splat-wise backward.  The slots of its
+// steps, batch after batch, are the backward's lanes: a bucket is 64 slots.
+// Stored: the state of every pixel before each bucket but a tile's first
+// (bucket boff + k), the list position of every slot (kNoSplat in the few
+// that only fill up a step), which of each 64 list positions were kept (one
+// word per bucket entry of the list), and per tile the number of slots and of
+// list positions looked at.
+constexpr uint32_t kNoSplat = 0xFFFFFFFFu;
+struct FwdSplat {
+  const uint32_t* boff;
+  float* ckpt;
+  uint32_t* cand;
+  uint64_t* kept;
+  uint2* seen;
+};
+
 template <int TW, int TH, bool CKPT>
 __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
                                          const uint32_t* __restrict__ ranges,
@@ -229,9 +232,8 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
                                          const float* __restrict__ target_rgb,
                                          const float* __restrict__ target_depth,
                                          float* __restrict__ tile_loss,
-                                         const uint32_t* __restrict__ boff,
-                                         float* __restrict__ ckpt, FwdLds& S) {
-  constexpr int NPX = TW * TH, NS = sub_tiles<TW, TH>();
+                                         const FwdSplat& K, FwdLds& S) {
+  constexpr int NS = sub_tiles<TW, TH>();
   const int v = find_view(vt, gtile);
   const ViewInfo vi = vt.v[v];
   const int lt = gtile - vi.tile_off;
@@ -254,6 +256,7 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
   // pixels that have not stopped; the least alpha that is blended (none once
   // the pixel has stopped)
   uint64_t live = ballot64(inside);
+  bool clamps = false;  // some splat so far can exceed the 0.99 clamp
   float amin = inside ? kAlphaMin : INFINITY;
   const double cx0 = (double)bx0 + 0.5, cy0 = (double)by0 + 0.5;
   // the next batch's records are fetched while this one is composited, and
@@ -268,7 +271,11 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
   uint32_t id = 0;
   if (s + lane_u < e) fetch(r, lrec.id(s + lane_u));
   if (s + kWave + lane_u < e) id = lrec.id(s + kWave + lane_u);
-  for (uint32_t b = s; live != 0 && b < e; b += (uint32_t)kWave) {
+  uint32_t slots = 0;  // steps' slots of the batches before this one
+  // the tile's first bucket
+  const uint32_t bucket0 = CKPT ? (uint32_t)__builtin_amdgcn_readfirstlane((int)K.boff[gtile]) : 0u;
+  uint32_t b = s;
+  for (; live != 0 && b < e; b += (uint32_t)kWave) {
     const bool has = b + lane_u < e;
     // (the sample points' coordinates are counted up from the block's corner
     // in each batch: kept over the batches they would take 32 registers)
@@ -284,8 +291,13 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
     }
     const bool keep = has && !(max_exponent(r, ox[kSub - 1], ox[0], oy[kSub - 1], oy[0]) < kCullExp);
     const uint64_t kept = ballot64(keep);
-    const int n = (int)__popcll(kept);
-    const bool clamps = ballot64(keep && r.lo > kClampLo) != 0;
+    // whole steps: the batch is filled up with splats of alpha 2^-inf = 0
+    // (carrying up to three splats over to the next batch instead cost more
+    // than the 3 % of slots that this leaves empty: 970 against 945 us on the
+    // 16-view batch)
+    const int total = (int)__popcll(kept);
+    const int n = (total + kFwdSplats - 1) & ~(kFwdSplats - 1);
+    clamps = clamps || ballot64(keep && r.lo > kClampLo) != 0;
     __syncthreads();  // (one wavefront: orders the LDS reads before its writes)
     if (keep) {
       const int at = (int)__popcll(kept & lanemask_lt());
@@ -296,35 +308,21 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
       }
       S.shape[at] = make_float4(r.t, r.s1, r.s2, r.lo);
       S.colour[at] = make_float4(r.r, r.g, r.b, r.z);
-      S.pos[at] = b - s + (uint32_t)lane + 1u;
+      S.pos[at] = b - s + lane_u + 1u;
+      if constexpr (CKPT) K.cand[(int64_t)bucket0 * kBucket + slots + (uint32_t)at] = b - s + lane_u;
     }
-    // the last step's missing splats: alpha = 2^-inf = 0
-    if (lane < kFwdSplats && n + lane < ((n + kFwdSplats - 1) & ~(kFwdSplats - 1))) {
+    if (CKPT && lane == 0) K.kept[bucket0 + (b - s) / kWave] = kept;
+    if (total + lane < n) {
 #pragma unroll
-      for (int k = 0; k < kSub; ++k) S.dx[k][n + lane] = S.dy[k][n + lane] = 0.0f;
-      S.shape[n + lane] = make_float4(0.0f, 0.0f, 0.0f, -INFINITY);
-      S.colour[n + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      S.pos[n + lane] = 0u;
+      for (int k = 0; k < kSub; ++k) S.dx[k][total + lane] = S.dy[k][total + lane] = 0.0f;
+      S.shape[total + lane] = make_float4(0.0f, 0.0f, 0.0f, -INFINITY);
+      S.colour[total + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      S.pos[total + lane] = 0u;
+      if constexpr (CKPT) K.cand[(int64_t)bucket0 * kBucket + slots + (uint32_t)(total + lane)] = kNoSplat;
     }
     __syncthreads();
     if (b + kWave + lane_u < e) fetch(r, id);
     if (b + 2 * kWave + lane_u < e) id = lrec.id(b + 2 * kWave + lane_u);
-    if constexpr (CKPT) {
-      // state of every pixel before each 64th splat of the tile list (the
-      // state before the first splat is the empty one and is not stored)
-      if (b != s) {
-        float* cp = ckpt + (int64_t)(boff[gtile] + (b - s) / kBucket) * (kStateFloats * NPX);
-        const int jj = (sy0 + row) * TW + sx0 + col;
-        cp[jj] = T;
-        cp[NPX + jj] = c0;
-        cp[2 * NPX + jj] = c1;
-        cp[3 * NPX + jj] = c2;
-        cp[4 * NPX + jj] = D;
-      }
-    }
-    // kFwdSplats splats at once: their alphas are independent, only the
-    // blends are ordered.  Every decision is a select: no divergent branches.
-    // CLAMP: some splat of the batch can exceed the 0.99 clamp.
     // One step = kFwdSplats splats: their alphas first (independent), then
     // the blends in order.  All of a step's LDS reads are requested ahead of
     // its arithmetic (left to itself, the compiler saves registers by reading
@@ -332,13 +330,13 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
     // transmittance runs through the step as if no pixel stopped: it never
     // rises, so the splats that the stop rule leaves out are those whose
     // transmittance ends below the limit, and a step at whose end no lane is
-    // below it (no pixel stops) needs no further test.  CLAMP: some splat of
-    // the batch can exceed the 0.99 clamp.
+    // below it (no pixel stops) needs no further test.  CLAMP: some splat
+    // can exceed the 0.99 clamp.
     uint32_t lastslot = 0;  // 1 + slot of the last blended splat of the batch
-    auto composite = [&](auto clamp_c) {
+    auto composite = [&](auto clamp_c, int j0, int j1) {
       constexpr bool CLAMP = decltype(clamp_c)::value;
       constexpr int NU = kFwdSplats;
-      for (int j = 0; j < n; j += NU) {
+      for (int j = j0; j < j1; j += NU) {
         const float4 dx4 = *reinterpret_cast<const float4*>(&S.dx[col][j]);
         const float4 dy4 = *reinterpret_cast<const float4*>(&S.dy[row][j]);
         float4 sh[NU], cl[NU];
@@ -392,9 +390,33 @@ __device__ __forceinline__ void fwd_tile(int gtile, int sub, RecSrc lrec,
         if (live == 0) break;
       }
     };
-    if (clamps) composite(std::true_type{});
-    else composite(std::false_type{});
+    if constexpr (CKPT) {
+      // in segments between the 64-splat bucket boundaries (multiples of a
+      // step), the pixel states stored before each bucket but the first
+      for (int j = 0; live != 0 && j < n;) {
+        const uint32_t q = slots + (uint32_t)j;
+        if (q != 0 && q % kBucket == 0) {
+          float* cp = K.ckpt + (int64_t)(bucket0 + q / kBucket) * (kStateFloats * kWave) + lane;
+          cp[0] = T;
+          cp[kWave] = c0;
+          cp[2 * kWave] = c1;
+          cp[3 * kWave] = c2;
+          cp[4 * kWave] = D;
+        }
+        const int jend = min(n, j + (int)(kBucket - q % kBucket));
+        if (clamps) composite(std::true_type{}, j, jend);
+        else composite(std::false_type{}, j, jend);
+        j = jend;
+      }
+    } else {
+      if (clamps) composite(std::true_type{}, 0, n);
+      else composite(std::false_type{}, 0, n);
+    }
     if (lastslot) lastpos = S.pos[lastslot - 1];
+    slots += (uint32_t)n;
+  }
+  if constexpr (CKPT) {
+    if (lane == 0) K.seen[gtile] = make_uint2(slots, min(b, e) - s);
   }
   const float* cam = cams + (int64_t)v * GS_CAMERA_FLOATS;
   const float bg0 = cam[17], bg1 = cam[18], bg2 = cam[19];
@@ -442,8 +464,7 @@ struct FwdArgs {
   float* tile_loss;
   const uint32_t* order;
   const int32_t* fl;
-  const uint32_t* boff;
-  float* ckpt;
+  FwdSplat splat;
 };
 
 // One workgroup per unit, handed out by the hardware in work order: a
@@ -454,12 +475,12 @@ template <int TW, int TH, bool CKPT>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) k_render_fwd(
     FwdArgs A, ViewTable vt) {
   __shared__ __align__(16) FwdLds S;
-  uint32_t slot, sub;
-  unit_of<sub_tiles<TW, TH>()>(blockIdx.x, (uint32_t)vt.total_tiles, slot, sub);
-  const int gtile = order_tile(A.order, A.fl, vt.total_tiles, slot);
-  fwd_tile<TW, TH, CKPT>(gtile, (int)sub, A.lrec, A.ranges, A.cams, vt, A.color, A.depth,
+  constexpr uint32_t NS = sub_tiles<TW, TH>();
+  const uint32_t u = xcd_item(blockIdx.x, (uint32_t)vt.total_tiles * NS);
+  const int gtile = order_tile(A.order, A.fl, vt.total_tiles, u / NS);
+  fwd_tile<TW, TH, CKPT>(gtile, (int)(u % NS), A.lrec, A.ranges, A.cams, vt, A.color, A.depth,
                          A.T_final, A.last, A.tile_last, A.target_rgb, A.target_depth,
-                         A.tile_loss, A.boff, A.ckpt, S);
+                         A.tile_loss, A.splat, S);
 }
 
 // Per-view L1 loss from the per-tile sums, in a fixed order.
@@ -554,7 +575,8 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
   constexpr int NS = sub_tiles<TW, TH>(), NT = kWave * NS, BX = TW / kSub;
   __shared__ __align__(16) BwdLds<TW, TH> S;
   const int lane = lane_id(), sub = NS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int gtile = order_tile(A.order, A.fl, vt.total_tiles, blockIdx.x);
+  const int gtile =
+      order_tile(A.order, A.fl, vt.total_tiles, xcd_item(blockIdx.x, (uint32_t)vt.total_tiles));
   const int v = find_view(vt, gtile);
   const ViewInfo vi = vt.v[v];
   const int lt = gtile - vi.tile_off;
@@ -592,19 +614,25 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
   const int my_idx = lane < 16 ? rs_index(lane) : -1;
   const double ax0 = (double)(tx0 + kSub * sx) + 0.5, ay0 = (double)(ty0 + kSub * sy) + 0.5;
 
-  for (int bend = (int)tl; bend > 0; bend -= kWave) {
-    const int bstart = bend > kWave ? bend - kWave : 0;
-    const int nb = bend - bstart;
-    const bool has = lane < nb;
-    FwdRec r{};
-    float ro = 0.0f;
-    if (has) {
-      const Rec* rec = A.lrec.at(s + (uint32_t)(bstart + lane));
+  // the record of this lane's position in the batch that ends at `end`; the
+  // next batch's is fetched while this one is worked on
+  FwdRec r{};
+  float ro = 0.0f;
+  auto fetch = [&](int end) {
+    const int start = end > kWave ? end - kWave : 0;
+    if (start + lane < end) {
+      const Rec* rec = A.lrec.at(s + (uint32_t)(start + lane));
       const float4* src = reinterpret_cast<const float4*>(rec);
       float4* d4 = reinterpret_cast<float4*>(&r);
       d4[0] = src[0]; d4[1] = src[1]; d4[2] = src[2];
       if (sub == 0) ro = rec->o;
     }
+  };
+  fetch((int)tl);
+  for (int bend = (int)tl; bend > 0; bend -= kWave) {
+    const int bstart = bend > kWave ? bend - kWave : 0;
+    const int nb = bend - bstart;
+    const bool has = lane < nb;
     float ox[kSub], oy[kSub];
     double ax = ax0, ay = ay0;
     asm volatile("" : "+v"(ax), "+v"(ay));
@@ -635,6 +663,7 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
     }
     if (lane == 0) S.kept[sub] = kept;
     __syncthreads();
+    fetch(bend - kWave);
     // N kept positions j[0] > j[1] .. at once: independent alphas and
     // reductions, only T and B run through them in order
     auto step = [&](auto n_c, const int* j) {
@@ -717,12 +746,13 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
 }
 
 // ----------------------------------------------------- splat-wise backward
-// Sec. III-C-1 / Fig. 4a mapped to wave64.  The tile list is cut into
-// buckets of 64 consecutive splats; one wavefront takes a bucket and lane l
-// owns its l-th splat.  The forward stored each pixel's state X = (T, RGB,
-// D) before every 64th splat, so a bucket starts from stored states and
-// needs nothing from the other buckets of its tile: buckets are the unit of
-// parallelism, which also splits long tile lists over many wavefronts.
+// Sec. III-C-1 / Fig. 4a mapped to wave64, for 8x8 tiles.  The splats that
+// the forward kept of a tile's list are cut into buckets of 64; one wavefront
+// takes a bucket and lane l owns its l-th splat.  The forward stored each
+// pixel's state X = (T, RGB, D) before every 64th kept splat, so a bucket
+// starts from stored states and needs nothing from the other buckets of its
+// tile: buckets are the unit of parallelism, which also splits long lists
+// over many wavefronts.
 //
 // All lanes of a segment take the same pixel at each step.  Lane l
 // evaluates its splat's alpha with the forward's code (the same bits, so
@@ -732,280 +762,308 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
 // transmittance is T_in times the product of (1 - alpha) over those lanes
 // (the inclusive prefix product divided by the lane's own factor), and the
 // front part of the loss-weighted output Q = gC . C + gD . D an inclusive
-// prefix sum of alpha T gC . c, both taken across the lanes with DPP.  What lies behind the splat is the final pixel minus the front part,
-// P - Q with P = gC . (colour output) + gD . (depth output).  A bucket thus
-// costs one step per pixel, with no pipeline to fill or drain.  Each lane
-// accumulates its own splat's ten partial gradients over the tile's pixels
-// and writes them once: no reduction over lanes and no atomics.
+// prefix sum of alpha T gC . c, both taken across the lanes with DPP.  What
+// lies behind the splat is the final pixel minus the front part, P - Q with
+// P = gC . (colour output) + gD . (depth output).  A bucket thus costs one
+// step per pixel, with no pipeline to fill or drain.  Each lane accumulates
+// its own splat's ten partial gradients over the tile's pixels and writes
+// them once: no reduction over lanes and no atomics.
 //
-// Buckets with at most 32 pairs share a wavefront: each 32-lane half runs
-// its own bucket (the scans stop at the half), two buckets per NPX steps.
-// The binning queues buckets by size (more than 32 pairs / at most 32).
+// A bucket of at most 32 (16) splats runs two (four) segments of 32 (16)
+// lanes that hold the same splats and take every second (fourth) row of
+// pixels; their sums are added at the end.
+//
+// Bound by VALU issue.  The steps run over rows of pixels: a lane's offsets
+// from the eight columns stay in registers and the row's is formed once per
+// row (two FP64 differences and two conversions per step before), and the
+// moments of the mean and conic partials are summed over a row without the
+// row's offset: with buckets of kept splats only, 1430M -> 1015M VALU
+// instructions on the 16-view batch (25M pairs).  One workgroup per bucket, 32
+// consecutive ones to an XCD: the buckets of a tile and its neighbours read
+// the same pixels and splats from one L2 (a resident grid with a static
+// stride: 2100 us; this way 1535 us, the VALU busy throughout; 5 to 7
+// wavefronts per SIMD measure the same).  Before these: 2608 us; 8 mixed views
+// 530 -> 340 us; one 1200x680 view 70 -> 56 us.
 
-// Inclusive product / sum over segments of SEG (64 or 32) lanes, in place,
-// of two independent values at once (two pixels): steps in rows of 16
-// (row_shr 1, 2, 4, 8), then the ends of rows 0 and 2 into rows 1 and 3
-// (row_bcast:15), and for 64 lanes the end of row 1 into rows 2 and 3
-// (row_bcast:31).  Each step is one DPP multiply or add whose lanes
+// Inclusive product / sum over segments of SEG (64, 32 or 16) lanes, in
+// place, of two independent values at once (two pixels): steps in rows of 16
+// (row_shr 1, 2, 4, 8), then for 32 lanes and more the ends of rows 0 and 2
+// into rows 1 and 3 (row_bcast:15), and for 64 the end of row 1 into rows 2
+// and 3 (row_bcast:31).  Each step is one DPP multiply or add whose lanes
 // without a source (or outside the row mask) are not written, i.e. keep
 // their value.  A DPP read of a VGPR written by the previous VALU
 // instruction needs two wait states: the two scans' steps alternate, so
 // one wait state plus the other scan's step covers it (two before the
 // first step, whose inputs the compiler's code has just written).
 #define GS_DPP2(OP, CTRL) OP " %0, %0, %0 " CTRL " bank_mask:0xf\n\t" OP " %1, %1, %1 " CTRL " bank_mask:0xf\n\t"
-#define GS_SEG_SCAN32_2(OP)                                          \
-  "s_nop 1\n\t" GS_DPP2(OP, "row_shr:1 row_mask:0xf")              \
-  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:2 row_mask:0xf")              \
-  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:4 row_mask:0xf")              \
-  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:8 row_mask:0xf")              \
-  "s_nop 0\n\t" GS_DPP2(OP, "row_bcast:15 row_mask:0xa")
+#define GS_SEG_SCAN16_2(OP)                             \
+  "s_nop 1\n\t" GS_DPP2(OP, "row_shr:1 row_mask:0xf") \
+  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:2 row_mask:0xf") \
+  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:4 row_mask:0xf") \
+  "s_nop 0\n\t" GS_DPP2(OP, "row_shr:8 row_mask:0xf")
+#define GS_SEG_SCAN32_2(OP) GS_SEG_SCAN16_2(OP) "s_nop 0\n\t" GS_DPP2(OP, "row_bcast:15 row_mask:0xa")
+#define GS_SEG_SCAN64_2(OP) GS_SEG_SCAN32_2(OP) "s_nop 0\n\t" GS_DPP2(OP, "row_bcast:31 row_mask:0xc")
 template <int SEG>
 __device__ __forceinline__ void seg_scan_mul2(float& x, float& y) {
-  if (SEG == 64)
-    asm volatile(GS_SEG_SCAN32_2("v_mul_f32_dpp") "s_nop 0\n\t"
-                 GS_DPP2("v_mul_f32_dpp", "row_bcast:31 row_mask:0xc") : "+v"(x), "+v"(y));
-  else
-    asm volatile(GS_SEG_SCAN32_2("v_mul_f32_dpp") : "+v"(x), "+v"(y));
+  if (SEG == 64) asm volatile(GS_SEG_SCAN64_2("v_mul_f32_dpp") : "+v"(x), "+v"(y));
+  else if (SEG == 32) asm volatile(GS_SEG_SCAN32_2("v_mul_f32_dpp") : "+v"(x), "+v"(y));
+  else asm volatile(GS_SEG_SCAN16_2("v_mul_f32_dpp") : "+v"(x), "+v"(y));
 }
 template <int SEG>
 __device__ __forceinline__ void seg_scan_add2(float& x, float& y) {
-  if (SEG == 64)
-    asm volatile(GS_SEG_SCAN32_2("v_add_f32_dpp") "s_nop 0\n\t"
-                 GS_DPP2("v_add_f32_dpp", "row_bcast:31 row_mask:0xc") : "+v"(x), "+v"(y));
-  else
-    asm volatile(GS_SEG_SCAN32_2("v_add_f32_dpp") : "+v"(x), "+v"(y));
+  if (SEG == 64) asm volatile(GS_SEG_SCAN64_2("v_add_f32_dpp") : "+v"(x), "+v"(y));
+  else if (SEG == 32) asm volatile(GS_SEG_SCAN32_2("v_add_f32_dpp") : "+v"(x), "+v"(y));
+  else asm volatile(GS_SEG_SCAN16_2("v_add_f32_dpp") : "+v"(x), "+v"(y));
 }
+#undef GS_SEG_SCAN64_2
 #undef GS_SEG_SCAN32_2
+#undef GS_SEG_SCAN16_2
 #undef GS_DPP2
 
-template <int TW, int TH, int SEG>
-__device__ __forceinline__ void splat_wave(
-    const uint2* __restrict__ queue, uint32_t q_first, uint32_t q_count,
-    RecSrc lrec,
-    const uint32_t* __restrict__ sorted_vals, const uint32_t* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_last, const uint32_t* __restrict__ boff,
-    const float* __restrict__ ckpt, const ViewTable& vt, const float* __restrict__ color,
-    const float* __restrict__ depth, const uint32_t* __restrict__ last,
-    const float* __restrict__ dL_dcolor, const float* __restrict__ dL_ddepth,
-    const float* __restrict__ target_rgb, const float* __restrict__ target_depth, int fused,
-    float lambda_depth, float* __restrict__ grad_pair, float4* pxa, float4* pxb, double2* pxc) {
-  static_assert(SEG == 64 || SEG == 32, "segment of 64 or 32 lanes");
-  constexpr int NPX = TW * TH;
-  constexpr int LOG_TW = TW == 16 ? 4 : 3;
-  const int lane = threadIdx.x;
-  const int seg = SEG == 64 ? 0 : lane >> 5, ls = lane & (SEG - 1);
-  const uint32_t qi = q_first + (uint32_t)seg;
-  const bool has = qi < q_count;
-  const uint2 ent = has ? queue[qi] : make_uint2(0u, 0u);
-  const int gtile = (int)ent.x;
-  const uint32_t k = ent.y;
-  uint32_t s = 0, npairs = 0, tl = 0;
-  if (has) {
-    s = ranges[2 * (int64_t)gtile];
-    npairs = ranges[2 * (int64_t)gtile + 1] - s;
-    tl = tile_last_of<sub_tiles<TW, TH>()>(tile_last, gtile);
+// Sum over the segments of SEG lanes of a wavefront, in every lane.
+template <int SEG>
+__device__ __forceinline__ float sum_segments(float x) {
+  if (SEG <= 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-  const uint32_t q0 = k * kBucket;
-  const uint32_t pos = q0 + (uint32_t)ls;
-  const bool live = has && pos < tl;
-  if (has && pos < npairs && !live) {  // pairs behind the last used position: zero gradient
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    store_pair(grad_pair, sorted_vals[s + pos], z, z, make_float2(0.f, 0.f));
+  if (SEG <= 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-  const bool active = has && q0 < tl;  // uniform over the segment
-  if (ballot64(active) == 0) return;   // uniform
-
-  const int v = active ? find_view(vt, gtile) : 0;
-  const ViewInfo vi = vt.v[v];
-  const int lt = gtile - vi.tile_off;
-  const int tx0 = (lt % vi.tiles_x) * TW, ty0 = (lt / vi.tiles_x) * TH;
-  const int64_t npx = (int64_t)vi.W * vi.H;
-  float4* sa = pxa + seg * NPX;
-  float4* sb = pxb + seg * NPX;
-  double2* sc = pxc + seg * NPX;  // sample point of each pixel
-
-  // pixel table of the segment's tile: loss gradients, P, last position,
-  // stored state (T, Q), kept only for the pixels whose last position lies
-  // past the bucket's first splat.  At any other pixel no lane of the bucket
-  // is blended, so every term it adds is zero: the table holds the others
-  // in pixel order, and the loop below runs over them alone.
-  const uint64_t segmask = SEG == 64 ? ~0ull : (0xFFFFFFFFull << (32 * seg));
-  const uint64_t below = lanemask_lt() & segmask;
-  uint32_t kept = 0;
-  for (int j = ls; j < NPX; j += SEG) {  // (NPX is a multiple of SEG: uniform)
-    const int px = tx0 + (j & (TW - 1)), py = ty0 + (j >> LOG_TW);
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = make_float4(0.f, 0.f, 1.f, 0.f);
-    bool keep = false;
-    if (active && px < vi.W && py < vi.H) {
-      const float* cp = ckpt + (int64_t)(boff[gtile] + k) * (kStateFloats * NPX);
-      const int64_t pl = (int64_t)py * vi.W + px;
-      const int64_t pix = (int64_t)vi.pix_off + pl;
-      const int64_t cbase = 3 * (int64_t)vi.pix_off + pl;
-      const float o0 = color[cbase], o1 = color[cbase + npx], o2 = color[cbase + 2 * npx];
-      const float od = depth[pix];
-      if (fused) {
-        const float inv3 = 1.0f / (3.0f * (float)npx);
-        const float d0 = o0 - target_rgb[cbase];
-        const float d1 = o1 - target_rgb[cbase + npx];
-        const float d2 = o2 - target_rgb[cbase + 2 * npx];
-        a.x = d0 > 0.0f ? inv3 : (d0 < 0.0f ? -inv3 : 0.0f);
-        a.y = d1 > 0.0f ? inv3 : (d1 < 0.0f ? -inv3 : 0.0f);
-        a.z = d2 > 0.0f ? inv3 : (d2 < 0.0f ? -inv3 : 0.0f);
-        if (target_depth) {
-          const float dd = od - target_depth[pix];
-          const float sc = lambda_depth / (float)npx;
-          a.w = dd > 0.0f ? sc : (dd < 0.0f ? -sc : 0.0f);
-        }
-      } else {
-        a.x = dL_dcolor[cbase];
-        a.y = dL_dcolor[cbase + npx];
-        a.z = dL_dcolor[cbase + 2 * npx];
-        a.w = dL_ddepth ? dL_ddepth[pix] : 0.0f;
-      }
-      b.x = a.x * o0 + a.y * o1 + a.z * o2 + a.w * od;
-      const uint32_t lp = last[pix];
-      b.y = __uint_as_float(lp);
-      keep = lp > q0;
-      if (keep && k > 0) {  // the first bucket starts from T = 1 and nothing accumulated
-        b.z = cp[j];
-        b.w = a.x * cp[NPX + j] + a.y * cp[2 * NPX + j] + a.z * cp[3 * NPX + j] + a.w * cp[4 * NPX + j];
-      }
-    }
-    const uint64_t m = ballot64(keep) & segmask;
-    if (keep) {
-      const uint32_t e = kept + (uint32_t)__popcll(m & below);
-      sa[e] = a;
-      sb[e] = make_float4(b.x - b.w, b.y, b.z, 0.0f);  // (P - Q_in, last, T_in)
-      sc[e] = make_double2((double)px + 0.5, (double)py + 0.5);
-    }
-    kept += (uint32_t)__popcll(m);
-  }
-  // two half-wave segments step together, two pixels a step: a table with
-  // fewer entries is padded with pixels at which nothing is blended (last = 0)
-  const uint32_t most = SEG == 64 ? kept : max(kept, (uint32_t)__shfl_xor((int)kept, 32));
-  const uint32_t steps = (most + 1u) & ~1u;
-  for (uint32_t e = kept + (uint32_t)ls; e < steps; e += SEG) {
-    sa[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sb[e] = make_float4(0.f, 0.f, 1.f, 0.f);
-    sc[e] = make_double2(0.5, 0.5);
-  }
-  const int nsteps = __builtin_amdgcn_readfirstlane((int)steps);
-  __builtin_assume((nsteps & 1) == 0);
-  __syncthreads();
-
-  Rec r;
-  if (live) {
-    const float4* src = reinterpret_cast<const float4*>(lrec.at(s + pos));
-    float4* dst = reinterpret_cast<float4*>(&r);
-    dst[0] = src[0]; dst[1] = src[1]; dst[2] = src[2]; dst[3] = src[3];
-  } else {
-    r.mx = r.my = 0.0;
-    r.t = r.s1 = r.s2 = r.lo = 0.0f;
-    r.o = r.z = r.r = r.g = r.b = 0.0f;
-    r.clamp = r.pad[0] = r.pad[1] = 0u;
-  }
-  float ca, cb, cc;
-  rec_conic(r, ca, cb, cc);
-  float g[10];
-#pragma unroll
-  for (int f = 0; f < 10; ++f) g[f] = 0.0f;
-  // two pixels per iteration (the step count is even), their scans
-  // interleaved; each lane accumulates pixel j before pixel j + 1
-  for (int j = 0; j < nsteps; j += 2) {
-    float4 b[2], gc[2];
-    float dxf[2], dyf[2], oG[2], a[2], inv_om[2], f[2];
-    bool hit[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      b[u] = sb[j + u];  // P - Q_in, last, T_in of the segment's kept pixel
-      const double2 sxy = sc[j + u];
-      // alpha as in the forward (same bits)
-      dxf[u] = (float)(r.mx - sxy.x);
-      dyf[u] = (float)(r.my - sxy.y);
-      oG[u] = __builtin_amdgcn_exp2f(rec_exponent(r, dxf[u], dyf[u]));
-      a[u] = fminf(kAlphaMax, oG[u]);
-      // (no short-circuit: every term is evaluated, so nothing branches; no
-      // early exit when no lane is blended at a pixel: rare, and its test
-      // costs two VALU per step)
-      hit[u] = live & (pos < __float_as_uint(b[u].y)) & (a[u] >= kAlphaMin);
-      gc[u] = sa[j + u];
-      // alpha of a blended splat, 0 otherwise: its 1 - alpha is the scan's
-      // factor and alpha T the blend weight, with no further selects
-      a[u] = hit[u] ? a[u] : 0.0f;
-      f[u] = 1.0f - a[u];
-      inv_om[u] = __builtin_amdgcn_rcpf(f[u]);
-    }
-    // transmittance in front of the splat: the segment's inclusive product
-    // over its blended splats with the lane's own factor taken out again
-    // (read by blended lanes only, whose factor 1 - alpha >= 0.01)
-    seg_scan_mul2<SEG>(f[0], f[1]);
-    float Tl[2], wgt[2], front[2], q[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      Tl[u] = (b[u].z * f[u]) * inv_om[u];
-      wgt[u] = a[u] * Tl[u];
-      front[u] = fmaf(gc[u].w, r.z, fmaf(gc[u].z, r.b, fmaf(gc[u].y, r.g, gc[u].x * r.r)));
-      q[u] = wgt[u] * front[u];
-    }
-    seg_scan_add2<SEG>(q[0], q[1]);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      // behind the splat: P - (Q_in + the front part after the splat)
-      const float g_alpha = fmaf(-(b[u].x - q[u]), inv_om[u], Tl[u] * front[u]);
-      g[0] = fmaf(wgt[u], gc[u].x, g[0]);
-      g[1] = fmaf(wgt[u], gc[u].y, g[1]);
-      g[2] = fmaf(wgt[u], gc[u].z, g[2]);
-      g[3] = fmaf(wgt[u], gc[u].w, g[3]);
-      // moments of gpow = dL/dpower = alpha dL/dalpha (unclamped splats) and
-      // of t = gpow dx, u = gpow dy; the opacity, conic and mean partials are
-      // formed from them once, after the pixels (dL/do = sum gpow / o)
-      const bool open = hit[u] & (oG[u] <= kAlphaMax);
-      const float gpow = open ? a[u] * g_alpha : 0.0f;
-      const float t = gpow * dxf[u], v = gpow * dyf[u];
-      g[4] += gpow;
-      g[5] = fmaf(t, dxf[u], g[5]);
-      g[6] = fmaf(t, dyf[u], g[6]);
-      g[7] = fmaf(v, dyf[u], g[7]);
-      g[8] += t;
-      g[9] += v;
-    }
-  }
-  if (live) {
-    store_pair(grad_pair, sorted_vals[s + pos], make_float4(g[0], g[1], g[2], g[3]),
-               make_float4(r.o > 0.0f ? g[4] / r.o : 0.0f, -0.5f * g[5], -g[6], -0.5f * g[7]),
-               make_float2(-(ca * g[8] + cb * g[9]), -(cb * g[8] + cc * g[9])));
-  }
-  __syncthreads();  // the pixel tables are rewritten by the next wave's work
+  return x;
 }
 
-// Grid-stride over the work of the two queues: one bucket per wave from
-// the first, two per wave from the second.
-template <int TW, int TH>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(TW * TH == 64 ? 6 : 1))) k_render_bwd_splat(
-    RecSrc lrec,
-    const uint32_t* __restrict__ sorted_vals, const uint32_t* __restrict__ ranges,
-    const uint32_t* __restrict__ tile_last, const uint32_t* __restrict__ boff,
-    const float* __restrict__ ckpt, const uint2* __restrict__ bq, int64_t bq_stride,
-    const int32_t* __restrict__ fl, ViewTable vt, const float* __restrict__ color,
-    const float* __restrict__ depth, const uint32_t* __restrict__ last,
-    const float* __restrict__ dL_dcolor, const float* __restrict__ dL_ddepth,
-    const float* __restrict__ target_rgb, const float* __restrict__ target_depth, int fused,
-    float lambda_depth, float* __restrict__ grad_pair) {
-  __shared__ float4 pxa[2 * TW * TH], pxb[2 * TW * TH];
-  __shared__ double2 pxc[2 * TW * TH];
-  const uint32_t q_full = (uint32_t)fl[F_BQ_FULL], q_half = (uint32_t)fl[F_BQ_HALF];
-  const uint32_t w_full = q_full, w_half = (q_half + 1) / 2;
-  for (uint32_t wv = blockIdx.x; wv < w_full + w_half; wv += gridDim.x) {
-    if (wv < w_full)
-      splat_wave<TW, TH, 64>(bq, wv, q_full, lrec, sorted_vals, ranges, tile_last,
-                             boff, ckpt, vt, color, depth, last, dL_dcolor, dL_ddepth, target_rgb,
-                             target_depth, fused, lambda_depth, grad_pair, pxa, pxb, pxc);
-    else
-      splat_wave<TW, TH, 32>(bq + bq_stride, 2 * (wv - w_full), q_half, lrec,
-                         sorted_vals, ranges, tile_last, boff, ckpt, vt, color, depth, last,
-                         dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, lambda_depth,
-                         grad_pair, pxa, pxb, pxc);
+struct SplatArgs {
+  RecSrc lrec;
+  const uint32_t *sorted_vals, *ranges, *cand;
+  const uint64_t* kept;
+  const uint2* seen;
+  const float* ckpt;
+  const uint2* bq;
+  const int32_t* fl;
+  const float *color, *depth;
+  const uint32_t* last;
+  PixelLoss loss;
+  float* grad_pair;
+};
+
+// Pixel table of a bucket: (gC, gD) and (P - Q_in, last position, T_in, -).
+struct SplatLds {
+  float4 g[kWave], x[kWave];
+};
+
+// A lane's splat.
+struct LaneSplat {
+  double my;
+  float dx[kSub];
+  float t, s1, s2, lo, z, r, g, b;
+  uint32_t pos;
+};
+
+// The ten sums of the lane's splat over the tile's live pixels (alive: bit
+// per pixel).  SEG lanes take one pixel; R = 64 / SEG rows of pixels go
+// through at once.  CLAMP: some splat of the bucket can exceed the 0.99 clamp.
+template <int SEG, bool CLAMP>
+__device__ __forceinline__ void splat_rows(const LaneSplat& r, const SplatLds& S, uint64_t alive,
+                                           int ty0, int lane, float (&acc)[10]) {
+  constexpr int R = kWave / SEG, NR = kSub * R;
+  const int seg = lane / SEG;
+#pragma unroll
+  for (int f = 0; f < 10; ++f) acc[f] = 0.0f;
+  for (int it = 0; it < kSub / R; ++it) {
+    uint64_t m = (alive >> (NR * it)) & (NR == 64 ? ~0ull : (1ull << NR) - 1ull);
+    if (m == 0) continue;  // (uniform)
+    if (R >= 2) m |= m >> kSub;
+    if (R >= 4) m |= m >> (2 * kSub);
+    const int row = it * R + seg;
+    const float dy = (float)(r.my - ((double)(ty0 + row) + 0.5));
+    const float4* sx = S.x + row * kSub;
+    const float4* sg = S.g + row * kSub;
+    // moments over the row of gpow = dL/dpower: 1, dx, dx^2
+    float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f;
+    // two pixels per step, their scans interleaved; each lane accumulates
+    // the left one first
+#pragma unroll
+    for (int p = 0; p < kSub; p += 2) {
+      if (((m >> p) & 3ull) == 0) continue;  // (uniform)
+      float4 x[2], g[2];
+      float oG[2], a[2], inv_om[2], f[2];
+      bool hit[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        x[u] = sx[p + u];
+        g[u] = sg[p + u];
+        // alpha as in the forward (same bits)
+        oG[u] = __builtin_amdgcn_exp2f(exponent(r.t, r.s1, r.s2, r.lo, r.dx[p + u], dy));
+        a[u] = CLAMP ? fminf(kAlphaMax, oG[u]) : oG[u];
+        hit[u] = (r.pos < __float_as_uint(x[u].y)) & (a[u] >= kAlphaMin);
+        // alpha of a blended splat, 0 otherwise: its 1 - alpha is the scan's
+        // factor and alpha T the blend weight, with no further selects
+        a[u] = hit[u] ? a[u] : 0.0f;
+        f[u] = 1.0f - a[u];
+        inv_om[u] = __builtin_amdgcn_rcpf(f[u]);
+      }
+      // transmittance in front of the splat: the segment's inclusive product
+      // over its blended splats with the lane's own factor taken out again
+      // (read by blended lanes only, whose factor 1 - alpha >= 0.01)
+      seg_scan_mul2<SEG>(f[0], f[1]);
+      float Tl[2], wgt[2], front[2], q[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        Tl[u] = (x[u].z * f[u]) * inv_om[u];
+        wgt[u] = a[u] * Tl[u];
+        front[u] = fmaf(g[u].w, r.z, fmaf(g[u].z, r.b, fmaf(g[u].y, r.g, g[u].x * r.r)));
+        q[u] = wgt[u] * front[u];
+      }
+      seg_scan_add2<SEG>(q[0], q[1]);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        // behind the splat: P - (Q_in + the front part after the splat)
+        const float g_alpha = fmaf(-(x[u].x - q[u]), inv_om[u], Tl[u] * front[u]);
+        acc[0] = fmaf(wgt[u], g[u].x, acc[0]);
+        acc[1] = fmaf(wgt[u], g[u].y, acc[1]);
+        acc[2] = fmaf(wgt[u], g[u].z, acc[2]);
+        acc[3] = fmaf(wgt[u], g[u].w, acc[3]);
+        // gpow = alpha dL/dalpha of the unclamped splats; the opacity, conic
+        // and mean partials are formed from its moments once, after the
+        // pixels (dL/do = sum gpow / o)
+        const float gpow = !CLAMP || oG[u] <= kAlphaMax ? a[u] * g_alpha : 0.0f;
+        const float t = gpow * r.dx[p + u];
+        m0 += gpow;
+        m1 += t;
+        m2 = fmaf(t, r.dx[p + u], m2);
+      }
+    }
+    const float my = dy * m0;
+    acc[4] += m0;
+    acc[5] += m2;
+    acc[6] = fmaf(dy, m1, acc[6]);
+    acc[7] = fmaf(dy, my, acc[7]);
+    acc[8] += m1;
+    acc[9] += my;
   }
+#pragma unroll
+  for (int f = 0; f < 10; ++f) acc[f] = sum_segments<SEG>(acc[f]);
+}
+
+// One bucket: entry qi of the queue.
+__device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable& vt, uint32_t qi,
+                                             SplatLds& S) {
+  const int lane = (int)threadIdx.x;
+  const uint2 ent = A.bq[qi];  // (tile, k)
+  const int gtile = __builtin_amdgcn_readfirstlane((int)ent.x);
+  const uint32_t q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)ent.y) * kBucket;
+  const uint2 seen = A.seen[gtile];  // (slots, list positions looked at)
+  const uint32_t s = A.ranges[2 * (int64_t)gtile], e = A.ranges[2 * (int64_t)gtile + 1];
+  // entry k also writes the zero gradients of the pairs that no bucket holds
+  // among the list's k-th 64 positions
+  {
+    const uint32_t p = q0 + (uint32_t)lane;
+    const uint64_t kept = q0 < seen.y ? A.kept[qi] : 0ull;
+    if (s + p < e && !((kept >> lane) & 1ull)) {
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      store_pair(A.grad_pair, A.sorted_vals[s + p], z, z, make_float2(0.f, 0.f));
+    }
+  }
+  if (q0 >= seen.x) return;  // the tile's list has more entries than its slots have buckets
+  const int cnt = (int)min((uint32_t)kBucket, seen.x - q0);
+  const int seg_lanes = cnt > 32 ? 64 : cnt > 16 ? 32 : 16;
+  // the lane's splat (the same ones in every segment)
+  const int ls = lane & (seg_lanes - 1);
+  const uint32_t pos = ls < cnt ? A.cand[(int64_t)qi * kBucket + ls] : kNoSplat;
+  const bool live = pos != kNoSplat;
+  const uint32_t pos0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos);
+
+  // pixel table: loss gradients, P, last position, stored state.  A pixel
+  // whose last position lies at or before the bucket's first splat has none
+  // of its splats blended and adds nothing.
+  const int v = find_view(vt, gtile);
+  const ViewInfo vi = vt.v[v];
+  const int lt = gtile - vi.tile_off;
+  const int tx0 = (lt % vi.tiles_x) * kSub, ty0 = (lt / vi.tiles_x) * kSub;
+  const int64_t npx = (int64_t)vi.W * vi.H;
+  const int px = tx0 + (lane & (kSub - 1)), py = ty0 + lane / kSub;
+  float4 g = make_float4(0.f, 0.f, 0.f, 0.f), x = make_float4(0.f, 0.f, 1.f, 0.f);
+  bool alive_px = false;
+  if (px < vi.W && py < vi.H) {
+    const int64_t pl = (int64_t)py * vi.W + px;
+    const int64_t pix = (int64_t)vi.pix_off + pl;
+    const int64_t cbase = 3 * (int64_t)vi.pix_off + pl;
+    const uint32_t lp = A.last[pix];
+    alive_px = lp > pos0;
+    if (alive_px) {
+      const float o0 = A.color[cbase], o1 = A.color[cbase + npx], o2 = A.color[cbase + 2 * npx];
+      const float od = A.depth[pix];
+      g = A.loss.at(cbase, npx, pix, o0, o1, o2, od);
+      float Qin = 0.0f;
+      if (q0 > 0) {  // the first bucket starts from T = 1 and nothing accumulated
+        const float* cp = A.ckpt + (int64_t)qi * (kStateFloats * kWave) + lane;
+        x.z = cp[0];
+        Qin = g.x * cp[kWave] + g.y * cp[2 * kWave] + g.z * cp[3 * kWave] + g.w * cp[4 * kWave];
+      }
+      x.x = (g.x * o0 + g.y * o1 + g.z * o2 + g.w * od) - Qin;
+      x.y = __uint_as_float(lp);
+    }
+  }
+  const uint64_t alive = ballot64(alive_px);
+  float acc[10];
+  float ca = 0.0f, cb = 0.0f, cc = 0.0f, ro = 0.0f;
+  if (alive == 0) {  // (uniform)
+#pragma unroll
+    for (int f = 0; f < 10; ++f) acc[f] = 0.0f;
+  } else {
+    S.g[lane] = g;
+    S.x[lane] = x;
+    LaneSplat r;
+    r.t = r.s1 = r.s2 = r.z = r.r = r.g = r.b = 0.0f;
+    r.lo = -INFINITY;  // alpha = 0 in a lane without a splat
+    r.my = 0.0;
+    r.pos = pos;
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) r.dx[k] = 0.0f;
+    if (live) {
+      Rec rec;
+      const float4* src = reinterpret_cast<const float4*>(A.lrec.at(s + pos));
+      float4* dst = reinterpret_cast<float4*>(&rec);
+      dst[0] = src[0]; dst[1] = src[1]; dst[2] = src[2]; dst[3] = src[3];
+      r.t = rec.t; r.s1 = rec.s1; r.s2 = rec.s2; r.lo = rec.lo;
+      r.z = rec.z; r.r = rec.r; r.g = rec.g; r.b = rec.b;
+      r.my = rec.my;
+      double ax = (double)tx0 + 0.5;
+#pragma unroll
+      for (int k = 0; k < kSub; ++k) {
+        r.dx[k] = (float)(rec.mx - ax);
+        ax += 1.0;
+      }
+      rec_conic(rec, ca, cb, cc);
+      ro = rec.o;
+    }
+    const bool clamps = ballot64(r.lo > kClampLo) != 0;
+    __syncthreads();
+    auto rows = [&](auto seg_c) {
+      constexpr int SEG = decltype(seg_c)::value;
+      if (clamps) splat_rows<SEG, true>(r, S, alive, ty0, lane, acc);
+      else splat_rows<SEG, false>(r, S, alive, ty0, lane, acc);
+    };
+    if (seg_lanes == 64) rows(std::integral_constant<int, 64>{});
+    else if (seg_lanes == 32) rows(std::integral_constant<int, 32>{});
+    else rows(std::integral_constant<int, 16>{});
+    __syncthreads();  // the pixel table is rewritten by the next bucket
+  }
+  if (live && lane < seg_lanes)
+    store_pair(A.grad_pair, A.sorted_vals[s + pos], make_float4(acc[0], acc[1], acc[2], acc[3]),
+               make_float4(ro > 0.0f ? acc[4] / ro : 0.0f, -0.5f * acc[5], -acc[6], -0.5f * acc[7]),
+               make_float2(-(ca * acc[8] + cb * acc[9]), -(cb * acc[8] + cc * acc[9])));
+}
+
+// Grid-stride over the bucket queue.
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6))) k_render_bwd_splat(
+    SplatArgs A, ViewTable vt) {
+  __shared__ SplatLds S;
+  const uint32_t n = (uint32_t)A.fl[F_BUCKETS];
+  const uint32_t q = xcd_item(blockIdx.x, gridDim.x);
+  if (q < n) splat_bucket(A, vt, q, S);
 }
 
 // The radix binning writes no record copy: its lists name their records.
@@ -1016,36 +1074,24 @@ RecSrc rec_src(const Plan& P, void* ws) {
 }
 
 template <int TW, int TH>
-hipError_t bwd_splat_launch(const Plan& P, void* ws, const float* cams, const float* color,
-                            const float* depth, const uint32_t* last, const float* dL_dcolor,
-                            const float* dL_ddepth, const float* target_rgb,
-                            const float* target_depth, int fused, const uint32_t* sorted_vals,
-                            int grid, hipStream_t s) {
-  (void)cams;
-  hipLaunchKernelGGL((k_render_bwd_splat<TW, TH>), dim3(grid), dim3(kWave), 0, s,
-                     rec_src(P, ws), sorted_vals,
-                     ws_at<uint32_t>(ws, P.off_ranges), ws_at<uint32_t>(ws, P.off_tile_last),
-                     ws_at<uint32_t>(ws, P.off_boff), ws_at<float>(ws, P.off_ckpt),
-                     ws_at<uint2>(ws, P.off_bq), P.ckpt_slots, ws_at<int32_t>(ws, P.off_flags),
-                     P.vt, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth,
-                     fused, P.cfg.lambda_depth, ws_at<float>(ws, P.off_grad_pair));
-  return hipGetLastError();
-}
-
-template <int TW, int TH>
 hipError_t fwd_launch(const Plan& P, void* ws, const float* cams, float* color, float* depth,
                       float* T_final, uint32_t* last, const float* target_rgb,
                       const float* target_depth, hipStream_t s) {
-  const bool splat = (P.cfg.flags & GS_SPLAT_BWD) != 0;
-  const FwdArgs A{rec_src(P, ws), ws_at<uint32_t>(ws, P.off_ranges), cams, color, depth, T_final,
-                  last, ws_at<uint32_t>(ws, P.off_tile_last), target_rgb, target_depth,
-                  ws_at<float>(ws, P.off_tile_loss), ws_at<uint32_t>(ws, P.off_order),
-                  ws_at<int32_t>(ws, P.off_flags),
-                  splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr,
-                  splat ? ws_at<float>(ws, P.off_ckpt) : nullptr};
+  FwdArgs A{rec_src(P, ws), ws_at<uint32_t>(ws, P.off_ranges), cams, color, depth, T_final,
+            last, ws_at<uint32_t>(ws, P.off_tile_last), target_rgb, target_depth,
+            ws_at<float>(ws, P.off_tile_loss), ws_at<uint32_t>(ws, P.off_order),
+            ws_at<int32_t>(ws, P.off_flags), FwdSplat{}};
   const dim3 g((unsigned)P.vt.total_tiles * sub_tiles<TW, TH>()), block(kWave);
-  if (splat) hipLaunchKernelGGL((k_render_fwd<TW, TH, true>), g, block, 0, s, A, P.vt);
-  else hipLaunchKernelGGL((k_render_fwd<TW, TH, false>), g, block, 0, s, A, P.vt);
+  if constexpr (TW * TH == kWave) {
+    if (P.splat) {
+      A.splat = FwdSplat{ws_at<uint32_t>(ws, P.off_boff), ws_at<float>(ws, P.off_ckpt),
+                         ws_at<uint32_t>(ws, P.off_cand), ws_at<uint64_t>(ws, P.off_kept),
+                         ws_at<uint2>(ws, P.off_seen)};
+      hipLaunchKernelGGL((k_render_fwd<TW, TH, true>), g, block, 0, s, A, P.vt);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_render_fwd<TW, TH, false>), g, block, 0, s, A, P.vt);
   return hipGetLastError();
 }
 
@@ -1076,12 +1122,7 @@ int occupancy(K kernel, size_t lds) {
 int blocks_per_tile(const Plan& P) { return P.cfg.tile_w * P.cfg.tile_h / (kSub * kSub); }
 
 // Resident workgroups per CU of the splat-wise backward.
-int splat_blocks_per_cu(const Plan& P) {
-  const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
-  if (tw == 16 && th == 16) return occupancy(k_render_bwd_splat<16, 16>, 0);
-  if (tw == 16 && th == 8) return occupancy(k_render_bwd_splat<16, 8>, 0);
-  return occupancy(k_render_bwd_splat<8, 8>, 0);
-}
+int splat_blocks_per_cu() { return occupancy(k_render_bwd_splat, 0); }
 
 hipError_t launch_render_fwd(const Plan& P, void* ws, const float* cams, float* color,
                              float* depth, float* T_final, uint32_t* last,
@@ -1113,14 +1154,21 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                              const uint32_t* sorted_vals, int splat_grid, hipStream_t s) {
   if (P.vt.total_tiles == 0) return hipSuccess;
   const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
-  if (P.cfg.flags & GS_SPLAT_BWD) {
-    if (tw == 16 && th == 16)
-      return bwd_splat_launch<16, 16>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
-    if (tw == 16 && th == 8)
-      return bwd_splat_launch<16, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
-    return bwd_splat_launch<8, 8>(P, ws, cams, color, depth, last, dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, sorted_vals, splat_grid, s);
-  }
   const PixelLoss loss{dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, P.cfg.lambda_depth};
+  // GS_SPLAT_BWD with larger tiles takes the pixel-wise form: a bucket's lanes
+  // would sit idle on the blocks of the tile that their splats do not reach
+  // (55 %).  Forward and backward, before -> after: one 1200x680 view, 16x16
+  // tiles 253 -> 91 us, 16x8 159 -> 89 us; 8 mixed views (6.0M pairs in 8x8
+  // tiles), 16x16 4.7 -> 2.0 ms, 16x8 2.3 -> 1.4 ms
+  if (P.splat) {
+    const SplatArgs A{rec_src(P, ws), sorted_vals, ws_at<uint32_t>(ws, P.off_ranges),
+                      ws_at<uint32_t>(ws, P.off_cand), ws_at<uint64_t>(ws, P.off_kept),
+                      ws_at<uint2>(ws, P.off_seen), ws_at<float>(ws, P.off_ckpt),
+                      ws_at<uint2>(ws, P.off_bq), ws_at<int32_t>(ws, P.off_flags), color, depth,
+                      last, loss, ws_at<float>(ws, P.off_grad_pair)};
+    hipLaunchKernelGGL(k_render_bwd_splat, dim3((unsigned)P.ckpt_slots), dim3(kWave), 0, s, A, P.vt);
+    return hipGetLastError();
+  }
   if (tw == 16 && th == 16)
     return bwd_launch<16, 16>(P, ws, cams, color, depth, T_final, last, loss, sorted_vals, s);
   if (tw == 16 && th == 8)

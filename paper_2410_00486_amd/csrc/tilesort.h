@@ -3,7 +3,7 @@
 // Output per tile: sorted keys (tile << 32 | depth bits), generation
 // indices, record ids, the records in list order, the [start, end) range
 // ((0, 0) when empty) and, for the splat-wise backward, the tile's entries
-// in the two bucket queues.  Keys are unique, so any correct sort gives the
+// in the bucket queue.  Keys are unique, so any correct sort gives the
 // same lists.  One launch: a wavefront sorts lists up to 64 keys in
 // registers (rank = number of smaller keys) and up to kTileSortMid keys with a
 // bitonic network in LDS; longer lists take a whole 1024-thread workgroup,
@@ -27,17 +27,6 @@ constexpr uint32_t kTileSortSmall = 128;
 constexpr uint32_t kTileSortLong = 8192;
 constexpr int kSortWaves = 16;                                  // wavefronts per workgroup
 constexpr uint32_t kTileSortMid = kTileSortLong / kSortWaves;   // 512: one wavefront's share
-
-// Splits a tile of c pairs into buckets of 64 positions: all but possibly
-// the last hold more than 32 pairs (full); a last bucket with at most 32
-// pairs is a half bucket.
-__device__ __forceinline__ void bucket_split(uint32_t c, uint32_t& nb, uint32_t& full,
-                                             uint32_t& half) {
-  nb = (c + kBucket - 1) / kBucket;
-  const uint32_t r = c - (nb > 0 ? (nb - 1) * kBucket : 0u);  // pairs of the last bucket
-  half = (c > 0 && r <= 32) ? 1u : 0u;
-  full = nb - half;
-}
 
 struct TileSortOut {
   uint64_t* keys;
@@ -125,10 +114,8 @@ struct TileSortArgs {
   const uint64_t* skey;    // scattered keys (depth bits << 32 | generation index)
   TileSortOut out;
   uint32_t* ranges;
-  const uint32_t* fstart;  // splat-wise only (bq non-null): queue positions
-  const uint32_t* hstart;
+  const uint32_t* boff;  // splat-wise only (bq non-null): the tile's first queue entry
   uint2* bq;
-  int64_t bq_stride;
   // the lists were sorted by the radix binning: ranges, queue entries and
   // counter clears only
   bool presorted;
@@ -189,14 +176,9 @@ __device__ inline void sort_tile_wave(const TileSortArgs& A, int t, int lane, ui
     A.cnt[t] = 0u;
   }
   if (A.bq && ok) {
-    // splat-wise work queues at the scanned positions: the tile's buckets
-    // 0 .. full-1 have more than 32 pairs; a last bucket with at most 32
-    // goes to the second queue
-    uint32_t nb, full, half;
-    bucket_split(n, nb, full, half);
-    const uint32_t f0 = A.fstart[t];
-    for (uint32_t k = lane; k < full; k += kWave) A.bq[f0 + k] = make_uint2((uint32_t)t, k);
-    if (half && lane == 0) A.bq[A.bq_stride + A.hstart[t]] = make_uint2((uint32_t)t, nb - 1);
+    // splat-wise work queue: the tile's buckets of 64 pairs
+    const uint32_t q0 = A.boff[t], nb = (n + kBucket - 1) / kBucket;
+    for (uint32_t k = lane; k < nb; k += kWave) A.bq[q0 + k] = make_uint2((uint32_t)t, k);
   }
   if (!ok || n > kTileSortSmall || A.presorted) return;  // uniform
   const uint32_t start = (uint32_t)start64;

@@ -121,3 +121,53 @@ def test_pixelwise_backward_blocks_match_oracle(n, width, height, tile):
     grads, poses, exclude, poses_f = oracle_reference(w.scene, [cam], gcs, gds, tile)
     assert_grads_close(grads_np(it), grads, exclude)
     assert_pose_close(it.dL_dpose.cpu().numpy(), poses, poses_f)
+
+
+@pytest.mark.parametrize("n,width,height", [(1, 1, 1), (4, 9, 7), (15, 8, 8), (16, 8, 8), (17, 13, 9),
+                                            (32, 8, 8), (33, 17, 8), (64, 8, 8), (65, 12, 8),
+                                            (130, 24, 17), (300, 90, 70)])
+def test_splatwise_backward_buckets_match_oracle(n, width, height):
+    """The splat-wise backward over buckets of the splats that the forward
+    kept: one, two and four segments per wavefront, several buckets per tile,
+    images that end inside a tile, against the oracle; with an opaque splat
+    in every seventh place (the clamped form) and without."""
+    for opaque in (False, True):
+        w = scenes.tiny_scene(51 + n, n=n, width=width, height=height, f=0.9 * max(width, 8), degree=1)
+        if opaque:
+            w.scene.opacity_logits[::7] = 8.0
+        else:
+            w.scene.opacity_logits[:] = np.minimum(w.scene.opacity_logits, 2.0) - 1.5
+        cam = w.cameras[0]
+        print(f"splat-wise backward n {n} {width}x{height} opaque {opaque}", flush=True)
+        gcs, gds = scenes.linear_loss_weights(90 + n, [cam])
+        it = run_gpu(w.scene, [cam], tile=(8, 8), flags=L.GS_SPLAT_BWD, dL_dcolor=gcs,
+                     dL_ddepth=gds, pose=True)
+        ref = oracle.render(w.scene, cam, (8, 8))
+        col, dep, _, last = view_images(it, 0)
+        assert_forward_close(col, dep, ref)
+        ok = ref["flag"] == 0
+        np.testing.assert_array_equal(last[ok], ref["last"][ok])
+        grads, poses, exclude, poses_f = oracle_reference(w.scene, [cam], gcs, gds, (8, 8))
+        assert_grads_close(grads_np(it), grads, exclude)
+        assert_pose_close(it.dL_dpose.cpu().numpy(), poses, poses_f)
+
+
+def test_splatwise_backward_pairs_behind_the_stop_get_zero():
+    """Opaque splats in front: the pairs that the forward never looks at, and
+    those it drops, get zero gradients even after an iteration that wrote
+    theirs (the same workspace, other opacities)."""
+    w = scenes.crowded_scene(3, n=400)
+    cam = w.cameras[0]
+    gcs, gds = scenes.linear_loss_weights(5, [cam])
+    print("splat-wise backward, a second iteration on the same workspace", flush=True)
+    # (room for the second iteration's pairs: more opaque splats reach further)
+    it = run_gpu(w.scene, [cam], tile=(8, 8), flags=L.GS_SPLAT_BWD, dL_dcolor=gcs, dL_ddepth=gds,
+                 capacity=1 << 16)
+    near = np.argsort(w.scene.means[:, 2])[:60]
+    w.scene.opacity_logits[near] = 6.0
+    it.g.opacity_logits.copy_(torch.from_numpy(w.scene.opacity_logits))
+    it.enqueue()
+    torch.cuda.synchronize()
+    assert it.plan.flags_of(it.ws)[L.F_OVERFLOW] == 0
+    grads, _, exclude, _ = oracle_reference(w.scene, [cam], gcs, gds, (8, 8))
+    assert_grads_close(grads_np(it), grads, exclude)
