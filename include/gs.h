@@ -373,7 +373,7 @@ gs_status gs_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int32_t key_b
  * device memory (code under stream capture, tight serving loops, hosts that
  * forbid hipMalloc).  Same arguments and result as gs_sort_pairs without
  * tmp: the scratch is a device array inside the library, one per GPU, of
- * GS_SORT_NOALLOC_MAX pairs (about 12.9 MB), held from the first call on
+ * GS_SORT_NOALLOC_MAX pairs (about 13.1 MB), held from the first call on
  * that GPU until the process ends.  n above GS_SORT_NOALLOC_MAX is
  * rejected with GS_ERR_INVALID_ARG before any GPU work.  No hipMalloc,
  * hipFree or allocating library routine is called.  Every call on one GPU

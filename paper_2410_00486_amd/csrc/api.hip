@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "sort.h"
 #include "tilesort.h"
 
 namespace gs {
@@ -21,10 +22,6 @@ int64_t rb_blocks(int64_t count);
 int64_t rb_gen_blocks(int64_t records);
 int64_t rb_gen_items(int64_t records, int64_t pairs);
 int rb_max_radix();
-hipError_t launch_radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0, uint32_t* vals1,
-                             const int32_t* cnt, uint32_t* hist, uint32_t* digit_tot,
-                             int64_t nb_cap, int key_bits, bool iota, int* which, hipStream_t s);
-hipError_t launch_set_i32(int32_t* p, int32_t v, hipStream_t s);
 hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s);
 uint32_t* sorted_vals(const Plan& P, void* ws);
 hipError_t launch_render_fwd(const Plan& P, void* ws, const float* cams, float* color,
@@ -575,52 +572,6 @@ gs_status gs_densify_prune(const gs_gaussians* g, const gs_gaussian_grads* m,
 
 namespace {
 
-// Scratch of the stand-alone sort for n pairs: second key and value buffers,
-// the per-block digit histograms, the digit totals and the pair count.
-struct SortTmp {
-  size_t k1, v1, hist, dtot, cnt, bytes;
-};
-
-constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
-
-constexpr SortTmp sort_tmp_layout(int64_t n) {
-  const int64_t nb = n > kSortTile ? (n + kSortTile - 1) / kSortTile : 1;
-  SortTmp t{};
-  t.k1 = 0;
-  t.v1 = align256(t.k1 + (size_t)n * 8 + 8);
-  t.hist = align256(t.v1 + (size_t)n * 4 + 4);
-  t.dtot = align256(t.hist + (size_t)kRadix * nb * 4);
-  t.cnt = align256(t.dtot + kRadix * 4);
-  t.bytes = align256(t.cnt + 16);
-  return t;
-}
-
-// Sort with caller-provided scratch `tmp` (sort_tmp_layout(n).bytes, 256-byte
-// aligned); n >= 1 and the arguments already checked.
-gs_status sort_pairs_in(uint64_t* keys, uint32_t* vals, int64_t n, int32_t key_bits, void* tmp,
-                        hipStream_t s, const char* what) {
-  const int64_t nb = std::max<int64_t>(1, (n + kSortTile - 1) / kSortTile);
-  const SortTmp L = sort_tmp_layout(n);
-  char* base = static_cast<char*>(tmp);
-  uint64_t* k1 = reinterpret_cast<uint64_t*>(base + L.k1);
-  uint32_t* v1 = reinterpret_cast<uint32_t*>(base + L.v1);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(base + L.hist);
-  uint32_t* dtot = reinterpret_cast<uint32_t*>(base + L.dtot);
-  int32_t* cnt = reinterpret_cast<int32_t*>(base + L.cnt);
-  // the pair count is written by a kernel on every call, every histogram
-  // entry the passes read is written by the same call: nothing in the
-  // scratch has to start at zero
-  hipError_t e = launch_set_i32(cnt, (int32_t)n, s);
-  int which = 0;
-  if (e == hipSuccess)
-    e = launch_radix_sort(keys, k1, vals, v1, cnt, hist, dtot, nb, key_bits, false, &which, s);
-  if (e == hipSuccess && which == 1) {
-    e = hipMemcpyAsync(keys, k1, (size_t)n * 8, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(vals, v1, (size_t)n * 4, hipMemcpyDeviceToDevice, s);
-  }
-  return hip_check(e, what);
-}
-
 gs_status check_sort_args(const uint64_t* keys, const uint32_t* vals, int64_t n, int64_t n_max,
                           int32_t key_bits) {
   if (n < 0 || n > n_max) return fail(GS_ERR_INVALID_ARG, "n must be 0..%lld", (long long)n_max);
@@ -634,7 +585,7 @@ gs_status check_sort_args(const uint64_t* keys, const uint32_t* vals, int64_t n,
 // Host code never passes the array's own name to a kernel or a copy (on the
 // host it is only a stand-in for the symbol): each device's address comes
 // from hipGetSymbolAddress, taken once per device with that device current.
-constexpr SortTmp kNoallocLayout = sort_tmp_layout(GS_SORT_NOALLOC_MAX);
+constexpr SortScratch kNoallocLayout = sort_scratch(GS_SORT_NOALLOC_MAX);
 static __device__ __align__(256) unsigned char scratch[kNoallocLayout.bytes];
 
 constexpr int kMaxDevices = 64;
@@ -666,7 +617,7 @@ extern "C" {
 
 size_t gs_sort_tmp_bytes(int64_t n) {
   if (n < 0) return 0;
-  return sort_tmp_layout(n).bytes;
+  return sort_scratch(n).bytes;
 }
 
 gs_status gs_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int32_t key_bits, void* tmp,
@@ -675,8 +626,9 @@ gs_status gs_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int32_t key_b
   if (st != GS_OK || n == 0) return st;
   if (!tmp) return fail(GS_ERR_INVALID_ARG, "null pointer");
   if (!aligned(tmp, 256)) return fail(GS_ERR_INVALID_ARG, "tmp must be 256-byte aligned");
-  return sort_pairs_in(keys, vals, n, key_bits, tmp, static_cast<hipStream_t>(stream),
-                       "gs_sort_pairs");
+  return hip_check(launch_sort_pairs(keys, vals, n, key_bits, tmp,
+                                     static_cast<hipStream_t>(stream)),
+                   "gs_sort_pairs");
 }
 
 gs_status gs_sort_pairs_noalloc(uint64_t* keys, uint32_t* vals, int64_t n, int32_t key_bits,
@@ -685,8 +637,9 @@ gs_status gs_sort_pairs_noalloc(uint64_t* keys, uint32_t* vals, int64_t n, int32
   if (st != GS_OK || n == 0) return st;
   void* tmp = nullptr;
   if ((st = scratch_of_current_device(&tmp)) != GS_OK) return st;
-  return sort_pairs_in(keys, vals, n, key_bits, tmp, static_cast<hipStream_t>(stream),
-                       "gs_sort_pairs_noalloc");
+  return hip_check(launch_sort_pairs(keys, vals, n, key_bits, tmp,
+                                     static_cast<hipStream_t>(stream)),
+                   "gs_sort_pairs_noalloc");
 }
 
 static gs_status check_gather(const Plan& P, const gs_view_gather* g, const float* cams_out,

@@ -14,9 +14,7 @@
 // spin-waits; graph-capturable.
 //
 // The scan also writes the work order of the render kernels: tiles with long
-// lists first.  The general stable LSD
-// radix sort (8-bit digits, wave64 ballot ranking) below serves the
-// standalone key/value sort.
+// lists first.
 #include "tilesort.h"
 #include "wavescan.h"
 
@@ -27,8 +25,6 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t value, int64_t cou
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) p[i] = value;
 }
-
-__global__ void k_set_i32(int32_t* __restrict__ p, int32_t value) { *p = value; }
 
 // Clears a[0, na) and b[0, nb).
 __global__ void k_fill2_u32(uint32_t* __restrict__ a, int64_t na, uint32_t* __restrict__ b,
@@ -562,179 +558,6 @@ __global__ void __launch_bounds__(kSortWaves * kWave) __attribute__((amdgpu_wave
   }
 }
 
-// ---------------------------------------------------------------- radix sort
-__device__ __forceinline__ int sort_count(const int32_t* cnt) { return *cnt; }
-
-// Up to this many sort blocks (1M keys) the per-digit scan runs inside the
-// downsweep instead of as its own launch.
-constexpr int64_t kFusedScanBlocks = 256;
-
-__global__ void __launch_bounds__(kSortThreads) k_radix_upsweep(const uint64_t* __restrict__ keys,
-                                                                const int32_t* __restrict__ cnt,
-                                                                uint32_t* __restrict__ hist,
-                                                                int64_t nb_cap, int shift) {
-  const int P = sort_count(cnt);
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  if (base >= P) return;
-  __shared__ uint32_t h[kSortThreads / kWave][kRadix];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  for (int k = threadIdx.x; k < (kSortThreads / kWave) * kRadix; k += kSortThreads)
-    (&h[0][0])[k] = 0;
-  __syncthreads();
-#pragma unroll 4
-  for (int r = 0; r < kSortItems; ++r) {
-    const int64_t idx = base + (int64_t)w * (kWave * kSortItems) + r * kWave + lane;
-    if (idx < P) {
-      const uint32_t d = (uint32_t)(keys[idx] >> shift) & (kRadix - 1);
-      atomicAdd(&h[w][d], 1u);
-    }
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < kRadix; d += kSortThreads) {
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kSortThreads / kWave; ++k) s += h[k][d];
-    hist[(int64_t)d * nb_cap + blockIdx.x] = s;
-  }
-}
-
-// One block per digit: exclusive scan over the active blocks of that digit.
-__global__ void __launch_bounds__(256) k_radix_scan(uint32_t* __restrict__ hist,
-                                                    const int32_t* __restrict__ cnt,
-                                                    uint32_t* __restrict__ digit_tot,
-                                                    int64_t nb_cap) {
-  const int P = sort_count(cnt);
-  const int64_t nb = (P + kSortTile - 1) / kSortTile;
-  uint32_t* row = hist + (int64_t)blockIdx.x * nb_cap;
-  __shared__ uint32_t wsum[256 / kWave];
-  __shared__ uint32_t carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  const int lane = lane_id(), w = threadIdx.x / kWave;
-  for (int64_t base = 0; base < nb; base += 256) {
-    const int64_t idx = base + threadIdx.x;
-    const uint32_t x = idx < nb ? row[idx] : 0u;
-    uint32_t incl = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += y;
-    }
-    if (lane == kWave - 1) wsum[w] = incl;
-    __syncthreads();
-    uint32_t woff = carry;
-    for (int k = 0; k < w; ++k) woff += wsum[k];
-    if (idx < nb) row[idx] = woff + incl - x;
-    __syncthreads();
-    if (threadIdx.x == 255) carry = woff + incl;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
-}
-
-// Stable in-block ranking and scatter.  Keys of a block are processed in
-// rounds of 64 per wave, in index order; lanes holding the same digit in a
-// round are found with 8 ballots (one per digit bit); the lowest such lane
-// advances the wave's counter for that digit.  Ranks are thus increasing in
-// index within each digit: the pass is stable.
-// FUSED: the per-digit scan over blocks is done here (each thread sums the
-// counts of its digit over the active blocks), for small block counts.
-template <bool FUSED>
-__global__ void __launch_bounds__(kSortThreads) k_radix_downsweep(
-    const uint64_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-    uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out,
-    const int32_t* __restrict__ cnt, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ digit_tot, int64_t nb_cap, int shift, int iota_vals) {
-  const int P = sort_count(cnt);
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  if (base >= P) return;
-  constexpr int NW = kSortThreads / kWave;
-  __shared__ uint32_t wcnt[NW][kRadix];
-  __shared__ uint32_t boff[kRadix];
-  __shared__ uint32_t dsum[NW];
-  const int w = threadIdx.x / kWave, lane = lane_id();
-  for (int k = threadIdx.x; k < NW * kRadix; k += kSortThreads) (&wcnt[0][0])[k] = 0;
-  // block offset of each digit: exclusive scan of the digit totals plus this
-  // block's exclusive prefix within the digit
-  {
-    const int d = threadIdx.x;  // kSortThreads == kRadix
-    uint32_t x, before;
-    if (FUSED) {
-      const int64_t nb = (P + kSortTile - 1) / kSortTile;
-      const uint32_t* row = hist + (int64_t)d * nb_cap;
-      uint32_t tot = 0, pre = 0;
-      for (int64_t b = 0; b < nb; ++b) {
-        const uint32_t h = row[b];
-        pre += (b < (int64_t)blockIdx.x) ? h : 0u;
-        tot += h;
-      }
-      x = tot;
-      before = pre;
-    } else {
-      x = digit_tot[d];
-      before = hist[(int64_t)d * nb_cap + blockIdx.x];
-    }
-    uint32_t incl = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t y = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl += y;
-    }
-    if (lane == kWave - 1) dsum[w] = incl;
-    __syncthreads();
-    uint32_t woff = 0;
-    for (int k = 0; k < w; ++k) woff += dsum[k];
-    boff[d] = woff + incl - x + before;
-  }
-  __syncthreads();
-
-  uint64_t key[kSortItems];
-  uint32_t rank[kSortItems];
-  const uint64_t lt = lanemask_lt();
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int64_t idx = base + (int64_t)w * (kWave * kSortItems) + r * kWave + lane;
-    const bool valid = idx < P;
-    key[r] = valid ? keys_in[idx] : 0ull;
-    const uint32_t d = (uint32_t)(key[r] >> shift) & (kRadix - 1);
-    uint64_t peers = ballot64(valid);
-#pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bb = ballot64(bit);
-      peers &= bit ? bb : ~bb;
-    }
-    uint32_t old = 0;
-    if (valid) old = wcnt[w][d];
-    const uint64_t below = peers & lt;
-    if (valid && below == 0) wcnt[w][d] = old + (uint32_t)__popcll(peers);
-    rank[r] = old + (uint32_t)__popcll(below);
-  }
-  __syncthreads();
-  // exclusive prefix over waves, per digit
-  {
-    const int d = threadIdx.x;
-    uint32_t run = 0;
-#pragma unroll
-    for (int k = 0; k < NW; ++k) {
-      const uint32_t c = wcnt[k][d];
-      wcnt[k][d] = run;
-      run += c;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int64_t idx = base + (int64_t)w * (kWave * kSortItems) + r * kWave + lane;
-    if (idx < P) {
-      const uint32_t d = (uint32_t)(key[r] >> shift) & (kRadix - 1);
-      const uint32_t pos = boff[d] + wcnt[w][d] + rank[r];
-      keys_out[pos] = key[r];
-      vals_out[pos] = iota_vals ? (uint32_t)idx : vals_in[idx];
-    }
-  }
-}
-
 }  // namespace
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t s) {
@@ -744,47 +567,9 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream
   return hipGetLastError();
 }
 
-// Radix sort of `count` (device int) pairs held in keys[0]/vals[0] over the
-// low key_bits bits; ping-pongs through keys[1]/vals[1].  Returns in *which
-// the buffer index holding the result.  iota: values are the indices.
-hipError_t launch_radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0,
-                             uint32_t* vals1, const int32_t* cnt, uint32_t* hist,
-                             uint32_t* digit_tot, int64_t nb_cap, int key_bits, bool iota,
-                             int* which, hipStream_t s) {
-  uint64_t* kb[2] = {keys0, keys1};
-  uint32_t* vb[2] = {vals0, vals1};
-  const int passes = (key_bits + kRadixBits - 1) / kRadixBits;
-  int cur = 0;
-  const bool fused = nb_cap <= kFusedScanBlocks;
-  for (int p = 0; p < passes; ++p) {
-    const int shift = p * kRadixBits;
-    hipLaunchKernelGGL(k_radix_upsweep, dim3((unsigned)nb_cap), dim3(kSortThreads), 0, s,
-                       kb[cur], cnt, hist, nb_cap, shift);
-    if (fused) {
-      hipLaunchKernelGGL(k_radix_downsweep<true>, dim3((unsigned)nb_cap), dim3(kSortThreads), 0, s,
-                         kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], cnt, hist, digit_tot, nb_cap,
-                         shift, (iota && p == 0) ? 1 : 0);
-    } else {
-      hipLaunchKernelGGL(k_radix_scan, dim3(kRadix), dim3(256), 0, s, hist, cnt, digit_tot,
-                         nb_cap);
-      hipLaunchKernelGGL(k_radix_downsweep<false>, dim3((unsigned)nb_cap), dim3(kSortThreads), 0,
-                         s, kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], cnt, hist, digit_tot,
-                         nb_cap, shift, (iota && p == 0) ? 1 : 0);
-    }
-    cur ^= 1;
-  }
-  *which = cur;
-  return hipGetLastError();
-}
-
 hipError_t launch_rb_generate(const Plan& P, void* ws, hipStream_t s);
 hipError_t launch_rb_tile_sort(const Plan& P, void* ws, hipStream_t s);
 hipError_t launch_rb_runs(const Plan& P, void* ws, hipStream_t s);
-
-hipError_t launch_set_i32(int32_t* p, int32_t v, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_i32, dim3(1), dim3(1), 0, s, p, v);
-  return hipGetLastError();
-}
 
 hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s) {
   // per-iteration flags 0..10 and the per-tile pair counters

@@ -201,13 +201,6 @@ inline T* ws_at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
-// Radix sort geometry: 256 threads x 16 keys per block, 8-bit digits.
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int kRadixBits = 8;
-constexpr int kRadix = 1 << kRadixBits;
-
 constexpr int kProjThreads = 128;
 
 // Splat-wise backward: splats per bucket (one per lane) and the floats of a

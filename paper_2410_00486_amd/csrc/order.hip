@@ -10,14 +10,9 @@
 // is deterministic.
 #include <cfloat>
 
-#include "gs_internal.h"
+#include "sort.h"
 
 namespace gs {
-hipError_t launch_radix_sort(uint64_t* keys0, uint64_t* keys1, uint32_t* vals0, uint32_t* vals1,
-                             const int32_t* cnt, uint32_t* hist, uint32_t* digit_tot,
-                             int64_t nb_cap, int key_bits, bool iota, int* which, hipStream_t s);
-hipError_t launch_set_i32(int32_t* p, int32_t v, hipStream_t s);
-
 namespace {
 
 constexpr int kBoxThreads = 256;
@@ -109,20 +104,14 @@ __global__ void __launch_bounds__(256) k_gather_rows(const float* __restrict__ s
 }
 
 struct OrderTmp {
-  size_t k0, k1, v1, part, hist, dtot, cnt, bytes;
+  size_t keys, part, sort, bytes;
 };
 OrderTmp order_layout(int64_t n) {
-  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const int64_t nb = n > kSortTile ? (n + kSortTile - 1) / kSortTile : 1;
   OrderTmp t{};
-  t.k0 = 0;
-  t.k1 = up(t.k0 + (size_t)n * 8 + 8);
-  t.v1 = up(t.k1 + (size_t)n * 8 + 8);
-  t.part = up(t.v1 + (size_t)n * 4 + 4);
-  t.hist = up(t.part + (size_t)kBoxBlocks * 6 * 4);
-  t.dtot = up(t.hist + (size_t)kRadix * nb * 4);
-  t.cnt = up(t.dtot + kRadix * 4);
-  t.bytes = up(t.cnt + 16);
+  t.keys = 0;
+  t.part = sort_align(t.keys + (size_t)n * 8 + 8);
+  t.sort = sort_align(t.part + (size_t)kBoxBlocks * 6 * 4);
+  t.bytes = t.sort + sort_scratch(n).bytes;
   return t;
 }
 
@@ -135,28 +124,16 @@ hipError_t launch_spatial_order(const float* means, int64_t n, int32_t* perm, vo
                                 hipStream_t s) {
   const OrderTmp L = order_layout(n);
   char* b = static_cast<char*>(tmp);
-  uint64_t* k0 = reinterpret_cast<uint64_t*>(b + L.k0);
-  uint64_t* k1 = reinterpret_cast<uint64_t*>(b + L.k1);
-  uint32_t* v1 = reinterpret_cast<uint32_t*>(b + L.v1);
+  uint64_t* keys = reinterpret_cast<uint64_t*>(b + L.keys);
   float* part = reinterpret_cast<float*>(b + L.part);
-  uint32_t* hist = reinterpret_cast<uint32_t*>(b + L.hist);
-  uint32_t* dtot = reinterpret_cast<uint32_t*>(b + L.dtot);
-  int32_t* cnt = reinterpret_cast<int32_t*>(b + L.cnt);
   const int nbox = (int)std::min<int64_t>(kBoxBlocks, (n + kBoxThreads - 1) / kBoxThreads);
   hipLaunchKernelGGL(k_box_part, dim3(nbox), dim3(kBoxThreads), 0, s, means, n, part);
-  // the permutation doubles as the sort's value buffer
-  uint32_t* v0 = reinterpret_cast<uint32_t*>(perm);
+  // the permutation doubles as the sort's values
+  uint32_t* vals = reinterpret_cast<uint32_t*>(perm);
   hipLaunchKernelGGL(k_morton, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, means, n,
-                     part, nbox, k0, v0);
-  hipError_t e = launch_set_i32(cnt, (int32_t)n, s);
-  if (e != hipSuccess) return e;
-  const int64_t nb = std::max<int64_t>(1, (n + kSortTile - 1) / kSortTile);
-  int which = 0;
-  e = launch_radix_sort(k0, k1, v0, v1, cnt, hist, dtot, nb, 3 * kMortonBits, false, &which, s);
-  if (e == hipSuccess && which == 1)
-    e = hipMemcpyAsync(v0, v1, (size_t)n * 4, hipMemcpyDeviceToDevice, s);
-  if (e != hipSuccess) return e;
-  return hipGetLastError();
+                     part, nbox, keys, vals);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_sort_pairs(keys, vals, n, 3 * kMortonBits, b + L.sort, s) : e;
 }
 
 hipError_t launch_gather_rows(const float* src, const int32_t* perm, int64_t n, int width,

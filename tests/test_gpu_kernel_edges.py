@@ -10,7 +10,7 @@ import paper_2410_00486_amd as gsr
 from paper_2410_00486_amd import _lib as L
 from synth import scenes
 
-from gpu_common import (assert_forward_close, assert_grads_close, assert_pose_close, grads_np,
+from gpu_common import (DEV, assert_forward_close, assert_grads_close, assert_pose_close, grads_np,
                         oracle_reference, run_gpu, view_images)
 
 pytestmark = pytest.mark.gpu
@@ -171,3 +171,26 @@ def test_splatwise_backward_pairs_behind_the_stop_get_zero():
     assert it.plan.flags_of(it.ws)[L.F_OVERFLOW] == 0
     grads, _, exclude, _ = oracle_reference(w.scene, [cam], gcs, gds, (8, 8))
     assert_grads_close(grads_np(it), grads, exclude)
+
+
+# ------------------------------------------------------------------------ sort
+
+@pytest.mark.parametrize("n", [2, 255, 2047, 8191, 8192,   # one workgroup
+                               8193, 32768,                # counts summed by the scatter
+                               32769, 524288, 524289])     # scanned, one and two chunks
+@pytest.mark.parametrize("bits", [5, 24, 46])              # one, three and six passes
+def test_sort_sizes_and_passes(n, bits):
+    """Equal keys keep their order; every number of passes ends in the
+    caller's arrays; the sort covers whole bytes of the key and no more."""
+    print(f"sort n {n} bits {bits}", flush=True)
+    rng = np.random.default_rng(n + bits)
+    keys = rng.integers(0, 1 << 62, n, dtype=np.int64)
+    keys[::3] = keys[0]
+    vals = np.arange(n, dtype=np.int32)
+    kt, vt = torch.from_numpy(keys).to(DEV), torch.from_numpy(vals).to(DEV)
+    gsr.sort_pairs(kt, vt, bits)
+    torch.cuda.synchronize()
+    low = keys & ((1 << ((bits + 7) // 8 * 8)) - 1)
+    order = np.argsort(low, kind="stable")
+    np.testing.assert_array_equal(kt.cpu().numpy(), keys[order])
+    np.testing.assert_array_equal(vt.cpu().numpy(), vals[order])
