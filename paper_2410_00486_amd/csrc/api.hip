@@ -57,8 +57,8 @@ hipError_t launch_gather_views(const Plan& P, const gs_view_gather& g, float* ca
 size_t spatial_order_tmp_bytes(int64_t n);
 hipError_t launch_spatial_order(const float* means, int64_t n, int32_t* perm, void* tmp,
                                 hipStream_t s);
-hipError_t launch_gather_rows(const float* src, const int32_t* perm, int64_t n, int width,
-                              float* dst, hipStream_t s);
+hipError_t launch_permute(const gs_gaussians& src, const int32_t* perm,
+                          const gs_gaussian_grads& dst, hipStream_t s);
 hipError_t launch_pose_retract(const float* cams_in, const float* xi, float* cams_out,
                                int n_views, hipStream_t s);
 hipError_t launch_pose_vjp(const float* xi, const float* g_delta, float* g_xi, int n_views,
@@ -502,14 +502,8 @@ gs_status gs_permute_gaussians(const gs_gaussians* src, const int32_t* perm,
   if (!src->means || !src->log_scales || !src->quats || !src->opacity_logits || !src->sh ||
       !dst->means || !dst->log_scales || !dst->quats || !dst->opacity_logits || !dst->sh)
     return fail(GS_ERR_INVALID_ARG, "null parameter pointer");
-  const int K3 = 3 * (src->sh_degree + 1) * (src->sh_degree + 1);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = launch_gather_rows(src->means, perm, src->n, 3, dst->means, s);
-  if (e == hipSuccess) e = launch_gather_rows(src->log_scales, perm, src->n, 3, dst->log_scales, s);
-  if (e == hipSuccess) e = launch_gather_rows(src->quats, perm, src->n, 4, dst->quats, s);
-  if (e == hipSuccess) e = launch_gather_rows(src->opacity_logits, perm, src->n, 1, dst->opacity_logits, s);
-  if (e == hipSuccess) e = launch_gather_rows(src->sh, perm, src->n, K3, dst->sh, s);
-  return hip_check(e, "gs_permute_gaussians");
+  return hip_check(launch_permute(*src, perm, *dst, static_cast<hipStream_t>(stream)),
+                   "gs_permute_gaussians");
 }
 
 gs_status gs_pose_retract(const float* cams_in, const float* xi, float* cams_out,

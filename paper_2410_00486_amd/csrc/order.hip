@@ -10,6 +10,7 @@
 // is deterministic.
 #include <cfloat>
 
+#include "rowcopy.h"
 #include "sort.h"
 
 namespace gs {
@@ -65,14 +66,26 @@ __global__ void __launch_bounds__(256) k_morton(const float* __restrict__ means,
                                                 const float* __restrict__ part, int n_part,
                                                 uint64_t* __restrict__ keys,
                                                 uint32_t* __restrict__ vals) {
-  __shared__ float box[6];
-  if (threadIdx.x < 6) {
-    float v = threadIdx.x < 3 ? FLT_MAX : -FLT_MAX;
-    for (int b = 0; b < n_part; ++b) {
-      const float x = part[b * 6 + threadIdx.x];
-      v = threadIdx.x < 3 ? fminf(v, x) : fmaxf(v, x);
+  // the box: thread t takes partial t (at most one each), then wave
+  // butterflies and the four wavefronts' results
+  static_assert(kBoxBlocks <= 256, "one partial per thread");
+  __shared__ float wbox[256 / kWave][6], box[6];
+  const int t = (int)threadIdx.x;
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    float v = t < n_part ? part[t * 6 + d] : (d < 3 ? FLT_MAX : -FLT_MAX);
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const float x = __shfl_xor(v, o, kWave);
+      v = d < 3 ? fminf(v, x) : fmaxf(v, x);
     }
-    box[threadIdx.x] = v;
+    if (lane_id() == 0) wbox[t / kWave][d] = v;
+  }
+  __syncthreads();
+  if (t < 6) {
+    float v = wbox[0][t];
+    for (int k = 1; k < 256 / kWave; ++k) v = t < 3 ? fminf(v, wbox[k][t]) : fmaxf(v, wbox[k][t]);
+    box[t] = v;
   }
   __syncthreads();
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -90,17 +103,29 @@ __global__ void __launch_bounds__(256) k_morton(const float* __restrict__ means,
   vals[i] = (uint32_t)i;
 }
 
-// dst[j] = src[perm[j]] for rows of `width` floats.
-__global__ void __launch_bounds__(256) k_gather_rows(const float* __restrict__ src,
-                                                     const int32_t* __restrict__ perm,
-                                                     int64_t n, int width,
-                                                     float* __restrict__ dst) {
-  const int64_t total = n * width;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = e / width, c = e - j * width;
-    dst[e] = src[(int64_t)perm[j] * width + c];
-  }
+// Row j of every array of dst = row perm[j] of src.  A workgroup takes 128
+// rows of all five arrays: one launch for a set, the order read once.  Bound
+// by HBM; one launch per array, with a 64-bit division per element, took
+// 92 us for 300k Gaussians of degree 3 (146 MB, and as much again because a
+// random row of 4 to 16 bytes costs a whole cache line), now 47 us.  Rows per
+// workgroup (32 to 256) and loads in flight (2 to 8) change nothing.
+constexpr int kPermRows = 128;
+
+template <int K3>
+__global__ void __launch_bounds__(kCopyThreads) k_permute(gs_gaussians src,
+                                                          const int32_t* __restrict__ perm,
+                                                          gs_gaussian_grads dst) {
+  __shared__ int32_t from[kPermRows];
+  const int64_t j0 = (int64_t)blockIdx.x * kPermRows;
+  const int nrow = (int)min((int64_t)kPermRows, src.n - j0);
+  if ((int)threadIdx.x < nrow) from[threadIdx.x] = perm[j0 + threadIdx.x];
+  __syncthreads();
+  const auto row = [&](int r) -> int64_t { return from[r]; };
+  copy_rows<K3>(src.sh, dst.sh + j0 * K3, nrow, row);
+  copy_rows<4>(src.quats, dst.quats + j0 * 4, nrow, row);
+  copy_rows<3>(src.means, dst.means + j0 * 3, nrow, row);
+  copy_rows<3>(src.log_scales, dst.log_scales + j0 * 3, nrow, row);
+  copy_rows<1>(src.opacity_logits, dst.opacity_logits + j0, nrow, row);
 }
 
 struct OrderTmp {
@@ -136,12 +161,15 @@ hipError_t launch_spatial_order(const float* means, int64_t n, int32_t* perm, vo
   return e == hipSuccess ? launch_sort_pairs(keys, vals, n, 3 * kMortonBits, b + L.sort, s) : e;
 }
 
-hipError_t launch_gather_rows(const float* src, const int32_t* perm, int64_t n, int width,
-                              float* dst, hipStream_t s) {
-  const int64_t total = n * width;
-  const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_rows, dim3(blocks), dim3(256), 0, s, src, perm, n, width, dst);
+hipError_t launch_permute(const gs_gaussians& src, const int32_t* perm,
+                          const gs_gaussian_grads& dst, hipStream_t s) {
+  if (src.n == 0) return hipSuccess;
+  const dim3 grid((unsigned)((src.n + kPermRows - 1) / kPermRows));
+  const auto kernel = src.sh_degree == 0   ? k_permute<3>
+                      : src.sh_degree == 1 ? k_permute<12>
+                      : src.sh_degree == 2 ? k_permute<27>
+                                           : k_permute<48>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kCopyThreads), 0, s, src, perm, dst);
   return hipGetLastError();
 }
 

@@ -1,12 +1,15 @@
 """Kernel variants at the sizes where they could go wrong (edges of work
 items, of batches and of buckets), against the FP64 oracle or another form of
 the same path."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2410_00486_amd as gsr
+from oracle import densify as oracle_densify
 from paper_2410_00486_amd import _lib as L
 from synth import scenes
 
@@ -173,7 +176,7 @@ def test_splatwise_backward_pairs_behind_the_stop_get_zero():
     assert_grads_close(grads_np(it), grads, exclude)
 
 
-# ------------------------------------------------------------------------ sort
+# ------------------------------------------------------- sort, rows of the pool
 
 @pytest.mark.parametrize("n", [2, 255, 2047, 8191, 8192,   # one workgroup
                                8193, 32768,                # counts summed by the scatter
@@ -194,3 +197,86 @@ def test_sort_sizes_and_passes(n, bits):
     order = np.argsort(low, kind="stable")
     np.testing.assert_array_equal(kt.cpu().numpy(), keys[order])
     np.testing.assert_array_equal(vt.cpu().numpy(), vals[order])
+
+
+def _pool(rng, n, deg, shift):
+    """Parameters and moments on the device; with shift, arrays that begin 4
+    bytes after a 16-byte boundary."""
+    k = (deg + 1) ** 2
+    shapes = [(n, 3), (n, 3), (n, 4), (n,), (n, k, 3)]
+    host = [rng.normal(size=s).astype(np.float32) for s in shapes]
+    dev = []
+    for h in host:
+        buf = torch.empty(h.size + 8, dtype=torch.float32, device=DEV)
+        t = buf[1:1 + h.size] if shift else buf[:h.size]
+        dev.append(t.view(h.shape).copy_(torch.from_numpy(h)))
+    return dict(zip(gsr.Gaussians.FIELDS, host)), gsr.Gaussians(*dev, deg)
+
+
+@pytest.mark.parametrize("n,deg,shift", [(1, 0, False), (127, 1, False), (128, 2, True),
+                                         (129, 3, False), (257, 3, True), (300, 1, True)])
+def test_permute_rows(n, deg, shift):
+    print(f"permute n {n} degree {deg} shift {shift}", flush=True)
+    rng = np.random.default_rng(n)
+    host, g = _pool(rng, n, deg, shift)
+    perm = rng.permutation(n).astype(np.int32)
+    out = gsr.permute(g, torch.from_numpy(perm).to(DEV))
+    torch.cuda.synchronize()
+    for f in gsr.Gaussians.FIELDS:
+        np.testing.assert_array_equal(getattr(out, f).cpu().numpy(), host[f][perm])
+
+
+@pytest.mark.parametrize("n,deg,shift,roles", [
+    (1, 0, False, "s"), (255, 1, False, "kcs-"), (256, 3, False, "c"), (257, 3, True, "s"),
+    (2048, 2, False, "kcs-"), (2049, 0, True, "-"), (2305, 3, False, "cs--k"),
+])
+def test_densify_rows_and_capacity(n, deg, shift, roles):
+    """Rows of kept (k), cloned (c), split (s) and pruned (-) Gaussians, with
+    room for all outputs and with one row too few: then the prefix that fits
+    is the same, whole Gaussians only, and nothing behind it is written."""
+    print(f"densify n {n} degree {deg} shift {shift} {roles}", flush=True)
+    rng = np.random.default_rng(n + deg)
+    role = np.array([roles[i % len(roles)] for i in range(n)])
+    (P, g), (M, m), (V, v) = (_pool(rng, n, deg, shift) for _ in range(3))
+    P["opacity_logits"][:] = np.where(role == "-", -6.0, 1.0)
+    P["log_scales"][:] = np.where(role == "s", -2.0, -6.0)[:, None]
+    for f in ("opacity_logits", "log_scales"):
+        getattr(g, f).copy_(torch.from_numpy(P[f]))
+    denom = np.ones(n, np.float32)
+    accum = np.where((role == "c") | (role == "s"), 0.01, 0.0).astype(np.float32)
+    normals = rng.standard_normal((n, 2, 3)).astype(np.float32)
+    dev = lambda x: torch.from_numpy(x).to(DEV)
+    a_t, d_t, n_t = dev(accum), dev(denom), dev(normals.reshape(-1))
+    ref = oracle_densify.densify_prune(P, M, V, accum, denom, normals, 0.001, 0.02, 0.01, 1.0)
+    total = ref[0]["means"].shape[0]
+    count = np.select([role == "-", role == "k"], [0, 1], 2)
+    mark = 12345.0
+    for cap in (total, total - 1):
+        if cap < 0:
+            continue
+        ends = np.cumsum(count)
+        fits = int(ends[ends <= cap].max(initial=0))
+        outs = [_pool(rng, total + 1, deg, shift)[1] for _ in range(3)]
+        for o in outs:
+            for x in o.tensors():
+                x.fill_(mark)
+        n_out = torch.zeros(1, dtype=torch.int32, device=DEV)
+        tmp = torch.empty(max(int(L.lib().gs_densify_tmp_bytes(n)), 256), dtype=torch.uint8,
+                          device=DEV)
+        c = [g.c(), m.grads_c(), v.grads_c()] + [o.grads_c() for o in outs]
+        r = [ctypes.byref(x) for x in c]
+        L.check(L.lib().gs_densify_prune(*r[:3], a_t.data_ptr(), d_t.data_ptr(), n_t.data_ptr(),
+                                         0.001, 0.02, 0.01, 1.0, *r[3:], cap, n_out.data_ptr(),
+                                         tmp.data_ptr(),
+                                         torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert int(n_out.item()) == total
+        for k, o in enumerate(outs):
+            for f in gsr.Gaussians.FIELDS:
+                x = getattr(o, f).cpu().numpy()
+                want = ref[k][f].reshape((total,) + x.shape[1:])[:fits]
+                if k == 0 and f in ("means", "log_scales"):
+                    np.testing.assert_allclose(x[:fits], want, rtol=2e-7, atol=1e-7)
+                else:
+                    np.testing.assert_array_equal(x[:fits], want)
+                assert (x[fits:] == mark).all()
