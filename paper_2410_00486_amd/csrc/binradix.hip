@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(256) k_rb_visible(
     const uint32_t* __restrict__ tt, uint32_t* __restrict__ poff,
     const uint2* __restrict__ chunk_pre, int64_t chunks_per_view, int64_t n_chunks,
     const Rec* __restrict__ rec, const uint2* __restrict__ rect, int64_t n,
-    const int32_t* __restrict__ fl, uint32_t* __restrict__ vis_list,
+    int32_t* __restrict__ fl, HeavyList heavy, uint32_t* __restrict__ vis_list,
     uint32_t* __restrict__ vis_clamp, uint32_t* __restrict__ dkey, uint4* __restrict__ pay,
     uint32_t* __restrict__ zrec) {
   const int w = threadIdx.x / kWave, lane = lane_id();
@@ -120,6 +120,7 @@ __global__ void __launch_bounds__(256) k_rb_visible(
     const uint32_t vp = cp.y + (uint32_t)__popcll(vmask & lanemask_lt());
     vis_list[vp] = (uint32_t)ri;
     vis_clamp[vp] = cbits;
+    note_heavy(heavy, fl, c, (uint32_t)ri);
     dkey[vp] = __float_as_uint(z);
     zrec[ri] = __float_as_uint(z);
     const uint2 b = rect[ri];
@@ -648,7 +649,8 @@ hipError_t launch_rb_generate(const Plan& P, void* ws, hipStream_t s) {
   if (P.n_chunks <= 0 || P.rb_rec_blocks <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_rb_visible, dim3((unsigned)((P.n_chunks + 3) / 4)), dim3(256), 0, s, B.tt,
                      B.poff, ws_at<uint2>(ws, P.off_chunk_pre), P.chunks_per_view, P.n_chunks,
-                     ws_at<Rec>(ws, P.off_rec), ws_at<uint2>(ws, P.off_rect), P.n, B.fl, B.vis,
+                     ws_at<Rec>(ws, P.off_rec), ws_at<uint2>(ws, P.off_rect), P.n,
+                     ws_at<int32_t>(ws, P.off_flags), heavy_list(P, ws), B.vis,
                      ws_at<uint32_t>(ws, P.off_vis_clamp), B.dk[0], B.pay,
                      ws_at<uint32_t>(ws, P.off_rb_zrec));
   // depth bits in four 8-bit passes; values: visible-list positions (the

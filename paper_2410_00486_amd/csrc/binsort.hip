@@ -314,6 +314,7 @@ __device__ __forceinline__ void scan_finish(const ScanArgs& A, const uint64_t (&
   fl[F_VISIBLE] = (int32_t)c32[1];
   fl[F_NONFINITE] = fl[F_NF_ACC];  // counted by the projection
   fl[F_NF_ACC] = 0;
+  fl[F_HEAVY] = 0;  // counted by the kernel that lists the visible records
   if (!chunks_only) {
     // the bucket queue is filled by the tile sort at the positions scanned
     // here; the long lists are sorted by their own kernel (none on overflow)
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(256) k_scatter(
     const uint32_t* __restrict__ tt, uint32_t* __restrict__ poff,
     const uint2* __restrict__ chunk_pre, int64_t chunks_per_view, int64_t n_chunks,
     const ushort4* __restrict__ rect, const Rec* __restrict__ rec, int64_t n, ViewTable vt,
-    const int32_t* __restrict__ fl, const uint32_t* __restrict__ tstart,
+    int32_t* __restrict__ fl, HeavyList heavy, const uint32_t* __restrict__ tstart,
     uint32_t* __restrict__ cursor, uint64_t* __restrict__ skey, uint32_t* __restrict__ pair_rec,
     uint32_t* __restrict__ vis_list, uint32_t* __restrict__ vis_clamp) {
   constexpr int NW = 256 / kWave;
@@ -477,6 +478,7 @@ __global__ void __launch_bounds__(256) k_scatter(
     const uint32_t vp = cp.y + (uint32_t)__popcll(vmask & lanemask_lt());
     vis_list[vp] = (uint32_t)ri;
     vis_clamp[vp] = cbits;
+    note_heavy(heavy, fl, c, (uint32_t)ri);
     x0y0 = (uint32_t)r.x | ((uint32_t)r.y << 16);
     tile0 = (uint32_t)(r.z - r.x);  // box width in tiles
   }
@@ -672,7 +674,7 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
     const int64_t blocks = (P.n_chunks + 3) / 4;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(256), 0, s, tt, poff, chunk_pre,
                        P.chunks_per_view, P.n_chunks, ws_at<ushort4>(ws, P.off_rect),
-                       ws_at<Rec>(ws, P.off_rec), P.n, P.vt, fl, tstart, tcnt, skey, pair_rec,
+                       ws_at<Rec>(ws, P.off_rec), P.n, P.vt, fl, heavy_list(P, ws), tstart, tcnt, skey, pair_rec,
                        ws_at<uint32_t>(ws, P.off_vis_list), ws_at<uint32_t>(ws, P.off_vis_clamp));
   }
   if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;

@@ -25,6 +25,7 @@ enum Flag : int {
   F_PAIRS_WANTED = 6,
   F_LONG_TILES = 7,  // tiles whose lists go to the long-list sort
   F_BUCKETS = 8,     // entries of the splat-wise bucket queue
+  F_HEAVY = 9,       // records with more than kHeavyPairs pairs (several views)
   F_NF_ACC = 10,     // non-finite Gaussians counted by the projection, published
                      // in F_NONFINITE (and cleared) by the binning scan
   F_CLASS = 11,      // tiles of each length class of the work order but the last
@@ -109,6 +110,20 @@ struct RecSrc {
 // rgb(3), depth, opacity, conic a b c, mean x y: ten floats, 40 bytes, so
 // slots are 8-byte aligned and move as five float2.
 constexpr int kPairGrad = 10;
+// Records of a several-view plan with more pairs than this are listed by the
+// binning and summed by a wavefront each (k_project_heavy).
+constexpr uint32_t kHeavyPairs = 32;
+struct HeavyList {
+  uint32_t* recs;  // null in plans of one view
+  uint32_t cap;
+};
+__device__ __forceinline__ void note_heavy(const HeavyList& h, int32_t* fl, uint32_t pairs,
+                                           uint32_t ri) {
+  if (pairs <= kHeavyPairs || !h.recs) return;
+  const uint32_t at = (uint32_t)atomicAdd(&fl[F_HEAVY], 1);
+  if (at < h.cap) h.recs[at] = ri;
+}
+
 struct PairSlot {
   float4 a, b;  // rgb, depth | opacity, conic a b c
   float2 c;     // mean x y
@@ -164,6 +179,8 @@ struct Plan {
   size_t off_chunk_cnt, off_chunk_pre;  // per chunk: (pairs, visible) counts and offsets
   size_t off_vis_list;                  // visible records in index order
   size_t off_vis_clamp;                 // their colour clamp bits, same order
+  size_t off_heavy;                     // several views: records of many pairs
+  uint32_t heavy_cap, pad2;
   size_t off_tile_cnt, off_tile_start, off_long;
   size_t off_keys, off_scatter, off_vals, off_pair_rec, off_sorted_rec, off_srec;
   size_t off_ranges, off_tile_last, off_tile_loss;
@@ -199,6 +216,10 @@ inline Plan* plan_of(gs_plan* p) { return reinterpret_cast<Plan*>(p->opaque); }
 template <typename T>
 inline T* ws_at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
+}
+
+inline HeavyList heavy_list(const Plan& P, void* ws) {
+  return HeavyList{P.heavy_cap ? ws_at<uint32_t>(ws, P.off_heavy) : nullptr, P.heavy_cap};
 }
 
 constexpr int kProjThreads = 128;

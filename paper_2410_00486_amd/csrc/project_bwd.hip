@@ -508,8 +508,9 @@ __global__ void __launch_bounds__((SPLIT && COMPACT) ? kSumWaves * kWave : kProj
   else run(F{}, T{});
 }
 
-// Several views, no camera tangent: two launches, each on full wavefronts
+// Several views, no camera tangent: launches that each run on full wavefronts
 // whatever the visibility pattern.
+//   k_project_heavy: the pair sums of the records with many pairs.
 //   k_project_rec: one thread per visible (view, Gaussian) record (the
 //     visible list): the record's pair partials summed in pair order, then
 //     that view's projection chain; the record's terms (mean and covariance
@@ -518,17 +519,56 @@ __global__ void __launch_bounds__((SPLIT && COMPACT) ? kSumWaves * kWave : kProj
 //   k_project_gauss: one thread per Gaussian: its records' terms added in
 //     view order, the colour chain of each view (SH coefficients held in
 //     registers), then the covariance -> scale / rotation chain.
-// The operations and their order are those of one thread looping over the
-// views (projection sums, colour sums, then their total), so the gradients
-// do not depend on how the records are spread over threads.
+// The operations and their order depend on the record's own pairs alone, so
+// the gradients do not depend on how the records are spread over threads.
 constexpr int kTermWords = 14;  // doubles per record slot (112 bytes)
 constexpr int kRecThreads = 256;
 constexpr int kGaussThreads = 128;
 
-template <int DEG>
+// A wavefront per listed record: lane 10 s + c adds component c of the slots
+// s, s + 6, s + 12, ... and the six sums are added in order; they wait in the
+// record's slot for k_project_rec.  Bound by the latency of a few round trips.
+// One thread's walk over 858 pairs was most of k_project_rec on a batch with
+// close-ups (eight views, 500k Gaussians, median 4 pairs a record): 295 us,
+// now 121 and 21 here; 16 views of 2M Gaussians 641 us, now 526 and 25; four
+// 640x480 views 49 us, now 21 and 5.  The line at 32 pairs: at 16 the last
+// two are 516 + 89 and 19 + 11, at 64 538 + 12 and 25 + 5, at 128 550 + 12
+// and 30 + 5.
+constexpr int kHeavyStrips = kWave / kPairGrad;
+constexpr int kHeavyBlocks = 512;
+
+__global__ void __launch_bounds__(kRecThreads) k_project_heavy(
+    const uint32_t* __restrict__ tt, const uint32_t* __restrict__ poff,
+    const float* __restrict__ grad_pair, const int32_t* __restrict__ fl,
+    const uint32_t* __restrict__ heavy, uint32_t cap, double* __restrict__ terms) {
+  const uint32_t m = min((uint32_t)fl[F_HEAVY], cap);
+  const int lane = lane_id(), s = lane / kPairGrad, c = lane - s * kPairGrad;
+  for (uint32_t h = blockIdx.x * (kRecThreads / kWave) + threadIdx.x / kWave; h < m;
+       h += gridDim.x * (kRecThreads / kWave)) {
+    const uint32_t ri = heavy[h];
+    const uint32_t np = s < kHeavyStrips ? tt[ri] : 0u;
+    const float* x = grad_pair + (int64_t)poff[ri] * kPairGrad + c;
+    double sum = 0.0;
+    constexpr int U = 8;
+    uint32_t q = (uint32_t)s;
+    for (; q + (U - 1) * kHeavyStrips < np; q += U * kHeavyStrips) {
+      float y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) y[u] = x[(int64_t)(q + u * kHeavyStrips) * kPairGrad];
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += y[u];
+    }
+    for (; q < np; q += kHeavyStrips) sum += x[(int64_t)q * kPairGrad];
+    double total = sum;
+#pragma unroll
+    for (int k = 1; k < kHeavyStrips; ++k) total += __shfl(sum, lane + k * kPairGrad, kWave);
+    if (s == 0) terms[(int64_t)ri * kTermWords + c] = total;
+  }
+}
+
 __global__ void __launch_bounds__(kRecThreads) k_project_rec(
     const float* __restrict__ means, const float* __restrict__ log_scales,
-    const float* __restrict__ quats, int64_t n, const float* __restrict__ cams, ViewTable vt,
+    const float* __restrict__ quats, uint32_t n, const float* __restrict__ cams, ViewTable vt,
     const uint32_t* __restrict__ tt, const uint32_t* __restrict__ poff,
     const float* __restrict__ grad_pair, const int32_t* __restrict__ fl,
     const uint32_t* __restrict__ vis_list, const uint32_t* __restrict__ vis_clamp,
@@ -537,10 +577,12 @@ __global__ void __launch_bounds__(kRecThreads) k_project_rec(
   const int64_t nv = fl[F_OVERFLOW] ? 0 : (int64_t)fl[F_VISIBLE];
   if (j >= nv) return;
   const uint32_t ri = vis_list[j];
-  const int v = (int)(ri / (uint64_t)n);
-  const int64_t i = (int64_t)ri - (int64_t)v * n;
-  const uint32_t np = tt[ri];
+  const uint32_t v = ri / n;
+  const int64_t i = ri - v * n;
+  const bool heavy = tt[ri] > kHeavyPairs;
+  const uint32_t np = heavy ? 0u : tt[ri];
   const float* gp = grad_pair + (int64_t)poff[ri] * kPairGrad;
+  double2* dst = reinterpret_cast<double2*>(terms + (int64_t)ri * kTermWords);
   // fixed-order sums of the pair partials: colour 0..2, projection 3..9
   double g2[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   auto add = [&](const PairSlot& p) {
@@ -557,6 +599,14 @@ __global__ void __launch_bounds__(kRecThreads) k_project_rec(
     for (int u = 0; u < 4; ++u) add(a[u]);
   }
   for (; q < np; ++q) add(load_pair(gp, q));
+  if (heavy) {
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+      const double2 x = dst[e];
+      g2[2 * e] = x.x;
+      g2[2 * e + 1] = x.y;
+    }
+  }
   // world covariance of the Gaussian
   double qv[4] = {quats[4 * i], quats[4 * i + 1], quats[4 * i + 2], quats[4 * i + 3]};
   const double qn = sqrt(qv[0] * qv[0] + qv[1] * qv[1] + qv[2] * qv[2] + qv[3] * qv[3]);
@@ -599,7 +649,6 @@ __global__ void __launch_bounds__(kRecThreads) k_project_rec(
   o[11] = g2[1];
   o[12] = g2[2];
   o[13] = (double)vis_clamp[j];
-  double2* dst = reinterpret_cast<double2*>(terms + (int64_t)ri * kTermWords);
 #pragma unroll
   for (int e = 0; e < kTermWords / 2; ++e) dst[e] = make_double2(o[2 * e], o[2 * e + 1]);
 }
@@ -826,8 +875,14 @@ hipError_t launch_project_bwd(const Plan& P, const gs_gaussians& g, const float*
 // (one statement: the three launches of the several-view form)
 #define GS_PBMV(D)                                                                                \
   do {                                                                                            \
-    hipLaunchKernelGGL((k_project_rec<D>), dim3((unsigned)rec_blocks), dim3(kRecThreads), 0, s,    \
-                       g.means, g.log_scales, g.quats, P.n, cams, P.vt,                           \
+    if (P.heavy_cap > 0)                                                                           \
+      hipLaunchKernelGGL(k_project_heavy, dim3(kHeavyBlocks), dim3(kRecThreads), 0, s,             \
+                         ws_at<uint32_t>(ws, P.off_tt), ws_at<uint32_t>(ws, P.off_poff),           \
+                         ws_at<float>(ws, P.off_grad_pair), ws_at<int32_t>(ws, P.off_flags),       \
+                         ws_at<uint32_t>(ws, P.off_heavy), P.heavy_cap,                            \
+                         ws_at<double>(ws, P.off_rec_terms));                                      \
+    hipLaunchKernelGGL(k_project_rec, dim3((unsigned)rec_blocks), dim3(kRecThreads), 0, s,         \
+                       g.means, g.log_scales, g.quats, (uint32_t)P.n, cams, P.vt,                  \
                        ws_at<uint32_t>(ws, P.off_tt), ws_at<uint32_t>(ws, P.off_poff),             \
                        ws_at<float>(ws, P.off_grad_pair), ws_at<int32_t>(ws, P.off_flags),         \
                        ws_at<uint32_t>(ws, P.off_vis_list), ws_at<uint32_t>(ws, P.off_vis_clamp),  \

@@ -280,3 +280,31 @@ def test_densify_rows_and_capacity(n, deg, shift, roles):
                 else:
                     np.testing.assert_array_equal(x[:fits], want)
                 assert (x[fits:] == mark).all()
+
+
+# ------------------------------------------------- projection backward, many pairs
+
+@pytest.mark.parametrize("flags", [0, L.GS_RADIX_BIN])
+def test_projection_backward_records_of_many_pairs(flags):
+    """Several views whose records reach few to many tiles: on both sides of
+    the length from which a wavefront sums a record, and more than one
+    wavefront's step long; then fewer such records on the same workspace."""
+    w = scenes.tiny_scene(17, n=40, width=64, height=32, f=30.0, degree=2)
+    w.scene.log_scales[:24] = -0.2
+    w.scene.opacity_logits[:] = -2.5
+    eye, zero = np.eye(3, dtype=np.float32), np.zeros(3, np.float32)
+    cams = [scenes.Camera(wd, ht, f, f, wd / 2, ht / 2, eye, zero)
+            for wd, ht, f in ((248, 8, 60.0), (64, 32, 30.0), (88, 24, 40.0), (203, 117, 90.0))]
+    gcs, gds = scenes.linear_loss_weights(23, cams)
+    print(f"records of many pairs, flags {flags}", flush=True)
+    it = run_gpu(w.scene, cams, tile=(8, 8), flags=flags, dL_dcolor=gcs, dL_ddepth=gds)
+    tt = it.plan.region(it.ws, L.GS_WS_TILES_TOUCHED, torch.int32, len(cams) * 40).cpu().numpy()
+    assert {32, 33} <= set(tt.tolist()) and tt.max() > 100
+    grads, _, exclude, _ = oracle_reference(w.scene, cams, gcs, gds, (8, 8))
+    assert_grads_close(grads_np(it), grads, exclude)
+    w.scene.log_scales[12:24] = -3.0
+    it.g.log_scales.copy_(torch.from_numpy(w.scene.log_scales))
+    it.enqueue()
+    torch.cuda.synchronize()
+    grads, _, exclude, _ = oracle_reference(w.scene, cams, gcs, gds, (8, 8))
+    assert_grads_close(grads_np(it), grads, exclude)
