@@ -76,23 +76,26 @@ constexpr double kLn2 = 0.6931471805599453;    // ln(2), its inverse
 // Base-2 exponent of record r at offset (dx, dy) = mean - sample point (the
 // FP64 difference rounded to FP32): the splat's opacity times its Gaussian
 // is 2^that.  Never above lo <= 0.
-__device__ __forceinline__ float exponent(float t, float s1, float s2, float lo, float dx,
-                                          float dy) {
-  const float p = fmaf(t, dy, dx), q = fmaf(-t, dx, dy);
+__device__ __forceinline__ float exponent_pq(float s1, float s2, float lo, float p, float q) {
   const float u = s1 * p, w = s2 * q;
   return fmaf(-u, p, fmaf(-w, q, lo));
+}
+__device__ __forceinline__ float exponent(float t, float s1, float s2, float lo, float dx,
+                                          float dy) {
+  return exponent_pq(s1, s2, lo, fmaf(t, dy, dx), fmaf(-t, dx, dy));
 }
 __device__ __forceinline__ float rec_exponent(const Rec& r, float dx, float dy) {
   return exponent(r.t, r.s1, r.s2, r.lo, dx, dy);
 }
 
-// The conic [[a, b], [b, c]] of record r (natural exponent -d^T Q d / 2),
-// for the mean gradient.
-__device__ __forceinline__ void rec_conic(const Rec& r, float& a, float& b, float& c) {
-  const float sc = (float)(2.0 * kLn2), tt = r.t * r.t;  // 1 / (log2(e) / 2)
-  a = sc * fmaf(r.s2, tt, r.s1);
-  b = sc * (r.t * (r.s1 - r.s2));
-  c = sc * fmaf(r.s1, tt, r.s2);
+// Gradient of the mean of a record (its splat's log2 exponent falls by
+// s1 p^2 + s2 q^2, p = dx + t dy, q = dy - t dx) from the sums over the pixels
+// of gpow p and gpow q, gpow = dL/d(natural exponent).  Sums along the
+// footprint's own axes: formed from sums of gpow dx and gpow dy, the thin
+// axis' part would be a small difference of large rounded numbers.
+__device__ __forceinline__ float2 mean_grad(double t, double s1, double s2, double sp, double sq) {
+  const double u = s1 * sp, w = s2 * sq;
+  return make_float2((float)(-2.0 * kLn2 * (u - t * w)), (float)(-2.0 * kLn2 * (t * u + w)));
 }
 
 // Where the raster kernels read the records of the tile lists: a copy in

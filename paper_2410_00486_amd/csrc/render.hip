@@ -668,14 +668,15 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
     // reductions, only T and B run through them in order
     auto step = [&](auto n_c, const int* j) {
       constexpr int N = decltype(n_c)::value;
-      float dx[N], dy[N], oG[N], a[N], front[N];
+      float p_ax[N], q_ax[N], oG[N], a[N], front[N];
       bool hit[N];
 #pragma unroll
       for (int k = 0; k < N; ++k) {
-        dx[k] = S.dx[kSub * sx + col][j[k]];
-        dy[k] = S.dy[kSub * sy + row][j[k]];
+        const float dx = S.dx[kSub * sx + col][j[k]], dy = S.dy[kSub * sy + row][j[k]];
         const float4 sh = S.shape[j[k]], cl = S.colour[j[k]];
-        oG[k] = __builtin_amdgcn_exp2f(exponent(sh.x, sh.y, sh.z, sh.w, dx[k], dy[k]));
+        p_ax[k] = fmaf(sh.x, dy, dx);
+        q_ax[k] = fmaf(-sh.x, dx, dy);
+        oG[k] = __builtin_amdgcn_exp2f(exponent_pq(sh.y, sh.z, sh.w, p_ax[k], q_ax[k]));
         front[k] = fmaf(g.w, cl.w, fmaf(g.z, cl.z, fmaf(g.y, cl.y, g.x * cl.x)));
         a[k] = fminf(kAlphaMax, oG[k]);
         hit[k] = (a[k] >= kAlphaMin) & ((uint32_t)(bstart + j[k]) < L);
@@ -692,12 +693,12 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
         const float g_alpha = fmaf(T, front[k], -(B * inv_om));
         B = fmaf(front[k], wgt, B);
         // unclamped alpha only (no gradient through the 0.99 clamp); the
-        // conic and mean partials are moments of gpow = alpha dL/dalpha,
-        // their signs and factors applied after the sums
+        // conic and mean partials are moments of gpow = alpha dL/dalpha along
+        // the footprint's axes, put together after the sums
         const float gpow = oG[k] <= kAlphaMax ? a[k] * g_alpha : 0.0f;
-        const float t = gpow * dx[k], u = gpow * dy[k];
+        const float t = gpow * p_ax[k], u = gpow * q_ax[k];
         const float p[10] = {wgt * g.x, wgt * g.y, wgt * g.z, wgt * g.w, gpow,
-                             t * dx[k], t * dy[k], u * dy[k], t,         u};
+                             t * p_ax[k], t * q_ax[k], u * q_ax[k], t, u};
         z[k] = reduce_scatter10(p);
       }
       if (my_idx >= 0) {
@@ -728,18 +729,17 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
 #pragma unroll
           for (int k = 0; k < 10; ++k) f[k] += S.part[b][q][k];
         }
-      Rec c;
       const float4 sh = S.shape[q];
-      c.t = sh.x;
-      c.s1 = sh.y;
-      c.s2 = sh.z;
-      float ca, cb, cc;
-      rec_conic(c, ca, cb, cc);
+      const double t = sh.x, n2 = (1.0 + t * t) * (1.0 + t * t);
+      const double pp = f[5], pq = f[6], qq = f[7];  // dx = (p - t q) / (1 + t^2), dy = (q + t p) / ..
       const float o = S.o[q];
       store_pair(A.grad_pair, A.sorted_vals[s + (uint32_t)(bstart + q)],
                  make_float4(f[0], f[1], f[2], f[3]),
-                 make_float4(o > 0.0f ? f[4] / o : 0.0f, -0.5f * f[5], -f[6], -0.5f * f[7]),
-                 make_float2(-(ca * f[8] + cb * f[9]), -(cb * f[8] + cc * f[9])));
+                 make_float4(o > 0.0f ? f[4] / o : 0.0f,
+                             (float)(-0.5 * (pp - 2.0 * t * pq + t * t * qq) / n2),
+                             (float)(-((1.0 - t * t) * pq + t * (pp - qq)) / n2),
+                             (float)(-0.5 * (qq + 2.0 * t * pq + t * t * pp) / n2)),
+                 mean_grad(t, sh.y, sh.z, f[8], f[9]));
     }
     __syncthreads();
   }
@@ -880,7 +880,7 @@ __device__ __forceinline__ void splat_rows(const LaneSplat& r, const SplatLds& S
     const float dy = (float)(r.my - ((double)(ty0 + row) + 0.5));
     const float4* sx = S.x + row * kSub;
     const float4* sg = S.g + row * kSub;
-    // moments over the row of gpow = dL/dpower: 1, dx, dx^2
+    // moments over the row of gpow = dL/dpower: 1, p, p^2, p = dx + t dy
     float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f;
     // two pixels per step, their scans interleaved; each lane accumulates
     // the left one first
@@ -888,14 +888,16 @@ __device__ __forceinline__ void splat_rows(const LaneSplat& r, const SplatLds& S
     for (int p = 0; p < kSub; p += 2) {
       if (((m >> p) & 3ull) == 0) continue;  // (uniform)
       float4 x[2], g[2];
-      float oG[2], a[2], inv_om[2], f[2];
+      float p_ax[2], oG[2], a[2], inv_om[2], f[2];
       bool hit[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         x[u] = sx[p + u];
         g[u] = sg[p + u];
         // alpha as in the forward (same bits)
-        oG[u] = __builtin_amdgcn_exp2f(exponent(r.t, r.s1, r.s2, r.lo, r.dx[p + u], dy));
+        p_ax[u] = fmaf(r.t, dy, r.dx[p + u]);
+        oG[u] = __builtin_amdgcn_exp2f(
+            exponent_pq(r.s1, r.s2, r.lo, p_ax[u], fmaf(-r.t, r.dx[p + u], dy)));
         a[u] = CLAMP ? fminf(kAlphaMax, oG[u]) : oG[u];
         hit[u] = (r.pos < __float_as_uint(x[u].y)) & (a[u] >= kAlphaMin);
         // alpha of a blended splat, 0 otherwise: its 1 - alpha is the scan's
@@ -929,10 +931,10 @@ __device__ __forceinline__ void splat_rows(const LaneSplat& r, const SplatLds& S
         // and mean partials are formed from its moments once, after the
         // pixels (dL/do = sum gpow / o)
         const float gpow = !CLAMP || oG[u] <= kAlphaMax ? a[u] * g_alpha : 0.0f;
-        const float t = gpow * r.dx[p + u];
+        const float t = gpow * p_ax[u];
         m0 += gpow;
         m1 += t;
-        m2 = fmaf(t, r.dx[p + u], m2);
+        m2 = fmaf(t, p_ax[u], m2);
       }
     }
     const float my = dy * m0;
@@ -1008,7 +1010,7 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
   }
   const uint64_t alive = ballot64(alive_px);
   float acc[10];
-  float ca = 0.0f, cb = 0.0f, cc = 0.0f, ro = 0.0f;
+  float ro = 0.0f, rt = 0.0f, rs1 = 0.0f, rs2 = 0.0f;
   if (alive == 0) {  // (uniform)
 #pragma unroll
     for (int f = 0; f < 10; ++f) acc[f] = 0.0f;
@@ -1036,8 +1038,8 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
         r.dx[k] = (float)(rec.mx - ax);
         ax += 1.0;
       }
-      rec_conic(rec, ca, cb, cc);
       ro = rec.o;
+      rt = rec.t; rs1 = rec.s1; rs2 = rec.s2;
     }
     const bool clamps = ballot64(r.lo > kClampLo) != 0;
     __syncthreads();
@@ -1051,10 +1053,16 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
     else rows(std::integral_constant<int, 16>{});
     __syncthreads();  // the pixel table is rewritten by the next bucket
   }
-  if (live && lane < seg_lanes)
+  if (live && lane < seg_lanes) {
+    // acc: sums of gpow times p^2, p dy, dy^2, p, dy; dx = p - t dy and
+    // q = (1 + t^2) dy - t p
+    const double t = rt, pp = acc[5], pd = acc[6], yy = acc[7], sp = acc[8], sy = acc[9];
     store_pair(A.grad_pair, A.sorted_vals[s + pos], make_float4(acc[0], acc[1], acc[2], acc[3]),
-               make_float4(ro > 0.0f ? acc[4] / ro : 0.0f, -0.5f * acc[5], -acc[6], -0.5f * acc[7]),
-               make_float2(-(ca * acc[8] + cb * acc[9]), -(cb * acc[8] + cc * acc[9])));
+               make_float4(ro > 0.0f ? acc[4] / ro : 0.0f,
+                           (float)(-0.5 * (pp - 2.0 * t * pd + t * t * yy)),
+                           (float)(-(pd - t * yy)), -0.5f * acc[7]),
+               mean_grad(t, rs1, rs2, sp, (1.0 + t * t) * sy - t * sp));
+  }
 }
 
 // Grid-stride over the bucket queue.
