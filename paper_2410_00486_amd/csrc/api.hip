@@ -222,7 +222,18 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_vis_clamp = take(nrec * 4);
   P->heavy_cap = n_views > 1 ? (uint32_t)std::min(nrec, cap / (kHeavyPairs + 1)) : 0u;
   P->off_heavy = take((size_t)P->heavy_cap * 4);
-  P->off_tile_cnt = take(T * 4);
+  // Copies of the pair counters where lists are long.  Below 48 pairs a tile
+  // the scan's extra work eats the gain (1200x680, 12750 lists of 34 pairs:
+  // 289 us an iteration with one copy and with eight; 640x480, 16 pairs: the
+  // scan 9 -> 18 us).  A plan whose scan is one workgroup takes four: 192
+  // lists of 65 pairs, projection 14 -> 9 us and scatter 12 -> 9, scan 9 ->
+  // 11.5 (15.8 with eight).
+  P->scan_rounds = scan_rounds(*P);
+  P->cnt_copies = (cfg->flags & GS_RADIX_BIN) || cap < 48 * T ? 1
+                  : P->scan_rounds > 1                        ? kCountCopies
+                                                              : kCountCopies / 2;
+  P->cnt_stride = (int64_t)((T + 31) / 32 * 32);
+  P->off_tile_cnt = take((size_t)P->cnt_stride * P->cnt_copies * 4);
   P->off_tile_start = take(T * 4);
   P->off_long = take(T * 16);  // (tile, list start, pairs, -) per long list
   // the per-tile binning's scattered keys, pair records and record copies
@@ -261,7 +272,6 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_kept = take((size_t)P->ckpt_slots * 8);
   P->off_seen = take(splat ? T * 8 : 0);
   P->off_ckpt = take((size_t)P->ckpt_slots * 64 * kStateFloats * 4);
-  P->scan_rounds = scan_rounds(*P);
   P->off_scan_part = take((size_t)P->scan_rounds * 64);
   // radix binning buffers, only when the plan asks for that binning
   P->rb_rec_blocks = radix ? rb_blocks(P->n_rec) : 0;

@@ -59,7 +59,8 @@ struct ScanArgs {
   const uint2* chunk_cnt;  // (pairs, visible records) per chunk
   uint2* chunk_pre;        // (generation offset, visible-list position) per chunk
   int64_t n_chunks;
-  uint32_t* cnt;           // pairs per tile; cleared here (the scatter's cursors)
+  TileCounters cnt;        // pairs per tile; set to each copy's place in the list here
+                           // (the scatter's cursors)
   uint32_t* tstart;        // list start per tile
   int64_t n_tiles;
   uint32_t* boff;          // splat-wise only (else null): bucket offset per tile, [T] = total
@@ -205,7 +206,17 @@ __device__ __forceinline__ void scan_load(const ScanArgs& A, int64_t r, ScanRoun
   const uint32_t* chunk_in = reinterpret_cast<const uint32_t*>(A.chunk_cnt);
 #pragma unroll
   for (int k = 0; k < kScanVec; ++k) {
-    uint4 x = load4(A.cnt, R.it + 4 * k, T);
+    uint4 x = load4(A.cnt.at, R.it + 4 * k, T);
+    if (A.cnt.copies > 1) {
+      uint4 y[kCountCopies];
+#pragma unroll
+      for (int j = 1; j < kCountCopies; ++j)
+        y[j] = j < A.cnt.copies ? load4(A.cnt.at + j * A.cnt.stride, R.it + 4 * k, T)
+                                : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int j = 1; j < kCountCopies; ++j)
+        x = make_uint4(x.x + y[j].x, x.y + y[j].y, x.z + y[j].z, x.w + y[j].w);
+    }
     if (A.mode == kScanTiles) {  // list end (0: no pairs) minus list start
       const uint4 st = load4(A.tstart, R.it + 4 * k, T);
       x = make_uint4(x.x ? x.x - st.x : 0u, x.y ? x.y - st.y : 0u, x.z ? x.z - st.z : 0u,
@@ -237,7 +248,7 @@ __device__ __forceinline__ void scan_load(const ScanArgs& A, int64_t r, ScanRoun
 // Writes the round's outputs from the thread's exclusive starts (R.s64 /
 // R.s32 after the block scan): list starts, bucket offsets and queue
 // positions, work order, long-list entries (in tile order), chunk offsets;
-// and clears the tile counters (the scatter's cursors).
+// and sets the tile counters to the list starts (the scatter's cursors).
 __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
   const int64_t T = A.n_tiles, C = A.n_chunks;
   uint32_t* chunk_out = reinterpret_cast<uint32_t*>(A.chunk_pre);
@@ -271,12 +282,25 @@ __device__ __forceinline__ void scan_emit(const ScanArgs& A, ScanRound& R) {
       for (int k5 = 0; k5 < kOrderClasses - 1; ++k5) R.s32[kScanClass + k5] += oc == k5 ? 1u : 0u;
     }
     store4(A.tstart, R.it + 4 * k, T, make_uint4(ts[0], ts[1], ts[2], ts[3]));
-    // the scatter's cursors start at zero; the radix binning's per-tile
-    // pass reads the counts
-    store4(A.cnt, R.it + 4 * k, T,
-           A.mode == kScanTiles ? make_uint4(R.tc[4 * k], R.tc[4 * k + 1], R.tc[4 * k + 2],
-                                             R.tc[4 * k + 3])
-                                : make_uint4(0u, 0u, 0u, 0u));
+    // the scatter's cursors start where the copy's pairs begin in the list;
+    // the radix binning's per-tile pass reads the counts
+    if (A.mode == kScanTiles) {
+      store4(A.cnt.at, R.it + 4 * k, T,
+             make_uint4(R.tc[4 * k], R.tc[4 * k + 1], R.tc[4 * k + 2], R.tc[4 * k + 3]));
+    } else if (A.cnt.copies == 1) {
+      store4(A.cnt.at, R.it + 4 * k, T, make_uint4(ts[0], ts[1], ts[2], ts[3]));
+    } else {
+      uint4 y[kCountCopies], at = make_uint4(ts[0], ts[1], ts[2], ts[3]);
+#pragma unroll
+      for (int j = 0; j < kCountCopies; ++j)
+        if (j < A.cnt.copies) y[j] = load4(A.cnt.at + j * A.cnt.stride, R.it + 4 * k, T);
+#pragma unroll
+      for (int j = 0; j < kCountCopies; ++j)
+        if (j < A.cnt.copies) {
+          store4(A.cnt.at + j * A.cnt.stride, R.it + 4 * k, T, at);
+          at = make_uint4(at.x + y[j].x, at.y + y[j].y, at.z + y[j].z, at.w + y[j].w);
+        }
+    }
     if (A.boff) store4(A.boff, R.it + 4 * k, T, make_uint4(bs[0], bs[1], bs[2], bs[3]));
     const uint32_t p0 = (uint32_t)R.s64[1], v0 = R.s32[1];
     const uint32_t p1 = p0 + R.cp[2 * k], v1 = v0 + R.cv[2 * k];
@@ -440,8 +464,7 @@ __global__ void __launch_bounds__(256) k_scatter(
     const uint32_t* __restrict__ tt, uint32_t* __restrict__ poff,
     const uint2* __restrict__ chunk_pre, int64_t chunks_per_view, int64_t n_chunks,
     const ushort4* __restrict__ rect, const Rec* __restrict__ rec, int64_t n, ViewTable vt,
-    int32_t* __restrict__ fl, HeavyList heavy, const uint32_t* __restrict__ tstart,
-    uint32_t* __restrict__ cursor, uint64_t* __restrict__ skey, uint32_t* __restrict__ pair_rec,
+    int32_t* __restrict__ fl, HeavyList heavy, TileCounters cursors, uint64_t* __restrict__ skey, uint32_t* __restrict__ pair_rec,
     uint32_t* __restrict__ vis_list, uint32_t* __restrict__ vis_clamp) {
   constexpr int NW = 256 / kWave;
   __shared__ uint32_t s_pre[NW][kWave];
@@ -491,6 +514,7 @@ __global__ void __launch_bounds__(256) k_scatter(
   wave_lds_sync();
   const ViewInfo vi = vt.v[v];
   const uint32_t rec0 = (uint32_t)(ri - lane);
+  uint32_t* cursor = count_copy(cursors, gw - (int64_t)v * chunks_per_view);
   for (uint32_t q = (uint32_t)lane; q < total; q += kWave) {
     // owner: the last lane whose prefix is <= q (it has pairs)
     int lo = 0, hi = kWave - 1;
@@ -504,7 +528,7 @@ __global__ void __launch_bounds__(256) k_scatter(
     const int y = (int)(xy >> 16) + (int)(k / bw);
     const int t = vi.tile_off + y * vi.tiles_x + x;
     const uint32_t p = s_p0[w][lo] + k;
-    const uint64_t slot = (uint64_t)tstart[t] + atomicAdd(&cursor[t], 1u);
+    const uint32_t slot = atomicAdd(&cursor[t], 1u);
     if (slot < P) skey[slot] = ((uint64_t)s_dbits[w][lo] << 32) | p;
     pair_rec[p] = rec0 + (uint32_t)lo;
   }
@@ -575,11 +599,11 @@ hipError_t launch_rb_runs(const Plan& P, void* ws, hipStream_t s);
 
 hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s) {
   // per-iteration flags 0..10 and the per-tile pair counters
-  const int64_t T = P.vt.total_tiles;
-  const int64_t m = T > 4 ? T : 4;
+  const int64_t words = P.cnt_stride * P.cnt_copies;
+  const int64_t m = std::max<int64_t>(words, F_NF_ACC + 1);
   hipLaunchKernelGGL(k_fill2_u32, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s,
                      ws_at<uint32_t>(ws, P.off_flags), (int64_t)(F_NF_ACC + 1),
-                     ws_at<uint32_t>(ws, P.off_tile_cnt), T);
+                     ws_at<uint32_t>(ws, P.off_tile_cnt), words);
   return hipGetLastError();
 }
 
@@ -587,7 +611,7 @@ hipError_t launch_clear_counters(const Plan& P, void* ws, hipStream_t s) {
 static TileSortArgs tile_sort_args(const Plan& P, void* ws) {
   const bool splat = P.splat != 0;
   TileSortArgs A{};
-  A.cnt = ws_at<uint32_t>(ws, P.off_tile_cnt);
+  A.cnt = tile_counters(P, ws);
   A.tstart = ws_at<uint32_t>(ws, P.off_tile_start);
   A.fl = ws_at<int32_t>(ws, P.off_flags);
   const bool radix = (P.cfg.flags & GS_RADIX_BIN) != 0;  // (no scattered keys, no copies)
@@ -610,14 +634,13 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
   int32_t* fl = ws_at<int32_t>(ws, P.off_flags);
   uint32_t* tt = ws_at<uint32_t>(ws, P.off_tt);
   uint32_t* poff = ws_at<uint32_t>(ws, P.off_poff);
-  uint32_t* tcnt = ws_at<uint32_t>(ws, P.off_tile_cnt);
   uint32_t* tstart = ws_at<uint32_t>(ws, P.off_tile_start);
   const int T = P.vt.total_tiles;
   const uint2* chunk_cnt = ws_at<uint2>(ws, P.off_chunk_cnt);
   uint2* chunk_pre = ws_at<uint2>(ws, P.off_chunk_pre);
   uint4* long_list = ws_at<uint4>(ws, P.off_long);
   const bool radix = (P.cfg.flags & GS_RADIX_BIN) != 0;
-  ScanArgs sa{chunk_cnt, chunk_pre, P.n_chunks, tcnt, tstart, (int64_t)T,
+  ScanArgs sa{chunk_cnt, chunk_pre, P.n_chunks, tile_counters(P, ws), tstart, (int64_t)T,
               P.splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr,
               ws_at<uint32_t>(ws, P.off_order), long_list, kScanBoth};
   // always launched, so that the flags are always set: one block for a
@@ -674,7 +697,8 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
     const int64_t blocks = (P.n_chunks + 3) / 4;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(256), 0, s, tt, poff, chunk_pre,
                        P.chunks_per_view, P.n_chunks, ws_at<ushort4>(ws, P.off_rect),
-                       ws_at<Rec>(ws, P.off_rec), P.n, P.vt, fl, heavy_list(P, ws), tstart, tcnt, skey, pair_rec,
+                       ws_at<Rec>(ws, P.off_rec), P.n, P.vt, fl, heavy_list(P, ws), tile_counters(P, ws),
+                       skey, pair_rec,
                        ws_at<uint32_t>(ws, P.off_vis_list), ws_at<uint32_t>(ws, P.off_vis_clamp));
   }
   if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;

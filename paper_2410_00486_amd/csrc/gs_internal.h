@@ -183,7 +183,9 @@ struct Plan {
   size_t off_vis_list;                  // visible records in index order
   size_t off_vis_clamp;                 // their colour clamp bits, same order
   size_t off_heavy;                     // several views: records of many pairs
-  uint32_t heavy_cap, pad2;
+  uint32_t heavy_cap;
+  int32_t cnt_copies;  // copies of the tiles' pair counters, cnt_stride words apart
+  int64_t cnt_stride;
   size_t off_tile_cnt, off_tile_start, off_long;
   size_t off_keys, off_scatter, off_vals, off_pair_rec, off_sorted_rec, off_srec;
   size_t off_ranges, off_tile_last, off_tile_loss;
@@ -219,6 +221,30 @@ inline Plan* plan_of(gs_plan* p) { return reinterpret_cast<Plan*>(p->opaque); }
 template <typename T>
 inline T* ws_at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
+}
+
+// The per-tile binning counts pairs and claims list slots with one atomic a
+// pair.  Atomics on one cache line execute one after another (8.9 ns each,
+// measured), so lists of any length make that line the bottleneck: such
+// plans have several copies of the counters, by the projection's workgroup
+// (256 Gaussians; workgroups go to the eight dies in turn, so with eight
+// copies each die has its own).  16x16 tiles, one copy and eight: one
+// 1200x680 view, 627k pairs, projection 78 -> 30 us and scatter 74 -> 25;
+// four such views, 2.7M pairs, 174 -> 108 and 254 -> 90.  Copies, not wider
+// spacing: neighbouring tiles of a wavefront stay one access (64 bytes a
+// counter: 54 and 51 us for the former, 154 and 173 for the latter).
+constexpr int kCountCopies = 8;
+struct TileCounters {
+  uint32_t* at;
+  int64_t stride;
+  int32_t copies;  // a power of two up to kCountCopies
+};
+__device__ __forceinline__ uint32_t* count_copy(const TileCounters& c, int64_t chunk) {
+  return c.at + ((chunk >> 2) & (c.copies - 1)) * c.stride;
+}
+
+inline TileCounters tile_counters(const Plan& P, void* ws) {
+  return TileCounters{ws_at<uint32_t>(ws, P.off_tile_cnt), P.cnt_stride, P.cnt_copies};
 }
 
 inline HeavyList heavy_list(const Plan& P, void* ws) {

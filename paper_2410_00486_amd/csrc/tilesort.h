@@ -108,7 +108,7 @@ __device__ inline void bitonic_sort_wave(uint64_t* k, uint32_t n, uint32_t lane)
 
 // Everything a wavefront needs to sort one tile's list.
 struct TileSortArgs {
-  uint32_t* cnt;           // pairs per tile (the scatter's cursors); cleared after use
+  TileCounters cnt;        // pairs per tile (the scatter's cursors); cleared after use
   const uint32_t* tstart;  // list start per tile
   const int32_t* fl;
   const uint64_t* skey;    // scattered keys (depth bits << 32 | generation index)
@@ -165,16 +165,18 @@ __device__ inline void sort_list_wave(const TileSortOut& o, const uint64_t* __re
 // kTileSortSmall keys of LDS of this wavefront.
 __device__ inline void sort_tile_wave(const TileSortArgs& A, int t, int lane, uint64_t* sk) {
   const uint64_t P = (uint64_t)A.fl[F_PAIRS];
-  const uint32_t c = A.cnt[t];
+  // (radix binning: the count; else the last copy's cursor is the list's end)
+  const uint32_t c = A.cnt.at[(A.cnt.copies - 1) * A.cnt.stride + t] -
+                     (A.presorted ? 0u : A.tstart[t]);
   const uint32_t n = A.fl[F_OVERFLOW] ? 0u : c;
   const uint64_t start64 = A.tstart[t];
   const bool ok = n > 0 && start64 + n <= P;
   if (lane == 0) {
     A.ranges[2 * (int64_t)t] = ok ? (uint32_t)start64 : 0u;
     A.ranges[2 * (int64_t)t + 1] = ok ? (uint32_t)(start64 + n) : 0u;
-    // the counter is consumed: zero again for the next projection
-    A.cnt[t] = 0u;
   }
+  // the counters are consumed: zero again for the next projection
+  if (lane < A.cnt.copies) A.cnt.at[lane * A.cnt.stride + t] = 0u;
   if (A.bq && ok) {
     // splat-wise work queue: the tile's buckets of 64 pairs
     const uint32_t q0 = A.boff[t], nb = (n + kBucket - 1) / kBucket;

@@ -308,3 +308,43 @@ def test_projection_backward_records_of_many_pairs(flags):
     torch.cuda.synchronize()
     grads, _, exclude, _ = oracle_reference(w.scene, cams, gcs, gds, (8, 8))
     assert_grads_close(grads_np(it), grads, exclude)
+
+
+# ------------------------------------------------------- copies of the pair counters
+
+@pytest.mark.parametrize("n,width,height", [(3000, 203, 117),    # scan of one workgroup
+                                            (3000, 1200, 680),   # several
+                                            (100, 203, 117)])    # some copies unused
+def test_tile_counter_copies(n, width, height):
+    """A plan with room for many pairs a tile counts in several copies of the
+    counters, one with less room in a single one: same lists, on a first and
+    a second iteration, and after one that did not fit."""
+    w = scenes.tiny_scene(31, n=n, width=width, height=height, f=0.8 * width, degree=0)
+    w.scene.log_scales[:] = -4.5
+    cam = w.cameras[0]
+    g = gsr.Gaussians.from_scene(w.scene, DEV)
+    ct = gsr.cameras_tensor([cam], DEV)
+    wh = [(width, height)]
+    pairs = int(gsr.required_pairs(*g.tensors(), ct, wh, 0, (8, 8)))
+    tiles = -(-width // 8) * -(-height // 8)
+    assert pairs < 48 * tiles - 1
+    print(f"counter copies n {n} {width}x{height}: {pairs} pairs, {tiles} tiles", flush=True)
+    got = []
+    for cap in (48 * tiles - 1, 48 * tiles):
+        plan = gsr.Plan(n, 0, wh, tile=(8, 8), pair_capacity=cap)
+        ws = plan.new_workspace(DEV)
+        for log_scale in (-4.5, -0.5, -4.5):  # (the second one may overflow)
+            g.log_scales.fill_(log_scale)
+            gsr.preprocess(plan, ws, g, ct)
+            gsr.bin_sort(plan, ws)
+            torch.cuda.synchronize()
+        assert plan.flags_of(ws)[L.F_OVERFLOW] == 0 and plan.flags_of(ws)[L.F_PAIRS] == pairs
+        got.append([plan.region(ws, r, dt, c).cpu().numpy().copy() for r, dt, c in (
+            (L.GS_WS_SORTED_KEYS, torch.int64, pairs), (L.GS_WS_SORTED_VALS, torch.int32, pairs),
+            (L.GS_WS_SORTED_RECS, torch.int32, pairs), (L.GS_WS_RANGES, torch.int32, 2 * tiles))])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    pre = oracle.preprocess(w.scene, cam, (8, 8))
+    keys, vals, _ = oracle.sort_pairs(pre, cam, (8, 8))
+    np.testing.assert_array_equal(got[1][0].view(np.uint64), keys)
+    np.testing.assert_array_equal(got[1][2], vals.astype(np.int32))
