@@ -236,9 +236,8 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_tile_cnt = take((size_t)P->cnt_stride * P->cnt_copies * 4);
   P->off_tile_start = take(T * 4);
   P->off_long = take(T * 16);  // (tile, list start, pairs, -) per long list
-  // the per-tile binning's scattered keys, pair records and record copies
-  // in list order; the radix binning has buffers of its own (below) and
-  // its lists name their records
+  // the per-tile binning's scattered keys and pair records; the radix
+  // binning has buffers of its own (below)
   const bool radix = (cfg->flags & GS_RADIX_BIN) != 0;
   const size_t tcap = radix ? 0 : cap;
   P->off_keys = take(cap * 8);
@@ -246,7 +245,6 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_vals = take(cap * 4);
   P->off_pair_rec = take(tcap * 4);
   P->off_sorted_rec = take(cap * 4);
-  P->off_srec = take(tcap * sizeof(Rec));
   P->off_ranges = take(T * 2 * 4);
   // (per 8x8 block of pixels of a tile)
   const size_t blocks8 = T * (size_t)(tw * th / 64);

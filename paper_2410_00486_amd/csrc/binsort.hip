@@ -618,8 +618,7 @@ static TileSortArgs tile_sort_args(const Plan& P, void* ws) {
   A.skey = radix ? nullptr : ws_at<uint64_t>(ws, P.off_scatter);
   A.out = TileSortOut{ws_at<uint64_t>(ws, P.off_keys), ws_at<uint32_t>(ws, P.off_vals),
                       ws_at<uint32_t>(ws, P.off_sorted_rec),
-                      radix ? nullptr : ws_at<uint32_t>(ws, P.off_pair_rec),
-                      ws_at<Rec>(ws, P.off_rec), radix ? nullptr : ws_at<Rec>(ws, P.off_srec)};
+                      radix ? nullptr : ws_at<uint32_t>(ws, P.off_pair_rec)};
   A.ranges = ws_at<uint32_t>(ws, P.off_ranges);
   A.boff = splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr;
   A.bq = splat ? ws_at<uint2>(ws, P.off_bq) : nullptr;

@@ -98,15 +98,13 @@ __device__ __forceinline__ float2 mean_grad(double t, double s1, double s2, doub
   return make_float2((float)(-2.0 * kLn2 * (u - t * w)), (float)(-2.0 * kLn2 * (t * u + w)));
 }
 
-// Where the raster kernels read the records of the tile lists: a copy in
-// list order written by the binning (idx null: list position k is base[k]),
-// or the per-view record array itself, through each pair's record id
-// (base[idx[k]]).
+// Where the raster kernels read the records of the tile lists: the per-view
+// record array, through each pair's record id.
 struct RecSrc {
   const Rec* base;
   const uint32_t* idx;
-  __device__ __forceinline__ uint32_t id(uint32_t k) const { return idx ? idx[k] : k; }
-  __device__ __forceinline__ const Rec* at(uint32_t k) const { return base + id(k); }
+  __device__ __forceinline__ uint32_t id(uint32_t k) const { return idx[k]; }
+  __device__ __forceinline__ const Rec* at(uint32_t k) const { return base + idx[k]; }
 };
 
 // Per-pair gradient partial written by the backward raster kernel:
@@ -187,7 +185,7 @@ struct Plan {
   int32_t cnt_copies;  // copies of the tiles' pair counters, cnt_stride words apart
   int64_t cnt_stride;
   size_t off_tile_cnt, off_tile_start, off_long;
-  size_t off_keys, off_scatter, off_vals, off_pair_rec, off_sorted_rec, off_srec;
+  size_t off_keys, off_scatter, off_vals, off_pair_rec, off_sorted_rec;
   size_t off_ranges, off_tile_last, off_tile_loss;
   size_t off_grad_pair, off_pose_part, off_order;
   // several views: per record, its projection-backward terms; per

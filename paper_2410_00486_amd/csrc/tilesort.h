@@ -33,12 +33,10 @@ struct TileSortOut {
   uint32_t* vals;
   uint32_t* sorted_rec;
   const uint32_t* pair_rec;
-  const Rec* rec;
-  Rec* lrec;  // records in list order, read contiguously by the render kernels
 };
 
 // Writes the pair of key (depth bits << 32 | generation index) at list
-// position pos: sorted key, generation index, record id, record.
+// position pos: sorted key, generation index, record id.
 __device__ __forceinline__ void emit_sorted(const TileSortOut& o, uint32_t pos, uint64_t tkey,
                                             uint64_t key) {
   const uint32_t g = (uint32_t)key;
@@ -46,10 +44,6 @@ __device__ __forceinline__ void emit_sorted(const TileSortOut& o, uint32_t pos, 
   o.keys[pos] = tkey | (key >> 32);
   o.vals[pos] = g;
   o.sorted_rec[pos] = r;
-  const float4* src = reinterpret_cast<const float4*>(o.rec + r);
-  float4* dst = reinterpret_cast<float4*>(o.lrec + pos);
-  const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-  dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
 }
 
 __device__ __forceinline__ void cmp_swap(uint64_t* k, uint32_t a, uint32_t b, uint32_t n) {
@@ -124,7 +118,7 @@ struct TileSortArgs {
 // Sorts the n <= MAX keys of a list with one wavefront and writes the sorted
 // outputs: the lane's positions are written out and their record ids looked
 // up all at once (one memory round trip for all of them instead of one per
-// position), then the records.  sk: MAX keys of LDS of this wavefront.
+// position).  sk: MAX keys of LDS of this wavefront.
 template <uint32_t MAX>
 __device__ inline void sort_list_wave(const TileSortOut& o, const uint64_t* __restrict__ skey,
                                       uint64_t tkey, uint32_t start, uint32_t n, int lane,
@@ -149,13 +143,7 @@ __device__ inline void sort_list_wave(const TileSortOut& o, const uint64_t* __re
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {
     const uint32_t k = (uint32_t)lane + (uint32_t)q * kWave;
-    if (k < n) {
-      o.sorted_rec[start + k] = r[q];
-      const float4* src = reinterpret_cast<const float4*>(o.rec + r[q]);
-      float4* dst = reinterpret_cast<float4*>(o.lrec + start + k);
-      const float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3];
-      dst[0] = a0; dst[1] = a1; dst[2] = a2; dst[3] = a3;
-    }
+    if (k < n) o.sorted_rec[start + k] = r[q];
   }
   wave_lds_sync();  // every key read before the next list overwrites them
 }
