@@ -23,8 +23,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:  # (the handle alone: building a Stream object costs more than a launch)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def _need(t: torch.Tensor, name: str, dtype=torch.float32):
@@ -82,9 +83,11 @@ class Plan:
 
     def flags_of(self, ws: torch.Tensor) -> np.ndarray:
         """Device flags (synchronises the current stream)."""
-        ptr = L.lib().gs_flags_ptr(ctypes.byref(self.c), _ptr(ws))
-        off = ptr - ws.data_ptr()
-        return ws[off:off + 64].view(torch.int32).cpu().numpy()
+        return self._flags(ws).cpu().numpy()
+
+    def _flags(self, ws: torch.Tensor) -> torch.Tensor:
+        off = L.lib().gs_flags_ptr(ctypes.byref(self.c), _ptr(ws)) - ws.data_ptr()
+        return ws[off:off + 64].view(torch.int32)
 
     def region(self, ws: torch.Tensor, region: int, dtype, count: int) -> torch.Tensor:
         off = self.ws_offset(region)
@@ -164,6 +167,19 @@ class Frame:
         self.T_final = torch.empty(P, dtype=torch.float32, device=device)
         self.last = torch.empty(P, dtype=torch.int32, device=device)
         self.loss = torch.zeros(plan.n_views, dtype=torch.float32, device=device)
+
+
+def _frame_without_loss(plan: Plan, device) -> Frame:
+    """A Frame of a render without targets: its loss is never read, so it is
+    not cleared."""
+    fr = Frame.__new__(Frame)
+    P = plan.total_pixels
+    fr.color = torch.empty(3 * P, dtype=torch.float32, device=device)
+    fr.depth = torch.empty(P, dtype=torch.float32, device=device)
+    fr.T_final = torch.empty(P, dtype=torch.float32, device=device)
+    fr.last = torch.empty(P, dtype=torch.int32, device=device)
+    fr.loss = None
+    return fr
 
 
 # ---------------------------------------------------------------- entry points
@@ -713,19 +729,44 @@ class Rasterizer:
     def forward_buffers(self, g: "Gaussians", cams: torch.Tensor):
         """Preprocess, binning and forward into fresh output buffers; returns
         (plan, ws, frame).  Retries once with a larger capacity on overflow."""
+        return self._forward(g, cams, False)
+
+    def _forward(self, g: "Gaussians", cams: torch.Tensor, held: bool):
+        """held: the caller keeps the workspace and cams until its backward, so
+        the render may still run when this returns; otherwise it is waited
+        for (the workspace goes back to the pool, where another stream's next
+        call may take it)."""
         for attempt in range(2):
             plan = self._plan_for(g.n)
             ws = self.acquire(g.means.device)
             preprocess(plan, ws, g, cams)
             bin_sort(plan, ws)
-            fr = Frame(plan, g.means.device)
+            # the binning settles the flags: they are copied out before the
+            # render, and the host goes on to the backward while it runs
+            # (forward and backward, 128x96, 2000 Gaussians: 307 -> 220 us;
+            # 1200x680, 300k: 640 -> 554)
+            early = held and self.check_overflow
+            if early:
+                s = torch.cuda.current_stream(ws.device)
+                host = torch.empty(16, dtype=torch.int32, pin_memory=True)
+                host.copy_(plan._flags(ws), non_blocking=True)
+                copied = s.record_event()
+                for t in (ws, cams):  # (if the graph is dropped before the render has run)
+                    t.record_stream(s)
+            fr = _frame_without_loss(plan, g.means.device)
             render_fwd(plan, ws, cams, fr)
             self._last_ws = ws
             if not self.check_overflow:
                 return plan, ws, fr
-            fl = plan.flags_of(ws)
+            if early:
+                copied.synchronize()
+                fl = host.numpy()
+            else:
+                fl = plan.flags_of(ws)
             if not fl[L.F_OVERFLOW]:
                 return plan, ws, fr
+            if early:
+                s.synchronize()
             self.release(plan, ws)
             self.capacity = int(fl[L.F_PAIRS_WANTED] * 1.25) + 1024
             if self.capacity > 0x7FFFFFFF:
@@ -754,7 +795,7 @@ class _Rasterize(torch.autograd.Function):
         if pose_tangent is not None:
             xi = pose_tangent.detach().contiguous()
             cams = pose_retract(cams, xi)
-        plan, ws, fr = rz.forward_buffers(g, cams)
+        plan, ws, fr = rz._forward(g, cams, keep)
         if keep:
             ctx.rz, ctx.plan, ctx.ws, ctx.frame, ctx.g, ctx.cams, ctx.xi = (
                 rz, plan, ws, fr, g, cams, xi)

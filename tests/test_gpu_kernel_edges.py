@@ -348,3 +348,39 @@ def test_tile_counter_copies(n, width, height):
     keys, vals, _ = oracle.sort_pairs(pre, cam, (8, 8))
     np.testing.assert_array_equal(got[1][0].view(np.uint64), keys)
     np.testing.assert_array_equal(got[1][2], vals.astype(np.int32))
+
+
+# ------------------------------------------------- differentiable call, early flags
+
+def test_differentiable_call_grows_and_may_be_dropped():
+    """A recorded call returns before its render has run: with a capacity that
+    has to grow, with its graph dropped at once, and from two streams in turn
+    the images and gradients are those of a fresh rasterizer."""
+    w = scenes.slab_128x96()
+    cam = w.cameras[0]
+    ct = gsr.cameras_tensor([cam], DEV)
+    wh = [(cam.width, cam.height)]
+    leaves = [x.requires_grad_(True) for x in gsr.Gaussians.from_scene(w.scene, DEV).tensors()]
+    weight = torch.linspace(-1.0, 1.0, 3 * cam.width * cam.height, device=DEV)
+
+    def call(rz):
+        color, _, _ = rz(*leaves, ct)
+        return color.detach().clone(), torch.autograd.grad((color * weight).sum(), leaves)
+
+    print("differentiable call, early flags", flush=True)
+    want = call(gsr.Rasterizer(wh, w.scene.sh_degree, pair_capacity=1 << 18))
+    rz = gsr.Rasterizer(wh, w.scene.sh_degree, pair_capacity=16)  # overflows, then fits
+    side = torch.cuda.Stream()
+    got = [call(rz)]
+    for _ in range(3):
+        rz(*leaves, ct)  # dropped
+        got.append(call(rz))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            got.append(call(rz))
+        side.synchronize()
+    torch.cuda.synchronize()
+    for color, grads in got:
+        assert torch.equal(color, want[0])
+        for a, b in zip(grads, want[1]):
+            assert torch.equal(a, b)
