@@ -214,12 +214,13 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_flags = take(F_COUNT * 4 * 4);
   P->off_rec = take(nrec * sizeof(Rec));
   P->off_rect = take(nrec * 8);
+  P->off_zbits = take(nrec * 4);
+  P->off_clamp = take(nrec);
   P->off_tt = take(nrec * 4);
   P->off_poff = take(nrec * 4);
   P->off_chunk_cnt = take((size_t)P->n_chunks * 8);
   P->off_chunk_pre = take((size_t)P->n_chunks * 8);
   P->off_vis_list = take(nrec * 4);
-  P->off_vis_clamp = take(nrec * 4);
   P->heavy_cap = n_views > 1 ? (uint32_t)std::min(nrec, cap / (kHeavyPairs + 1)) : 0u;
   P->off_heavy = take((size_t)P->heavy_cap * 4);
   // Copies of the pair counters where lists are long.  Below 48 pairs a tile
@@ -289,7 +290,6 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_rb_items = take(radix ? (size_t)(1 + rb_gen_items(P->n_rec, pair_capacity)) * 8 : 0);
   P->off_rb_pay = take(rrec * 4);   // 16 bytes per visible record, list order
   P->off_rb_spay = take(rrec * 4);  // the same in depth order
-  P->off_rb_zrec = take(rrec);      // depth bits by record id
   P->ws_size = o;
   P->magic = kPlanMagic;
   return GS_OK;

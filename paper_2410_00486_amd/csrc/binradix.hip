@@ -44,6 +44,7 @@ constexpr int kGenRecs = 1024;
 constexpr int kGenPer = kGenRecs / kRbThreads;
 constexpr uint32_t kGenPairs = 8192;
 constexpr int kGenScanThreads = 1024;
+constexpr int kRunsPer = 4;  // sorted keys per thread of the run search
 
 static_assert(kRbMaxRadix == 2 * kRbThreads, "two digits per thread in the block scans");
 
@@ -55,9 +56,11 @@ __device__ __forceinline__ int64_t rb_count(const int32_t* fl, int which) {
 
 // Lanes of the wavefront whose digit equals this lane's (among `valid`
 // lanes), from one ballot per digit bit.
-__device__ __forceinline__ uint64_t rb_peers(uint32_t d, bool valid, int bits) {
+template <int BITS>
+__device__ __forceinline__ uint64_t rb_peers(uint32_t d, bool valid) {
   uint64_t peers = ballot64(valid);
-  for (int b = 0; b < bits; ++b) {
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) {
     const bool bit = (d >> b) & 1u;
     const uint64_t bb = ballot64(bit);
     peers &= bit ? bb : ~bb;
@@ -89,14 +92,15 @@ __device__ __forceinline__ uint32_t pay_tiles(const uint4 p) {
 // 1. Visible records in record order: pair offset (first generation index),
 // visible-list entry, depth key and generation payload.  One wavefront per
 // chunk of 64 Gaussians of a view, at the positions the binning scan gave
-// the chunk.
+// the chunk.  Bound by HBM: the depth and the box come from arrays of their
+// own (a 64-byte record per visible Gaussian: 32M records, 6.1M of them
+// visible, 173 us, now 101).
 __global__ void __launch_bounds__(256) k_rb_visible(
     const uint32_t* __restrict__ tt, uint32_t* __restrict__ poff,
     const uint2* __restrict__ chunk_pre, int64_t chunks_per_view, int64_t n_chunks,
-    const Rec* __restrict__ rec, const uint2* __restrict__ rect, int64_t n,
+    const uint32_t* __restrict__ zbits, const uint2* __restrict__ rect, int64_t n,
     int32_t* __restrict__ fl, HeavyList heavy, uint32_t* __restrict__ vis_list,
-    uint32_t* __restrict__ vis_clamp, uint32_t* __restrict__ dkey, uint4* __restrict__ pay,
-    uint32_t* __restrict__ zrec) {
+    uint32_t* __restrict__ dkey, uint4* __restrict__ pay) {
   const int w = threadIdx.x / kWave, lane = lane_id();
   const int64_t gw = (int64_t)blockIdx.x * (256 / kWave) + w;  // chunk
   if (gw >= n_chunks) return;
@@ -105,11 +109,11 @@ __global__ void __launch_bounds__(256) k_rb_visible(
   const int64_t ri = (int64_t)v * n + gi;
   const bool over = fl[F_OVERFLOW] != 0;
   const uint32_t c = (gi < n && !over) ? tt[ri] : 0u;
-  float z = 0.0f;
-  uint32_t cbits = 0;
+  uint32_t z = 0;
+  uint2 b = make_uint2(0u, 0u);
   if (c > 0) {
-    z = rec[ri].z;
-    cbits = rec[ri].clamp;  // (same line as the depth)
+    z = zbits[ri];
+    b = rect[ri];
   }
   const uint32_t incl = scan_dpp<6>(c);
   const uint2 cp = chunk_pre[gw];
@@ -119,46 +123,47 @@ __global__ void __launch_bounds__(256) k_rb_visible(
     poff[ri] = p0;
     const uint32_t vp = cp.y + (uint32_t)__popcll(vmask & lanemask_lt());
     vis_list[vp] = (uint32_t)ri;
-    vis_clamp[vp] = cbits;
     note_heavy(heavy, fl, c, (uint32_t)ri);
-    dkey[vp] = __float_as_uint(z);
-    zrec[ri] = __float_as_uint(z);
-    const uint2 b = rect[ri];
+    dkey[vp] = z;
     pay[vp] = make_uint4(b.x, b.y, p0, (uint32_t)ri);
   }
 }
 
 // Upsweep: per-block counts of the digit (key >> shift) & (2^bits - 1),
-// stored digit-major: hist[d * nb_cap + block].
+// stored digit-major: hist[d * nb_cap + block].  LDS atomics on a row per
+// wavefront: ranking by ballots only to count, 25M pairs took 90 to 99 us,
+// now 37 to 41 (1.5M keys 12 -> 5); conflicts cost most on the depth's top
+// byte (few values: 8.5 us, 5 otherwise).  Neighbouring blocks on one XCD, as
+// in the downsweep, so that their counts of a digit (one cache line) meet in
+// one L2: 64 -> 40 us of that.
 __global__ void __launch_bounds__(kRbThreads) k_rb_hist(const uint32_t* __restrict__ keys,
                                                         const int32_t* __restrict__ fl, int which,
                                                         uint32_t* __restrict__ hist,
                                                         int64_t nb_cap, int shift, int bits) {
   const int64_t cnt = rb_count(fl, which);
-  const int64_t base = (int64_t)blockIdx.x * kRbTile;
+  const uint32_t blk = xcd_item(blockIdx.x, gridDim.x);
+  const int64_t base = (int64_t)blk * kRbTile;
   if (base >= cnt) return;
   __shared__ uint32_t h[kRbWaves][kRbMaxRadix];
-  const int w = threadIdx.x / kWave, lane = lane_id();
+  const int w = threadIdx.x / kWave;
   for (int k = threadIdx.x; k < kRbWaves * kRbMaxRadix; k += kRbThreads) (&h[0][0])[k] = 0u;
   __syncthreads();
   const uint32_t mask = (1u << bits) - 1u;
-  const uint64_t lt = lanemask_lt();
-#pragma unroll 4
+  uint32_t key[kRbItems];
+#pragma unroll
   for (int r = 0; r < kRbItems; ++r) {
-    const int64_t idx = base + (int64_t)w * (kWave * kRbItems) + r * kWave + lane;
-    const bool valid = idx < cnt;
-    const uint32_t d = valid ? (keys[idx] >> shift) & mask : 0u;
-    const uint64_t peers = rb_peers(d, valid, bits);
-    // one lane per distinct digit adds the digit's lanes (no two lanes of a
-    // wavefront touch the same word; each wavefront has its own row)
-    if (valid && (peers & lt) == 0) h[w][d] += (uint32_t)__popcll(peers);
+    const int64_t idx = base + r * kRbThreads + threadIdx.x;
+    key[r] = idx < cnt ? keys[idx] : 0u;
   }
+#pragma unroll
+  for (int r = 0; r < kRbItems; ++r)
+    if (base + r * kRbThreads + threadIdx.x < cnt) atomicAdd(&h[w][(key[r] >> shift) & mask], 1u);
   __syncthreads();
   for (int d = threadIdx.x; d <= (int)mask; d += kRbThreads) {
     uint32_t s = 0;
 #pragma unroll
     for (int k = 0; k < kRbWaves; ++k) s += h[k][d];
-    hist[(int64_t)d * nb_cap + blockIdx.x] = s;
+    hist[(int64_t)d * nb_cap + blk] = s;
   }
 }
 
@@ -172,17 +177,36 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_digit_scan(uint32_t* __restri
   const int64_t cnt = rb_count(fl, which);
   const int64_t nb = (cnt + kRbTile - 1) / kRbTile;
   uint32_t* row = hist + (int64_t)blockIdx.x * nb_cap;
-  __shared__ uint32_t ws[kRbWaves];
-  __shared__ uint32_t tot;
+  // four counts per thread in flight (one at a time: 24 us for 8100 blocks,
+  // now 11)
+  constexpr int V = 4;
+  const int w = threadIdx.x / kWave, lane = lane_id();
+  __shared__ uint32_t ws[V][kRbWaves];
   uint32_t carry = 0;
-  for (int64_t b0 = 0; b0 < nb; b0 += kRbThreads) {
-    const int64_t b = b0 + threadIdx.x;
-    const uint32_t x = b < nb ? row[b] : 0u;
-    const uint32_t ex = rb_block_exscan(x, ws);
-    if (b < nb) row[b] = carry + ex;
-    if (threadIdx.x == kRbThreads - 1) tot = ex + x;
+  for (int64_t b0 = 0; b0 < nb; b0 += V * kRbThreads) {
+    uint32_t x[V], incl[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      const int64_t b = b0 + k * kRbThreads + threadIdx.x;
+      x[k] = b < nb ? row[b] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      incl[k] = scan_dpp<6>(x[k]);
+      if (lane == kWave - 1) ws[k][w] = incl[k];
+    }
     __syncthreads();
-    carry += tot;
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      const int64_t b = b0 + k * kRbThreads + threadIdx.x;
+      uint32_t at = carry;
+#pragma unroll
+      for (int j = 0; j < kRbWaves; ++j) {
+        at += j < w ? ws[k][j] : 0u;
+        carry += ws[k][j];
+      }
+      if (b < nb) row[b] = at + incl[k] - x[k];
+    }
     __syncthreads();
   }
   if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
@@ -203,9 +227,15 @@ struct RbEmit {
 // Downsweep: stable ranking of the block's keys by digit, reorder in LDS,
 // then each digit's run written contiguously at the digit's global offset
 // (digit totals scanned over digits + the block's offset within the digit).
+// A block's run of one digit is 24 to 48 bytes, part of a cache line whose
+// rest the neighbouring blocks write, so 32 neighbours share an XCD: 25M pairs
+// 332 -> 256 us and 297 -> 269 (emitting), the last depth pass of 6.1M
+// records 140 -> 98.  Bound by those writes (12 to 16 bytes a pair; 600 to
+// 700 MB in all, 120 us at the rate of a large copy).  Keys per block: 8 rows
+// of 256 302 + 261 us, 12 259 + 271, 16 259 + 284, 20 249 + 317.
 // EMIT: the last pass of the tile sort (keys are tile ids, values
 // generation indices): writes the sorted lists instead of keys / values.
-template <bool EMIT, bool TWO>
+template <bool EMIT, bool TWO, int BITS>
 __global__ void __launch_bounds__(kRbThreads) k_rb_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     const uint32_t* __restrict__ vals2_in, uint32_t* __restrict__ keys_out,
@@ -213,7 +243,8 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_scatter(
     const int32_t* __restrict__ fl, int which, const uint32_t* __restrict__ hist,
     const uint32_t* __restrict__ dtot, int64_t nb_cap, int shift, int bits) {
   const int64_t cnt = rb_count(fl, which);
-  const int64_t base = (int64_t)blockIdx.x * kRbTile;
+  const uint32_t blk = xcd_item(blockIdx.x, gridDim.x);
+  const int64_t base = (int64_t)blk * kRbTile;
   if (base >= cnt) return;
   __shared__ uint32_t wcnt[kRbWaves][kRbMaxRadix];
   __shared__ uint32_t lstart[kRbMaxRadix];
@@ -232,8 +263,8 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_scatter(
   {
     const uint32_t x0 = h0 ? dtot[d0] : 0u, x1 = h1 ? dtot[d1] : 0u;
     const uint32_t ex = rb_block_exscan(x0 + x1, ws);  // (its barrier also orders the clear)
-    if (h0) gofs[d0] = ex + hist[(int64_t)d0 * nb_cap + blockIdx.x];
-    if (h1) gofs[d1] = ex + x0 + hist[(int64_t)d1 * nb_cap + blockIdx.x];
+    if (h0) gofs[d0] = ex + hist[(int64_t)d0 * nb_cap + blk];
+    if (h1) gofs[d1] = ex + x0 + hist[(int64_t)d1 * nb_cap + blk];
   }
   // (the values are loaded only when they are staged: fewer registers held
   // through the ranking)
@@ -246,7 +277,7 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_scatter(
     const bool valid = idx < cnt;
     key[r] = valid ? keys_in[idx] : 0u;
     const uint32_t d = (key[r] >> shift) & mask;
-    const uint64_t peers = rb_peers(d, valid, bits);
+    const uint64_t peers = rb_peers<BITS>(d, valid);
     const uint64_t below = peers & lt;
     uint32_t old = 0;
     if (valid) old = wcnt[w][d];
@@ -557,17 +588,37 @@ __global__ void __launch_bounds__(kRbThreads) k_rb_generate(
 
 // 5. Per-tile list bounds from the sorted keys (tile << 32 | depth): the
 // first position of each tile's run to tstart, one past its last to cnt.
-// Tiles without pairs keep cnt = 0 (the per-tile pass zeroed it).
+// Tiles without pairs keep cnt = 0 (the per-tile pass zeroed it).  A read of
+// 8 bytes a pair: each key once (its neighbours come from the next lanes),
+// four in flight; with three loads per key, 25M pairs took 81 us, now 37
+// (5.3 TB/s).
 __global__ void __launch_bounds__(kRbThreads) k_rb_runs(const uint64_t* __restrict__ keys,
                                                         const int32_t* __restrict__ fl,
                                                         uint32_t* __restrict__ tstart,
                                                         uint32_t* __restrict__ tend) {
   const int64_t P = rb_count(fl, F_PAIRS);
-  const int64_t q = (int64_t)blockIdx.x * kRbThreads + threadIdx.x;
-  if (q >= P) return;
-  const uint32_t t = (uint32_t)(keys[q] >> 32);
-  if (q == 0 || (uint32_t)(keys[q - 1] >> 32) != t) tstart[t] = (uint32_t)q;
-  if (q == P - 1 || (uint32_t)(keys[q + 1] >> 32) != t) tend[t] = (uint32_t)(q + 1);
+  const int64_t b0 = (int64_t)blockIdx.x * (kRbThreads * kRunsPer), q0 = b0 + threadIdx.x;
+  if (b0 >= P) return;
+  // (the first and last lane fetch the neighbour outside the wavefront)
+  const uint32_t* tile = reinterpret_cast<const uint32_t*>(keys) + 1;
+  constexpr uint32_t kNone = 0xFFFFFFFFu;  // (no tile id)
+  const int lane = lane_id();
+  uint32_t t[kRunsPer], side[kRunsPer];
+#pragma unroll
+  for (int k = 0; k < kRunsPer; ++k) {
+    const int64_t q = q0 + k * kRbThreads, n = lane == 0 ? q - 1 : q + 1;
+    t[k] = q < P ? tile[2 * q] : kNone;
+    side[k] = (lane == 0 || lane == kWave - 1) && n >= 0 && n < P ? tile[2 * n] : kNone;
+  }
+#pragma unroll
+  for (int k = 0; k < kRunsPer; ++k) {
+    const int64_t q = q0 + k * kRbThreads;
+    const uint32_t up = __shfl_up(t[k], 1, kWave), down = __shfl_down(t[k], 1, kWave);
+    if (q < P) {
+      if ((lane == 0 ? side[k] : up) != t[k]) tstart[t[k]] = (uint32_t)q;
+      if ((lane == kWave - 1 ? side[k] : down) != t[k]) tend[t[k]] = (uint32_t)(q + 1);
+    }
+  }
 }
 
 }  // namespace
@@ -602,7 +653,7 @@ RbBuffers rb_buffers(const Plan& P, void* ws) {
   B.spay = ws_at<uint4>(ws, P.off_rb_spay);
   B.items = ws_at<uint2>(ws, P.off_rb_items);
   B.emit = RbEmit{ws_at<uint64_t>(ws, P.off_keys), ws_at<uint32_t>(ws, P.off_vals),
-                  ws_at<uint32_t>(ws, P.off_sorted_rec), ws_at<uint32_t>(ws, P.off_rb_zrec),
+                  ws_at<uint32_t>(ws, P.off_sorted_rec), ws_at<uint32_t>(ws, P.off_zbits),
                   nullptr, nullptr};
   return B;
 }
@@ -618,16 +669,26 @@ void rb_pass(const RbBuffers& B, hipStream_t s, const uint32_t* kin, const uint3
   hipLaunchKernelGGL(k_rb_hist, grid, block, 0, s, kin, B.fl, which, B.hist, nb_cap, shift, bits);
   hipLaunchKernelGGL(k_rb_digit_scan, dim3(1u << bits), block, 0, s, B.hist, B.fl, which, B.dtot,
                      nb_cap);
-#define GS_RB_SCATTER(E, T, OUT)                                                                \
-  hipLaunchKernelGGL((k_rb_scatter<E, T>), grid, block, 0, s, kin, vin, vin2, kout, vout, vout2, \
-                     OUT, B.fl, which, B.hist, B.dtot, nb_cap, shift, bits)
+#define GS_RB_SCATTER_N(E, T, N, OUT)                                                          \
+  hipLaunchKernelGGL((k_rb_scatter<E, T, N>), grid, block, 0, s, kin, vin, vin2, kout, vout,  \
+                     vout2, OUT, B.fl, which, B.hist, B.dtot, nb_cap, shift, bits)
+#define GS_RB_SCATTER(E, T, OUT)             \
+  if (bits > 8)                              \
+    GS_RB_SCATTER_N(E, T, kRbMaxBits, OUT);  \
+  else                                       \
+    GS_RB_SCATTER_N(E, T, 8, OUT)
   if (emit) {  // (the lists' record ids come along as second values)
     GS_RB_SCATTER(true, true, B.emit);
   } else {
-    if (vin2) GS_RB_SCATTER(false, true, RbEmit{});
-    else GS_RB_SCATTER(false, false, (RbEmit{nullptr, nullptr, nullptr, nullptr, B.pay, spay}));
+    if (vin2) {
+      GS_RB_SCATTER(false, true, RbEmit{});
+    } else {
+      const RbEmit out{nullptr, nullptr, nullptr, nullptr, B.pay, spay};
+      GS_RB_SCATTER(false, false, out);
+    }
   }
 #undef GS_RB_SCATTER
+#undef GS_RB_SCATTER_N
 }
 
 }  // namespace
@@ -649,10 +710,9 @@ hipError_t launch_rb_generate(const Plan& P, void* ws, hipStream_t s) {
   if (P.n_chunks <= 0 || P.rb_rec_blocks <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_rb_visible, dim3((unsigned)((P.n_chunks + 3) / 4)), dim3(256), 0, s, B.tt,
                      B.poff, ws_at<uint2>(ws, P.off_chunk_pre), P.chunks_per_view, P.n_chunks,
-                     ws_at<Rec>(ws, P.off_rec), ws_at<uint2>(ws, P.off_rect), P.n,
+                     ws_at<uint32_t>(ws, P.off_zbits), ws_at<uint2>(ws, P.off_rect), P.n,
                      ws_at<int32_t>(ws, P.off_flags), heavy_list(P, ws), B.vis,
-                     ws_at<uint32_t>(ws, P.off_vis_clamp), B.dk[0], B.pay,
-                     ws_at<uint32_t>(ws, P.off_rb_zrec));
+                     B.dk[0], B.pay);
   // depth bits in four 8-bit passes; values: visible-list positions (the
   // first pass takes each key's own position); the last pass writes the
   // records' generation payloads in depth order instead
@@ -699,7 +759,8 @@ hipError_t launch_rb_tile_sort(const Plan& P, void* ws, hipStream_t s) {
 // Step 5: list bounds per tile from the sorted keys (for the tile scan).
 hipError_t launch_rb_runs(const Plan& P, void* ws, hipStream_t s) {
   if (P.rb_pair_blocks <= 0) return hipSuccess;
-  const int64_t blocks = P.rb_pair_blocks * (kRbTile / kRbThreads);
+  constexpr int64_t per = kRbThreads * kRunsPer;
+  const int64_t blocks = (P.rb_pair_blocks * kRbTile + per - 1) / per;
   hipLaunchKernelGGL(k_rb_runs, dim3((unsigned)blocks), dim3(kRbThreads), 0, s,
                      ws_at<uint64_t>(ws, P.off_keys), ws_at<int32_t>(ws, P.off_flags),
                      ws_at<uint32_t>(ws, P.off_tile_start), ws_at<uint32_t>(ws, P.off_tile_cnt));

@@ -463,9 +463,9 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_down(ScanArgs A,
 __global__ void __launch_bounds__(256) k_scatter(
     const uint32_t* __restrict__ tt, uint32_t* __restrict__ poff,
     const uint2* __restrict__ chunk_pre, int64_t chunks_per_view, int64_t n_chunks,
-    const ushort4* __restrict__ rect, const Rec* __restrict__ rec, int64_t n, ViewTable vt,
+    const ushort4* __restrict__ rect, const uint32_t* __restrict__ zbits, int64_t n, ViewTable vt,
     int32_t* __restrict__ fl, HeavyList heavy, TileCounters cursors, uint64_t* __restrict__ skey, uint32_t* __restrict__ pair_rec,
-    uint32_t* __restrict__ vis_list, uint32_t* __restrict__ vis_clamp) {
+    uint32_t* __restrict__ vis_list) {
   constexpr int NW = 256 / kWave;
   __shared__ uint32_t s_pre[NW][kWave];
   __shared__ uint32_t s_p0[NW][kWave], s_dbits[NW][kWave], s_x0y0[NW][kWave];
@@ -483,11 +483,10 @@ __global__ void __launch_bounds__(256) k_scatter(
   // the record's tile box and depth are fetched before the scan of the
   // counts, which then runs while they are in flight (DPP, no LDS)
   ushort4 r = make_ushort4(0, 0, 0, 0);
-  uint32_t dbits = 0, cbits = 0;
+  uint32_t dbits = 0;
   if (c > 0) {
     r = rect[ri];
-    dbits = __float_as_uint(rec[ri].z);
-    cbits = rec[ri].clamp;  // (same line as the depth)
+    dbits = zbits[ri];
   }
   const uint32_t incl = scan_dpp<6>(c);
   const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
@@ -500,7 +499,6 @@ __global__ void __launch_bounds__(256) k_scatter(
     poff[ri] = p0;
     const uint32_t vp = cp.y + (uint32_t)__popcll(vmask & lanemask_lt());
     vis_list[vp] = (uint32_t)ri;
-    vis_clamp[vp] = cbits;
     note_heavy(heavy, fl, c, (uint32_t)ri);
     x0y0 = (uint32_t)r.x | ((uint32_t)r.y << 16);
     tile0 = (uint32_t)(r.z - r.x);  // box width in tiles
@@ -696,9 +694,9 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
     const int64_t blocks = (P.n_chunks + 3) / 4;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(256), 0, s, tt, poff, chunk_pre,
                        P.chunks_per_view, P.n_chunks, ws_at<ushort4>(ws, P.off_rect),
-                       ws_at<Rec>(ws, P.off_rec), P.n, P.vt, fl, heavy_list(P, ws), tile_counters(P, ws),
+                       ws_at<uint32_t>(ws, P.off_zbits), P.n, P.vt, fl, heavy_list(P, ws), tile_counters(P, ws),
                        skey, pair_rec,
-                       ws_at<uint32_t>(ws, P.off_vis_list), ws_at<uint32_t>(ws, P.off_vis_clamp));
+                       ws_at<uint32_t>(ws, P.off_vis_list));
   }
   if ((e = mk.at(GS_MARK_BIN_SCATTER, s)) != hipSuccess) return e;
   if (T > 0) {

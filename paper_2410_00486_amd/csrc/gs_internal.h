@@ -107,6 +107,16 @@ struct RecSrc {
   __device__ __forceinline__ const Rec* at(uint32_t k) const { return base + idx[k]; }
 };
 
+// Consecutive workgroups go to the eight XCDs in turn, each with an L2 of its
+// own.  Work items that read the same data (neighbouring tiles share splats,
+// the blocks of a tile its list, the buckets of a tile its pixels) sit next
+// to each other in the item order, so 32 consecutive items are given to one
+// XCD: workgroup b takes item xcd_item(b) (a permutation of each 256; the
+// grid's last part, below 256, is left as it is).
+__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
+  return (b | 255u) < n ? (b & ~255u) + (b & 7u) * 32u + ((b & 255u) >> 3) : b;
+}
+
 // Per-pair gradient partial written by the backward raster kernel:
 // rgb(3), depth, opacity, conic a b c, mean x y: ten floats, 40 bytes, so
 // slots are 8-byte aligned and move as five float2.
@@ -179,7 +189,7 @@ struct Plan {
   size_t off_flags, off_rec, off_rect, off_tt, off_poff;
   size_t off_chunk_cnt, off_chunk_pre;  // per chunk: (pairs, visible) counts and offsets
   size_t off_vis_list;                  // visible records in index order
-  size_t off_vis_clamp;                 // their colour clamp bits, same order
+  size_t off_zbits, off_clamp;          // per record: depth (float bits), colour clamp bits (bytes)
   size_t off_heavy;                     // several views: records of many pairs
   uint32_t heavy_cap;
   int32_t cnt_copies;  // copies of the tiles' pair counters, cnt_stride words apart
@@ -207,7 +217,6 @@ struct Plan {
   // the pair offsets and work items of groups of depth-sorted records
   size_t off_rb_dkey[2], off_rb_rid[2], off_rb_tkey[2], off_rb_gidx[2], off_rb_ridx[2];
   size_t off_rb_hist, off_rb_dtot, off_rb_part, off_rb_items, off_rb_pay, off_rb_spay;
-  size_t off_rb_zrec;
   int64_t rb_rec_blocks, rb_pair_blocks;
   size_t ws_size;
 };

@@ -59,7 +59,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     const float* __restrict__ quats, const float* __restrict__ logits,
     const float* __restrict__ sh, int64_t n, const float* __restrict__ cams, ViewTable vt,
     uint32_t flags, Rec* __restrict__ rec, ushort4* __restrict__ rect,
-    uint32_t* __restrict__ tt, TileCounters counters, uint2* __restrict__ chunk_cnt,
+    uint32_t* __restrict__ zbits, uint8_t* __restrict__ clamp, uint32_t* __restrict__ tt,
+    TileCounters counters, uint2* __restrict__ chunk_cnt,
     int64_t chunks_per_view, int32_t* __restrict__ fl) {
   constexpr int K = (DEG + 1) * (DEG + 1);
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -250,6 +251,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         r.b = rgb[2];
         r.clamp = clamp_mask;
         rec[ri] = r;
+        // (again apart from the record, for kernels that need only these)
+        zbits[ri] = __float_as_uint(r.z);
+        clamp[ri] = (uint8_t)clamp_mask;
         rect[ri] = make_ushort4((unsigned short)x0, (unsigned short)y0, (unsigned short)x1,
                                 (unsigned short)y1);
         count = (uint32_t)((x1 - x0) * (y1 - y0));
@@ -313,13 +317,15 @@ hipError_t launch_preprocess(const Plan& P, const gs_gaussians& g, const float* 
   Rec* rec = ws_at<Rec>(ws, P.off_rec);
   ushort4* rect = ws_at<ushort4>(ws, P.off_rect);
   uint32_t* tt = ws_at<uint32_t>(ws, P.off_tt);
+  uint32_t* zbits = ws_at<uint32_t>(ws, P.off_zbits);
+  uint8_t* clamp = ws_at<uint8_t>(ws, P.off_clamp);
   uint2* chunk_cnt = ws_at<uint2>(ws, P.off_chunk_cnt);
   int32_t* fl = ws_at<int32_t>(ws, P.off_flags);
   const uint32_t flags = P.cfg.flags;
 #define GS_PRE(D)                                                                          \
   hipLaunchKernelGGL(k_preprocess<D>, dim3((unsigned)blocks), dim3(threads), 0, s, g.means, \
                      g.log_scales, g.quats, g.opacity_logits, g.sh, P.n, cams, P.vt, flags,  \
-                     rec, rect, tt, tile_counters(P, ws), chunk_cnt, P.chunks_per_view, fl)
+                     rec, rect, zbits, clamp, tt, tile_counters(P, ws), chunk_cnt, P.chunks_per_view, fl)
   switch (P.deg) {
     case 0: GS_PRE(0); break;
     case 1: GS_PRE(1); break;

@@ -132,16 +132,6 @@ constexpr int sub_tiles() {
   return TW * TH / (kSub * kSub);
 }
 
-// Consecutive workgroups go to the eight XCDs in turn, each with an L2 of its
-// own.  Work items that read the same data (neighbouring tiles share splats,
-// the blocks of a tile its list, the buckets of a tile its pixels) sit next
-// to each other in the item order, so 32 consecutive items are given to one
-// XCD: workgroup b takes item xcd_item(b) (a permutation of each 256; the
-// grid's last part, below 256, is left as it is).
-__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t n) {
-  return (b | 255u) < n ? (b & ~255u) + (b & 7u) * 32u + ((b & 255u) >> 3) : b;
-}
-
 // The largest last position over a tile's sub-tiles.
 template <int NS>
 __device__ __forceinline__ uint32_t tile_last_of(const uint32_t* __restrict__ tile_last,

@@ -384,3 +384,34 @@ def test_differentiable_call_grows_and_may_be_dropped():
         assert torch.equal(color, want[0])
         for a, b in zip(grads, want[1]):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,log_scale,capacity", [
+    (9000, -2.2, 1 << 20),    # more blocks in the grid than the 256 that are dealt to the dies
+    (700_000, -6.0, 1 << 20),  # and in the depth passes
+])
+def test_radix_passes_over_many_blocks(n, log_scale, capacity):
+    """The radix binning's lists equal the per-tile binning's where the passes
+    run over many blocks, most of them or few of them with keys."""
+    w = scenes.tiny_scene(41, n=n, width=640, height=480, f=500.0)
+    cam = w.cameras[0]
+    g = gsr.Gaussians.from_scene(w.scene, DEV)
+    g.log_scales.fill_(log_scale)
+    ct = gsr.cameras_tensor([cam, cam], DEV)
+    wh = [(640, 480)] * 2
+    print(f"radix passes n {n} log-scale {log_scale}", flush=True)
+    got = []
+    for flags in (0, L.GS_RADIX_BIN):
+        plan = gsr.Plan(n, 0, wh, tile=(8, 8), flags=flags, pair_capacity=8 * capacity)
+        ws = plan.new_workspace(DEV)
+        gsr.preprocess(plan, ws, g, ct)
+        gsr.bin_sort(plan, ws)
+        torch.cuda.synchronize()
+        fl = plan.flags_of(ws)
+        assert fl[L.F_OVERFLOW] == 0 and fl[L.F_PAIRS] > capacity // 2
+        P, T = int(fl[L.F_PAIRS]), plan.total_tiles
+        got.append([plan.region(ws, r, dt, c).cpu().numpy().copy() for r, dt, c in (
+            (L.GS_WS_SORTED_KEYS, torch.int64, P), (L.GS_WS_SORTED_VALS, torch.int32, P),
+            (L.GS_WS_SORTED_RECS, torch.int32, P), (L.GS_WS_RANGES, torch.int32, 2 * T))])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
