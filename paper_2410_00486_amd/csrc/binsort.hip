@@ -372,9 +372,10 @@ __global__ void __launch_bounds__(kScanBlock) k_scans(ScanArgs A, int64_t cap,
   if (threadIdx.x == 0) scan_finish(A, c64, c32, cap, fl, st);
 }
 
-// Larger plans: one block per round in three launches.  Per-round totals of
-// every channel (reduce), their exclusive scan and the flags (top, one
-// block), then every round again from its carry (down).
+// Larger plans: one block per round in two launches.  Per-round totals of
+// every channel (reduce), then every round again from its carry (down; the
+// last block sets the flags).  The carries were scanned by a launch of one
+// block in between: 23.3 -> 19.6 us for 12750 tiles and 4700 chunks.
 struct ScanPart {
   uint64_t p64[2];
   uint32_t p32[kScanN32];
@@ -402,19 +403,24 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_reduce(ScanArgs A,
   }
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_scan_top(ScanArgs A, ScanPart* __restrict__ part,
-                                                         int64_t n_parts, int64_t cap,
-                                                         int32_t* __restrict__ fl, StepAdvance st) {
+// Each block adds up the partial sums before its own instead of waiting for
+// a launch that scans them; the last block has the totals.
+__global__ void __launch_bounds__(kScanBlock) k_scan_down(ScanArgs A,
+                                                          const ScanPart* __restrict__ part,
+                                                          int64_t cap, int32_t* __restrict__ fl,
+                                                          StepAdvance st) {
   constexpr int NW = kScanBlock / kWave;
   __shared__ uint64_t w64[2 * (NW + 1)];
   __shared__ uint32_t w32[kScanN32 * (NW + 1)];
+  ScanRound R;
+  scan_load(A, blockIdx.x, R);  // (in flight while the partial sums are added)
   uint64_t c64[2] = {0, 0};
   uint32_t c32[kScanN32] = {};
-  for (int64_t base = 0; base < n_parts; base += kScanBlock) {
-    const int64_t i = base + threadIdx.x;
+  for (uint32_t base = 0; base < blockIdx.x; base += kScanBlock) {
+    const uint32_t i = base + threadIdx.x;
     uint64_t s64[2] = {0, 0};
     uint32_t s32[kScanN32] = {};
-    if (i < n_parts) {
+    if (i < blockIdx.x) {
       const ScanPart p = part[i];
       s64[0] = p.p64[0];
       s64[1] = p.p64[1];
@@ -422,33 +428,10 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_top(ScanArgs A, ScanPart* _
       for (int c = 0; c < kScanN32; ++c) s32[c] = p.p32[c];
     }
     block_exscan<2, kScanN32>(s64, s32, c64, c32, w64, w32);
-    if (i < n_parts) {
-      ScanPart p;
-      p.p64[0] = s64[0];
-      p.p64[1] = s64[1];
-#pragma unroll
-      for (int c = 0; c < kScanN32; ++c) p.p32[c] = s32[c];
-      p.pad = 0u;
-      part[i] = p;
-    }
   }
-  if (threadIdx.x == 0) scan_finish(A, c64, c32, cap, fl, st);
-}
-
-__global__ void __launch_bounds__(kScanBlock) k_scan_down(ScanArgs A,
-                                                          const ScanPart* __restrict__ part) {
-  constexpr int NW = kScanBlock / kWave;
-  __shared__ uint64_t w64[2 * (NW + 1)];
-  __shared__ uint32_t w32[kScanN32 * (NW + 1)];
-  const ScanPart p = part[blockIdx.x];  // exclusive carry of this round
-  uint64_t c64[2] = {p.p64[0], p.p64[1]};
-  uint32_t c32[kScanN32];
-#pragma unroll
-  for (int c = 0; c < kScanN32; ++c) c32[c] = p.p32[c];
-  ScanRound R;
-  scan_load(A, blockIdx.x, R);
   round_exscan(R.s64, R.s32, c64, c32, w64, w32);
   scan_emit(A, R);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) scan_finish(A, c64, c32, cap, fl, st);
 }
 
 // ---------------------------------------------------------------- scatter
@@ -641,7 +624,7 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
               P.splat ? ws_at<uint32_t>(ws, P.off_boff) : nullptr,
               ws_at<uint32_t>(ws, P.off_order), long_list, kScanBoth};
   // always launched, so that the flags are always set: one block for a
-  // plan of one round, one block per round in three launches beyond
+  // plan of one round, one block per round in two launches beyond
   const StepAdvance adv = step ? *step : StepAdvance{};
   auto scan = [&](const ScanArgs& a, const StepAdvance& st) {
     if (P.scan_rounds <= 1) {
@@ -651,9 +634,8 @@ hipError_t launch_bin_sort(const Plan& P, void* ws, hipStream_t s, const StepAdv
       ScanPart* part = ws_at<ScanPart>(ws, P.off_scan_part);
       const unsigned rounds = (unsigned)P.scan_rounds;
       hipLaunchKernelGGL(k_scan_reduce, dim3(rounds), dim3(kScanBlock), 0, s, a, part);
-      hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanBlock), 0, s, a, part, P.scan_rounds,
-                         P.pair_cap, fl, st);
-      hipLaunchKernelGGL(k_scan_down, dim3(rounds), dim3(kScanBlock), 0, s, a, part);
+      hipLaunchKernelGGL(k_scan_down, dim3(rounds), dim3(kScanBlock), 0, s, a, part, P.pair_cap, fl,
+                         st);
     }
   };
   if (radix) {
