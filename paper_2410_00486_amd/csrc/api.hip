@@ -254,7 +254,8 @@ gs_status gs_plan_init(gs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_vi
   P->off_grad_pair = take(cap * kPairGrad * 4);
   P->off_pose_part = take((size_t)n_views * std::max<int64_t>(P->proj_blocks, 1) * 6 * 8);
   P->off_order = take(T * 4 * kOrderClasses);
-  P->off_rec_terms = take(n_views > 1 ? nrec * 14 * 8 : 0);
+  P->off_rec_terms = take(n_views > 1 ? nrec * 10 * 8 : 0);
+  P->off_rec_colour = take(n_views > 1 ? nrec * 4 * 8 : 0);
   P->off_gp_tmp = take(n_views > 1 ? (size_t)n * 4 * 8 : 0);
   P->off_ssim_maps = take((size_t)pix * 9 * 4);
   P->off_ssim_part = take((size_t)ssim_tiles(*P) * 12 * 4);

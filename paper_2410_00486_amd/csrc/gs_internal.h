@@ -200,7 +200,7 @@ struct Plan {
   size_t off_grad_pair, off_pose_part, off_order;
   // several views: per record, its projection-backward terms; per
   // Gaussian, the projection half's mean gradient
-  size_t off_rec_terms, off_gp_tmp;
+  size_t off_rec_terms, off_rec_colour, off_gp_tmp;
   size_t off_ssim_maps, off_ssim_part;
   // splat-wise backward (8x8 tiles): bucket offsets, bucket queue, pixel
   // states, and what the forward kept of the lists
