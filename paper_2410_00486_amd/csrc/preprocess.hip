@@ -24,6 +24,7 @@ constexpr double kSH3e = 1.445305721320277;    // sqrt(105/pi)/4
 // Real orthonormal SH with the Condon-Shortley phase at unit direction (x,y,z).
 template <int DEG>
 __device__ __forceinline__ void sh_basis(double x, double y, double z, double* Y) {
+#pragma clang fp contract(fast)
   Y[0] = kSH0;
   if (DEG >= 1) {
     Y[1] = -kSH1 * y;
@@ -51,6 +52,28 @@ __device__ __forceinline__ void sh_basis(double x, double y, double z, double* Y
 
 __device__ __forceinline__ bool finite_f(float v) { return __builtin_isfinite(v); }
 
+// FP64 sums of products, with fused multiply-adds (half the instructions; the
+// FP32 code beside them is compiled without: its bits decide the forward's
+// thresholds).  The projection is bound by VALU issue (16 views of 2M
+// Gaussians, 277 instructions a wavefront and view, most of them FP64): with
+// these and the view's constants taken out of the loop 395 -> 340 us; eight
+// mixed views of 500k 94 -> 83, four views of 500k (one in three records
+// visible) 106 -> 96.
+__device__ __forceinline__ double dot3(double a0, double a1, double a2, double b0, double b1,
+                                       double b2) {
+  return fma(a2, b2, fma(a1, b1, a0 * b0));
+}
+__device__ __forceinline__ double dot3(double a0, double a1, double a2, double b0, double b1,
+                                       double b2, double c) {
+  return fma(a2, b2, fma(a1, b1, fma(a0, b0, c)));
+}
+
+// What a view's projections share: the limits of the clamped ray and the
+// camera centre -W^T t.
+struct ViewConsts {
+  double limx, limy, cx, cy, cz, pad;
+};
+
 
 // (three waves per SIMD: at most 168 VGPRs)
 template <int DEG>
@@ -63,6 +86,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     TileCounters counters, uint2* __restrict__ chunk_cnt,
     int64_t chunks_per_view, int32_t* __restrict__ fl) {
   constexpr int K = (DEG + 1) * (DEG + 1);
+  // once per workgroup: three FP64 divisions' worth of work per view that
+  // every wavefront repeated
+  __shared__ ViewConsts s_view[kMaxViews];
+  for (int v = (int)threadIdx.x; v < vt.n_views; v += (int)blockDim.x) {
+    const float* c = cams + (int64_t)v * GS_CAMERA_FLOATS;
+    const double t0 = c[13], t1 = c[14], t2 = c[15];
+    ViewConsts k;
+    k.limx = 1.3 * (double)vt.v[v].W / (2.0 * (double)c[0]);
+    k.limy = 1.3 * (double)vt.v[v].H / (2.0 * (double)c[1]);
+    k.cx = -dot3(c[4], c[7], c[10], t0, t1, t2);
+    k.cy = -dot3(c[5], c[8], c[11], t0, t1, t2);
+    k.cz = -dot3(c[6], c[9], c[12], t0, t1, t2);
+    k.pad = 0.0;
+    s_view[v] = k;
+  }
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   uint32_t* tile_cnt = count_copy(counters, (int64_t)blockIdx.x * (256 / kWave));
   // lanes past the end stay active (as an invalid Gaussian) so that the
@@ -109,6 +147,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
   float shv[K * 3];
 
   __shared__ uint32_t s_pre[256 / kWave][kWave], s_xy[256 / kWave][kWave], s_w[256 / kWave][kWave];
+  __syncthreads();  // s_view
   for (int v = 0; v < vt.n_views; ++v) {
     const ViewInfo vi = vt.v[v];
     const int64_t ri = (int64_t)v * n + i;
@@ -119,18 +158,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
       const double W0 = c[4], W1 = c[5], W2 = c[6], W3 = c[7], W4 = c[8], W5 = c[9];
       const double W6 = c[10], W7 = c[11], W8 = c[12];
       const double t0 = c[13], t1 = c[14], t2 = c[15], near_z = c[16];
-      const double tx = W0 * p[0] + W1 * p[1] + W2 * p[2] + t0;
-      const double ty = W3 * p[0] + W4 * p[1] + W5 * p[2] + t1;
-      const double tz = W6 * p[0] + W7 * p[1] + W8 * p[2] + t2;
+      const double tx = dot3(W0, W1, W2, p[0], p[1], p[2], t0);
+      const double ty = dot3(W3, W4, W5, p[0], p[1], p[2], t1);
+      const double tz = dot3(W6, W7, W8, p[0], p[1], p[2], t2);
       bool vis = tz > near_z;
       double mx = 0, my = 0, A = 0, B = 0, C = 0, det = 0;
       double j00 = 0, j02 = 0, j11 = 0, j12 = 0;
       if (vis) {
         const double itz = 1.0 / tz;
-        mx = fx * tx * itz + cx;
-        my = fy * ty * itz + cy;
-        const double limx = 1.3 * (double)vi.W / (2.0 * fx);
-        const double limy = 1.3 * (double)vi.H / (2.0 * fy);
+        mx = fma(fx * tx, itz, cx);
+        my = fma(fy * ty, itz, cy);
+        const double limx = s_view[v].limx, limy = s_view[v].limy;
         const double u = fmin(limx, fmax(-limx, tx * itz));
         const double w = fmin(limy, fmax(-limy, ty * itz));
         // rows of T2 = J W
@@ -152,19 +190,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         }
       }
       if (vis) {
-        const double a0 = j00 * W0 + j02 * W6, a1 = j00 * W1 + j02 * W7, a2 = j00 * W2 + j02 * W8;
-        const double b0 = j11 * W3 + j12 * W6, b1 = j11 * W4 + j12 * W7, b2 = j11 * W5 + j12 * W8;
+        const double a0 = fma(j02, W6, j00 * W0), a1 = fma(j02, W7, j00 * W1),
+                     a2 = fma(j02, W8, j00 * W2);
+        const double b0 = fma(j12, W6, j11 * W3), b1 = fma(j12, W7, j11 * W4),
+                     b2 = fma(j12, W8, j11 * W5);
         // Sigma a, Sigma b
-        const double Sa0 = S00 * a0 + S01 * a1 + S02 * a2;
-        const double Sa1 = S01 * a0 + S11 * a1 + S12 * a2;
-        const double Sa2 = S02 * a0 + S12 * a1 + S22 * a2;
-        const double Sb0 = S00 * b0 + S01 * b1 + S02 * b2;
-        const double Sb1 = S01 * b0 + S11 * b1 + S12 * b2;
-        const double Sb2 = S02 * b0 + S12 * b1 + S22 * b2;
-        A = a0 * Sa0 + a1 * Sa1 + a2 * Sa2 + 0.3;
-        B = 0.5 * ((a0 * Sb0 + a1 * Sb1 + a2 * Sb2) + (b0 * Sa0 + b1 * Sa1 + b2 * Sa2));
-        C = b0 * Sb0 + b1 * Sb1 + b2 * Sb2 + 0.3;
-        det = A * C - B * B;
+        const double Sa0 = dot3(S00, S01, S02, a0, a1, a2);
+        const double Sa1 = dot3(S01, S11, S12, a0, a1, a2);
+        const double Sa2 = dot3(S02, S12, S22, a0, a1, a2);
+        const double Sb0 = dot3(S00, S01, S02, b0, b1, b2);
+        const double Sb1 = dot3(S01, S11, S12, b0, b1, b2);
+        const double Sb2 = dot3(S02, S12, S22, b0, b1, b2);
+        A = dot3(a0, a1, a2, Sa0, Sa1, Sa2, 0.3);
+        B = 0.5 * (dot3(a0, a1, a2, Sb0, Sb1, Sb2) + dot3(b0, b1, b2, Sa0, Sa1, Sa2));
+        C = dot3(b0, b1, b2, Sb0, Sb1, Sb2, 0.3);
+        det = fma(A, C, -(B * B));
         vis = (det > 0.0) && (o >= 1.0 / 255.0);
       }
       int x0 = 0, y0 = 0, x1 = 0, y1 = 0;
@@ -207,12 +247,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         }
       }
       if (vis) {
-        // view direction from the camera centre c = -W^T t
-        const double cxw = -(W0 * t0 + W3 * t1 + W6 * t2);
-        const double cyw = -(W1 * t0 + W4 * t1 + W7 * t2);
-        const double czw = -(W2 * t0 + W5 * t1 + W8 * t2);
-        const double dx = p[0] - cxw, dy = p[1] - cyw, dz = p[2] - czw;
-        const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+        // view direction from the camera centre
+        const double dx = p[0] - s_view[v].cx, dy = p[1] - s_view[v].cy, dz = p[2] - s_view[v].cz;
+        const double inv = 1.0 / sqrt(dot3(dx, dy, dz, dx, dy, dz));
         double Y[16];
         sh_basis<DEG>(dx * inv, dy * inv, dz * inv, Y);
         float rgb[3];
@@ -221,7 +258,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         for (int ch = 0; ch < 3; ++ch) {
           double acc = 0.0;
 #pragma unroll
-          for (int k = 0; k < K; ++k) acc += (double)shv[3 * k + ch] * Y[k];
+          for (int k = 0; k < K; ++k) acc = fma((double)shv[3 * k + ch], Y[k], acc);
           rgb[ch] = (float)fmax(0.0, acc + 0.5);
           if (acc + 0.5 < 0.0) clamp_mask |= 1u << ch;
         }
