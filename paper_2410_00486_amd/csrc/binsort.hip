@@ -547,9 +547,8 @@ __global__ void __launch_bounds__(kSortWaves * kWave) __attribute__((amdgpu_wave
     const uint64_t tkey = (uint64_t)e.x << 32;
     constexpr uint32_t NT = kSortWaves * kWave;
     if (n <= kTileSortLong) {
-      for (uint32_t k = threadIdx.x; k < n; k += NT) sk[k] = skey[start + k];
+      sort_keys_block(skey + start, n, w, lane, sk);
       __syncthreads();
-      bitonic_sort(sk, n, threadIdx.x, NT);
       for (uint32_t k = threadIdx.x; k < n; k += NT) emit_sorted(A.out, start + k, tkey, sk[k]);
     } else {
       bitonic_sort(skey + start, n, threadIdx.x, NT);

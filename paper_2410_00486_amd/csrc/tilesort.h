@@ -77,25 +77,130 @@ __device__ inline void bitonic_sort(uint64_t* k, uint32_t n, uint32_t tid, uint3
   }
 }
 
-// Sorts k[0, n) ascending in LDS with the 64 lanes of one wavefront and
-// wavefront-level syncs only (the other wavefronts of its workgroup sort
-// their own lists meanwhile).
-__device__ inline void bitonic_sort_wave(uint64_t* k, uint32_t n, uint32_t lane) {
-  uint32_t m = 1;
-  while (m < n) m <<= 1;
-  for (uint32_t size = 2; size <= m; size <<= 1) {
-    const uint32_t half = size >> 1;
-    for (uint32_t idx = lane; idx < m / 2; idx += kWave) {
-      const uint32_t blk = idx / half, off = idx % half;
-      cmp_swap(k, blk * size + off, blk * size + size - 1 - off, n);
-    }
-    wave_lds_sync();
-    for (uint32_t stride = size >> 2; stride > 0; stride >>= 1) {
-      for (uint32_t idx = lane; idx < m / 2; idx += kWave) {
-        const uint32_t a = 2 * idx - (idx & (stride - 1));
-        cmp_swap(k, a, a + stride, n);
+// Both keys of a compare-exchange between lanes a distance of X apart: the
+// lane's own and its partner's, in either order.
+template <int X>
+__device__ __forceinline__ void lane_pair(uint32_t& a, uint32_t& b) {
+  if constexpr (X == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    a = r[0];
+    b = r[1];
+  } else if constexpr (X == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+    a = r[0];
+    b = r[1];
+  } else if constexpr (X == 8) {
+    b = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x128, 0xF, 0xF, true);  // row_ror:8
+  } else if constexpr (X == 4) {  // row_shl:4 into the lower four of eight lanes, row_shr:4 the upper
+    b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x104, 0xF, 0x5, true);
+    b = (uint32_t)__builtin_amdgcn_update_dpp((int)b, (int)a, 0x114, 0xF, 0xA, true);
+  } else {  // quad_perm [1,0,3,2] or [2,3,0,1]
+    b = (uint32_t)__builtin_amdgcn_mov_dpp((int)a, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+  }
+}
+
+// Stages of the bitonic network over 64 E keys (element lane E + r is k[r]):
+// elements STRIDE, STRIDE / 2 .. apart, ascending in every other run of SIZE;
+// a run of all keys ascends if `whole_up`.
+template <int E, int SIZE, int STRIDE>
+__device__ __forceinline__ void bitonic_stage(uint64_t (&k)[E], int lane, bool whole_up) {
+  const bool lane_up = SIZE == E * kWave ? whole_up : (lane & (SIZE / E)) == 0;
+  if constexpr (STRIDE < E) {
+#pragma unroll
+    for (int r = 0; r < E; ++r)
+      if ((r & STRIDE) == 0) {
+        const bool up = SIZE < E ? (r & SIZE) == 0 : lane_up;
+        const uint64_t x = k[r], y = k[r + STRIDE];
+        const bool keep = (x < y) == up;
+        k[r] = keep ? x : y;
+        k[r + STRIDE] = keep ? y : x;
       }
-      wave_lds_sync();
+  } else {
+    constexpr int X = STRIDE / E;
+    const bool low = lane_up == ((lane & X) == 0);  // keeps the smaller one
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      uint32_t al = (uint32_t)k[r], ah = (uint32_t)(k[r] >> 32), bl, bh;
+      lane_pair<X>(al, bl);
+      lane_pair<X>(ah, bh);
+      const uint64_t x = (uint64_t)ah << 32 | al, y = (uint64_t)bh << 32 | bl;
+      k[r] = (x < y) == low ? x : y;
+    }
+  }
+  if constexpr (STRIDE > 1) bitonic_stage<E, SIZE, STRIDE / 2>(k, lane, whole_up);
+}
+template <int E, int SIZE = 2>
+__device__ __forceinline__ void bitonic_regs(uint64_t (&k)[E], int lane, bool whole_up) {
+  bitonic_stage<E, SIZE, SIZE / 2>(k, lane, whole_up);
+  if constexpr (SIZE < E * kWave) bitonic_regs<E, 2 * SIZE>(k, lane, whole_up);
+}
+
+// Sorts n <= 64 E keys from src into sk (LDS) with one wavefront: the keys
+// stay in registers through the network.  With the network in LDS (two reads
+// and two writes a comparison) the sort was bound by it: 2.7M pairs in 12900
+// lists 133 us, now 88 (110 with only the lists up to 512 in registers); 433k
+// in 12750 lists 22.5 and 15.5; 12.5k in 192 lists 13.8 and 5.4.  Up to 64
+// pairs counting the smaller keys is as fast (15.2 and 17.2 us for the 433k).
+template <int E>
+__device__ __forceinline__ void sort_keys_wave(const uint64_t* __restrict__ src, uint32_t n,
+                                               int lane, uint64_t* sk) {
+  uint64_t k[E];
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t i = (uint32_t)(r * kWave + lane);
+    k[r] = i < n ? src[i] : ~0ull;
+  }
+  bitonic_regs<E>(k, lane, true);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t i = (uint32_t)(lane * E + r);
+    if (i < n) sk[i] = k[r];
+  }
+}
+
+// Sorts 512 < n <= 512 kSortWaves keys from src into sk (LDS, as many keys)
+// with the whole workgroup: 512 keys per wavefront, as above; only the stages
+// that compare keys of different wavefronts go through LDS.
+__device__ __forceinline__ void sort_keys_block(const uint64_t* __restrict__ src, uint32_t n,
+                                                int w, int lane, uint64_t* sk) {
+  constexpr int E = kTileSortMid / kWave;
+  int waves = 2;
+  while ((uint32_t)waves * kTileSortMid < n) waves <<= 1;
+  const bool on = w < waves;
+  uint64_t k[E];
+  if (on) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const uint32_t i = (uint32_t)w * kTileSortMid + (uint32_t)(r * kWave + lane);
+      k[r] = i < n ? src[i] : ~0ull;
+    }
+    bitonic_regs<E>(k, lane, (w & 1) == 0);
+  }
+  for (int size = 2; size <= waves; size <<= 1) {
+    const bool up = (w & size) == 0;
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      if (on) {
+#pragma unroll
+        for (int r = 0; r < E; ++r) sk[w * (int)kTileSortMid + r * kWave + lane] = k[r];
+      }
+      __syncthreads();
+      if (on) {
+        const bool low = up == ((w & d) == 0);
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+          const uint64_t y = sk[(w ^ d) * (int)kTileSortMid + r * kWave + lane];
+          k[r] = (k[r] < y) == low ? k[r] : y;
+        }
+      }
+      __syncthreads();
+    }
+    if (on) bitonic_stage<E, E * kWave, E * kWave / 2>(k, lane, up);
+  }
+  if (on) {
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      const uint32_t i = (uint32_t)w * kTileSortMid + (uint32_t)(lane * E + r);
+      if (i < n) sk[i] = k[r];
     }
   }
 }
@@ -124,9 +229,10 @@ __device__ inline void sort_list_wave(const TileSortOut& o, const uint64_t* __re
                                       uint64_t tkey, uint32_t start, uint32_t n, int lane,
                                       uint64_t* sk) {
   constexpr int KMAX = MAX / kWave;
-  for (uint32_t k = lane; k < n; k += kWave) sk[k] = skey[start + k];
+  if (MAX <= 2 * kWave || n <= 2 * kWave) sort_keys_wave<2>(skey + start, n, lane, sk);
+  else if (MAX <= 4 * kWave || n <= 4 * kWave) sort_keys_wave<4>(skey + start, n, lane, sk);
+  else sort_keys_wave<8>(skey + start, n, lane, sk);
   wave_lds_sync();
-  bitonic_sort_wave(sk, n, (uint32_t)lane);
   uint32_t r[KMAX];
 #pragma unroll
   for (int q = 0; q < KMAX; ++q) {

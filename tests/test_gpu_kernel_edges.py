@@ -87,7 +87,7 @@ def test_forward_blocks_match_oracle(n, width, height, log_scale):
             np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("n", [64, 65, 128, 129, 512, 513, 1025, 8192, 8193])
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 256, 257, 512, 513, 1025, 2048, 2049, 5000, 8192, 8193])
 def test_tile_sort_list_length_edges(n):
     """One tile's list at the lengths where the sort changes its form
     (registers, a wavefront in LDS, a workgroup in LDS, global memory): keys,
