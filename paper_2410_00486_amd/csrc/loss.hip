@@ -5,8 +5,13 @@
 // the paper retains (Sec. IV-A): per channel, 11x11 Gaussian window with
 // sigma 1.5, zero padding, C1 = 0.01^2, C2 = 0.03^2.
 //
-// Stencil work on 16x16 output tiles: the 26x26 halo of the image (and the
-// target) is staged in LDS, filtered along rows then columns.  Pass 1 forms
+// Stencil work on 32x32 output tiles: the 42x42 halo of the image (and the
+// target) is staged in LDS, filtered along rows then columns, a thread forming
+// eight (four) neighbouring outputs from the inputs it reads once.  On 16x16
+// tiles, with an LDS read per tap and the halo fetched one element after
+// another, 1200x680 took 47 and 35 us, now 32 and 25 (45 and 33 before the
+// loads of the halo were issued together).  Bound by VALU issue (16 us of the
+// first) and the phases' latencies; 59 and 49 MB move.  Pass 1 forms
 // the five windowed moments, the SSIM value and its derivatives with respect
 // to the moments of C (three maps); pass 2 filters those maps with the
 // (symmetric) window -- the adjoint of the forward filtering -- and
@@ -16,9 +21,12 @@
 namespace gs {
 namespace {
 
-constexpr int kT = 16;            // output tile edge
+constexpr int kT = 32;            // output tile edge
 constexpr int kR = 5;             // window radius
-constexpr int kH = kT + 2 * kR;   // halo edge, 26
+constexpr int kH = kT + 2 * kR;   // halo edge, 42
+constexpr int kRowOut = 8;        // outputs per thread, row filter
+constexpr int kColOut = 4;        // and column filter
+static_assert(kH * (kT / kRowOut) <= 256 && kT * (kT / kColOut) == 256, "one pass of 256 threads");
 constexpr float kC1 = 1e-4f;      // 0.01^2
 constexpr float kC2 = 9e-4f;      // 0.03^2
 
@@ -41,11 +49,23 @@ __device__ __forceinline__ int ssim_view(const SsimTable& t, int tile) {
   return v;
 }
 
+// The pixel (index in its plane) of the halo element that this thread loads
+// in round u, -1 outside the image.  The loads of all rounds are issued
+// unconditionally (from the plane's first pixel instead), so that they are in
+// flight together.
+constexpr int kLoads = (kH * kH + 255) / 256;
+__device__ __forceinline__ int64_t halo_pixel(int u, int x0, int y0, const SsimView& vi) {
+  const int k = (int)threadIdx.x + 256 * u;
+  const int gx = x0 + k % kH, gy = y0 + k / kH;
+  const bool in = k < kH * kH && gx >= 0 && gy >= 0 && gx < vi.W && gy < vi.H;
+  return in ? (int64_t)gy * vi.W + gx : -1;
+}
+
 // Pass 1: grid (tiles over all views, 3 channels), 256 threads.
 __global__ void __launch_bounds__(256) k_ssim_fwd(const float* __restrict__ color,
                                                   const float* __restrict__ target,
                                                   SsimTable tb, float* __restrict__ dmaps,
-                                                  float* __restrict__ part) {
+                                                  int64_t plane, float* __restrict__ part) {
   __shared__ float sx[kH][kH + 1], sy[kH][kH + 1];
   __shared__ float hm[5][kH][kT + 1];
   __shared__ float red[2][256 / kWave];
@@ -57,41 +77,74 @@ __global__ void __launch_bounds__(256) k_ssim_fwd(const float* __restrict__ colo
   const int64_t npx = (int64_t)vi.W * vi.H;
   const float* X = color + 3 * (int64_t)vi.pix_off + ch * npx;
   const float* Y = target + 3 * (int64_t)vi.pix_off + ch * npx;
-  for (int k = threadIdx.x; k < kH * kH; k += 256) {
-    const int r = k / kH, c = k % kH, gx = x0 + c, gy = y0 + r;
-    const bool in = gx >= 0 && gy >= 0 && gx < vi.W && gy < vi.H;
-    sx[r][c] = in ? X[(int64_t)gy * vi.W + gx] : 0.0f;
-    sy[r][c] = in ? Y[(int64_t)gy * vi.W + gx] : 0.0f;
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < kH * kT; k += 256) {
-    const int r = k / kT, c = k % kT;
-    float a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0;
+  {
+    float x[kLoads], y[kLoads];
 #pragma unroll
-    for (int j = 0; j < 11; ++j) {
-      const float w = c_win[j], x = sx[r][c + j], y = sy[r][c + j];
-      a0 = fmaf(w, x, a0);
-      a1 = fmaf(w, y, a1);
-      a2 = fmaf(w, x * x, a2);
-      a3 = fmaf(w, y * y, a3);
-      a4 = fmaf(w, x * y, a4);
+    for (int u = 0; u < kLoads; ++u) {
+      const int64_t at = halo_pixel(u, x0, y0, vi);
+      x[u] = X[at < 0 ? 0 : at];
+      y[u] = Y[at < 0 ? 0 : at];
+      if (at < 0) x[u] = y[u] = 0.0f;
     }
-    hm[0][r][c] = a0; hm[1][r][c] = a1; hm[2][r][c] = a2; hm[3][r][c] = a3; hm[4][r][c] = a4;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int k = (int)threadIdx.x + 256 * u;
+      if (k < kH * kH) {
+        sx[k / kH][k % kH] = x[u];
+        sy[k / kH][k % kH] = y[u];
+      }
+    }
   }
   __syncthreads();
-  const int c = threadIdx.x % kT, r = threadIdx.x / kT;
-  float m[5] = {0, 0, 0, 0, 0};
+  if (threadIdx.x < kH * (kT / kRowOut)) {
+    const int r = threadIdx.x / (kT / kRowOut), c = threadIdx.x % (kT / kRowOut) * kRowOut;
+    float a[kRowOut][5];
 #pragma unroll
-  for (int j = 0; j < 11; ++j) {
-    const float w = c_win[j];
+    for (int o = 0; o < kRowOut; ++o)
 #pragma unroll
-    for (int q = 0; q < 5; ++q) m[q] = fmaf(w, hm[q][r + j][c], m[q]);
+      for (int q = 0; q < 5; ++q) a[o][q] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kRowOut + 2 * kR; ++j) {
+      const float x = sx[r][c + j], y = sy[r][c + j];
+      const float in5[5] = {x, y, x * x, y * y, x * y};
+#pragma unroll
+      for (int o = 0; o < kRowOut; ++o)
+        if (j - o >= 0 && j - o < 11) {
+#pragma unroll
+          for (int q = 0; q < 5; ++q) a[o][q] = fmaf(c_win[j - o], in5[q], a[o][q]);
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < kRowOut; ++o)
+#pragma unroll
+      for (int q = 0; q < 5; ++q) hm[q][r][c + o] = a[o][q];
   }
-  const int gx = x0 + kR + c, gy = y0 + kR + r;
-  const bool in = gx < vi.W && gy < vi.H;
+  __syncthreads();
+  const int c = threadIdx.x % kT, r0 = threadIdx.x / kT * kColOut;
+  float m[kColOut][5];
+#pragma unroll
+  for (int o = 0; o < kColOut; ++o)
+#pragma unroll
+    for (int q = 0; q < 5; ++q) m[o][q] = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kColOut + 2 * kR; ++j) {
+    float h[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) h[q] = hm[q][r0 + j][c];
+#pragma unroll
+    for (int o = 0; o < kColOut; ++o)
+      if (j - o >= 0 && j - o < 11) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) m[o][q] = fmaf(c_win[j - o], h[q], m[o][q]);
+      }
+  }
+  const int gx = x0 + kR + c;
   float s_val = 0.0f, l1 = 0.0f;
-  if (in) {
-    const float m1 = m[0], my = m[1], m2 = m[2], myy = m[3], m3 = m[4];
+#pragma unroll
+  for (int o = 0; o < kColOut; ++o) {
+    const int r = r0 + o, gy = y0 + kR + r;
+    if (gx >= vi.W || gy >= vi.H) continue;
+    const float m1 = m[o][0], my = m[o][1], m2 = m[o][2], myy = m[o][3], m3 = m[o][4];
     const float A1 = 2.0f * m1 * my + kC1;
     const float A2 = 2.0f * (m3 - m1 * my) + kC2;
     const float B1 = m1 * m1 + my * my + kC1;
@@ -100,12 +153,12 @@ __global__ void __launch_bounds__(256) k_ssim_fwd(const float* __restrict__ colo
     const float d1 = S * (2.0f * my / A1 - 2.0f * my / A2 - 2.0f * m1 / B1 + 2.0f * m1 / B2);
     const float d2 = -S / B2;
     const float d3 = 2.0f * S / A2;
-    const int64_t p = 3 * ((int64_t)vi.pix_off * 3 + ch * npx + (int64_t)gy * vi.W + gx);
+    const int64_t p = (int64_t)vi.pix_off * 3 + ch * npx + (int64_t)gy * vi.W + gx;
     dmaps[p] = d1;
-    dmaps[p + 1] = d2;
-    dmaps[p + 2] = d3;
-    s_val = S;
-    l1 = fabsf(sx[r + kR][c + kR] - sy[r + kR][c + kR]);
+    dmaps[p + plane] = d2;
+    dmaps[p + 2 * plane] = d3;
+    s_val += S;
+    l1 += fabsf(sx[r + kR][c + kR] - sy[r + kR][c + kR]);
   }
   s_val = wave_sum(s_val);
   l1 = wave_sum(l1);
@@ -129,7 +182,7 @@ __global__ void __launch_bounds__(256) k_ssim_fwd(const float* __restrict__ colo
 __global__ void __launch_bounds__(256) k_ssim_bwd(
     const float* __restrict__ color, const float* __restrict__ target,
     const float* __restrict__ depth, const float* __restrict__ target_depth, SsimTable tb,
-    const float* __restrict__ dmaps, float lambda_ssim, float lambda_depth,
+    const float* __restrict__ dmaps, int64_t plane, float lambda_ssim, float lambda_depth,
     float* __restrict__ dL_dcolor, float* __restrict__ dL_ddepth, float* __restrict__ part) {
   __shared__ float sd[3][kH][kH + 1];
   __shared__ float hm[3][kH][kT + 1];
@@ -141,41 +194,69 @@ __global__ void __launch_bounds__(256) k_ssim_bwd(
   const int x0 = (lt % vi.tiles_x) * kT - kR, y0 = (lt / vi.tiles_x) * kT - kR;
   const int64_t npx = (int64_t)vi.W * vi.H;
   const int64_t cbase = 3 * (int64_t)vi.pix_off + ch * npx;
-  for (int k = threadIdx.x; k < kH * kH; k += 256) {
-    const int r = k / kH, c = k % kH, gx = x0 + c, gy = y0 + r;
-    const bool in = gx >= 0 && gy >= 0 && gx < vi.W && gy < vi.H;
-    const int64_t p = 3 * (cbase + (int64_t)gy * vi.W + gx);
-    sd[0][r][c] = in ? dmaps[p] : 0.0f;
-    sd[1][r][c] = in ? dmaps[p + 1] : 0.0f;
-    sd[2][r][c] = in ? dmaps[p + 2] : 0.0f;
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < kH * kT; k += 256) {
-    const int r = k / kT, c = k % kT;
-    float a0 = 0, a1 = 0, a2 = 0;
+  {
+    float d[kLoads][3];
 #pragma unroll
-    for (int j = 0; j < 11; ++j) {
-      const float w = c_win[j];
-      a0 = fmaf(w, sd[0][r][c + j], a0);
-      a1 = fmaf(w, sd[1][r][c + j], a1);
-      a2 = fmaf(w, sd[2][r][c + j], a2);
+    for (int u = 0; u < kLoads; ++u) {
+      const int64_t at = halo_pixel(u, x0, y0, vi);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        d[u][q] = dmaps[cbase + (at < 0 ? 0 : at) + q * plane];
+        if (at < 0) d[u][q] = 0.0f;
+      }
     }
-    hm[0][r][c] = a0; hm[1][r][c] = a1; hm[2][r][c] = a2;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int k = (int)threadIdx.x + 256 * u;
+      if (k < kH * kH) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sd[q][k / kH][k % kH] = d[u][q];
+      }
+    }
   }
   __syncthreads();
-  const int c = threadIdx.x % kT, r = threadIdx.x / kT;
-  float g1 = 0, g2 = 0, g3 = 0;
+  if (threadIdx.x < kH * (kT / kRowOut)) {
+    const int r = threadIdx.x / (kT / kRowOut), c = threadIdx.x % (kT / kRowOut) * kRowOut;
+    float a[kRowOut][3];
 #pragma unroll
-  for (int j = 0; j < 11; ++j) {
-    const float w = c_win[j];
-    g1 = fmaf(w, hm[0][r + j][c], g1);
-    g2 = fmaf(w, hm[1][r + j][c], g2);
-    g3 = fmaf(w, hm[2][r + j][c], g3);
+    for (int o = 0; o < kRowOut; ++o) a[o][0] = a[o][1] = a[o][2] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kRowOut + 2 * kR; ++j) {
+      const float d[3] = {sd[0][r][c + j], sd[1][r][c + j], sd[2][r][c + j]};
+#pragma unroll
+      for (int o = 0; o < kRowOut; ++o)
+        if (j - o >= 0 && j - o < 11) {
+#pragma unroll
+          for (int q = 0; q < 3; ++q) a[o][q] = fmaf(c_win[j - o], d[q], a[o][q]);
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < kRowOut; ++o)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) hm[q][r][c + o] = a[o][q];
   }
-  const int gx = x0 + kR + c, gy = y0 + kR + r;
-  const bool in = gx < vi.W && gy < vi.H;
+  __syncthreads();
+  const int c = threadIdx.x % kT, r0 = threadIdx.x / kT * kColOut;
+  float g[kColOut][3];
+#pragma unroll
+  for (int o = 0; o < kColOut; ++o) g[o][0] = g[o][1] = g[o][2] = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kColOut + 2 * kR; ++j) {
+    const float h[3] = {hm[0][r0 + j][c], hm[1][r0 + j][c], hm[2][r0 + j][c]};
+#pragma unroll
+    for (int o = 0; o < kColOut; ++o)
+      if (j - o >= 0 && j - o < 11) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) g[o][q] = fmaf(c_win[j - o], h[q], g[o][q]);
+      }
+  }
+  const int gx = x0 + kR + c;
   float ld = 0.0f;
-  if (in) {
+#pragma unroll
+  for (int o = 0; o < kColOut; ++o) {
+    const int gy = y0 + kR + r0 + o;
+    if (gx >= vi.W || gy >= vi.H) continue;
+    const float g1 = g[o][0], g2 = g[o][1], g3 = g[o][2];
     const int64_t p = cbase + (int64_t)gy * vi.W + gx;
     const float x = color[p], y = target[p];
     const float inv_n = 1.0f / (3.0f * (float)npx);
@@ -189,7 +270,7 @@ __global__ void __launch_bounds__(256) k_ssim_bwd(
       if (target_depth) {
         const float dd = depth[q] - target_depth[q];
         gd = dd > 0.0f ? lambda_depth / (float)npx : (dd < 0.0f ? -lambda_depth / (float)npx : 0.0f);
-        ld = fabsf(dd);
+        ld += fabsf(dd);
       }
       dL_ddepth[q] = gd;
     }
@@ -276,10 +357,13 @@ hipError_t launch_render_loss(const Plan& P, void* ws, const float* color, const
   if (t == 0) return hipSuccess;
   float* dmaps = ws_at<float>(ws, P.off_ssim_maps);
   float* part = ws_at<float>(ws, P.off_ssim_part);
-  hipLaunchKernelGGL(k_ssim_fwd, dim3(t, 3), dim3(256), 0, s, color, target_rgb, tb, dmaps, part);
+  const int64_t plane = 3 * ((int64_t)P.vt.v[P.vt.n_views - 1].pix_off +
+                             (int64_t)P.vt.v[P.vt.n_views - 1].W * P.vt.v[P.vt.n_views - 1].H);
+  hipLaunchKernelGGL(k_ssim_fwd, dim3(t, 3), dim3(256), 0, s, color, target_rgb, tb, dmaps, plane,
+                     part);
   hipLaunchKernelGGL(k_ssim_bwd, dim3(t, 3), dim3(256), 0, s, color, target_rgb, depth,
-                     target_depth, tb, dmaps, (float)lambda_ssim, P.cfg.lambda_depth, dL_dcolor,
-                     dL_ddepth, part);
+                     target_depth, tb, dmaps, plane, (float)lambda_ssim, P.cfg.lambda_depth,
+                     dL_dcolor, dL_ddepth, part);
   if (loss_per_view)
     hipLaunchKernelGGL(k_ssim_loss, dim3(P.vt.n_views), dim3(256), 0, s, part, tb,
                        (float)lambda_ssim, P.cfg.lambda_depth, target_depth ? 1 : 0,

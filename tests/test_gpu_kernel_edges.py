@@ -10,6 +10,7 @@ import torch
 import oracle
 import paper_2410_00486_amd as gsr
 from oracle import densify as oracle_densify
+from oracle import ssim as oracle_ssim
 from paper_2410_00486_amd import _lib as L
 from synth import scenes
 
@@ -415,3 +416,32 @@ def test_radix_passes_over_many_blocks(n, log_scale, capacity):
             (L.GS_WS_SORTED_RECS, torch.int32, P), (L.GS_WS_RANGES, torch.int32, 2 * T))])
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+# ------------------------------------------------------------------ SSIM tiles
+
+@pytest.mark.parametrize("views", [[(32, 32)], [(33, 31)], [(8, 8), (65, 64)], [(31, 97), (32, 1)]])
+def test_ssim_tile_edges(views):
+    """Image sides around multiples of the stencil's tile, several views in one
+    launch (the tolerances of the larger images' test)."""
+    print(f"ssim tiles {views}", flush=True)
+    rng = np.random.default_rng(views[0][0])
+    plan = gsr.Plan(10, 0, views, pair_capacity=16)
+    ws = plan.new_workspace(DEV)
+    fr = gsr.Frame(plan, DEV)
+    img = lambda c, w, h: rng.uniform(0.1, 0.9, (c, h, w)).astype(np.float32)
+    data = [(img(3, w, h), img(3, w, h), img(1, w, h)[0], img(1, w, h)[0]) for w, h in views]
+    flat = lambda k: torch.from_numpy(np.concatenate([d[k].reshape(-1) for d in data])).to(DEV)
+    fr.color.copy_(flat(0))
+    fr.depth.copy_(flat(2))
+    gC, gD = gsr.render_loss(plan, ws, fr, flat(1), flat(3), lambda_ssim=0.2)
+    torch.cuda.synchronize()
+    gCs, gDs = plan.split_views(gC, 3), plan.split_views(gD)
+    for v, (c, t, d, td) in enumerate(data):
+        loss, rC, rD = oracle_ssim.rendered_loss_and_grads(c, d, t, td, 0.2, 0.1)
+        assert abs(float(fr.loss[v]) - loss) <= 1e-5 * abs(loss)
+        ok = np.abs(c.astype(np.float64) - t) > 1e-6
+        err = np.abs(gCs[v].cpu().numpy().astype(np.float64) - rC)
+        tol = 1e-3 * np.abs(rC) + 1e-3 * np.sqrt(np.mean(rC ** 2))
+        assert (err <= tol)[ok].all()
+        np.testing.assert_allclose(gDs[v].cpu().numpy().astype(np.float64), rD, rtol=1e-6, atol=0)
