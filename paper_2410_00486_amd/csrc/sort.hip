@@ -5,12 +5,12 @@
 // otherwise: 4096 pairs of 46 bits took 101 us in 12 launches, 43 in this one;
 // 8192 took 136, now 49, and the passes below take 60 there).
 //
-// Larger: per pass the digit counts of each block of 2048 keys, their scan
+// Larger: per pass the digit counts of each block of 1024 or 2048 keys, their scan
 // over the blocks per digit, and a downsweep that ranks a block's keys
 // (wave64 ballots, in index order: stable), reorders them in LDS and writes
 // each digit's run contiguously.  Up to kFusedBlocks blocks the downsweep sums
-// the counts itself, one launch fewer per pass: 20 000 pairs (10 blocks) 67 us
-// so, but 60 000 (30 blocks) 86 us so and 78 us with the scan's own launch.
+// the counts itself, one launch fewer per pass: 20 000 pairs (20 blocks) 55 us
+// so and 58 with the scan's own launch; at 30 blocks of 2048 it was 86 and 78.
 // Before, every block summed up to 256 counts per digit in a serial loop and
 // wrote each key where its rank put it: 2^20 pairs of 46 bits, 58 us a pass in
 // the scatter alone; now 6 + 4 + 14 us a pass (eager), the whole sort 414 ->
@@ -23,7 +23,7 @@ namespace gs {
 namespace {
 
 constexpr int kSortWaves = kSortThreads / kWave;
-constexpr int64_t kFusedBlocks = 16;
+constexpr int64_t kFusedBlocks = 24;
 constexpr int kBlockThreads = 1024;
 constexpr int kBlockItems = 8;
 constexpr int kBlockSort = kBlockThreads * kBlockItems;  // 8192 pairs
@@ -60,6 +60,7 @@ __device__ __forceinline__ uint32_t exscan256(uint32_t x, uint32_t* ws) {
 }
 
 // Digit counts of each block, digit-major: hist[d * nb + block].
+template <int ITEMS>
 __global__ void __launch_bounds__(kSortThreads) k_sort_hist(const uint64_t* __restrict__ keys,
                                                             uint32_t n, uint32_t* __restrict__ hist,
                                                             uint32_t nb, int shift) {
@@ -68,9 +69,9 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_hist(const uint64_t* __re
 #pragma unroll
   for (int k = 0; k < kSortWaves; ++k) h[k][threadIdx.x] = 0u;
   __syncthreads();
-  const uint32_t base = blockIdx.x * (uint32_t)kSortTile + threadIdx.x;
+  const uint32_t base = blockIdx.x * (uint32_t)(kSortThreads * ITEMS) + threadIdx.x;
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
     const uint32_t idx = base + r * kSortThreads;
     if (idx < n) atomicAdd(&h[w][digit_of(keys[idx], shift)], 1u);
   }
@@ -119,16 +120,17 @@ __device__ __forceinline__ void rank_wave(const uint64_t (&key)[ITEMS], const bo
   }
 }
 
-template <bool FUSED>
+template <bool FUSED, int ITEMS>
 __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(
     const uint64_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, uint32_t n,
     const uint32_t* __restrict__ hist, const uint32_t* __restrict__ dtot, uint32_t nb, int shift) {
   __shared__ uint32_t wcnt[kSortWaves][kSortRadix];
   __shared__ uint32_t lstart[kSortRadix], gofs[kSortRadix], ws[4];
-  __shared__ uint64_t sbuf[kSortTile];  // keys, then the values in their place
+  constexpr int kTile = kSortThreads * ITEMS;
+  __shared__ uint64_t sbuf[kTile];  // keys, then the values in their place
   const int w = threadIdx.x / kWave, lane = lane_id();
-  const uint32_t d0 = threadIdx.x, base = blockIdx.x * (uint32_t)kSortTile;
+  const uint32_t d0 = threadIdx.x, base = blockIdx.x * (uint32_t)kTile;
 #pragma unroll
   for (int k = 0; k < kSortWaves; ++k) wcnt[k][d0] = 0u;
   {
@@ -145,16 +147,16 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(
     }
     gofs[d0] = exscan256(tot, ws) + before;  // (its barriers also order the clear)
   }
-  uint64_t key[kSortItems];
-  bool valid[kSortItems];
-  uint32_t rank[kSortItems];
-  const uint32_t ibase = base + (uint32_t)w * (kWave * kSortItems) + (uint32_t)lane;
+  uint64_t key[ITEMS];
+  bool valid[ITEMS];
+  uint32_t rank[ITEMS];
+  const uint32_t ibase = base + (uint32_t)w * (kWave * ITEMS) + (uint32_t)lane;
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
     valid[r] = ibase + r * kWave < n;
     key[r] = valid[r] ? keys_in[ibase + r * kWave] : 0ull;
   }
-  rank_wave<kSortItems>(key, valid, shift, wcnt[w], rank);
+  rank_wave<ITEMS>(key, valid, shift, wcnt[w], rank);
   __syncthreads();
   {
     uint32_t run = 0;
@@ -168,19 +170,19 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
     const uint32_t d = digit_of(key[r], shift);
     rank[r] += lstart[d] + wcnt[w][d];
     if (valid[r]) sbuf[rank[r]] = key[r];
   }
-  uint32_t val[kSortItems];
+  uint32_t val[ITEMS];
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) val[r] = valid[r] ? vals_in[ibase + r * kWave] : 0u;
+  for (int r = 0; r < ITEMS; ++r) val[r] = valid[r] ? vals_in[ibase + r * kWave] : 0u;
   __syncthreads();
-  const uint32_t nloc = min(n - base, (uint32_t)kSortTile);
-  uint32_t opos[kSortItems];
+  const uint32_t nloc = min(n - base, (uint32_t)kTile);
+  uint32_t opos[ITEMS];
 #pragma unroll
-  for (int q = 0; q < kSortItems; ++q) {
+  for (int q = 0; q < ITEMS; ++q) {
     const uint32_t i = threadIdx.x + q * kSortThreads;
     opos[q] = 0u;
     if (i < nloc) {
@@ -193,11 +195,11 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_scatter(
   __syncthreads();
   uint32_t* svals = reinterpret_cast<uint32_t*>(sbuf);
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r)
+  for (int r = 0; r < ITEMS; ++r)
     if (valid[r]) svals[rank[r]] = val[r];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kSortItems; ++q) {
+  for (int q = 0; q < ITEMS; ++q) {
     const uint32_t i = threadIdx.x + q * kSortThreads;
     if (i < nloc) vals_out[opos[q]] = svals[i];
   }
@@ -266,6 +268,21 @@ __global__ void __launch_bounds__(kBlockThreads) k_sort_block(uint64_t* __restri
     }
 }
 
+template <int ITEMS>
+void sort_pass(const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout, uint32_t n,
+               uint32_t* hist, uint32_t* dtot, uint32_t nb, int shift, hipStream_t s) {
+  const dim3 grid(nb), block(kSortThreads);
+  hipLaunchKernelGGL(k_sort_hist<ITEMS>, grid, block, 0, s, kin, n, hist, nb, shift);
+  if (nb <= kFusedBlocks) {
+    hipLaunchKernelGGL((k_sort_scatter<true, ITEMS>), grid, block, 0, s, kin, vin, kout, vout, n,
+                       hist, dtot, nb, shift);
+  } else {
+    hipLaunchKernelGGL(k_sort_scan, dim3(kSortRadix), block, 0, s, hist, dtot, nb);
+    hipLaunchKernelGGL((k_sort_scatter<false, ITEMS>), grid, block, 0, s, kin, vin, kout, vout, n,
+                       hist, dtot, nb, shift);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int key_bits, void* tmp,
@@ -283,18 +300,14 @@ hipError_t launch_sort_pairs(uint64_t* keys, uint32_t* vals, int64_t n, int key_
   uint32_t* hist = reinterpret_cast<uint32_t*>(base + L.hist);
   uint32_t* dtot = reinterpret_cast<uint32_t*>(base + L.dtot);
   const uint32_t nb = (uint32_t)sort_blocks(n);
-  const dim3 grid(nb), block(kSortThreads);
   int cur = 0;
   for (int shift = 0; shift < key_bits; shift += kSortBits) {
-    hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, kb[cur], (uint32_t)n, hist, nb, shift);
-    if (nb <= kFusedBlocks) {
-      hipLaunchKernelGGL(k_sort_scatter<true>, grid, block, 0, s, kb[cur], vb[cur], kb[cur ^ 1],
-                         vb[cur ^ 1], (uint32_t)n, hist, dtot, nb, shift);
-    } else {
-      hipLaunchKernelGGL(k_sort_scan, dim3(kSortRadix), block, 0, s, hist, dtot, nb);
-      hipLaunchKernelGGL(k_sort_scatter<false>, grid, block, 0, s, kb[cur], vb[cur], kb[cur ^ 1],
-                         vb[cur ^ 1], (uint32_t)n, hist, dtot, nb, shift);
-    }
+    if (n <= kSortFew)
+      sort_pass<kSortItemsFew>(kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], (uint32_t)n, hist, dtot,
+                               nb, shift, s);
+    else
+      sort_pass<kSortItemsMany>(kb[cur], vb[cur], kb[cur ^ 1], vb[cur ^ 1], (uint32_t)n, hist, dtot,
+                                nb, shift, s);
     cur ^= 1;
   }
   hipError_t e = hipGetLastError();

@@ -180,8 +180,9 @@ def test_splatwise_backward_pairs_behind_the_stop_get_zero():
 # ------------------------------------------------------- sort, rows of the pool
 
 @pytest.mark.parametrize("n", [2, 255, 2047, 8191, 8192,   # one workgroup
-                               8193, 32768,                # counts summed by the scatter
-                               32769, 524288, 524289])     # scanned, one and two chunks
+                               8193, 24576,                # counts summed by the scatter
+                               24577, 262145,              # scanned, one and two chunks
+                               524288, 524289])            # few and many keys a block
 @pytest.mark.parametrize("bits", [5, 24, 46])              # one, three and six passes
 def test_sort_sizes_and_passes(n, bits):
     """Equal keys keep their order; every number of passes ends in the
