@@ -56,7 +56,7 @@ SPAN_KERNELS = {
     "bin_scan": "k_scans",
     "bin_scatter": "k_scatter",
     "bin_short_sort": "k_tile_sort",
-    "bin_long_sort": "k_tile_sort_long",
+    "bin_long_sort": "k_tile_sort",
     "forward": "k_render_fwd",
     "loss": "(SSIM loss kernels)",
     "raster_bwd": "k_render_bwd_splat",
@@ -535,7 +535,11 @@ def roofline_of(span, ms, c, workload, tile):
     if span in ("forward", "raster_bwd"):
         flops = FWD_FLOPS_PER_POS if span == "forward" else BWD_FLOPS_PER_POS
         tf = flops * c["bwd_positions"] / (ms * 1e-3) / 1e12
-        full = f"{kname}<{tile[0]},{tile[1]}" + (",true>" if span == "forward" else ">")
+        # (the splat-wise backward is a form of the 8x8 tiles)
+        if span == "forward":
+            full = f"{kname}<{tile[0]},{tile[1]},true>"
+        else:
+            full = kname if tuple(tile) == (8, 8) else f"k_render_bwd<{tile[0]},{tile[1]}>"
         return {"bound": "alu", "kernel": full, "achieved": round(tf, 3),
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(tf / FP32_PEAK_TFLOPS, 4),

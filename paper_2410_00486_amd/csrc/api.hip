@@ -32,7 +32,7 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                              const float* depth, const float* T_final, const uint32_t* last,
                              const float* dL_dcolor, const float* dL_ddepth,
                              const float* target_rgb, const float* target_depth, int fused,
-                             const uint32_t* sorted_vals, int splat_grid, hipStream_t s);
+                             const uint32_t* sorted_vals, hipStream_t s);
 hipError_t launch_project_bwd(const Plan& P, const gs_gaussians& g, const float* cams, void* ws,
                               const gs_gaussian_grads& out, float* dL_dpose, int accumulate,
                               bool zeroed, hipStream_t s);
@@ -42,7 +42,6 @@ hipError_t launch_adam(const gs_param_group* groups, int n_groups, int step, dou
                        const int32_t* per = nullptr, const int32_t* overflow = nullptr,
                        const AdamFold* fold = nullptr);
 int blocks_per_tile(const Plan& P);
-int splat_blocks_per_cu();
 int64_t ssim_tiles(const Plan& P);
 size_t densify_tmp_bytes(int64_t n);
 hipError_t launch_grad_stats(const Plan& P, void* ws, float* accum, float* denom, hipStream_t s);
@@ -122,19 +121,6 @@ gs_status check_gaussians(const Plan& P, const gs_gaussians* g) {
     return fail(GS_ERR_INVALID_ARG, "a Gaussian parameter pointer is null");
   if (!aligned(g->quats, 16)) return fail(GS_ERR_INVALID_ARG, "quats must be 16-byte aligned");
   return GS_OK;
-}
-
-int device_cus() {
-  static int cus = 0;
-  static std::once_flag once;
-  std::call_once(once, [] {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-      cus = prop.multiProcessorCount;
-    if (cus <= 0) cus = 256;
-  });
-  return cus;
 }
 
 }  // namespace
@@ -405,14 +391,9 @@ gs_status gs_render_bwd_raster(const gs_plan* plan, void* ws, const float* cams_
   if (fused && !target_rgb) return fail(GS_ERR_INVALID_ARG, "GS_FUSED_L1 needs target_rgb");
   if (!fused && !dL_dcolor) return fail(GS_ERR_INVALID_ARG, "dL_dcolor is null (and GS_FUSED_L1 not set)");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // splat-wise: grid-stride over the buckets, as many waves as stay resident
-  const int splat_grid =
-      P.splat
-          ? (int)std::max<int64_t>(1, std::min<int64_t>(P.ckpt_slots, (int64_t)device_cus() * splat_blocks_per_cu()))
-          : 0;
   const hipError_t e = launch_render_bwd(P, ws, cams_dev, color, depth, T_final, last, dL_dcolor,
                                          dL_ddepth, target_rgb, target_depth, fused ? 1 : 0,
-                                         sorted_vals(P, ws), splat_grid, s);
+                                         sorted_vals(P, ws), s);
   return hip_check(e, "gs_render_bwd_raster");
 }
 

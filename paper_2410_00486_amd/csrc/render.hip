@@ -560,8 +560,7 @@ struct BwdLds {
 // kept splat and block, a third of them the reduction of the ten partials
 // over the lanes.
 template <int TW, int TH>
-__global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A,
-                                                                            ViewTable vt) {
+__global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt) {
   constexpr int NS = sub_tiles<TW, TH>(), NT = kWave * NS, BX = TW / kSub;
   __shared__ __align__(16) BwdLds<TW, TH> S;
   const int lane = lane_id(), sub = NS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1055,7 +1054,8 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
   }
 }
 
-// Grid-stride over the bucket queue.
+// One workgroup (a wavefront) per entry of the bucket queue; the grid covers
+// the plan's checkpoint slots.
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6))) k_render_bwd_splat(
     SplatArgs A, ViewTable vt) {
   __shared__ SplatLds S;
@@ -1107,21 +1107,10 @@ hipError_t bwd_launch(const Plan& P, void* ws, const float* cams, const float* c
   return hipGetLastError();
 }
 
-template <typename K>
-int occupancy(K kernel, size_t lds) {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kWave, lds) != hipSuccess || n < 1)
-    n = 4;
-  return n;
-}
-
 }  // namespace
 
 // 8x8 blocks of pixels per tile: the forward's wavefronts per tile.
 int blocks_per_tile(const Plan& P) { return P.cfg.tile_w * P.cfg.tile_h / (kSub * kSub); }
-
-// Resident workgroups per CU of the splat-wise backward.
-int splat_blocks_per_cu() { return occupancy(k_render_bwd_splat, 0); }
 
 hipError_t launch_render_fwd(const Plan& P, void* ws, const float* cams, float* color,
                              float* depth, float* T_final, uint32_t* last,
@@ -1150,7 +1139,7 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                              const float* depth, const float* T_final, const uint32_t* last,
                              const float* dL_dcolor, const float* dL_ddepth,
                              const float* target_rgb, const float* target_depth, int fused,
-                             const uint32_t* sorted_vals, int splat_grid, hipStream_t s) {
+                             const uint32_t* sorted_vals, hipStream_t s) {
   if (P.vt.total_tiles == 0) return hipSuccess;
   const int tw = P.cfg.tile_w, th = P.cfg.tile_h;
   const PixelLoss loss{dL_dcolor, dL_ddepth, target_rgb, target_depth, fused, P.cfg.lambda_depth};
