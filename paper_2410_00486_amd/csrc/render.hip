@@ -37,6 +37,9 @@ namespace {
 constexpr float kAlphaMax = 0.99f;
 constexpr float kAlphaMin = 1.0f / 255.0f;
 constexpr float kTMin = 1e-4f;
+// Pixel gradients and splat colours below this cannot overflow the raster
+// backward's sums of their products.
+constexpr float kTame = 1e15f;
 
 // DPP move with zero fill where the lane has no source or its row is masked.
 template <int CTRL, int ROW_MASK = 0xF>
@@ -607,7 +610,19 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
       g = A.loss.at(cbase, npx, pix, 0.f, 0.f, 0.f, 0.f);
     // behind: the background seen through T_final, nothing in depth
     B = T * (g.x * cam[17] + g.y * cam[18] + g.z * cam[19]);
+    if (L == 0) {  // nothing blended: its gradient reaches no splat
+      g = make_float4(0.f, 0.f, 0.f, 0.f);
+      T = 1.0f;
+      B = 0.0f;
+    }
   }
+  // A gradient that is no number, or so large that a product with it may not
+  // be one, must reach the splats blended at its pixel alone: 0 times it is
+  // not 0, so such blocks select what a splat adds by its hit.
+  const float gmax = fmaxf(fmaxf(fabsf(g.x), fabsf(g.y)), fmaxf(fabsf(g.z), fabsf(g.w)));
+  const bool tame_px = g.x == g.x && g.y == g.y && g.z == g.z && g.w == g.w && gmax < kTame &&
+                       fabsf(B) < kTame && T <= 1.0f;
+  const bool tame_block = ballot64(!tame_px) == 0;
   const uint32_t Lmax = wave_max(L);
   const int my_idx = lane < 16 ? rs_index(lane) : -1;
   const double ax0 = (double)(tx0 + kSub * sx) + 0.5, ay0 = (double)(ty0 + kSub * sy) + 0.5;
@@ -660,12 +675,16 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
       S.o[lane] = ro;
     }
     if (lane == 0) S.kept[sub] = kept;
+    const bool tame =
+        tame_block && ballot64(has && !(fmaxf(fmaxf(r.r, r.g), fmaxf(r.b, r.z)) < kTame)) == 0;
     __syncthreads();
     fetch(bend - kWave);
     // N kept positions j[0] > j[1] .. at once: independent alphas and
-    // reductions, only T and B run through them in order
-    auto step = [&](auto n_c, const int* j) {
+    // reductions, only T and B run through them in order.  TAME: a splat that
+    // is not blended adds its products with alpha 0.
+    auto step = [&](auto n_c, auto tame_c, const int* j) __attribute__((always_inline)) {
       constexpr int N = decltype(n_c)::value;
+      constexpr bool TAME = decltype(tame_c)::value;
       float p_ax[N], q_ax[N], oG[N], a[N], front[N];
       bool hit[N];
 #pragma unroll
@@ -689,14 +708,19 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
         T *= inv_om;  // in front of this splat
         const float wgt = a[k] * T;
         const float g_alpha = fmaf(T, front[k], -(B * inv_om));
-        B = fmaf(front[k], wgt, B);
+        const float Bn = fmaf(front[k], wgt, B);
+        B = TAME || hit[k] ? Bn : B;
         // unclamped alpha only (no gradient through the 0.99 clamp); the
         // conic and mean partials are moments of gpow = alpha dL/dalpha along
         // the footprint's axes, put together after the sums
         const float gpow = oG[k] <= kAlphaMax ? a[k] * g_alpha : 0.0f;
         const float t = gpow * p_ax[k], u = gpow * q_ax[k];
-        const float p[10] = {wgt * g.x, wgt * g.y, wgt * g.z, wgt * g.w, gpow,
-                             t * p_ax[k], t * q_ax[k], u * q_ax[k], t, u};
+        float p[10] = {wgt * g.x, wgt * g.y, wgt * g.z, wgt * g.w, gpow,
+                       t * p_ax[k], t * q_ax[k], u * q_ax[k], t, u};
+        if constexpr (!TAME) {
+#pragma unroll
+          for (int f = 0; f < 10; ++f) p[f] = hit[k] ? p[f] : 0.0f;
+        }
         z[k] = reduce_scatter10(p);
       }
       if (my_idx >= 0) {
@@ -704,18 +728,22 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
         for (int k = 0; k < N; ++k) S.part[sub][j[k]][my_idx] = z[k];
       }
     };
-    for (uint64_t m = kept; m;) {
-      int j[2];
-      j[0] = 63 - __builtin_clzll(m);
-      m &= ~(1ull << j[0]);
-      if (m == 0) {
-        step(std::integral_constant<int, 1>{}, j);
-        break;
+    auto walk = [&](auto tame_c) __attribute__((always_inline)) {
+      for (uint64_t m = kept; m;) {
+        int j[2];
+        j[0] = 63 - __builtin_clzll(m);
+        m &= ~(1ull << j[0]);
+        if (m == 0) {
+          step(std::integral_constant<int, 1>{}, tame_c, j);
+          break;
+        }
+        j[1] = 63 - __builtin_clzll(m);
+        m &= ~(1ull << j[1]);
+        step(std::integral_constant<int, 2>{}, tame_c, j);
       }
-      j[1] = 63 - __builtin_clzll(m);
-      m &= ~(1ull << j[1]);
-      step(std::integral_constant<int, 2>{}, j);
-    }
+    };
+    if (__builtin_expect(tame, 1)) walk(std::true_type{});
+    else walk(std::false_type{});
     __syncthreads();
     for (int q = (int)threadIdx.x; q < nb; q += NT) {
       float f[10];

@@ -446,3 +446,41 @@ def test_ssim_tile_edges(views):
         tol = 1e-3 * np.abs(rC) + 1e-3 * np.sqrt(np.mean(rC ** 2))
         assert (err <= tol)[ok].all()
         np.testing.assert_allclose(gDs[v].cpu().numpy().astype(np.float64), rD, rtol=1e-6, atol=0)
+
+
+# ------------------------------------------------ gradients that are no numbers
+
+def _pixelwise_gradients(w, tile, gcs, gds):
+    it = run_gpu(w.scene, w.cameras, tile=tile, dL_dcolor=gcs, dL_ddepth=gds)
+    last = it.plan.split_views(it.frame.last)[0].cpu().numpy()
+    n = w.scene.n
+    return np.concatenate([x.reshape(n, -1) for x in grads_np(it).values()], 1), last
+
+
+@pytest.mark.parametrize("tile", [(8, 8), (16, 8), (16, 16)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_pixelwise_backward_keeps_a_bad_gradient_to_its_pixel(tile, value):
+    """An upstream gradient that is NaN or infinite reaches the splats blended
+    at its pixel and no other: at a pixel that nothing covers it has no
+    effect, and at a covered one every Gaussian that a finite gradient there
+    does not move keeps the bits it has without it."""
+    w = scenes.tiny_scene(83, n=24, width=40, height=25, f=36.0, degree=1)
+    gcs, gds = scenes.linear_loss_weights(12, w.cameras)
+    print(f"bad gradient {value} tile {tile}", flush=True)
+    _, last = _pixelwise_gradients(w, tile, gcs, gds)
+    block = lambda a, y, x: a[y // 8 * 8:y // 8 * 8 + 8, x // 8 * 8:x // 8 * 8 + 8]
+    pixels = [(y, x) for y, x in np.argwhere(last == 0) if (block(last, y, x) > 0).sum() >= 20]
+    covered = [(y, x) for y, x in np.argwhere(last > 0) if (block(last, y, x) == 0).sum() >= 10]
+    assert len(pixels) > 4 and len(covered) > 4
+    for y, x in (pixels[0], pixels[-1], covered[0], covered[-1]):
+        run = []
+        for colour, depth in ((0.0, 0.0), (1e3, 1e3), (value, 0.0), (0.0, value)):
+            c, d = [gcs[0].copy()], [gds[0].copy()]
+            c[0][:, y, x], d[0][y, x] = colour, depth
+            run.append(_pixelwise_gradients(w, tile, c, d)[0])
+        base, moved = run[0], (run[1] != run[0]).any(axis=1)
+        assert np.isfinite(base).all() and not moved.all()
+        assert moved.any() == (last[y, x] > 0)
+        for got in run[2:]:
+            np.testing.assert_array_equal(got[~moved], base[~moved])
+            assert not moved.any() or not np.isfinite(got[moved]).all()
