@@ -729,9 +729,9 @@ class Rasterizer:
     def forward_buffers(self, g: "Gaussians", cams: torch.Tensor):
         """Preprocess, binning and forward into fresh output buffers; returns
         (plan, ws, frame).  Retries once with a larger capacity on overflow."""
-        return self._forward(g, cams, False)
+        return self._forward(g, cams, False, Frame)
 
-    def _forward(self, g: "Gaussians", cams: torch.Tensor, held: bool):
+    def _forward(self, g: "Gaussians", cams: torch.Tensor, held: bool, frame=_frame_without_loss):
         """held: the caller keeps the workspace and cams until its backward, so
         the render may still run when this returns; otherwise it is waited
         for (the workspace goes back to the pool, where another stream's next
@@ -753,7 +753,7 @@ class Rasterizer:
                 copied = s.record_event()
                 for t in (ws, cams):  # (if the graph is dropped before the render has run)
                     t.record_stream(s)
-            fr = _frame_without_loss(plan, g.means.device)
+            fr = frame(plan, g.means.device)
             render_fwd(plan, ws, cams, fr)
             self._last_ws = ws
             if not self.check_overflow:

@@ -186,3 +186,21 @@ def test_rasterizer_grows_pair_capacity_and_reuses_workspaces():
         col2, _, _ = rz(*leaves, ct)
     assert len(rz._free) == 1 and rz._free[0].data_ptr() == ws_ptr
     assert torch.equal(col2, fr.color)
+
+
+def test_forward_buffers_return_a_whole_frame():
+    """The frame of Rasterizer.forward_buffers holds a loss per view, cleared,
+    and takes the losses of render_fwd with targets and of render_loss."""
+    w = workload(1)
+    cam = w.cameras[0]
+    ct = gsr.cameras_tensor([cam], DEV)
+    g = gsr.Gaussians.from_scene(w.scene, DEV)
+    print("forward_buffers", flush=True)
+    plan, ws, fr = gsr.Rasterizer([(cam.width, cam.height)], 0, pair_capacity=1 << 18).forward_buffers(g, ct)
+    assert torch.equal(fr.loss, torch.zeros(1, device=DEV))
+    target = torch.zeros_like(fr.color)
+    gsr.render_fwd(plan, ws, ct, fr, target_rgb=target)
+    l1 = float(fr.color.abs().mean())
+    assert abs(float(fr.loss[0]) - l1) <= 1e-5 * l1
+    gsr.render_loss(plan, ws, fr, target, lambda_ssim=0.0)
+    assert abs(float(fr.loss[0]) - l1) <= 1e-5 * l1
