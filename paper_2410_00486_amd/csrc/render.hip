@@ -154,8 +154,10 @@ static_assert(sizeof(FwdRec) == 48 && offsetof(Rec, b) == 44, "first 48 bytes of
 
 // Highest exponent (base 2) at which a splat may still be skipped as a
 // whole: alpha < 1/255 is an exponent below -7.9944, so what lies under -8
-// is skipped at every pixel by the alpha test as well, whatever the rounding
-// of either (about 1e-6 of the exponent).
+// is skipped at every pixel by the alpha test as well.  Both start from the
+// same FP32 offsets and form p and q with one rounding each, so they differ
+// by a few ulp of terms of at most 8 (1e-6 measured), and by the bound's own
+// error far from the mean (max_exponent).
 constexpr float kCullExp = -8.0f;
 // Above this log2(opacity) the clamp at 0.99 can act (log2(0.99) = -0.0145).
 constexpr float kClampLo = -0.0146f;
@@ -165,8 +167,12 @@ constexpr float kClampLo = -0.0146f;
 // quadratic's minimum over the rectangle is 0 when it holds the origin, and
 // otherwise lies on an edge that faces the origin: the nearest x (y) of the
 // rectangle with the best y (x) on it.  Both candidates lie in the
-// rectangle, and near the best point an error of the argument is of second
-// order, so the bound holds to the rounding of the exponent itself.
+// rectangle.  The best y (x) is off by up to 8 half ulp (of cb, the edge's x,
+// cc, its reciprocal and their products), 4.8e-7 of the largest offset d, and
+// the quadratic there rises by at most cc (4.8e-7 d)^2, cc < 2.41 with the
+// dilation of 0.3 px^2: (1e-6 d)^2 is added to the bound.  That is below the
+// margin of kCullExp up to 7e4 pixels; splats close to the camera's plane
+// reach the image from further away.
 __device__ __forceinline__ float max_exponent(const FwdRec& r, float xl, float xh, float yl,
                                               float yh) {
   const float tt = r.t * r.t;
@@ -178,7 +184,9 @@ __device__ __forceinline__ float max_exponent(const FwdRec& r, float xl, float x
     const float p = fmaf(r.t, dy, dx), q = fmaf(-r.t, dx, dy);
     return fmaf(r.s1 * p, p, r.s2 * q * q);
   };
-  return r.lo - fminf(quad(x0, y1), quad(x1, y0));
+  // (the block's other offsets are within 8 pixels of the nearest one)
+  const float d = fmaf(1e-6f, fmaxf(fabsf(x0), fabsf(y0)), 8e-6f);
+  return fmaf(d, d, r.lo - fminf(quad(x0, y1), quad(x1, y0)));
 }
 
 // LDS of one forward wavefront: the batch's splats that can reach the

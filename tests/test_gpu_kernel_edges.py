@@ -484,3 +484,44 @@ def test_pixelwise_backward_keeps_a_bad_gradient_to_its_pixel(tile, value):
         for got in run[2:]:
             np.testing.assert_array_equal(got[~moved], base[~moved])
             assert not moved.any() or not np.isfinite(got[moved]).all()
+
+
+# ------------------------------------------------------- splats from far away
+
+@pytest.mark.parametrize("angle", [0.6, 0.9])
+@pytest.mark.parametrize("ratio", [3.27, 3.28, 3.29])
+def test_forward_keeps_the_tail_of_a_splat_millions_of_pixels_away(angle, ratio):
+    """One long thin splat whose mean lies 8 million pixels from the image, so
+    that alpha on its axis is just above 1/255 there: every pixel is that of
+    the alpha test on its own offsets (FP32 as documented for the records),
+    also in the blocks that only the axis crosses."""
+    dist, tz, fx, W, V = 8e6, np.float32(0.01), np.float32(500.0), 64, 8
+    u = np.array([np.cos(angle), np.sin(angle)])
+    mean = np.array([[*(u * dist * float(tz) / float(fx)), tz]], np.float32)
+    scene = scenes.Scene(mean, np.array([[np.log(dist / ratio * float(tz) / float(fx)), -20, -20]], np.float32),
+                         np.array([[np.cos(angle / 2), 0, 0, np.sin(angle / 2)]], np.float32),
+                         np.array([np.log(0.9 / 0.1)], np.float32),
+                         np.full((1, 1, 3), 0.5 / 0.28209479177387814, np.float32), 0)
+    rng = np.random.default_rng(1)
+    cams = [scenes.Camera(W, W, fx, fx, *np.float32(W / 2 + rng.uniform(-3, 3, 2)),
+                          np.eye(3, dtype=np.float32), np.zeros(3, np.float32), near=0.001)
+            for _ in range(V)]
+    print(f"far splat angle {angle} ratio {ratio}", flush=True)
+    it = run_gpu(scene, cams, tile=(8, 8))
+    raw = it.plan.region(it.ws, L.GS_WS_RECORDS, torch.uint8, 64 * V).cpu().numpy().reshape(V, 64)
+    k = np.arange(W) + 0.5
+    blended = 0
+    for v in range(V):
+        mx, my = raw[v, :16].view(np.float64)
+        t, s1, s2, lo, z, r = raw[v, 16:40].view(np.float32).astype(np.float64)
+        f32 = lambda x: np.asarray(x, np.float64).astype(np.float32).astype(np.float64)
+        dx, dy = f32(mx - k)[None, :], f32(my - k)[:, None]
+        p, q = f32(t * dy + dx), f32(dy - t * dx)
+        e = lo - s1 * p * p - s2 * q * q
+        # (roundings of the exponent: a few ulp of terms of at most 8)
+        sure = np.abs(e - np.log2(1.0 / 255.0)) > 1e-4
+        alpha = np.where(e >= np.log2(1.0 / 255.0), np.exp2(e), 0.0)
+        col = it.plan.split_views(it.frame.color, 3)[v].cpu().numpy()[0]
+        np.testing.assert_allclose(col[sure], (r * alpha)[sure], rtol=1e-4, atol=1e-7)
+        blended += int((alpha[sure] > 0).sum())
+    assert blended > 100
