@@ -204,3 +204,60 @@ def test_forward_buffers_return_a_whole_frame():
     assert abs(float(fr.loss[0]) - l1) <= 1e-5 * l1
     gsr.render_loss(plan, ws, fr, target, lambda_ssim=0.0)
     assert abs(float(fr.loss[0]) - l1) <= 1e-5 * l1
+
+
+def test_calls_on_two_streams_share_a_rasterizer():
+    """Recorded calls on two streams, one behind the other with no wait on
+    the host: each gives the images and gradients of a rasterizer of its own
+    (the workspaces of one stream's backward go to the other's forward)."""
+    w = scenes.tiny_scene(9, n=4000, width=640, height=480, f=500.0, degree=1)
+    cams = [w.cameras[0], scenes.perturb_camera(w.cameras[0], np.array([0.1, -0.05, 0.2, 0.02, 0.03, -0.01]))]
+    cts = [gsr.cameras_tensor([c], DEV) for c in cams]
+    leaves = _leaves(w.scene)
+    weight = torch.linspace(-1.0, 1.0, 3 * 640 * 480, device=DEV)
+
+    def call(rz, ct):
+        color, _, _ = rz(*leaves, ct)
+        return (color.detach(), *torch.autograd.grad((color * weight).sum(), leaves))
+
+    print("two streams, one rasterizer", flush=True)
+    want = [call(gsr.Rasterizer([(640, 480)], 1, pair_capacity=1 << 20), ct) for ct in cts]
+    torch.cuda.synchronize()
+    rz = gsr.Rasterizer([(640, 480)], 1, pair_capacity=1 << 20)
+    streams, got = [torch.cuda.Stream(), torch.cuda.Stream()], []
+    for k in range(12):
+        with torch.cuda.stream(streams[k % 2]):
+            got.append(call(rz, cts[k % 2]))
+    torch.cuda.synchronize()
+    assert 1 <= len(rz._free) <= 2
+    for k, result in enumerate(got):
+        for x, y in zip(result, want[k % 2]):
+            assert torch.equal(x, y)
+
+
+def test_recorded_render_keeps_its_workspace():
+    """A render recorded into a graph, replayed with eager renders of another
+    view on the same rasterizer in between: both stay those of a rasterizer
+    of their own."""
+    w = scenes.tiny_scene(10, n=3000, width=320, height=240, f=250.0, degree=1)
+    cams = [w.cameras[0], scenes.perturb_camera(w.cameras[0], np.array([0.1, -0.05, 0.2, 0.02, 0.03, -0.01]))]
+    cts = [gsr.cameras_tensor([c], DEV) for c in cams]
+    leaves = [x.detach() for x in _leaves(w.scene)]
+    new = lambda: gsr.Rasterizer([(320, 240)], 1, pair_capacity=1 << 20, check_overflow=False)
+    print("recorded render", flush=True)
+    want = [[x.clone() for x in new()(*leaves, ct)] for ct in cts]
+    rz = new()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        rz(*leaves, cts[0])  # warm-up: its workspace goes to the recording
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = rz(*leaves, cts[0])
+    for _ in range(3):
+        graph.replay()
+        eager = rz(*leaves, cts[1])
+        for got, ref in ((out, want[0]), (eager, want[1])):
+            for x, y in zip(got, ref):
+                assert torch.equal(x, y)
+    assert len(rz._free) == 2
