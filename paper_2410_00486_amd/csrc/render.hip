@@ -985,8 +985,7 @@ __device__ __forceinline__ void splat_rows(const LaneSplat& r, const SplatLds& S
 
 // One bucket: entry qi of the queue.
 __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable& vt, uint32_t qi,
-                                             SplatLds& S) {
-  const int lane = (int)threadIdx.x;
+                                             SplatLds& S, int lane) {
   const uint2 ent = A.bq[qi];  // (tile, k)
   const int gtile = __builtin_amdgcn_readfirstlane((int)ent.x);
   const uint32_t q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)ent.y) * kBucket;
@@ -1085,7 +1084,6 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
     if (seg_lanes == 64) rows(std::integral_constant<int, 64>{});
     else if (seg_lanes == 32) rows(std::integral_constant<int, 32>{});
     else rows(std::integral_constant<int, 16>{});
-    __syncthreads();  // the pixel table is rewritten by the next bucket
   }
   if (live && lane < seg_lanes) {
     // acc: sums of gpow times p^2, p dy, dy^2, p, dy; dx = p - t dy and
@@ -1099,14 +1097,34 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
   }
 }
 
-// One workgroup (a wavefront) per entry of the bucket queue; the grid covers
-// the plan's checkpoint slots.
+// One workgroup (a wavefront) per entry of the bucket queue.  The grid covers
+// the plan's checkpoint slots; but an idle workgroup costs 0.11 ns, a thirtieth
+// of one with a bucket, so that plans with room for a few hundred times their
+// pairs spent more on them than on the buckets.  Where the slots exceed
+// kGridBuckets a tile (512 pairs, four times the mean list of the batches
+// above) by more than kGridIdle, 7 us, the rest is left to a second, looping
+// launch (4 us if nothing is).  640x480, 61k pairs, whole iteration: with room
+// for 1.3 times as many 92 us, 256 times 130 without the second launch and
+// 100 with it, 1024 times 284 and 103.  As one looping launch the large
+// batches lose 4 % (1616 -> 1681 us, 79 registers instead of 69).
+constexpr int64_t kGridBuckets = 8, kGridLeast = 1 << 14, kGridIdle = 1 << 16, kGridRest = 1 << 14;
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6))) k_render_bwd_splat(
     SplatArgs A, ViewTable vt) {
   __shared__ SplatLds S;
   const uint32_t n = (uint32_t)A.fl[F_BUCKETS];
   const uint32_t q = xcd_item(blockIdx.x, gridDim.x);
-  if (q < n) splat_bucket(A, vt, q, S);
+  if (q < n) splat_bucket(A, vt, q, S, (int)threadIdx.x);
+}
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6))) k_render_bwd_splat_rest(
+    SplatArgs A, ViewTable vt, uint32_t first) {
+  __shared__ SplatLds S;
+  const uint32_t n = (uint32_t)A.fl[F_BUCKETS];
+  for (uint32_t q = first + xcd_item(blockIdx.x, gridDim.x); q < n; q += gridDim.x) {
+    int lane = (int)threadIdx.x;
+    asm volatile("" : "+v"(lane));  // (what hangs on it, kept over the buckets, would spill)
+    splat_bucket(A, vt, q, S, lane);
+    __syncthreads();  // the pixel table is rewritten by the next bucket
+  }
 }
 
 // (Until the kernels fetched the records of a batch while they worked on the
@@ -1199,7 +1217,13 @@ hipError_t launch_render_bwd(const Plan& P, void* ws, const float* cams, const f
                       ws_at<uint2>(ws, P.off_seen), ws_at<float>(ws, P.off_ckpt),
                       ws_at<uint2>(ws, P.off_bq), ws_at<int32_t>(ws, P.off_flags), color, depth,
                       last, loss, ws_at<float>(ws, P.off_grad_pair)};
-    hipLaunchKernelGGL(k_render_bwd_splat, dim3((unsigned)P.ckpt_slots), dim3(kWave), 0, s, A, P.vt);
+    const int64_t most = std::max(kGridBuckets * P.vt.total_tiles, kGridLeast);
+    const int64_t grid = P.ckpt_slots > most + kGridIdle ? most : P.ckpt_slots;
+    const int64_t rest = P.ckpt_slots - grid;
+    hipLaunchKernelGGL(k_render_bwd_splat, dim3((unsigned)grid), dim3(kWave), 0, s, A, P.vt);
+    if (rest > 0)
+      hipLaunchKernelGGL(k_render_bwd_splat_rest, dim3((unsigned)std::min(rest, kGridRest)),
+                         dim3(kWave), 0, s, A, P.vt, (uint32_t)grid);
     return hipGetLastError();
   }
   if (tw == 16 && th == 16)

@@ -525,3 +525,37 @@ def test_forward_keeps_the_tail_of_a_splat_millions_of_pixels_away(angle, ratio)
         np.testing.assert_allclose(col[sure], (r * alpha)[sure], rtol=1e-4, atol=1e-7)
         blended += int((alpha[sure] > 0).sum())
     assert blended > 100
+
+
+# ------------------------------------------- splat-wise launches of large plans
+
+def _away(width, height):
+    return scenes.Camera(width, height, 60.0, 60.0, width / 2.0, height / 2.0,
+                         np.diag([1.0, -1.0, -1.0]).astype(np.float32), np.zeros(3, np.float32))
+
+
+@pytest.mark.parametrize("n,room", [(30000, 4.0),   # 22,512 buckets in 48 tiles, the first launch takes 16,384
+                                    (300, 1000.0)])  # few buckets, room for 225,000
+def test_splatwise_backward_beyond_its_first_launch(n, room):
+    """Buckets that the first launch's grid does not reach, and a plan with
+    room for far more pairs than it gets: the gradients are, bit for bit,
+    those of a plan whose second view, which sees nothing, has so many tiles
+    that one launch takes all buckets."""
+    w = scenes.tiny_scene(61, n=n, width=64, height=48, f=60.0)
+    w.scene.log_scales[:] = 0.5
+    w.scene.opacity_logits[:] = -4.6
+    got = []
+    for wh, cap in (((8, 8), int(48 * n * room)), ((512, 384), 48 * n)):
+        cams = [w.cameras[0], _away(*wh)]
+        gcs, gds = scenes.linear_loss_weights(6, cams[:1])
+        gcs.append(np.zeros((3, wh[1], wh[0]), np.float32))
+        gds.append(np.zeros((wh[1], wh[0]), np.float32))
+        print(f"splat-wise launches n {n} second view {wh} capacity {cap}", flush=True)
+        it = run_gpu(w.scene, cams, tile=(8, 8), flags=L.GS_SPLAT_BWD, dL_dcolor=gcs, dL_ddepth=gds,
+                     capacity=cap)
+        fl = it.plan.flags_of(it.ws)
+        assert fl[L.F_OVERFLOW] == 0 and fl[L.F_PAIRS] == 48 * n
+        got.append(grads_np(it))
+    for f in got[0]:
+        assert np.abs(got[0][f]).max() > 0 and np.isfinite(got[0][f]).all()
+        np.testing.assert_array_equal(got[0][f], got[1][f])
