@@ -1,11 +1,15 @@
-"""Autotuner of the batched iteration: tile shape, LDS batch, work-chunk
-size of the persistent render kernels, the backward variant (pixel-wise
-or splat-wise) and the tile binning (per-tile slot claims and sorts, or
-the two radix sorts).  Each candidate is planned, captured
-as a whole-iteration HIP graph and timed by the library's gs_graph_time (HIP
-events on the replay stream); the fastest is returned and optionally cached
-as JSON keyed by the workload signature.  Tuning runs on a copy of the
-parameters, so the caller's model is not stepped.
+"""Autotuner of the batched iteration: tile shape, the backward variant
+(pixel-wise or, with 8x8 tiles, splat-wise) and the tile binning (per-tile
+slot claims and sorts, or the two radix sorts).  Each candidate is planned,
+captured as a whole-iteration HIP graph and timed by the library's
+gs_graph_time (HIP events on the replay stream); the fastest is returned and
+optionally cached as JSON keyed by the workload signature.  Tuning runs on a
+copy of the parameters, so the caller's model is not stepped.
+
+The LDS batch, the chunk and GS_PERSISTENT reach no kernel: their values are
+checked, every candidate takes the first of each, and none is timed twice for
+them.  A "splat" candidate of larger tiles runs the pixel-wise backward and is
+listed as that.
 
 Tile shape never changes the rendered image (the tile box is the exact
 alpha >= 1/255 box), so the choice is purely a performance one.
@@ -50,10 +54,14 @@ def autotune(g: Gaussians, cams: torch.Tensor, view_wh: Sequence[Tuple[int, int]
     work = Gaussians(*[t.clone() for t in g.tensors()], g.sh_degree)
     stream = torch.cuda.Stream()
     table = []
+    settings = list(itertools.product(lds_batches, chunks if persistent else [1]))
     for tile in tiles:
         cap = int(required_pairs(*work.tensors(), cams, view_wh, work.sh_degree, tile) * 1.3) + 4096
-        for lds, chunk, bwd, binning in itertools.product(
-                lds_batches, chunks if persistent else [1], backwards, binnings):
+        for lds, chunk in settings[1:]:
+            Plan(work.n, work.sh_degree, view_wh, tile=tile, lds_batch=lds, chunk=chunk,
+                 flags=base_flags, pair_capacity=cap)
+        forms = list(dict.fromkeys(b if tuple(tile) == (8, 8) else "pixel" for b in backwards))
+        for (lds, chunk), bwd, binning in itertools.product(settings[:1], forms, binnings):
             flags = (base_flags | (L.GS_SPLAT_BWD if bwd == "splat" else 0) |
                      (L.GS_RADIX_BIN if binning == "radix" else 0))
             plan = Plan(work.n, work.sh_degree, view_wh, tile=tile, lds_batch=lds, chunk=chunk,

@@ -210,3 +210,23 @@ def test_autotuner_searches_the_binning():
     assert sorted(r["binning"] for r in table) == ["radix", "tiles"]
     assert all(r["overflow"] == 0 and r["ms"] > 0 for r in table)
     assert best["binning"] in ("tiles", "radix") and best["ms"] == min(r["ms"] for r in table)
+
+
+def test_autotuner_times_each_path_once():
+    """Options that reach no kernel make no candidates, and the backward forms
+    of larger tiles are one: each path is listed once, under the form it
+    runs; a value that a plan refuses is refused."""
+    from paper_2410_00486_amd import tune
+    w = workload(1)
+    cam = w.cameras[0]
+    g = gsr.Gaussians.from_scene(w.scene, DEV)
+    args = (g, gsr.cameras_tensor([cam], DEV), [(cam.width, cam.height)])
+    kw = dict(target_rgb=t32(w.target_rgb[0].reshape(-1)), adam_lrs=LRS, tiles=[(8, 8), (16, 16)], reps=1)
+    print("autotuner, paths once", flush=True)
+    best, table = tune.autotune(*args, **kw)
+    assert sorted((r["tile"], r["backward"]) for r in table) == [("16x16", "pixel"), ("8x8", "pixel"),
+                                                                 ("8x8", "splat")]
+    assert best in table and all(r["lds_batch"] == 64 and r["chunk"] == 1 for r in table)
+    for bad in ({"lds_batches": [64, 7]}, {"chunks": [1, 99]}):
+        with pytest.raises(L.GsError):
+            tune.autotune(*args, **kw, **bad)
