@@ -9,7 +9,7 @@ batch: 16 views at 1200x680 over a 2M-Gaussian four-room pool (SH degree 3,
 30 % of the opacities below 0.05).  Two forms of the same iteration are
 timed in one process:
 
-* batched: one persistent whole-iteration HIP graph for all 16 views;
+* batched: one whole-iteration HIP graph for all 16 views;
 * per view: the same kernels launched view by view (one plan per view,
   gradients accumulated, one Adam step), stream-ordered, no graph.
 
@@ -392,10 +392,10 @@ def bench_scheduled(args, dev, w, cams, target_rgb, target_depth, tile, best, fl
 
 
 def bench_batched(args, dev, workload, search=False, marks=True, scheduled=False):
-    """One persistent whole-iteration graph for all views vs the same kernels
+    """One whole-iteration graph for all views vs the same kernels
     and tile shape launched view by view (one plan per view, gradients
     accumulated, one Adam step).  With `search` the configuration comes from
-    the autotuner, otherwise from --tile/--lds-batch/--chunk/--bwd."""
+    the autotuner, otherwise from --tile/--bwd/--binning."""
     import torch
 
     import paper_2410_00486_amd as gsr
@@ -409,18 +409,18 @@ def bench_batched(args, dev, workload, search=False, marks=True, scheduled=False
     table = []
     if search:
         best, table = tune.autotune(params, cams, view_wh, target_rgb, target_depth, adam_lrs=LRS,
-                                    persistent=True, tiles=[(8, 8), (16, 8), (16, 16)],
-                                    lds_batches=[64, 128], chunks=[1, 2], backwards=["splat"],
-                                    binnings=["tiles", "radix"], reps=4)
+                                    tiles=[(8, 8), (16, 8), (16, 16)],
+                                    lds_batches=[args.lds_batch], chunks=[args.chunk],
+                                    backwards=["splat"], binnings=["tiles", "radix"], reps=4)
     else:
         best = {"tile": args.tile, "lds_batch": args.lds_batch, "chunk": args.chunk,
-                "backward": args.bwd}
+                "backward": args.bwd if args.tile == "8x8" else "pixel"}
     tile = tuple(int(x) for x in best["tile"].split("x"))
     cap0 = gsr.required_pairs(*params.tensors(), cams, view_wh, 3, tile)
     binning = best.get("binning", args.binning)
     radix = L.GS_RADIX_BIN if binning == "radix" else 0
     best["binning"] = binning
-    flags = (L.GS_FUSED_L1 | L.GS_PERSISTENT | radix |
+    flags = (L.GS_FUSED_L1 | radix |
              (L.GS_SPLAT_BWD if best["backward"] == "splat" else 0))
     plan = gsr.Plan(w.scene.n, 3, view_wh, tile=tile, flags=flags, chunk=best["chunk"],
                     lds_batch=best["lds_batch"], pair_capacity=int(cap0 * 1.3) + 4096)
@@ -510,10 +510,11 @@ def bench_batched(args, dev, workload, search=False, marks=True, scheduled=False
             "ms_per_view": ms_p, "ms_per_view_trials": trials_p, "spans": spans}
 
 
-def stage_bytes(c, K=16):
+def stage_bytes(c, K=16, binning="tiles"):
     """Algorithmic (compulsory) HBM bytes of each span of one iteration for
     N Gaussians, V visible records, P pairs and the image pixels: parameter
-    and record reads, list and image writes, each once."""
+    and record reads, list and image writes, each once.  (The per-tile binning
+    sorts the lists of all lengths in one launch, the span of the short ones.)"""
     N, V, P, npx = c["gaussians"], c["visible_records"], c["pairs"], c["pixels"]
     views = c.get("views", 1)
     return {
@@ -521,7 +522,7 @@ def stage_bytes(c, K=16):
         "bin_scan": 16 * N * views // 64 + 12 * 4 * c.get("tiles", 0),
         "bin_scatter": 12 * P + 16 * V,
         "bin_short_sort": 24 * P,
-        "bin_long_sort": 24 * P,
+        "bin_long_sort": 24 * P if binning == "radix" else 0,
         "forward": 64 * P + 40 * npx,
         "raster_bwd": 108 * P + 40 * npx,
         "project_bwd": 44 * N + 12 * K * V + 236 * N + 8 * N + 40 * P,
@@ -529,24 +530,26 @@ def stage_bytes(c, K=16):
     }
 
 
-def roofline_of(span, ms, c, workload, tile):
+def roofline_of(span, ms, c, workload, tile, backward, binning):
     """Roofline entry of the kernel that a span of the iteration holds."""
     kname = SPAN_KERNELS.get(span, span)
     if span in ("forward", "raster_bwd"):
         flops = FWD_FLOPS_PER_POS if span == "forward" else BWD_FLOPS_PER_POS
         tf = flops * c["bwd_positions"] / (ms * 1e-3) / 1e12
-        # (the splat-wise backward is a form of the 8x8 tiles)
+        # (the splat-wise backward, for which the forward keeps pixel states,
+        # is a form of the 8x8 tiles)
+        splat = backward == "splat" and tuple(tile) == (8, 8)
         if span == "forward":
-            full = f"{kname}<{tile[0]},{tile[1]},true>"
+            full = f"{kname}<{tile[0]},{tile[1]},{'true' if splat else 'false'}>"
         else:
-            full = kname if tuple(tile) == (8, 8) else f"k_render_bwd<{tile[0]},{tile[1]}>"
+            full = kname if splat else f"k_render_bwd<{tile[0]},{tile[1]}>"
         return {"bound": "alu", "kernel": full, "achieved": round(tf, 3),
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(tf / FP32_PEAK_TFLOPS, 4),
                 "traffic": measured_traffic(workload, full),
                 "work": f"{flops} flop x {c['bwd_positions']} pixel-Gaussian positions per launch",
                 "launch_ms": round(ms, 4)}
-    b = stage_bytes(c)[span]
+    b = stage_bytes(c, binning=binning)[span]
     gbs = b / (ms * 1e-3) / 1e9
     return {"bound": "hbm", "kernel": kname, "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
@@ -590,7 +593,7 @@ def bench_single(args, dev, workload, pose=False):
     spans = {k: trimmed_mean(per[:, j]) for j, k in enumerate(gsr.Iteration.MARKS)}
     it.close()
     by = stage_bytes(c, (w.scene.sh_degree + 1) ** 2)
-    total = sum(by[k] for k in by if k not in ("bin_short_sort",))
+    total = sum(by.values())
     out = {"workload": w.name, "iters_per_s_graph": round(1e3 / ms_g, 2),
            "iters_per_s_eager": round(1e3 / float(np.median(trials_e)), 2),
            "ms_per_iter": round(ms_g, 4), "counts": c,
@@ -807,8 +810,8 @@ def main():
     # workloads on MI355X; --autotune reruns the search
     ap.add_argument("--autotune", action="store_true")
     ap.add_argument("--tile", default="8x8")
-    ap.add_argument("--lds-batch", type=int, default=64)
-    ap.add_argument("--chunk", type=int, default=1)
+    ap.add_argument("--lds-batch", type=int, default=64, help="checked by the plans, no effect")
+    ap.add_argument("--chunk", type=int, default=1, help="checked by the plans, no effect")
     ap.add_argument("--bwd", default="splat", choices=["pixel", "splat"])
     ap.add_argument("--binning", default="radix", choices=["tiles", "radix"],
                     help="tile binning: per-tile slot claims and sorts, or the two radix sorts")
@@ -870,10 +873,9 @@ def main():
         "config": {"workload": f"{head['workload']}: {n_views} views "
                                f"{head['views'][0][0]}x{head['views'][0][1]} over one pool of "
                                f"{c['gaussians']} Gaussians (SH 3), L1 RGB + 0.1 L1 depth, "
-                               "forward + backward + Adam per iteration, one persistent "
+                               "forward + backward + Adam per iteration, one "
                                "whole-iteration HIP graph",
-                   "tile": f"{tile[0]}x{tile[1]}", "lds_batch": head["config"]["lds_batch"],
-                   "chunk": head["config"]["chunk"], "persistent": True,
+                   "tile": f"{tile[0]}x{tile[1]}",
                    "binning": head["config"]["binning"],
                    "pool_order": ("sorted by the Morton code of the means (the mapping loop's "
                                   "layout; untimed set-up)" if args.order == "spatial"
@@ -895,13 +897,14 @@ def main():
         result["scheduled"] = head["scheduled"]
     spans = head["spans"]
     if spans is not None:
-        by = stage_bytes(c)
+        how = head["config"]["backward"], head["config"]["binning"]
+        by = stage_bytes(c, binning=how[1])
         result["span_ms"] = {k: round(v, 4) for k, v in spans.items()}
         result["span_sum_ms"] = round(sum(spans.values()), 4)
         dom = max((k for k in spans if k != "loss"), key=lambda k: spans[k])
-        result["roofline"] = roofline_of(dom, spans[dom], c, args.workload, tile)
+        result["roofline"] = roofline_of(dom, spans[dom], c, args.workload, tile, *how)
         result["roofline_raster"] = {
-            k: roofline_of(k, spans[k], c, args.workload, tile)
+            k: roofline_of(k, spans[k], c, args.workload, tile, *how)
             for k in ("forward", "raster_bwd") if k != dom}
         total = sum(by[k] for k in by if spans.get(k, 0) > 0)
         result["hbm_gbs_algorithmic"] = round(total / (ms_b * 1e-3) / 1e9, 1)
