@@ -86,11 +86,8 @@ typedef int32_t gs_status;
                                          of per-tile slot claims and per-tile sorts;
                                          the projection then counts no pairs per
                                          tile (the lists give the counts); same
-                                         lists, bit for bit.  The raster kernels
-                                         then read each pair's record through its
-                                         record id (no copy of the records in list
-                                         order).  About 20 B per record more and
-                                         52 B per pair of capacity less workspace */
+                                         lists, bit for bit.  About 48 B per record
+                                         and 13 B per pair of capacity more workspace */
 
 /* Gaussian parameters (Sec. III-B): SoA, float32, device pointers. */
 typedef struct gs_gaussians {
@@ -492,19 +489,20 @@ gs_status gs_graph_time(gs_graph* graph, void* stream, int32_t warmup, int32_t r
  * `stream` at each mark below, synchronises, and writes the milliseconds
  * between consecutive marks: ms[r * (GS_N_MARKS - 1) + k] is the span from
  * mark k to mark k + 1 of rep r (host array of reps * (GS_N_MARKS - 1)).
- * A span whose launches the iteration does not make (no SSIM term) is the
- * empty span between two marks. */
+ * A span whose launches the iteration does not make (no SSIM term; the
+ * long-list sort of the per-tile binning, which rides on the launch of the
+ * short lists) is the empty span between two marks. */
 #define GS_MARK_START 0
 #define GS_MARK_PREPROCESS 1       /* after the counter clear and the projection */
 #define GS_MARK_BIN_SCAN 2         /* after the binning's scans */
 #define GS_MARK_BIN_SCATTER 3      /* after the pair scatter (GS_RADIX_BIN: after the
                                       depth sort of the records and the pair
                                       generation) */
-#define GS_MARK_BIN_SHORT_SORT 4   /* after the per-tile sorts of short lists
-                                      (GS_RADIX_BIN: after the tile-id passes) */
-#define GS_MARK_BIN_LONG_SORT 5    /* after the long-list sorts (GS_RADIX_BIN: after
-                                      the per-tile counts, their scan and the
-                                      per-tile pass) */
+#define GS_MARK_BIN_SHORT_SORT 4   /* after the per-tile sorts of the lists of all
+                                      lengths (GS_RADIX_BIN: after the tile-id passes) */
+#define GS_MARK_BIN_LONG_SORT 5    /* directly after it (GS_RADIX_BIN: after the
+                                      per-tile counts, their scan and the per-tile
+                                      pass) */
 #define GS_MARK_FORWARD 6          /* after compositing (and the L1 loss sums) */
 #define GS_MARK_LOSS 7             /* after the SSIM loss kernels */
 #define GS_MARK_RASTER_BWD 8       /* after the raster backward */

@@ -9,9 +9,9 @@
 // offsets and queue positions); one scatter puts every pair into its tile's
 // list at an atomically taken slot with the key (depth bits << 32 |
 // generation index); a per-tile sort orders those keys (one wavefront per
-// tile: ranks in registers up to 64 keys, a bitonic network in LDS up to
-// 128; longer lists take a wavefront, or a 1024-thread block, each).  No
-// spin-waits; graph-capturable.
+// tile: ranks up to 64 keys, a bitonic network in registers up to 128; longer
+// lists take a wavefront, or a 1024-thread block, each).  No spin-waits;
+// graph-capturable.
 //
 // The scan also writes the work order of the render kernels: tiles with long
 // lists first.
@@ -522,12 +522,13 @@ __global__ void __launch_bounds__(256) k_scatter(
 // kTileSortMid pairs a workgroup each, the others a wavefront each.  The
 // other blocks: the tiles, a wavefront each (the long lists' wavefronts only
 // write the range and queue entries there).  One launch where there were
-// three: the long lists, first in the grid, hide behind the short ones
-// (1200x680 view, 12750 lists of 34 pairs on average: 44 -> 35 us; in 16x16
-// tiles, 3225 lists of 194: 116 -> 64 us; a 128x96 view: 30 -> 15 us).  Held
-// to 64 registers so that two workgroups share a CU (2.7M pairs in 12900
-// lists: 247 us with one, 183 us with two); bound by the LDS traffic of the
-// networks (two reads and two writes per compare).
+// three: the long lists, first in the grid, hide behind the short ones (with
+// the networks still in LDS: 1200x680 view, 12750 lists of 34 pairs on
+// average, 44 -> 35 us; in 16x16 tiles, 3225 lists of 194, 116 -> 64 us; a
+// 128x96 view 30 -> 15 us).  Held to 64 registers so that two workgroups share
+// a CU: the three now take 15, 32 and 6 us, with one workgroup a CU 17, 38 and
+// 6; 2.7M pairs in 12900 lists 87 and 130.  Bound by VALU issue (some 450
+// instructions a key of a list of 512) and the latency of its chain.
 __global__ void __launch_bounds__(kSortWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) k_tile_sort(
     TileSortArgs A, uint64_t* __restrict__ skey, const uint4* __restrict__ long_list,
     int long_blocks, int n_tiles) {

@@ -1,20 +1,20 @@
 // Per-tile list sort of the binning.
 //
 // Output per tile: sorted keys (tile << 32 | depth bits), generation
-// indices, record ids, the records in list order, the [start, end) range
-// ((0, 0) when empty) and, for the splat-wise backward, the tile's entries
-// in the bucket queue.  Keys are unique, so any correct sort gives the
-// same lists.  One launch: a wavefront sorts lists up to 64 keys in
-// registers (rank = number of smaller keys) and up to kTileSortMid keys with a
-// bitonic network in LDS; longer lists take a whole 1024-thread workgroup,
-// with the same network in LDS up to kTileSortLong keys and in place in
-// global memory beyond.  The workgroup's LDS holds kTileSortLong keys
+// indices, record ids, the [start, end) range ((0, 0) when empty) and, for the
+// splat-wise backward, the tile's entries in the bucket queue.  Keys are
+// unique, so any correct sort gives the same lists.  One launch: a wavefront
+// ranks lists of up to 64 keys (rank = number of smaller keys) and sorts up to
+// kTileSortMid in its registers, a bitonic network padded with keys above any
+// other; longer lists take a whole 1024-thread workgroup, the same network
+// with its widest exchanges through LDS up to kTileSortLong keys, and one in
+// place in global memory beyond.  The workgroup's LDS holds kTileSortLong keys
 // (64 KB), so that two share a CU (32 wavefronts, all it holds) and one's
 // barrier waits overlap the other's compares.
 //
-// The network keeps every merge ascending (the first compare of a merge
-// pairs i with its mirror in the block), so positions past the list end act
-// as +infinity and are never touched: no padding is written.
+// The network in global memory keeps every merge ascending (the first compare
+// of a merge pairs i with its mirror in the block), so positions past the list
+// end act as +infinity and are never touched: no padding is written.
 #pragma once
 
 #include "gs_internal.h"
@@ -55,7 +55,7 @@ __device__ __forceinline__ void cmp_swap(uint64_t* k, uint32_t a, uint32_t b, ui
   }
 }
 
-// Sorts k[0, n) ascending (LDS or global memory) with nthreads threads of
+// Sorts k[0, n) ascending (global memory) with nthreads threads of
 // the block; every thread of the block must call it.
 __device__ inline void bitonic_sort(uint64_t* k, uint32_t n, uint32_t tid, uint32_t nthreads) {
   uint32_t m = 1;

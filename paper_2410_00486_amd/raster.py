@@ -722,14 +722,16 @@ class _WorkspacePool:
 class Rasterizer:
     """Differentiable render of a fixed set of views (sizes, SH degree, tile
     configuration), reusable across calls: the plan is kept while the
-    Gaussian count stays the same, and workspaces are pooled -- a forward
-    takes one (allocating a zero-filled one only when none is free) and its
-    backward returns it, so steady-state calls allocate nothing beyond
+    Gaussian count stays the same, and workspaces are pooled per stream -- a
+    forward takes one (allocating a zero-filled one only when none is free)
+    and its backward returns it, so steady-state calls allocate nothing beyond
     torch's caching allocator.
 
     The pair capacity grows on demand: each forward reads the device flags
-    once (one host synchronisation, the overflow check) and, if the pairs
-    did not fit, re-plans with 25 % headroom and renders again.  With
+    (the overflow check) and, if the pairs did not fit, re-plans with 25 %
+    headroom and renders again.  A call that autograd records waits for its
+    binning alone and returns with its render in flight, like any operator of
+    its stream; one that it does not record waits for the render.  With
     check_overflow=False there is no synchronisation; the caller then reads
     ``overflowed()`` after its own synchronisation.
     """
