@@ -578,7 +578,9 @@ struct BwdLds {
 // 627k pairs, this form 228 us (a 128x96 view, 48 tiles: 369 -> 53 us).
 // Bound by VALU issue (88.6M instructions, 144 us of the 228): about 80 per
 // kept splat and block, a third of them the reduction of the ten partials
-// over the lanes.
+// over the lanes.  The walk over the kept positions is the scalar unit's,
+// which the last positions read into scalar registers see to (227 -> 221 us;
+// in 8x8 tiles 171 -> 158; eight mixed views 1504 -> 1436, 16x8 1091 -> 1046).
 template <int TW, int TH>
 __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt) {
   constexpr int NS = sub_tiles<TW, TH>(), NT = kWave * NS, BX = TW / kSub;
@@ -594,7 +596,8 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
   const int col = lane & (kSub - 1), row = lane / kSub;
   const int px = tx0 + kSub * sx + col, py = ty0 + kSub * sy + row;
   const uint32_t s = A.ranges[2 * (int64_t)gtile], e = A.ranges[2 * (int64_t)gtile + 1];
-  const uint32_t tl = tile_last_of<NS>(A.tile_last, gtile);
+  const uint32_t tl =
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_last_of<NS>(A.tile_last, gtile));
 
   // pairs beyond the last used position get zero gradients
   for (uint32_t k = tl + threadIdx.x; k < e - s; k += NT) {
@@ -631,7 +634,7 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
   const bool tame_px = g.x == g.x && g.y == g.y && g.z == g.z && g.w == g.w && gmax < kTame &&
                        fabsf(B) < kTame && T <= 1.0f;
   const bool tame_block = ballot64(!tame_px) == 0;
-  const uint32_t Lmax = wave_max(L);
+  const uint32_t Lmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_max(L));
   const int my_idx = lane < 16 ? rs_index(lane) : -1;
   const double ax0 = (double)(tx0 + kSub * sx) + 0.5, ay0 = (double)(ty0 + kSub * sy) + 0.5;
 
@@ -664,7 +667,8 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
       ax += 1.0;
       ay += 1.0;
     }
-    uint64_t kept = ballot64(has && !(max_exponent(r, ox[kSub - 1], ox[0], oy[kSub - 1], oy[0]) < kCullExp));
+    const bool keep = !(max_exponent(r, ox[kSub - 1], ox[0], oy[kSub - 1], oy[0]) < kCullExp);
+    uint64_t kept = ballot64(has & keep);
     // (nothing of this block is used from position Lmax on)
     const int used = (int)Lmax - bstart;
     kept &= used >= kWave ? ~0ull : (used <= 0 ? 0ull : (1ull << used) - 1ull);
@@ -734,6 +738,7 @@ __global__ void __launch_bounds__(TW * TH) k_render_bwd(BwdArgs A, ViewTable vt)
       if (my_idx >= 0) {
 #pragma unroll
         for (int k = 0; k < N; ++k) S.part[sub][j[k]][my_idx] = z[k];
+        asm volatile("" ::"i"(N));  // (merged with the other form's store, the walk leaves the scalar unit)
       }
     };
     auto walk = [&](auto tame_c) __attribute__((always_inline)) {
