@@ -8,7 +8,6 @@ path runs in libgs.so.  Nothing here computes pixels or gradients.
 from __future__ import annotations
 
 import ctypes
-import threading
 from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
@@ -27,6 +26,11 @@ def _stream_key():
     """The stream that launches go to: (device, handle)."""
     dev = torch._C._cuda_getDevice()
     return dev, torch._C._cuda_getCurrentRawStream(dev)
+
+
+def _recording() -> bool:
+    """Whether that stream is being recorded into a graph."""
+    return torch._C._cuda_isCurrentStreamCapturing()
 
 
 def _stream(stream=None):
@@ -688,8 +692,9 @@ class _WorkspacePool:
     OTHERS = 8
 
     def __init__(self):
-        self._lock = threading.Lock()
-        self._held: List[tuple] = []  # (workspace, stream, recorded), oldest first
+        # (workspace, stream, recorded), oldest first; threads only append to
+        # it, extend it and pop its end
+        self._held: List[tuple] = []
 
     def __reduce__(self):
         return (_WorkspacePool, ())
@@ -698,25 +703,44 @@ class _WorkspacePool:
     def workspaces(self) -> List[torch.Tensor]:
         return [h[0] for h in self._held]
 
+    def _drain(self) -> List[tuple]:
+        out = []
+        try:
+            while True:
+                out.append(self._held.pop())
+        except IndexError:
+            return out  # newest first
+
     def give(self, ws: torch.Tensor):
-        key, recorded = _stream_key(), torch.cuda.is_current_stream_capturing()
-        with self._lock:
-            self._held.append((ws, key, recorded))
-            others = [k for k, h in enumerate(self._held) if h[1] != key and not h[2]]
-            if len(others) > self.OTHERS:
-                del self._held[others[0]]
+        key = _stream_key()
+        self._held.append((ws, key, _recording()))
+        if len(self._held) > self.OTHERS:
+            kept, others = [], 0
+            for h in self._drain():
+                others += h[1] != key and not h[2]
+                if h[1] == key or h[2] or others <= self.OTHERS:
+                    kept.append(h)
+            self._held.extend(reversed(kept))
 
     def take(self, nbytes: int, device) -> Optional[torch.Tensor]:
-        key, recording = _stream_key(), torch.cuda.is_current_stream_capturing()
-        with self._lock:
-            for k in range(len(self._held) - 1, -1, -1):
-                ws, stream, recorded = self._held[k]
-                # (what an eager call on any stream left has run before a recording is replayed)
-                usable = recording and stream == key if recorded else recording or stream == key
-                if usable and ws.numel() >= nbytes and ws.device == device:
-                    del self._held[k]
-                    return ws
-        return None
+        key, recording = _stream_key(), _recording()
+
+        def fits(ws, stream, recorded):
+            # (what an eager call on any stream left has run before a recording is replayed)
+            usable = recording and stream == key if recorded else recording or stream == key
+            return usable and ws.numel() >= nbytes and ws.device == device
+
+        try:
+            last = self._held.pop()
+        except IndexError:
+            return None
+        if fits(*last):
+            return last[0]
+        rest = [last] + self._drain()
+        at = next((k for k, h in enumerate(rest) if fits(*h)), None)
+        ws = None if at is None else rest.pop(at)[0]
+        self._held.extend(reversed(rest))
+        return ws
 
 
 class Rasterizer:

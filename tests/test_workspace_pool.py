@@ -27,7 +27,7 @@ def now(monkeypatch):
     """The current stream and whether it is being recorded."""
     state = {"stream": "a", "recording": False}
     monkeypatch.setattr(raster, "_stream_key", lambda: (0, state["stream"]), raising=False)
-    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["recording"])
+    monkeypatch.setattr(raster, "_recording", lambda: state["recording"], raising=False)
     return state
 
 
