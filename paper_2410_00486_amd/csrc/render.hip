@@ -1110,7 +1110,7 @@ __device__ __forceinline__ void splat_bucket(const SplatArgs& A, const ViewTable
 // above) by more than kGridIdle, 7 us, the rest is left to a second, looping
 // launch (4 us if nothing is).  640x480, 61k pairs, whole iteration: with room
 // for 1.3 times as many 92 us, 256 times 130 without the second launch and
-// 100 with it, 1024 times 284 and 103.  As one looping launch the large
+// 100 with it, 1024 times 284 and 100.  As one looping launch the large
 // batches lose 4 % (1616 -> 1681 us, 79 registers instead of 69).
 constexpr int64_t kGridBuckets = 8, kGridLeast = 1 << 14, kGridIdle = 1 << 16, kGridRest = 1 << 14;
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(6))) k_render_bwd_splat(
